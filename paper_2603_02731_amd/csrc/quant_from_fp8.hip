@@ -153,6 +153,93 @@ __global__ void __launch_bounds__(THREADS) quant_from_fp8_kernel(const QuantArgs
     }
 }
 
+// ---- one wave per row
+//
+// A wave quantizes a segment of at most WAVE_SEG elements of one source row into its own 4 KiB of LDS (nibble bytes
+// then scale bytes, as they sit in a per-token record), takes the finished bytes back as 16-byte pieces and writes
+// them to every destination row.  No barrier: the waves of a workgroup are independent.
+constexpr uint32_t WAVE_SEG = 7680; // 240 nibble pieces and 15 scale pieces: at most four 16-byte pieces per lane
+constexpr int WAVE_CHUNKS = 8;      // 16-element chunks per lane
+constexpr int WAVE_PIECES = 4;
+constexpr int WAVE_LDS = 4096;
+
+struct RowPieces {
+    u32x4 v[WAVE_PIECES];
+    uint32_t sf_dword;         // rows whose scale bytes are not whole 16-byte pieces: this lane's dword of them
+};
+
+// Elements [k0, k0 + n) of the source row at src / src_scale; n is a multiple of 128, of 512 with WIDE_SF.
+// zero: the row of an index that names no source row.
+template <bool WIDE_SF>
+__device__ __forceinline__ void quant_segment(const uint8_t *src, const float *src_scale, uint32_t n, bool zero,
+                                              uint8_t *rec, uint32_t lane, RowPieces *out)
+{
+    const uint32_t n_chunks = n / 16u, nib_bytes = n / 2u;
+    u32x4 w[WAVE_CHUNKS];
+    float s[WAVE_CHUNKS];
+#pragma unroll
+    for (int u = 0; u < WAVE_CHUNKS; ++u) {
+        const uint32_t c = u * 64u + lane;
+        if (c < n_chunks) { // the 8 lanes of a tile pass or fail together
+            w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + c * 16u));
+            s[u] = src_scale[c >> 3];
+            if (zero) {
+                w[u] = u32x4{0u, 0u, 0u, 0u};
+                s[u] = 0.0f;
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < WAVE_CHUNKS; ++u) {
+        const uint32_t c = u * 64u + lane;
+        if (c < n_chunks) {
+            uint32_t o[2], b;
+            quant16(w[u], s[u], o, &b);
+            uint32_t t = b | (dpp_read<DPP_QUAD_XOR2>(b) << 8); // lanes 0,1 of the tile: B0 | B1 << 8
+            t |= row_shift_left4(t) << 16;                       // lane 0: ... | B2 << 16 | B3 << 24
+            *reinterpret_cast<u32x2 *>(rec + c * 8u) = u32x2{o[0], o[1]};
+            if ((lane & 7u) == 0u)
+                *reinterpret_cast<uint32_t *>(rec + nib_bytes + (c >> 3) * 4u) = t;
+        }
+    }
+    // the bytes of other lanes of this wave: ordered by the fence, no barrier of the workgroup needed
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint32_t nib_pieces = nib_bytes / 16u, pieces = nib_pieces + (WIDE_SF ? n / 512u : 0u);
+#pragma unroll
+    for (int i = 0; i < WAVE_PIECES; ++i) {
+        const uint32_t p = i * 64u + lane;
+        out->v[i] = u32x4{0u, 0u, 0u, 0u};
+        if (p < pieces)
+            out->v[i] = *reinterpret_cast<const u32x4 *>(rec + p * 16u);
+    }
+    out->sf_dword = 0u;
+    if (!WIDE_SF && lane < n / 128u)
+        out->sf_dword = *reinterpret_cast<const uint32_t *>(rec + nib_bytes + lane * 4u);
+    // the LDS bytes are in registers before the wave's next segment overwrites them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The finished segment to one destination: dq / dsf are where its nibbles and scale bytes start.
+template <bool WIDE_SF>
+__device__ __forceinline__ void store_segment(const RowPieces &r, uint32_t n, uint8_t *dq, uint8_t *dsf, uint32_t lane)
+{
+    const uint32_t nib_pieces = n / 32u, pieces = nib_pieces + (WIDE_SF ? n / 512u : 0u);
+    // piece p of either kind sits 16 * p bytes after a base: the scale pieces follow the last nibble piece
+    uint8_t *sf_base = dsf - n / 2u;
+#pragma unroll
+    for (int i = 0; i < WAVE_PIECES; ++i) {
+        const uint32_t p = i * 64u + lane;
+        if (p < pieces)
+            __builtin_nontemporal_store(r.v[i], reinterpret_cast<u32x4 *>((p < nib_pieces ? dq : sf_base) + lane * 16u + i * 1024u));
+    }
+    if (!WIDE_SF && lane < n / 128u)
+        *reinterpret_cast<uint32_t *>(dsf + lane * 4u) = r.sf_dword;
+}
+
 // The routing turned around: every source row is read and quantized once and written to each of
 // its `fanout` destination rows (a token and its top-k experts), instead of being read and
 // quantized again for every destination.  Same lane layout; dense source, strided outputs.
@@ -219,103 +306,108 @@ __global__ void __launch_bounds__(QUANT_THREADS_ROUTED) quant_from_fp8_scatter_k
     }
 }
 
-// The scatter form for 16-byte-aligned outputs: a workgroup quantizes SCATTER_ROWS whole source rows into LDS
-// (per row the K/2 nibble bytes followed by the K/32 scale bytes, as they sit in a per-token record) and
-// then writes every row to each of its destinations in 16-byte pieces, whole rows contiguous: one wave
-// instruction stores 1 KiB of one destination row, and the scale bytes leave in the same stream instead of
-// as scattered dwords.
-// The destination indices of a row are uniform over the workgroup.
-constexpr int SCATTER_ROWS = 4; // at most; the launcher picks 1, 2 or 4 rows per workgroup
+constexpr int SCATTER_WAVES = 4; // rows (or row segments) per workgroup, one per wave
+
+template <bool WIDE_SF>
+__global__ void __launch_bounds__(64 * SCATTER_WAVES) quant_from_fp8_scatter_wave_kernel(const QuantScatterArgs a,
+                                                                                        const uint32_t M_src,
+                                                                                        const uint32_t seg,
+                                                                                        const uint32_t segs_per_row)
+{
+    __shared__ __align__(16) uint8_t s_rec[SCATTER_WAVES][WAVE_LDS];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t unit = blockIdx.x * SCATTER_WAVES + wave;
+    const uint32_t row = unit / segs_per_row;
+    if (row >= M_src)
+        return;
+    const uint32_t K = a.chunks_per_row * 16u;
+    const uint32_t k0 = (unit - row * segs_per_row) * seg;
+    const uint32_t n = min(seg, K - k0);
+    RowPieces r;
+    quant_segment<WIDE_SF>(a.x + (size_t)row * K + k0, a.x_scale + (size_t)row * (K >> 7) + (k0 >> 7), n, false,
+                           s_rec[wave], lane, &r);
+    const int32_t *dst = a.dst_idx + (size_t)row * a.fanout;
+    for (uint32_t j = 0; j < a.fanout; ++j) {
+        const uint32_t d = (uint32_t)dst[j];
+        if (d < a.M_out) // also skips negative entries
+            store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u, a.sf + (size_t)d * a.ld_sf + k0 / 32u, lane);
+    }
+}
+
+// The scatter form for long rows: a workgroup quantizes one source row into LDS (the K/2 nibble bytes followed by the
+// K/32 scale bytes, as they sit in a per-token record) and writes it to each destination in 16-byte pieces, the
+// whole row by one instruction per wave.  The pieces are dealt to the lanes so that every wave instruction starts
+// on a 128-byte line of its destination (records of 3808 bytes start at any multiple of 32).
 constexpr int SCATTER_THREADS = 512;
-constexpr int SCATTER_UNROLL = 1;
 
 template <bool WIDE_SF> // the K/32 scale bytes of a row are a whole number of 16-byte pieces (K % 512 == 0)
-__global__ void __launch_bounds__(SCATTER_THREADS) quant_from_fp8_scatter_rows_kernel(const QuantScatterArgs a,
-                                                                                      const uint32_t M_src,
-                                                                                      const uint32_t rows_per_wg)
+__global__ void __launch_bounds__(SCATTER_THREADS) quant_from_fp8_scatter_row_kernel(const QuantScatterArgs a,
+                                                                                     const bool records)
 {
-    extern __shared__ __align__(16) uint8_t s_rows[]; // [SCATTER_ROWS][rec], rec = K/2 + K/32 rounded up to 16
-    const uint32_t tid = threadIdx.x;
-    const uint32_t C = a.chunks_per_row;              // 16-element chunks per row
-    const uint32_t nib_bytes = C * 8u, sf_bytes = C / 2u;
-    const uint32_t rec = (nib_bytes + sf_bytes + 15u) & ~15u;
-    const uint32_t row0 = blockIdx.x * rows_per_wg;
-    const uint32_t n_rows = min(rows_per_wg, M_src - row0);
-    const uint32_t n_chunks = n_rows * C;             // a multiple of 8
-    const uint8_t *src = a.x + (size_t)row0 * C * 16u;
-    const float *src_scale = a.x_scale + (size_t)row0 * (C / 8u);
+    extern __shared__ __align__(16) uint8_t s_row[];
+    const uint32_t tid = threadIdx.x, row = blockIdx.x;
+    const uint32_t C = a.chunks_per_row; // 16-element chunks per row
+    const uint32_t nib_bytes = C * 8u;
+    const uint8_t *src = a.x + (size_t)row * C * 16u;
+    const float *src_scale = a.x_scale + (size_t)row * (C / 8u);
+    const int32_t *dst = a.dst_idx + (size_t)row * a.fanout;
 
-    // the first eight destinations of every row, requested before anything else (uniform over the workgroup)
-    uint32_t dpre[SCATTER_ROWS][8];
+    // the first eight destinations, requested before anything else (uniform over the workgroup)
+    uint32_t d[8];
 #pragma unroll
-    for (int r = 0; r < SCATTER_ROWS; ++r)
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            dpre[r][j] = (uint32_t)r < n_rows && (uint32_t)j < a.fanout
-                             ? (uint32_t)a.dst_idx[(size_t)(row0 + r) * a.fanout + j]
-                             : 0xFFFFFFFFu;
+    for (int j = 0; j < 8; ++j)
+        d[j] = (uint32_t)j < a.fanout ? (uint32_t)dst[j] : 0xFFFFFFFFu;
 
-    for (uint32_t base = 0; base < n_chunks; base += SCATTER_THREADS * SCATTER_UNROLL) {
-        u32x4 w[SCATTER_UNROLL];
-        float s[SCATTER_UNROLL];
-#pragma unroll
-        for (int u = 0; u < SCATTER_UNROLL; ++u) {
-            const uint32_t c = base + u * SCATTER_THREADS + tid;
-            if (c < n_chunks) { // the 8 lanes of a tile pass or fail together
-                w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + (size_t)c * 16u));
-                s[u] = src_scale[c >> 3];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < SCATTER_UNROLL; ++u) {
-            const uint32_t c = base + u * SCATTER_THREADS + tid;
-            if (c < n_chunks) {
-                uint32_t out[2], b;
-                quant16(w[u], s[u], out, &b);
-                uint32_t t = b | (dpp_read<DPP_QUAD_XOR2>(b) << 8); // lanes 0,1 of the tile: B0 | B1 << 8
-                t |= row_shift_left4(t) << 16;                       // lane 0: ... | B2 << 16 | B3 << 24
-                const uint32_t r = c / C, cc = c - r * C;
-                uint8_t *row = s_rows + r * rec;
-                *reinterpret_cast<u32x2 *>(row + cc * 8u) = u32x2{out[0], out[1]};
-                if ((tid & 7u) == 0u)
-                    *reinterpret_cast<uint32_t *>(row + nib_bytes + (cc >> 3) * 4u) = t;
-            }
-        }
+    for (uint32_t c = tid; c < C; c += SCATTER_THREADS) { // the 8 lanes of a tile pass or fail together
+        const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + (size_t)c * 16u));
+        const float s = src_scale[c >> 3];
+        uint32_t out[2], b;
+        quant16(w, s, out, &b);
+        uint32_t t = b | (dpp_read<DPP_QUAD_XOR2>(b) << 8); // lanes 0,1 of the tile: B0 | B1 << 8
+        t |= row_shift_left4(t) << 16;                       // lane 0: ... | B2 << 16 | B3 << 24
+        *reinterpret_cast<u32x2 *>(s_row + c * 8u) = u32x2{out[0], out[1]};
+        if ((tid & 7u) == 0u)
+            *reinterpret_cast<uint32_t *>(s_row + nib_bytes + (c >> 3) * 4u) = t;
     }
     __syncthreads();
 
-    const uint32_t nib_pieces = nib_bytes / 16u;
-    const uint32_t sf_pieces = WIDE_SF ? sf_bytes / 16u : sf_bytes / 4u; // 16-byte pieces, or dwords
-    // the scale pieces go to the lanes after those of the last nibble pieces
-    const uint32_t sf_lane = (tid + SCATTER_THREADS - nib_pieces % SCATTER_THREADS) % SCATTER_THREADS;
-    auto store_row = [&](uint32_t r, uint32_t d) {
-        if (d >= a.M_out) // also skips negative entries and the slots past the fan-out
-            return;
-        const uint8_t *row = s_rows + r * rec;
-        uint8_t *dq = a.q + (size_t)d * a.ld_q;
-        uint8_t *dsf = a.sf + (size_t)d * a.ld_sf;
-        for (uint32_t p = tid; p < nib_pieces; p += SCATTER_THREADS)
-            __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(row + p * 16u),
-                                        reinterpret_cast<u32x4 *>(dq + p * 16u));
-        for (uint32_t p = sf_lane; p < sf_pieces; p += SCATTER_THREADS) {
-            if (WIDE_SF)
-                __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(row + nib_bytes + p * 16u),
-                                            reinterpret_cast<u32x4 *>(dsf + p * 16u));
-            else
-                *reinterpret_cast<uint32_t *>(dsf + p * 4u) = *reinterpret_cast<const uint32_t *>(row + nib_bytes + p * 4u);
-        }
-    };
+    const uint32_t nib_pieces = nib_bytes / 16u, pieces = nib_pieces + (WIDE_SF ? C / 32u : 0u);
+    for (uint32_t j0 = 0;;) {
 #pragma unroll
-    for (int r = 0; r < SCATTER_ROWS; ++r) {
+        for (int j = 0; j < 8; ++j) {
+            if (d[j] >= a.M_out) // also skips negative entries and the slots past the fan-out
+                continue;
+            uint8_t *dq = a.q + (size_t)d[j] * a.ld_q;
+            uint8_t *dsf = a.sf + (size_t)d[j] * a.ld_sf;
+            const uint32_t shift = (uint32_t)(reinterpret_cast<uintptr_t>(dq) >> 4) & 7u;
+            for (uint32_t i = tid; i < pieces + shift; i += SCATTER_THREADS) {
+                const uint32_t p = i - shift;
+                if (p < pieces) // wraps below zero for the lanes before the first piece
+                    __builtin_nontemporal_store(
+                        *reinterpret_cast<const u32x4 *>(s_row + p * 16u),
+                        reinterpret_cast<u32x4 *>(records || p < nib_pieces ? dq + p * 16u : dsf + (p - nib_pieces) * 16u));
+            }
+            if (!WIDE_SF)
+                for (uint32_t i = tid; i < C / 8u; i += SCATTER_THREADS)
+                    *reinterpret_cast<uint32_t *>(dsf + i * 4u) = *reinterpret_cast<const uint32_t *>(s_row + nib_bytes + i * 4u);
+        }
+        j0 += 8u;
+        if (j0 >= a.fanout)
+            break;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            store_row(r, dpre[r][j]);
-        if ((uint32_t)r < n_rows) {
-            const int32_t *dst = a.dst_idx + (size_t)(row0 + r) * a.fanout;
-            for (uint32_t j = 8; j < a.fanout; ++j) // fan-outs beyond 8: one index at a time
-                store_row(r, (uint32_t)dst[j]);
-        }
+            d[j] = j0 + j < a.fanout ? (uint32_t)dst[j0 + j] : 0xFFFFFFFFu;
     }
+}
+
+// Elements per segment of a row that a wave takes at a time: equal parts of at most WAVE_SEG, in whole 512s.
+static uint32_t wave_segment(int64_t K, uint32_t *segs_per_row)
+{
+    const uint32_t n = (uint32_t)((K + WAVE_SEG - 1) / WAVE_SEG);
+    const uint32_t seg = n == 1u ? (uint32_t)K : (uint32_t)((K / 128 + 4 * n - 1) / (4 * n)) * 512u;
+    *segs_per_row = (uint32_t)((K + seg - 1) / seg);
+    return seg;
 }
 
 hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
@@ -334,28 +426,39 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     a.chunks_per_row = (uint32_t)(K / 16);
     a.fanout = (uint32_t)fanout;
     a.M_out = (uint32_t)M_out;
-    // whole rows through LDS when every output row starts on a 16-byte boundary and four rows fit into LDS
+    const bool nib16 = ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) == 0u;
+    const bool sf16 = ((reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_sf) & 15u) == 0u;
+    const bool wide = K % 512 == 0 && sf16;
+    // Which kernel.  Source rows of 256 M elements and their copies in about 150 MB of records or planes (us: one lane
+    // per chunk / one wave per row / one workgroup per row), copies grouped by expert:
+    //   K = 512, 8 copies 60 / 62 / 170, 2 copies 51 / 102 / 397; K = 1024 44 / 45 / 92, 51 / 59 / 211;
+    //   K = 2048 36 / 36 / 56, 50 / 49 / 119, 1 copy 41 / 37 / 101; K = 3072 43 / 41 / 42, 50 / 52 / 86, 41 / 37 / 72;
+    //   K = 4096 34 / 33 / 35, 50 / 49 / 67, 40 / 36 / 57; K = 5120 45 / 40 / 36, 50 / 51 / 58, 40 / 37 / 50;
+    //   K = 7168 43 / 38 / 37, 51 / 51 / 49, 40 / 37 / 41; 65536 tokens of 7168, 8 copies (2 GB) 598 / 520 / 480.
+    // A wave per row leaves lanes idle below 1024 elements and has its stores contiguous above; a workgroup per row
+    // writes the longest runs, which pays for long rows with several copies.
+    uint32_t segs_per_row;
+    const uint32_t seg = wave_segment(K, &segs_per_row);
     const uint32_t rec = (uint32_t)((K / 2 + K / 32 + 15) & ~(int64_t)15);
-    const bool rows16 = ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_q |
-                          (uintptr_t)ld_sf) & 15u) == 0u;
-    if (rows16 && rec <= 48u * 1024u) {
-        // Rows per workgroup: about one 16-element chunk per lane.  Top-8 payload of 65536 tokens at K = 7168 into
-        // 3808-byte records, over rotated buffers, destinations shuffled / in token order: 512 lanes x 1 chunk, one
-        // row 552 / 427 us; 256 lanes x 4 chunks, one row 545 / 458, four rows 588 / 545; two rows on 896 lanes
-        // 597 / 559 (more, shorter workgroups overlap their loads, stores and the wait for the last store better).
-        // The kernel it replaces, with 8-byte nibble stores and the scale dwords on their own: 598 us shuffled.
-        // With shuffled destinations the records bound it: 3808 bytes are 29.75 lines, so both ends of every
-        // record are partial lines written by different workgroups (planes of 3584 + 224 bytes: 516 us; a kernel
-        // that only copies 16 bytes per lane to eight destination streams: 395-430 us).
-        const uint32_t C = a.chunks_per_row;
-        const uint32_t rows = 2u * C >= SCATTER_THREADS ? 1u : 4u * C >= SCATTER_THREADS ? 2u : 4u;
-        const uint32_t blocks = (uint32_t)((M_src + rows - 1) / rows);
-        if (K % 512 == 0)
-            hipLaunchKernelGGL(quant_from_fp8_scatter_rows_kernel<true>, dim3(blocks), dim3(SCATTER_THREADS),
-                               rows * rec, stream, a, (uint32_t)M_src, rows);
+    if (nib16 && K >= 6144 && fanout >= 2 && rec <= 48u * 1024u) {
+        const bool records = sf == q + K / 2 && ld_sf == ld_q;
+        if (wide)
+            hipLaunchKernelGGL(quant_from_fp8_scatter_row_kernel<true>, dim3((uint32_t)M_src), dim3(SCATTER_THREADS), rec,
+                               stream, a, records);
         else
-            hipLaunchKernelGGL(quant_from_fp8_scatter_rows_kernel<false>, dim3(blocks), dim3(SCATTER_THREADS),
-                               rows * rec, stream, a, (uint32_t)M_src, rows);
+            hipLaunchKernelGGL(quant_from_fp8_scatter_row_kernel<false>, dim3((uint32_t)M_src), dim3(SCATTER_THREADS), rec,
+                               stream, a, records);
+        return hipGetLastError();
+    }
+    const int64_t units = M_src * segs_per_row;
+    if (nib16 && K >= 2048 && units < ((int64_t)1 << 31)) {
+        const uint32_t blocks = (uint32_t)((units + SCATTER_WAVES - 1) / SCATTER_WAVES);
+        if (wide)
+            hipLaunchKernelGGL(quant_from_fp8_scatter_wave_kernel<true>, dim3(blocks), dim3(64 * SCATTER_WAVES), 0, stream,
+                               a, (uint32_t)M_src, seg, segs_per_row);
+        else
+            hipLaunchKernelGGL(quant_from_fp8_scatter_wave_kernel<false>, dim3(blocks), dim3(64 * SCATTER_WAVES), 0,
+                               stream, a, (uint32_t)M_src, seg, segs_per_row);
         return hipGetLastError();
     }
     constexpr uint32_t per_block = QUANT_THREADS_ROUTED * QUANT_UNROLL;
