@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(THREADS) quant_from_fp8_kernel(const QuantArgs
     }
 }
 
-// ---- one wave per row
+// ---- one wave per row: shared by the scatter of short rows and the gather by owners
 //
 // A wave quantizes a segment of at most WAVE_SEG elements of one source row into its own 4 KiB of LDS (nibble bytes
 // then scale bytes, as they sit in a per-token record), takes the finished bytes back as 16-byte pieces and writes
@@ -467,10 +467,231 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     return hipGetLastError();
 }
 
+// Gather by owners.  Every source row that several output rows ask for is read and quantized once: a workgroup owns
+// a range of source rows, scans the whole index for the output rows that want one of them, sorts these by source row
+// in LDS, and its waves write each of its rows to all of its destinations.  No communication between workgroups and
+// no scratch memory: all of them read the same index (a few bytes per output row against K * 17/32 written).
+//
+// Balance.  Routing maps ask for every token about equally often.  Where they do not (many output rows padded with
+// one and the same index, say) the owner of such rows would work on alone: every workgroup counts a sample of the
+// index per owner while it scans, all see the same counts, and the rows of an owner with several times its share
+// (and the zero rows of indices that name no source row) are dealt out by output row instead.
+constexpr int OWNER_WAVES = 16;
+constexpr uint32_t OWNER_THREADS = 64 * OWNER_WAVES;
+constexpr uint32_t OWNER_GROUPS = 512; // workgroups at most: counters of the sample
+constexpr uint32_t OWNER_ROWS = 256;   // source rows of a workgroup at most
+constexpr uint32_t OWNER_LIST = 8192;  // output rows a workgroup sorts; more of them take the unsorted path
+
+struct QuantOwnerArgs {
+    const uint8_t *x;
+    const float *x_scale;
+    const int32_t *gather_idx;
+    uint8_t *q;
+    uint8_t *sf;
+    int64_t ld_q;
+    int64_t ld_sf;
+    uint32_t M_src;
+    uint32_t M_out;
+    uint32_t K;
+    uint32_t seg;        // elements of a row taken at a time
+    uint32_t rows_per_wg;
+    uint32_t owner_of;   // ceil(2^32 / rows_per_wg): source row -> workgroup by a high multiplication, exact below 2^24
+    uint32_t heavy;      // sampled indices above which an owner's rows are dealt out
+};
+
+template <bool WIDE_SF>
+__device__ __forceinline__ void quant_row_to(const QuantOwnerArgs &a, uint32_t src_row, bool zero, uint8_t *rec,
+                                             uint32_t lane, const uint32_t *dst, uint32_t n_dst, uint32_t one_dst)
+{
+    for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
+        const uint32_t n = min(a.seg, a.K - k0);
+        RowPieces r;
+        quant_segment<WIDE_SF>(a.x + (size_t)src_row * a.K + k0, a.x_scale + (size_t)src_row * (a.K >> 7) + (k0 >> 7), n,
+                               zero, rec, lane, &r);
+        for (uint32_t j = 0; j < n_dst; ++j) {
+            const uint32_t d = dst ? __builtin_amdgcn_readfirstlane(dst[j]) : one_dst;
+            store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u, a.sf + (size_t)d * a.ld_sf + k0 / 32u, lane);
+        }
+    }
+}
+
+template <bool WIDE_SF>
+__global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(const QuantOwnerArgs a)
+{
+    __shared__ __align__(16) uint8_t s_rec[OWNER_WAVES][WAVE_LDS]; // first the unsorted list, then the waves' rows
+    __shared__ uint32_t s_sorted[OWNER_LIST];
+    __shared__ uint32_t s_sample[OWNER_GROUPS]; // sampled indices per owner
+    __shared__ uint32_t s_fill[OWNER_ROWS];     // output rows per owned row; then where the next one goes
+    __shared__ uint32_t s_start[OWNER_ROWS + 1];
+    __shared__ uint32_t s_n;
+    static_assert(sizeof(s_rec) >= OWNER_LIST * sizeof(uint32_t), "the unsorted list fits into the waves' rows");
+    uint32_t *s_list = reinterpret_cast<uint32_t *>(s_rec);
+
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t row0 = blockIdx.x * a.rows_per_wg;
+    const uint32_t n_rows = min(a.rows_per_wg, a.M_src - row0);
+    if (tid < OWNER_GROUPS)
+        s_sample[tid] = 0u;
+    if (tid < OWNER_ROWS)
+        s_fill[tid] = 0u;
+    if (tid == 0u)
+        s_n = 0u;
+    __syncthreads();
+
+    // ---- scan: lane l of a step takes the four indices 4l.. of a run
+    constexpr int STEP = 4;
+    auto take = [&](uint32_t src, uint32_t out) {
+        const uint32_t t = src - row0;
+        if (t < n_rows) {
+            const uint32_t at = atomicAdd(&s_n, 1u);
+            if (at < OWNER_LIST) {
+                s_list[at] = (t << 24) | out;
+                atomicAdd(&s_fill[t], 1u);
+            }
+        }
+    };
+    const uint32_t quads = a.M_out / 4u;
+    const u32x4_unaligned *idx4 = reinterpret_cast<const u32x4_unaligned *>(a.gather_idx);
+    for (uint32_t base = 0; base < quads; base += OWNER_THREADS * STEP) {
+        u32x4 v[STEP];
+#pragma unroll
+        for (int u = 0; u < STEP; ++u) {
+            const uint32_t p = base + u * OWNER_THREADS + tid;
+            v[u] = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+            if (p < quads)
+                v[u] = idx4[p];
+        }
+#pragma unroll
+        for (int u = 0; u < STEP; ++u) {
+            const uint32_t p = base + u * OWNER_THREADS + tid;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                take(v[u][e], p * 4u + e);
+            if ((lane & 3u) == 0u && v[u].x < a.M_src) // every sixteenth index
+                atomicAdd(&s_sample[__umulhi(v[u].x, a.owner_of)], 1u);
+        }
+    }
+    if (tid < (a.M_out & 3u))
+        take((uint32_t)a.gather_idx[quads * 4u + tid], quads * 4u + tid);
+    __syncthreads();
+
+    const bool shared_out = s_sample[blockIdx.x] > a.heavy; // this owner's rows are dealt out
+    const uint32_t listed = s_n;
+    const bool sorted = listed <= OWNER_LIST && !shared_out;
+    if (sorted) {
+        if (wave == 0u) { // where each owned row's destinations start
+            uint32_t before = 0;
+#pragma unroll
+            for (uint32_t b = 0; b < OWNER_ROWS; b += 64u) {
+                const uint32_t c = s_fill[b + lane];
+                const uint32_t incl = wave_inclusive_sum(c);
+                s_start[b + lane] = before + incl - c;
+                before += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            }
+            if (lane == 0u)
+                s_start[OWNER_ROWS] = before;
+        }
+        __syncthreads();
+        if (tid < OWNER_ROWS)
+            s_fill[tid] = s_start[tid];
+        __syncthreads();
+        for (uint32_t i = tid; i < listed; i += OWNER_THREADS) {
+            const uint32_t e = s_list[i];
+            s_sorted[atomicAdd(&s_fill[e >> 24], 1u)] = e & 0xFFFFFFu;
+        }
+        __syncthreads();
+        for (uint32_t t = wave; t < n_rows; t += OWNER_WAVES) {
+            const uint32_t j0 = __builtin_amdgcn_readfirstlane(s_start[t]);
+            const uint32_t j1 = __builtin_amdgcn_readfirstlane(s_start[t + 1u]);
+            if (j0 != j1)
+                quant_row_to<WIDE_SF>(a, row0 + t, false, s_rec[wave], lane, &s_sorted[j0], j1 - j0, 0u);
+        }
+    } else if (!shared_out) {
+        // more output rows than the list holds although the sample saw no crowd: one after the other
+        for (uint32_t base = wave * 64u; base < a.M_out; base += OWNER_THREADS) {
+            const uint32_t out = base + lane;
+            const uint32_t src = out < a.M_out ? (uint32_t)a.gather_idx[out] : 0xFFFFFFFFu;
+            uint64_t mine = __ballot(src - row0 < n_rows);
+            while (mine != 0ull) {
+                const int l = __ffsll((unsigned long long)mine) - 1;
+                mine &= mine - 1ull;
+                quant_row_to<WIDE_SF>(a, (uint32_t)__builtin_amdgcn_readlane((int)src, l), false, s_rec[wave], lane,
+                                      nullptr, 1u, base + l);
+            }
+        }
+    }
+
+    // ---- the rows that are dealt out by output row: 64 consecutive ones per wave
+    for (uint32_t base = (blockIdx.x + wave * gridDim.x) * 64u; base < a.M_out; base += gridDim.x * OWNER_THREADS) {
+        const uint32_t out = base + lane;
+        const uint32_t src = out < a.M_out ? (uint32_t)a.gather_idx[out] : 0u;
+        const bool none = src >= a.M_src; // also negative: a zero row
+        bool deal = none && out < a.M_out;
+        if (!none && out < a.M_out)
+            deal = s_sample[__umulhi(src, a.owner_of)] > a.heavy;
+        uint64_t todo = __ballot(deal);
+        while (todo != 0ull) {
+            const int l = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1ull;
+            const uint32_t r = (uint32_t)__builtin_amdgcn_readlane((int)src, l);
+            const bool zero = r >= a.M_src;
+            quant_row_to<WIDE_SF>(a, zero ? 0u : r, zero, s_rec[wave], lane, nullptr, 1u, base + l);
+        }
+    }
+}
+
+// One workgroup per compute unit, as many as its sample counters allow.
+static uint32_t owner_groups()
+{
+    const uint32_t cus = compute_units();
+    return cus < OWNER_GROUPS ? cus : OWNER_GROUPS;
+}
+
+// Gather by owners: where every source row is asked for at least twice on average, there are at least four of them per
+// workgroup, and the scan of the index (4 bytes per output row and workgroup, from the L2) and the latency of its
+// phases are small against the rows.  Measured (us, one lane per chunk -> by owners), copies grouped by expert:
+// K = 7168: 8192 rows x 8 123 -> 79, 1024 x 8 16.1 -> 12.1, 512 x 8 9.3 -> 9.7, 4096 x 2 17.5 -> 14.4, 65536 x 8
+// 1054 -> 603; K = 2048: 2048 x 8 10.2 -> 9.3, 1024 x 4 7.7 -> 8.1, 32768 x 8 139 -> 97, 65536 x 2 73 -> 67; K = 1536:
+// 16384 x 8 52 -> 46; K = 1280: 44 -> 45; K = 512: 65536 x 8 67 -> 104.
+static bool gather_by_owners(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q)
+{
+    const int64_t groups = owner_groups();
+    return K >= 1536 && M_src >= 4 * groups && M_src <= OWNER_ROWS * groups && M_out >= 2 * M_src &&
+           M_out <= OWNER_LIST / 2 * groups && M_out * K >= ((int64_t)1 << 25) &&
+           ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) == 0u;
+}
+
 hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
                                  const int32_t *gather_idx, int64_t M_out, uint8_t *q, int64_t ld_q,
                                  uint8_t *sf, int64_t ld_sf, hipStream_t stream)
 {
+    if (gather_idx && gather_by_owners(M_src, K, M_out, q, ld_q)) {
+        QuantOwnerArgs o;
+        o.x = x;
+        o.x_scale = x_scale;
+        o.gather_idx = gather_idx;
+        o.q = q;
+        o.sf = sf;
+        o.ld_q = ld_q;
+        o.ld_sf = ld_sf;
+        o.M_src = (uint32_t)M_src;
+        o.M_out = (uint32_t)M_out;
+        o.K = (uint32_t)K;
+        uint32_t segs_per_row;
+        o.seg = wave_segment(K, &segs_per_row);
+        const uint32_t most = owner_groups();
+        o.rows_per_wg = (uint32_t)((M_src + most - 1) / most);
+        o.owner_of = (uint32_t)((((uint64_t)1 << 32) + o.rows_per_wg - 1) / o.rows_per_wg);
+        const uint32_t groups = (o.M_src + o.rows_per_wg - 1) / o.rows_per_wg;
+        o.heavy = 16u + 4u * (o.M_out / 16u / groups); // every sixteenth index is sampled
+        const bool wide = K % 512 == 0 && ((reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_sf) & 15u) == 0u;
+        if (wide)
+            hipLaunchKernelGGL(quant_from_fp8_owner_kernel<true>, dim3(groups), dim3(OWNER_THREADS), 0, stream, o);
+        else
+            hipLaunchKernelGGL(quant_from_fp8_owner_kernel<false>, dim3(groups), dim3(OWNER_THREADS), 0, stream, o);
+        return hipGetLastError();
+    }
     QuantArgs a;
     a.x = x;
     a.x_scale = x_scale;

@@ -66,3 +66,66 @@ def test_scatter_kernels(K, M, fan, layout):
     mx.mxfp4_quant_from_fp8_scatter(dev(x8), dev(s), dev(dst), M_out, q=q, sf=sf, ld_q=ld_q, ld_sf=ld_sf)
     src, _ = np.nonzero(~nowhere)
     check(buf, at, ld_q, ld_sf, K, dst[~nowhere], wq[src], wsf[src])
+
+
+def index_of(kind, M, n, rng):
+    """int32 [n] gather indices into M source rows."""
+    idx = (np.arange(n) % M).astype(np.int32)
+    rng.shuffle(idx)
+    if kind == "padded":        # every fifth slot unused, some far outside
+        idx[::5] = -1
+        idx[7::50] = M
+        idx[9::50] = 2 ** 31 - 1
+    elif kind == "crowd":       # a quarter of the slots name one row: its owner's rows are dealt out
+        idx[rng.random(n) < 0.25] = 5
+    elif kind == "hidden":      # a crowd where no sample is taken (every sixteenth slot): the list overflows
+        idx[np.arange(n) % 16 != 0] = np.where(rng.random(n) < 0.5, 3, idx)[np.arange(n) % 16 != 0]
+    elif kind == "one":         # all slots name the last row
+        idx[:] = M - 1
+    elif kind == "sorted":
+        idx.sort()
+    return idx
+
+
+@pytest.mark.parametrize("layout", ["records", "planes8"])
+@pytest.mark.parametrize("K,M,n,kind", [
+    (1536, 1024, 21846, "mixed"), (1536, 1024, 21845, "mixed"),                     # work just above and below the rule
+    (1536, 1023, 21846, "mixed"), (1408, 1024, 32768, "mixed"),                     # too few rows; too short rows
+    (2048, 8193, 16387, "sorted"), (2048, 8193, 16385, "sorted"),                   # two copies a row, and just under
+    (1664, 1300, 30001, "padded"), (2048, 1029, 40003, "crowd"), (1536, 1024, 30010, "hidden"),
+    (7808, 1030, 5003, "padded"), (8192, 1024, 4099, "mixed"), (1536, 2047, 24577, "one")])
+def test_gather_by_owners(K, M, n, kind, layout):
+    """Both sides of the rule for gathering by owners, ends of the index that are no whole quad, an index that starts
+    at any multiple of 4 bytes, unused slots, crowds that the sample sees and ones that it does not."""
+    rng, x8, s, wq, wsf = source(M, K, K + n)
+    idx = index_of(kind, M, n, rng)
+    buf, q, sf, ld_q, ld_sf, at = outputs(n, K, layout)
+    padded = torch.zeros(n + 1, dtype=torch.int32, device=DEV)
+    padded[1:] = dev(idx)
+    mx.mxfp4_quant_from_fp8(dev(x8), dev(s), padded[1:], q=q, sf=sf, ld_q=ld_q, ld_sf=ld_sf)
+    src = np.where((idx >= 0) & (idx < M), idx, M)
+    check(buf, at, ld_q, ld_sf, K, np.arange(n), wq[src], wsf[src])
+
+
+def test_gather_by_owners_under_capture():
+    """Replays of a captured gather, with the inputs changed and eager work between the replays."""
+    K, M, n = 2048, 1024, 16384
+    rng, x8, s, _, _ = source(M, K, 1)
+    x, xs = dev(x8), dev(s)
+    idx = dev(index_of("padded", M, n, rng))
+    q, sf = mx.mxfp4_quant_from_fp8(x, xs, idx)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        mx.mxfp4_quant_from_fp8(x, xs, idx, q=q, sf=sf)
+    for i in range(4):
+        y8, ys = synth.student_t_fp8(M, K, seed=10 + i)
+        x.copy_(y8)
+        xs.copy_(ys)
+        idx.copy_(idx.roll(i * 977))
+        want = mx.mxfp4_quant_from_fp8(x, xs, idx)
+        q.zero_()
+        sf.fill_(7)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(q, want[0]) and torch.equal(sf, want[1]), f"replay {i}"
