@@ -180,13 +180,11 @@ __device__ __forceinline__ void quant_segment(const uint8_t *src, const float *s
 #pragma unroll
     for (int u = 0; u < WAVE_CHUNKS; ++u) {
         const uint32_t c = u * 64u + lane;
-        if (c < n_chunks) { // the 8 lanes of a tile pass or fail together
+        w[u] = u32x4{0u, 0u, 0u, 0u};
+        s[u] = 0.0f;
+        if (c < n_chunks && !zero) { // the 8 lanes of a tile pass or fail together
             w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + c * 16u));
             s[u] = src_scale[c >> 3];
-            if (zero) {
-                w[u] = u32x4{0u, 0u, 0u, 0u};
-                s[u] = 0.0f;
-            }
         }
     }
 #pragma unroll
@@ -480,6 +478,7 @@ constexpr int OWNER_WAVES = 16;
 constexpr uint32_t OWNER_THREADS = 64 * OWNER_WAVES;
 constexpr uint32_t OWNER_GROUPS = 512; // workgroups at most: counters of the sample
 constexpr uint32_t OWNER_ROWS = 256;   // source rows of a workgroup at most
+constexpr uint32_t DEALT_ROWS = 8;
 constexpr uint32_t OWNER_LIST = 8192;  // output rows a workgroup sorts; more of them take the unsorted path
 
 struct QuantOwnerArgs {
@@ -499,17 +498,30 @@ struct QuantOwnerArgs {
     uint32_t heavy;      // sampled indices above which an owner's rows are dealt out
 };
 
+// The output rows of `todo` (bit l: row base + l, source row in lane l's src), one after the other by one wave; runs of
+// the same source row, zero rows among them, are quantized once.
 template <bool WIDE_SF>
-__device__ __forceinline__ void quant_row_to(const QuantOwnerArgs &a, uint32_t src_row, bool zero, uint8_t *rec,
-                                             uint32_t lane, const uint32_t *dst, uint32_t n_dst, uint32_t one_dst)
+__device__ __forceinline__ void quant_rows_of(const QuantOwnerArgs &a, const uint64_t todo, uint32_t src, uint32_t base,
+                                              uint8_t *rec, uint32_t lane)
 {
+    if (todo == 0ull)
+        return;
+    src = min(src, a.M_src); // no source row, negative indices included: a zero row
     for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
         const uint32_t n = min(a.seg, a.K - k0);
         RowPieces r;
-        quant_segment<WIDE_SF>(a.x + (size_t)src_row * a.K + k0, a.x_scale + (size_t)src_row * (a.K >> 7) + (k0 >> 7), n,
-                               zero, rec, lane, &r);
-        for (uint32_t j = 0; j < n_dst; ++j) {
-            const uint32_t d = dst ? __builtin_amdgcn_readfirstlane(dst[j]) : one_dst;
+        uint32_t held = 0xFFFFFFFFu;
+        for (uint64_t rest = todo; rest != 0ull; rest &= rest - 1ull) {
+            const int l = __ffsll((unsigned long long)rest) - 1;
+            const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)src, l);
+            if (row != held) {
+                const bool zero = row == a.M_src;
+                const uint32_t from = zero ? 0u : row;
+                quant_segment<WIDE_SF>(a.x + (size_t)from * a.K + k0,
+                                       a.x_scale + (size_t)from * (a.K >> 7) + (k0 >> 7), n, zero, rec, lane, &r);
+                held = row;
+            }
+            const uint32_t d = base + (uint32_t)l;
             store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u, a.sf + (size_t)d * a.ld_sf + k0 / 32u, lane);
         }
     }
@@ -604,40 +616,40 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
         for (uint32_t t = wave; t < n_rows; t += OWNER_WAVES) {
             const uint32_t j0 = __builtin_amdgcn_readfirstlane(s_start[t]);
             const uint32_t j1 = __builtin_amdgcn_readfirstlane(s_start[t + 1u]);
-            if (j0 != j1)
-                quant_row_to<WIDE_SF>(a, row0 + t, false, s_rec[wave], lane, &s_sorted[j0], j1 - j0, 0u);
+            if (j0 == j1)
+                continue;
+            const uint32_t row = row0 + t;
+            for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
+                const uint32_t n = min(a.seg, a.K - k0);
+                RowPieces r;
+                quant_segment<WIDE_SF>(a.x + (size_t)row * a.K + k0,
+                                       a.x_scale + (size_t)row * (a.K >> 7) + (k0 >> 7), n, false, s_rec[wave], lane, &r);
+                for (uint32_t j = j0; j < j1; ++j) {
+                    const uint32_t d = __builtin_amdgcn_readfirstlane(s_sorted[j]);
+                    store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u, a.sf + (size_t)d * a.ld_sf + k0 / 32u,
+                                           lane);
+                }
+            }
         }
     } else if (!shared_out) {
         // more output rows than the list holds although the sample saw no crowd: one after the other
         for (uint32_t base = wave * 64u; base < a.M_out; base += OWNER_THREADS) {
             const uint32_t out = base + lane;
             const uint32_t src = out < a.M_out ? (uint32_t)a.gather_idx[out] : 0xFFFFFFFFu;
-            uint64_t mine = __ballot(src - row0 < n_rows);
-            while (mine != 0ull) {
-                const int l = __ffsll((unsigned long long)mine) - 1;
-                mine &= mine - 1ull;
-                quant_row_to<WIDE_SF>(a, (uint32_t)__builtin_amdgcn_readlane((int)src, l), false, s_rec[wave], lane,
-                                      nullptr, 1u, base + l);
-            }
+            quant_rows_of<WIDE_SF>(a, __ballot(src - row0 < n_rows), src, base, s_rec[wave], lane);
         }
     }
 
-    // ---- the rows that are dealt out by output row: 64 consecutive ones per wave
-    for (uint32_t base = (blockIdx.x + wave * gridDim.x) * 64u; base < a.M_out; base += gridDim.x * OWNER_THREADS) {
+    // ---- the rows that are dealt out by output row, a few consecutive ones per wave
+    for (uint32_t base = (blockIdx.x * OWNER_WAVES + wave) * DEALT_ROWS; base < a.M_out;
+         base += gridDim.x * OWNER_WAVES * DEALT_ROWS) {
         const uint32_t out = base + lane;
-        const uint32_t src = out < a.M_out ? (uint32_t)a.gather_idx[out] : 0u;
-        const bool none = src >= a.M_src; // also negative: a zero row
-        bool deal = none && out < a.M_out;
-        if (!none && out < a.M_out)
+        const bool there = lane < DEALT_ROWS && out < a.M_out;
+        const uint32_t src = there ? (uint32_t)a.gather_idx[out] : 0u;
+        bool deal = there && src >= a.M_src; // also negative: a zero row
+        if (there && src < a.M_src)
             deal = s_sample[__umulhi(src, a.owner_of)] > a.heavy;
-        uint64_t todo = __ballot(deal);
-        while (todo != 0ull) {
-            const int l = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1ull;
-            const uint32_t r = (uint32_t)__builtin_amdgcn_readlane((int)src, l);
-            const bool zero = r >= a.M_src;
-            quant_row_to<WIDE_SF>(a, zero ? 0u : r, zero, s_rec[wave], lane, nullptr, 1u, base + l);
-        }
+        quant_rows_of<WIDE_SF>(a, __ballot(deal), src, base, s_rec[wave], lane);
     }
 }
 
