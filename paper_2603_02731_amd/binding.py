@@ -1,16 +1,23 @@
-"""ctypes binding of libmxfp4 (include/mxfp4.h): argument marshalling only.
+"""Python binding of libmxfp4 (include/mxfp4.h): argument marshalling only.
 
 Every step of the conversions runs in the HIP kernels of the library.  PyTorch is used for
 device memory and streams, nothing else; there is no CPU or eager fallback: if the library
 is missing or cannot be loaded the calls raise.
+
+Each wrapper first hands its arguments to its native counterpart (csrc/call_path.cpp), which
+checks, allocates and calls the library for the plain case and returns None, with nothing
+launched, for any other; the wrapper then does the same in Python and raises where it has to.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmxfp4.so")
+CALL_PATH = os.path.join(_HERE, "_call_path.so")
 
 OK, ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_OFFSETS, ERR_LAUNCH = 0, -1, -2, -3, -4, -5
 
@@ -19,7 +26,13 @@ EXPORTS = ("mxfp4_quant_from_fp8", "mxfp4_quant_from_fp8_scatter", "mxfp4_quant_
            "mxfp4_row_to_fp8_col_grouped", "mxfp4_row_to_fp8_col_requant", "mxfp4_row_to_fp8_col_requant_grouped",
            "mxfp4_stream_copy", "mxfp4_stream_mix", "mxfp4_tile_copy", "mxfp4_record_fanout", "mxfp4_status_string")
 
+# the order in which csrc/call_path.cpp holds the entry points
+_NATIVE = ("mxfp4_quant_from_fp8", "mxfp4_quant_from_fp8_scatter", "mxfp4_quant_from_bf16", "mxfp4_dequant_to_fp8",
+           "mxfp4_row_to_col", "mxfp4_quant_from_fp8_grouped", "mxfp4_row_to_col_grouped", "mxfp4_row_to_fp8_col",
+           "mxfp4_row_to_fp8_col_requant", "mxfp4_row_to_fp8_col_grouped", "mxfp4_row_to_fp8_col_requant_grouped")
+
 _lib = None
+_call = None  # the native call path, loaded with the library
 _vp, _i64, _i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
 
 
@@ -31,7 +44,7 @@ class Mxfp4Error(RuntimeError):
 
 def lib():
     """Load libmxfp4.so (built in-tree by paper_2603_02731_amd/build.py)."""
-    global _lib
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             from . import build as _build
@@ -56,6 +69,11 @@ def lib():
             getattr(L, n).restype = ctypes.c_int
         L.mxfp4_status_string.argtypes = [ctypes.c_int]
         L.mxfp4_status_string.restype = ctypes.c_char_p
+        if os.path.exists(CALL_PATH):
+            loader = importlib.machinery.ExtensionFileLoader("_call_path", CALL_PATH)
+            module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_call_path", loader))
+            module.bind(*(ctypes.cast(getattr(L, n), _vp).value for n in _NATIVE))
+            _call = module
         _lib = L
     return _lib
 
@@ -159,6 +177,10 @@ def mxfp4_quant_from_fp8(x, x_scale, gather_idx=None, q=None, sf=None, ld_q=None
     """x uint8 [M_src,K] (E4M3), x_scale float32 [M_src,K/128] -> (q uint8 [M_out,K/2], sf uint8 [M_out,K/32]).
     gather_idx: optional int32 [M_out].  q/sf may be preallocated; with ld_q/ld_sf they may be views
     into a record buffer (row strides in bytes) that reach from their first byte to the end of the last row."""
+    if _call is not None:
+        done = _call.quant_from_fp8(x, x_scale, gather_idx, q, sf, ld_q, ld_sf, stream)
+        if done is not None:
+            return done
     M_src, K = _matrix(x, torch.uint8, "x", 128)
     _buf(x_scale, torch.float32, "x_scale", shape=(M_src, K // 128))
     if gather_idx is not None:
@@ -180,6 +202,10 @@ def mxfp4_quant_from_fp8(x, x_scale, gather_idx=None, q=None, sf=None, ld_q=None
 def mxfp4_quant_from_fp8_scatter(x, x_scale, dst_idx, M_out, q=None, sf=None, ld_q=None, ld_sf=None, stream=None):
     """Source row i of x -> output rows dst_idx[i, :] (int32 [M_src, fanout]; entries outside [0, M_out) are
     skipped).  Newly allocated q/sf are zero-filled, since rows that no entry names are not written."""
+    if _call is not None:
+        done = _call.quant_from_fp8_scatter(x, x_scale, dst_idx, M_out, q, sf, ld_q, ld_sf, stream)
+        if done is not None:
+            return done
     M_src, K = _matrix(x, torch.uint8, "x", 128)
     _buf(x_scale, torch.float32, "x_scale", shape=(M_src, K // 128))
     _buf(dst_idx, torch.int32, "dst_idx")
@@ -199,6 +225,10 @@ def mxfp4_quant_from_fp8_scatter(x, x_scale, dst_idx, M_out, q=None, sf=None, ld
 
 def mxfp4_quant_from_bf16(x, q=None, sf=None, ld_q=None, ld_sf=None, stream=None):
     """x bfloat16 [M,K] -> (q uint8 [M,K/2], sf uint8 [M,K/32])."""
+    if _call is not None:
+        done = _call.quant_from_bf16(x, q, sf, ld_q, ld_sf, stream)
+        if done is not None:
+            return done
     M, K = _matrix(x, torch.bfloat16, "x", 128)
     q, sf, ld_q, ld_sf = _quant_outputs(x, M, K, q, sf, ld_q, ld_sf, torch.empty)
     dev = _on_device(x=x, q=q, sf=sf)
@@ -211,6 +241,10 @@ def mxfp4_dequant_to_fp8(q, sf, M=None, K=None, ld_q=None, ld_sf=None, x=None, x
     """q uint8 [M,K/2], sf uint8 [M,K/32] -> (x uint8 [M,K] E4M3, x_scale float32 [M,K/128]).
     With M, K, ld_q, ld_sf the inputs may be views into a record buffer (row strides in bytes) that reach
     from their first byte to the end of the last row."""
+    if _call is not None:
+        done = _call.dequant_to_fp8(q, sf, M, K, ld_q, ld_sf, x, x_scale, stream)
+        if done is not None:
+            return done
     if M is None or K is None:
         if M is not None or K is not None or ld_q is not None or ld_sf is not None:
             raise ValueError("M and K go together; row strides need both")
@@ -277,6 +311,10 @@ def _experts(expert_offsets, M, offsets_host, units):
 
 def mxfp4_row_to_col(q_row, sf_row, q_col=None, sf_col=None, stream=None):
     """[M,K/2] + [M,K/32] row-blocked -> column-blocked, stored transposed ([K,M/2], [K,M/32])."""
+    if _call is not None:
+        done = _call.row_to_col(q_row, sf_row, q_col, sf_col, stream)
+        if done is not None:
+            return done
     M, K = _row_blocked(q_row, sf_row)
     if M % 32 != 0:
         raise ValueError(f"M must be a multiple of 32, got {M}")
@@ -290,6 +328,10 @@ def mxfp4_row_to_col(q_row, sf_row, q_col=None, sf_col=None, stream=None):
 
 
 def mxfp4_quant_from_fp8_grouped(x, x_scale, expert_offsets, q=None, sf=None, stream=None):
+    if _call is not None:
+        done = _call.quant_from_fp8_grouped(x, x_scale, expert_offsets, q, sf, stream)
+        if done is not None:
+            return done
     M, K = _matrix(x, torch.uint8, "x", 128)
     _buf(x_scale, torch.float32, "x_scale", shape=(M, K // 128))
     _experts(expert_offsets, M, None, ())
@@ -307,6 +349,10 @@ def mxfp4_row_to_col_grouped(q_row, sf_row, expert_offsets, q_col=None, sf_col=N
     at K*sum_{j<e} ceil(T_j/32) (K*off_e/2 and K*off_e/32 for multiples of 32); any T_e.  Buffers allocated here,
     and buffers passed without `offsets_host` (the same offsets as host integers), must have the upper-bound
     sizes K*(M//2 + num_experts) and K*(M//32 + num_experts); with `offsets_host` the exact sizes are enough."""
+    if _call is not None and offsets_host is None:
+        done = _call.row_to_col_grouped(q_row, sf_row, expert_offsets, q_col, sf_col, stream)
+        if done is not None:
+            return done
     M, K = _row_blocked(q_row, sf_row)
     E, (n2, n32) = _experts(expert_offsets, M, offsets_host, (2, 32))
     q_col = _out(q_col, torch.uint8, "q_col", q_row, K * n2)
@@ -321,6 +367,10 @@ def mxfp4_row_to_col_grouped(q_row, sf_row, expert_offsets, q_col=None, sf_col=N
 def mxfp4_row_to_fp8_col(q_row, sf_row, x_col=None, x_col_scale=None, stream=None, requant=False):
     """[M,K/2] + [M,K/32] row-blocked MXFP4 -> the transposed matrix as FP8: (E4M3 [K,M], float32 [K,M/128]).
     requant=True calls mxfp4_row_to_fp8_col_requant (scale from the group maximum)."""
+    if _call is not None:
+        done = _call.row_to_fp8_col(q_row, sf_row, x_col, x_col_scale, stream, requant)
+        if done is not None:
+            return done
     M, K = _row_blocked(q_row, sf_row)
     if M % 128 != 0:
         raise ValueError(f"M must be a multiple of 128, got {M}")
@@ -338,6 +388,10 @@ def mxfp4_row_to_fp8_col_grouped(q_row, sf_row, expert_offsets, x_col=None, x_co
     """Outputs are flat buffers: expert e's [K,T_e] at K*off_e, its float32 [K,ceil(T_e/128)] at
     K*sum_{j<e} ceil(T_j/128); any T_e.  A scale buffer allocated here, or passed without `offsets_host` (the
     same offsets as host integers), must have the upper-bound size K*(M//128 + num_experts)."""
+    if _call is not None and offsets_host is None:
+        done = _call.row_to_fp8_col_grouped(q_row, sf_row, expert_offsets, x_col, x_col_scale, stream, requant)
+        if done is not None:
+            return done
     M, K = _row_blocked(q_row, sf_row)
     E, (n128,) = _experts(expert_offsets, M, offsets_host, (128,))
     x_col = _out(x_col, torch.uint8, "x_col", q_row, M * K)

@@ -1,11 +1,14 @@
-"""Compile the gfx950 kernels and their C ABI into paper_2603_02731_amd/libmxfp4.so (in-tree)."""
+"""Compile the gfx950 kernels and their C ABI into paper_2603_02731_amd/libmxfp4.so, and the native half of the Python
+binding into paper_2603_02731_amd/_call_path.so (both in-tree)."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmxfp4.so")
+CALL_PATH = os.path.join(HERE, "_call_path.so")
 SOURCES = ["mxfp4_api.hip", "quant_from_fp8.hip", "quant_from_bf16.hip", "dequant_to_fp8.hip", "row_to_col.hip",
            "row_to_fp8_col.hip", "row_to_fp8_col_requant.hip", "stream_copy.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -18,23 +21,48 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wal
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-def _deps():
-    out = [os.path.join(CSRC, f) for f in os.listdir(CSRC)]
+
+def _deps(ends):
+    out = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(ends)]
     out.append(os.path.join(os.path.dirname(HERE), "include", "mxfp4.h"))
     return out
 
 
-def build(force: bool = True) -> str:
-    if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in _deps()):
-        return LIB
-    cmd = [HIPCC] + FLAGS + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB + ".tmp"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
+def _run(cmd, target):
+    r = subprocess.run(cmd + ["-o", target + ".tmp"], capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + err)
     if err.strip():
         sys.stderr.write(err + "\n")
-    os.replace(LIB + ".tmp", LIB)
+    os.replace(target + ".tmp", target)
+
+
+def _fresh(target, deps):
+    return os.path.exists(target) and all(os.path.getmtime(target) >= os.path.getmtime(d) for d in deps)
+
+
+def build_call_path(force: bool = True) -> str:
+    """Host code only: compiled against the headers of the PyTorch that will load it."""
+    import torch
+    if not force and _fresh(CALL_PATH, _deps(".cpp")):
+        return CALL_PATH
+    t = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
+           os.path.join(CSRC, "call_path.cpp"), "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
+           "-ltorch", "-ltorch_python", "-Wall"]
+    _run(cmd, CALL_PATH)
+    return CALL_PATH
+
+
+def build(force: bool = True) -> str:
+    if force or not _fresh(LIB, _deps((".hip", ".hpp"))):
+        _run([HIPCC] + FLAGS + [os.path.join(CSRC, s) for s in SOURCES], LIB)
+    build_call_path(force)
     return LIB
 
 
