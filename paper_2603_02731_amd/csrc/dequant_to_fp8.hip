@@ -23,7 +23,7 @@
 namespace mxfp4 {
 
 // Cache policy and launch shape, measured at [65536,7168] over rotated buffer sets (every byte from and to HBM).
-// Non-temporal loads; the E4M3 bytes, two thirds of the traffic and written in address order by the whole grid,
+// Non-temporal loads (above KEEP_BYTES of nibbles); the E4M3 bytes, two thirds of the traffic and written in address order by the whole grid,
 // leave with streaming stores (store_streaming): 111 us, against 115 us with the non-temporal hint alone and
 // 114 us with plain loads.  The 4-byte tile scales must not be streamed (146 us).  128 lanes x 2 runs per
 // workgroup: 256 x 2 111.4, 512 x 2 112.1, 128 x 4 117, 256 x 4 119, 1024 x 1 129 us (one load in flight per lane
@@ -152,7 +152,8 @@ struct DequantArgs {
 // One workgroup covers DEQUANT_UNROLL runs of DEQUANT_THREADS consecutive half-blocks; a lane takes
 // half-block `tid` of each run: 512 B loaded and 1 KiB stored per wave instruction, both
 // contiguous, which is what lets the stores go out non-temporally at full rate.
-template <bool DENSE>
+// KEEP: at most KEEP_BYTES of nibbles, left in the memory-side cache for their next reader.
+template <bool DENSE, bool KEEP>
 __global__ void __launch_bounds__(DEQUANT_THREADS) dequant_to_fp8_kernel(const DequantArgs a)
 {
     const uint32_t c0 = blockIdx.x * (DEQUANT_THREADS * DEQUANT_UNROLL) + threadIdx.x;
@@ -175,7 +176,10 @@ __global__ void __launch_bounds__(DEQUANT_THREADS) dequant_to_fp8_kernel(const D
             src = a.q + (size_t)row * a.ld_q + (size_t)ch * 8;
             src_sf = a.sf + (size_t)row * a.ld_sf + (ch >> 1);
         }
-        w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(src));
+        if (KEEP)
+            w[u] = *reinterpret_cast<const u32x2 *>(src);
+        else
+            w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(src));
         sfb[u] = *src_sf;
     }
 
@@ -212,10 +216,10 @@ hipError_t launch_dequant_to_fp8(const uint8_t *q, int64_t ld_q, const uint8_t *
     constexpr uint32_t per_block = DEQUANT_THREADS * DEQUANT_UNROLL;
     const uint32_t blocks = (a.n_halves + per_block - 1) / per_block;
     const bool dense = ld_q == K / 2 && ld_sf == K / 32;
-    if (dense)
-        hipLaunchKernelGGL(dequant_to_fp8_kernel<true>, dim3(blocks), dim3(DEQUANT_THREADS), 0, stream, a);
-    else
-        hipLaunchKernelGGL(dequant_to_fp8_kernel<false>, dim3(blocks), dim3(DEQUANT_THREADS), 0, stream, a);
+    const bool keep = M * (K / 2) <= KEEP_BYTES;
+    const auto kernel = dense ? (keep ? dequant_to_fp8_kernel<true, true> : dequant_to_fp8_kernel<true, false>)
+                              : (keep ? dequant_to_fp8_kernel<false, true> : dequant_to_fp8_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(DEQUANT_THREADS), 0, stream, a);
     return hipGetLastError();
 }
 

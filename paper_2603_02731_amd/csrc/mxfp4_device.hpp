@@ -280,6 +280,22 @@ __device__ __forceinline__ void store_streaming(void *p, u32x4 v)
     asm volatile("global_store_dwordx4 %0, %1, off sc1 nt" : : "v"(p), "v"(v) : "memory");
 }
 
+// A packed matrix (its nibble bytes) up to this size is expected to be read again from the 256 MB memory-side cache:
+// what is quantized is then de-quantized and transposed.  The dense quantizer sends such nibbles off with
+// store_through, which passes them on like a streaming store but leaves them in that cache, and the de-quantizer reads
+// them without the non-temporal hint, so that they stay there for the next reader.  Quantize, de-quantize, transpose
+// in this order (us, hints everywhere -> this; the same with warm and with cold inputs): [4096,7168] 29.0 -> 26.0,
+// [8192,7168] 50.8 -> 42.2, [16384,7168] 88.0 -> 76.4, [16384,2048] 30.9 -> 27.4.  Alone, cold: quantizer 9.7 -> 9.9,
+// 16.2 -> 16.3, 29.5 -> 29.7; de-quantizer 9.9 -> 10.0, 17.1 -> 17.3, 30.3 -> 30.9 (warm 8.8 -> 7.9, 17.1 -> 14.0,
+// 30.5 -> 26.4).  Above, the chain still gains but the single kernels lose: [32768,7168] 55.6 -> 57.9 and 57.1 -> 58.8.
+constexpr int64_t KEEP_BYTES = (int64_t)64 << 20;
+
+// Write-through at device scope (sc1) without the non-temporal hint.
+__device__ __forceinline__ void store_through(void *p, u32x2 v)
+{
+    asm volatile("global_store_dwordx2 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+}
+
 // The first n (1..15) bytes of v to dst, any alignment, in at most four pieces.
 __device__ __forceinline__ void store_head_bytes(uint8_t *dst, const u32x4 v, uint32_t n)
 {

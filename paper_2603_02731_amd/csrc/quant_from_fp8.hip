@@ -89,7 +89,8 @@ __device__ __forceinline__ void quant16(const u32x4 w, float s, uint32_t out[2],
 // `tid` of each run, so every load and store instruction of a wave stays contiguous
 // (1 KiB in, 512 B out) while each lane keeps QUANT_UNROLL loads in flight.
 // DENSE: no gather and dense outputs -- every address is a multiple of the flat chunk index.
-template <bool DENSE, bool GATHER, int THREADS>
+// KEEP: a dense output of at most KEEP_BYTES, left in the memory-side cache.
+template <bool DENSE, bool GATHER, bool KEEP, int THREADS>
 __global__ void __launch_bounds__(THREADS) quant_from_fp8_kernel(const QuantArgs a)
 {
     const uint32_t c0 = blockIdx.x * (THREADS * QUANT_UNROLL) + threadIdx.x;
@@ -142,7 +143,10 @@ __global__ void __launch_bounds__(THREADS) quant_from_fp8_kernel(const QuantArgs
             break;
         uint32_t out[2], b;
         quant16(w[u], s[u], out, &b);
-        __builtin_nontemporal_store(u32x2{out[0], out[1]}, reinterpret_cast<u32x2 *>(dst_q[u]));
+        if (KEEP)
+            store_through(dst_q[u], u32x2{out[0], out[1]});
+        else
+            __builtin_nontemporal_store(u32x2{out[0], out[1]}, reinterpret_cast<u32x2 *>(dst_q[u]));
 
         // lanes 2j, 2j+1 of the tile's 8 hold block j's byte: gather the four into lane 0
         uint32_t t = b | (dpp_read<DPP_QUAD_XOR2>(b) << 8); // lanes 0,1: B0 | B1 << 8
@@ -719,14 +723,17 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
     const bool dense = gather_idx == nullptr && ld_q == K / 2 && ld_sf == K / 32;
     const uint32_t per_block = (dense ? QUANT_THREADS : QUANT_THREADS_ROUTED) * QUANT_UNROLL;
     const uint32_t blocks = (a.n_chunks + per_block - 1) / per_block;
-    if (dense)
-        hipLaunchKernelGGL((quant_from_fp8_kernel<true, false, QUANT_THREADS>), dim3(blocks), dim3(QUANT_THREADS), 0,
+    if (dense && M_out * (K / 2) <= KEEP_BYTES)
+        hipLaunchKernelGGL((quant_from_fp8_kernel<true, false, true, QUANT_THREADS>), dim3(blocks), dim3(QUANT_THREADS), 0,
+                           stream, a);
+    else if (dense)
+        hipLaunchKernelGGL((quant_from_fp8_kernel<true, false, false, QUANT_THREADS>), dim3(blocks), dim3(QUANT_THREADS), 0,
                            stream, a);
     else if (gather_idx)
-        hipLaunchKernelGGL((quant_from_fp8_kernel<false, true, QUANT_THREADS_ROUTED>), dim3(blocks),
+        hipLaunchKernelGGL((quant_from_fp8_kernel<false, true, false, QUANT_THREADS_ROUTED>), dim3(blocks),
                            dim3(QUANT_THREADS_ROUTED), 0, stream, a);
     else
-        hipLaunchKernelGGL((quant_from_fp8_kernel<false, false, QUANT_THREADS_ROUTED>), dim3(blocks),
+        hipLaunchKernelGGL((quant_from_fp8_kernel<false, false, false, QUANT_THREADS_ROUTED>), dim3(blocks),
                            dim3(QUANT_THREADS_ROUTED), 0, stream, a);
     return hipGetLastError();
 }
