@@ -147,6 +147,7 @@ struct DequantArgs {
     int64_t ld_sf;
     uint32_t n_halves;      // M * K / 16
     uint32_t halves_per_row; // K / 16
+    FastDiv row_of;          // by halves_per_row
 };
 
 // One workgroup covers DEQUANT_UNROLL runs of DEQUANT_THREADS consecutive half-blocks; a lane takes
@@ -171,7 +172,7 @@ __global__ void __launch_bounds__(DEQUANT_THREADS) dequant_to_fp8_kernel(const D
             src = a.q + (size_t)c * 8;
             src_sf = a.sf + (c >> 1);
         } else {
-            const uint32_t row = c / a.halves_per_row;
+            const uint32_t row = a.row_of(c);
             const uint32_t ch = c - row * a.halves_per_row;
             src = a.q + (size_t)row * a.ld_q + (size_t)ch * 8;
             src_sf = a.sf + (size_t)row * a.ld_sf + (ch >> 1);
@@ -213,6 +214,7 @@ hipError_t launch_dequant_to_fp8(const uint8_t *q, int64_t ld_q, const uint8_t *
     a.ld_sf = ld_sf;
     a.n_halves = (uint32_t)(M * (K / 16));
     a.halves_per_row = (uint32_t)(K / 16);
+    a.row_of = FastDiv(a.halves_per_row);
     constexpr uint32_t per_block = DEQUANT_THREADS * DEQUANT_UNROLL;
     const uint32_t blocks = (a.n_halves + per_block - 1) / per_block;
     const bool dense = ld_q == K / 2 && ld_sf == K / 32;

@@ -27,6 +27,7 @@ struct QuantBf16Args {
     int64_t ld_sf;
     uint32_t n_chunks;       // M * K / 8
     uint32_t chunks_per_row; // K / 8
+    FastDiv row_of;          // by chunks_per_row
 };
 
 template <bool DENSE>
@@ -75,7 +76,7 @@ __global__ void __launch_bounds__(QBF_THREADS) quant_from_bf16_kernel(const Quan
             dst_q = a.q + (size_t)c * 4;
             dst_sf = a.sf + (size_t)(c >> 4) * 4;
         } else {
-            const uint32_t row = c / a.chunks_per_row;
+            const uint32_t row = a.row_of(c);
             const uint32_t cc = c - row * a.chunks_per_row;
             dst_q = a.q + (size_t)row * a.ld_q + (size_t)cc * 4;
             dst_sf = a.sf + (size_t)row * a.ld_sf + (size_t)(cc >> 4) * 4;
@@ -101,6 +102,7 @@ hipError_t launch_quant_from_bf16(const uint16_t *x, int64_t M, int64_t K, uint8
     a.ld_sf = ld_sf;
     a.n_chunks = (uint32_t)(M * (K / 8));
     a.chunks_per_row = (uint32_t)(K / 8);
+    a.row_of = FastDiv(a.chunks_per_row);
     constexpr uint32_t per_block = QBF_THREADS * QBF_UNROLL;
     const uint32_t blocks = (a.n_chunks + per_block - 1) / per_block;
     if (ld_q == K / 2 && ld_sf == K / 32)

@@ -38,6 +38,7 @@ struct QuantArgs {
     int64_t ld_sf;
     uint32_t n_chunks;       // M_out * K / 16
     uint32_t chunks_per_row; // K / 16
+    FastDiv row_of;          // by chunks_per_row
     uint32_t K;
     uint32_t M_src;
 };
@@ -113,7 +114,7 @@ __global__ void __launch_bounds__(THREADS) quant_from_fp8_kernel(const QuantArgs
             dst_q[u] = a.q + (size_t)c * 8;
             dst_sf[u] = a.sf + (size_t)(c >> 3) * 4;
         } else {
-            const uint32_t row = c / a.chunks_per_row;
+            const uint32_t row = a.row_of(c);
             const uint32_t cc = c - row * a.chunks_per_row;
             uint32_t src_row = row;
             if (GATHER) {
@@ -255,6 +256,7 @@ struct QuantScatterArgs {
     int64_t ld_sf;
     uint32_t n_chunks;       // M_src * K / 16
     uint32_t chunks_per_row; // K / 16
+    FastDiv row_of;          // by chunks_per_row
     uint32_t fanout;
     uint32_t M_out;
 };
@@ -285,7 +287,7 @@ __global__ void __launch_bounds__(QUANT_THREADS_ROUTED) quant_from_fp8_scatter_k
         uint32_t t = b | (dpp_read<DPP_QUAD_XOR2>(b) << 8); // lanes 0,1: B0 | B1 << 8
         t |= row_shift_left4(t) << 16;                       // lane 0: ... | B2 << 16 | B3 << 24
 
-        const uint32_t row = c / a.chunks_per_row;
+        const uint32_t row = a.row_of(c);
         const uint32_t cc = c - row * a.chunks_per_row;
         const int32_t *dst = a.dst_idx + (size_t)row * a.fanout;
         // the destinations are read eight at a time before any store: a store (bytes, may alias
@@ -426,6 +428,7 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     a.ld_sf = ld_sf;
     a.n_chunks = (uint32_t)(M_src * (K / 16));
     a.chunks_per_row = (uint32_t)(K / 16);
+    a.row_of = FastDiv(a.chunks_per_row);
     a.fanout = (uint32_t)fanout;
     a.M_out = (uint32_t)M_out;
     const bool nib16 = ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) == 0u;
@@ -718,6 +721,7 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
     a.ld_sf = ld_sf;
     a.n_chunks = (uint32_t)(M_out * (K / 16));
     a.chunks_per_row = (uint32_t)(K / 16);
+    a.row_of = FastDiv(a.chunks_per_row);
     a.K = (uint32_t)K;
     a.M_src = (uint32_t)M_src;
     const bool dense = gather_idx == nullptr && ld_q == K / 2 && ld_sf == K / 32;
