@@ -466,7 +466,18 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
     const uint32_t total = a.tiles_m * a.tiles_k;
     a.stage_in = total >= 3u * compute_units() ? 1u : 0u; // at least 3 tiles per compute unit
     const dim3 grid((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD);
-    hipLaunchKernelGGL(row_to_col_kernel, grid, dim3(T_THREADS), 0, stream, a);
+    // Un-padded splits: k-rows start at any byte, and every tile shares its outer 64-byte segments with its neighbours.  The
+    // two halves meet in the L2 if the tiles finish close together; what leaves it half written costs the memory a
+    // read, modify and write, once the matrix is too large for the 256 MB memory-side cache.  Three workgroups per compute
+    // unit instead of four keep less in flight between the halves.  Measured (us, four -> three, Zipf-sized experts of any
+    // length): [65536,7168] in 32 154.5 -> 137.1, 16 150 -> 130, 64 148 -> 132; [32768,7168] in 16 73.1 -> 68.9, 32 75.8 ->
+    // 73.9; [65536,4096] in 32 88.5 -> 81.5.  Smaller matrices (40.6 -> 41.4 at [32768,4096]), splits of 512 rows (143 ->
+    // 150) and padded ones (95.3 -> 96.8) do not gain: total rows that are no multiple of 128 tell that some split is
+    // not padded to whole tile halves.
+    const bool unpadded = expert_offsets && M % 128 != 0;
+    const bool three_per_cu = unpadded && M >= 1024 * (int64_t)num_experts && M * K >= (int64_t)32768 * 7168;
+    constexpr uint32_t LDS_FOR_THREE = 52u * 1024u, LDS_STATIC = 37376u; // a compute unit has 160 KiB
+    hipLaunchKernelGGL(row_to_col_kernel, grid, dim3(T_THREADS), three_per_cu ? LDS_FOR_THREE - LDS_STATIC : 0u, stream, a);
     return hipGetLastError();
 }
 
