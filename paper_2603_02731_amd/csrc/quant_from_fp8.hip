@@ -162,7 +162,11 @@ __global__ void __launch_bounds__(THREADS) quant_from_fp8_kernel(const QuantArgs
 //
 // A wave quantizes a segment of at most WAVE_SEG elements of one source row into its own 4 KiB of LDS (nibble bytes
 // then scale bytes, as they sit in a per-token record), takes the finished bytes back as 16-byte pieces and writes
-// them to every destination row.  No barrier: the waves of a workgroup are independent.
+// them to every destination row.  No barrier: the waves of a workgroup are independent, which is what short rows need:
+// with a workgroup of 512 lanes per 2048 elements three quarters of the lanes idle and every row waits for a barrier
+// (65536 such rows, two copies each: 127 us; this form 49 us = 5.2 TB/s).  Bound by the writes; the pieces leave with
+// non-temporal stores (65536 x 7168 gathered to eight records each: 603 us, plain stores 653; 16384 rows of 1536 the other
+// way round, 46 against 43).
 constexpr uint32_t WAVE_SEG = 7680; // 240 nibble pieces and 15 scale pieces: at most four 16-byte pieces per lane
 constexpr int WAVE_CHUNKS = 8;      // 16-element chunks per lane
 constexpr int WAVE_PIECES = 4;
@@ -343,6 +347,9 @@ __global__ void __launch_bounds__(64 * SCATTER_WAVES) quant_from_fp8_scatter_wav
 // K/32 scale bytes, as they sit in a per-token record) and writes it to each destination in 16-byte pieces, the
 // whole row by one instruction per wave.  The pieces are dealt to the lanes so that every wave instruction starts
 // on a 128-byte line of its destination (records of 3808 bytes start at any multiple of 32).
+// Bound by the writes to many places: 65536 tokens of 7168, eight copies grouped by expert 508 -> 479 us = 5.2 TB/s with the
+// pieces dealt that way (shuffled copies 553 -> 511; a kernel that only copies finished records: 477 and 500); 256 lanes and
+// four workgroups per compute unit 484, 1024 lanes 584, one wave per row 520.
 constexpr int SCATTER_THREADS = 512;
 
 template <bool WIDE_SF> // the K/32 scale bytes of a row are a whole number of 16-byte pieces (K % 512 == 0)
@@ -481,6 +488,12 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
 // one and the same index, say) the owner of such rows would work on alone: every workgroup counts a sample of the
 // index per owner while it scans, all see the same counts, and the rows of an owner with several times its share
 // (and the zero rows of indices that name no source row) are dealt out by output row instead.
+// Bound by the writes: 8192 rows of 7168 to eight records each 78 us = 4.0 TB/s of what has to move (lane-wise 115, where
+// half is reading every row eight times from the memory-side cache and a quarter quantizing it as often; the scatter form
+// of the same routing 60 us, without the scan and with four workgroups per compute unit).  One workgroup of 16 waves
+// per compute unit (110 registers): two of them at 64 registers spill, 93 us.  Skewed maps of 65536 slots (lane-wise / by
+// owners): half of the slots unused 88 / 79, a quarter naming one row 101 / 90, all naming one row 86 / 64; slots that name
+// 512 of the 8192 rows at random 94 / 117 and a power law 97 / 129 are what the dealing does not pay for.
 constexpr int OWNER_WAVES = 16;
 constexpr uint32_t OWNER_THREADS = 64 * OWNER_WAVES;
 constexpr uint32_t OWNER_GROUPS = 512; // workgroups at most: counters of the sample
