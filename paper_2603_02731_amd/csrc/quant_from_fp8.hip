@@ -680,18 +680,23 @@ static uint32_t owner_groups()
     return cus < OWNER_GROUPS ? cus : OWNER_GROUPS;
 }
 
-// Gather by owners: where every source row is asked for at least twice on average, there are at least four of them per
-// workgroup, and the scan of the index (4 bytes per output row and workgroup, from the L2) and the latency of its
-// phases are small against the rows.  Measured (us, one lane per chunk -> by owners), copies grouped by expert:
-// K = 7168: 8192 rows x 8 123 -> 79, 1024 x 8 16.1 -> 12.1, 512 x 8 9.3 -> 9.7, 4096 x 2 17.5 -> 14.4, 65536 x 8
-// 1054 -> 603; K = 2048: 2048 x 8 10.2 -> 9.3, 1024 x 4 7.7 -> 8.1, 32768 x 8 139 -> 97, 65536 x 2 73 -> 67; K = 1536:
-// 16384 x 8 52 -> 46; K = 1280: 44 -> 45; K = 512: 65536 x 8 67 -> 104.
+// Gather by owners: where every source row is asked for at least twice on average and there are at least four of them per
+// workgroup, if what it saves exceeds its phases, its waves' time per row and the scan of the index (4 bytes per output row
+// and workgroup, from the L2).  Per million elements the lane-wise kernel takes 0.245 us of output, this one 0.106 us of
+// output and 0.158 us of source, 0.124 us per thousand source rows and some 3 us to begin with, 5 where rows are short.
+// Measured (us, one lane per chunk -> by owners), copies grouped by expert: K = 7168: 8192 rows x 8 115 -> 78, 1929 x 3 12.2
+// -> 10.4, 4179 x 2 17.0 -> 15.8, 65536 x 8 1054 -> 603; K = 3584: 1639 x 8 12.7 -> 11.0, 13111 x 2 26.3 -> 25.2, but 8358 x 2
+// 17.0 -> 18.1; K = 2560: 2295 x 8 12.6 -> 12.5, 45886 x 2 65.2 -> 64.0, but 18355 x 2 25.3 -> 26.9; K = 2048: 2868 x 8 12.2 ->
+// 11.3, 57357 x 2 65.2 -> 61.7, but 22943 x 2 25.0 -> 26.1; K = 1536: 9560 x 8 29.2 -> 28.6, but 6798 x 5 15.0 -> 15.9; K = 512:
+// 65536 x 8 67 -> 104.
 static bool gather_by_owners(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q)
 {
     const int64_t groups = owner_groups();
-    return K >= 1536 && M_src >= 4 * groups && M_src <= OWNER_ROWS * groups && M_out >= 2 * M_src &&
-           M_out <= OWNER_LIST / 2 * groups && M_out * K >= ((int64_t)1 << 25) &&
-           ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) == 0u;
+    if (K < 2048 || M_src < 4 * groups || M_src > OWNER_ROWS * groups || M_out < 2 * M_src ||
+        M_out > OWNER_LIST / 2 * groups || ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) != 0u)
+        return false;
+    const int64_t saved_fs = (139 * M_out - 158 * M_src) * K - 124000 * M_src; // in 10^-15 s, from the rates above
+    return saved_fs >= (K < 3584 ? (int64_t)5000000000 : (int64_t)3000000000);
 }
 
 hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,

@@ -89,11 +89,11 @@ def index_of(kind, M, n, rng):
 
 @pytest.mark.parametrize("layout", ["records", "planes8"])
 @pytest.mark.parametrize("K,M,n,kind", [
-    (1536, 1024, 21846, "mixed"), (1536, 1024, 21845, "mixed"),                     # work just above and below the rule
-    (1536, 1023, 21846, "mixed"), (1408, 1024, 32768, "mixed"),                     # too few rows; too short rows
-    (2048, 8193, 16387, "sorted"), (2048, 8193, 16385, "sorted"),                   # two copies a row, and just under
-    (1664, 1300, 30001, "padded"), (2048, 1029, 40003, "crowd"), (1536, 1024, 30010, "hidden"),
-    (7808, 1030, 5003, "padded"), (8192, 1024, 4099, "mixed"), (1536, 2047, 24577, "one")])
+    (2048, 1024, 19175, "mixed"), (2048, 1024, 19174, "mixed"),                     # work just above and below the rule
+    (2048, 1023, 21846, "mixed"), (1920, 1024, 32768, "mixed"),                     # too few rows; too short rows
+    (7168, 4200, 8401, "sorted"), (7168, 4200, 8399, "sorted"),                     # two copies a row, and just under
+    (2176, 1300, 30001, "padded"), (2048, 1029, 40003, "crowd"), (2048, 1024, 30010, "hidden"),
+    (7808, 1030, 5003, "padded"), (8192, 1024, 5003, "mixed"), (2048, 2047, 24577, "one")])
 def test_gather_by_owners(K, M, n, kind, layout):
     """Both sides of the rule for gathering by owners, ends of the index that are no whole quad, an index that starts
     at any multiple of 4 bytes, unused slots, crowds that the sample sees and ones that it does not."""
@@ -109,7 +109,7 @@ def test_gather_by_owners(K, M, n, kind, layout):
 
 def test_gather_by_owners_under_capture():
     """Replays of a captured gather, with the inputs changed and eager work between the replays."""
-    K, M, n = 2048, 1024, 16384
+    K, M, n = 2048, 1024, 20480
     rng, x8, s, _, _ = source(M, K, 1)
     x, xs = dev(x8), dev(s)
     idx = dev(index_of("padded", M, n, rng))
