@@ -288,7 +288,9 @@ __device__ __forceinline__ void store_streaming(void *p, u32x4 v)
 // [8192,7168] 50.8 -> 42.2, [16384,7168] 88.0 -> 76.4, [16384,2048] 30.9 -> 27.4.  Alone, cold: quantizer 9.7 -> 9.9,
 // 16.2 -> 16.3, 29.5 -> 29.7; de-quantizer 9.9 -> 10.0, 17.1 -> 17.3, 30.3 -> 30.9 (warm 8.8 -> 7.9, 17.1 -> 14.0,
 // 30.5 -> 26.4).  Above, the chain still gains but the single kernels lose: [32768,7168] 55.6 -> 57.9 and 57.1 -> 58.8.
+// Below 12 MiB the quantizer's non-temporal stores are the faster ones: [3000,7168] alone 7.0 against 7.3 us.
 constexpr int64_t KEEP_BYTES = (int64_t)64 << 20;
+constexpr int64_t KEEP_FROM = (int64_t)12 << 20; // of the quantizer's output
 
 // Write-through at device scope (sc1) without the non-temporal hint.
 __device__ __forceinline__ void store_through(void *p, u32x2 v)

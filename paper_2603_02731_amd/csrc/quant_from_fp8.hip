@@ -90,7 +90,7 @@ __device__ __forceinline__ void quant16(const u32x4 w, float s, uint32_t out[2],
 // `tid` of each run, so every load and store instruction of a wave stays contiguous
 // (1 KiB in, 512 B out) while each lane keeps QUANT_UNROLL loads in flight.
 // DENSE: no gather and dense outputs -- every address is a multiple of the flat chunk index.
-// KEEP: a dense output of at most KEEP_BYTES, left in the memory-side cache.
+// KEEP: a dense output of KEEP_FROM to KEEP_BYTES, left in the memory-side cache.
 template <bool DENSE, bool GATHER, bool KEEP, int THREADS>
 __global__ void __launch_bounds__(THREADS) quant_from_fp8_kernel(const QuantArgs a)
 {
@@ -438,9 +438,9 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     a.row_of = FastDiv(a.chunks_per_row);
     a.fanout = (uint32_t)fanout;
     a.M_out = (uint32_t)M_out;
-    const bool nib16 = ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) == 0u;
-    const bool sf16 = ((reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_sf) & 15u) == 0u;
-    const bool wide = K % 512 == 0 && sf16;
+    const bool rows16 = ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_q |
+                          (uintptr_t)ld_sf) & 15u) == 0u;
+    const bool wide = K % 512 == 0; // the scale bytes of a row are whole 16-byte pieces
     // Which kernel.  Source rows of 256 M elements and their copies in about 150 MB of records or planes (us: one lane
     // per chunk / one wave per row / one workgroup per row), copies grouped by expert:
     //   K = 512, 8 copies 60 / 62 / 170, 2 copies 51 / 102 / 397; K = 1024 44 / 45 / 92, 51 / 59 / 211;
@@ -448,11 +448,14 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     //   K = 4096 34 / 33 / 35, 50 / 49 / 67, 40 / 36 / 57; K = 5120 45 / 40 / 36, 50 / 51 / 58, 40 / 37 / 50;
     //   K = 7168 43 / 38 / 37, 51 / 51 / 49, 40 / 37 / 41; 65536 tokens of 7168, 8 copies (2 GB) 598 / 520 / 480.
     // A wave per row leaves lanes idle below 1024 elements and has its stores contiguous above; a workgroup per row
-    // writes the longest runs, which pays for long rows with several copies.
+    // writes the longest runs, which pays for long rows with several copies, and it is done soonest where there are few
+    // rows (us, wave / workgroup: 61 rows of 4096, 8 copies 5.6 / 3.8, 488 rows 6.1 / 5.7).  Scale planes that are not on
+    // 16-byte boundaries stay with the lanes (1860 rows of 8064, 4 copies 8.7 against 11.0 us by workgroups).
     uint32_t segs_per_row;
     const uint32_t seg = wave_segment(K, &segs_per_row);
     const uint32_t rec = (uint32_t)((K / 2 + K / 32 + 15) & ~(int64_t)15);
-    if (nib16 && K >= 6144 && fanout >= 2 && rec <= 48u * 1024u) {
+    const int64_t units = M_src * segs_per_row;
+    if (rows16 && K >= 2048 && ((K >= 6144 && fanout >= 2) || units < 1024) && rec <= 48u * 1024u) {
         const bool records = sf == q + K / 2 && ld_sf == ld_q;
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_scatter_row_kernel<true>, dim3((uint32_t)M_src), dim3(SCATTER_THREADS), rec,
@@ -462,8 +465,7 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
                                stream, a, records);
         return hipGetLastError();
     }
-    const int64_t units = M_src * segs_per_row;
-    if (nib16 && K >= 2048 && units < ((int64_t)1 << 31)) {
+    if (rows16 && K >= 2048 && units < ((int64_t)1 << 31)) {
         const uint32_t blocks = (uint32_t)((units + SCATTER_WAVES - 1) / SCATTER_WAVES);
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_scatter_wave_kernel<true>, dim3(blocks), dim3(64 * SCATTER_WAVES), 0, stream,
@@ -745,7 +747,7 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
     const bool dense = gather_idx == nullptr && ld_q == K / 2 && ld_sf == K / 32;
     const uint32_t per_block = (dense ? QUANT_THREADS : QUANT_THREADS_ROUTED) * QUANT_UNROLL;
     const uint32_t blocks = (a.n_chunks + per_block - 1) / per_block;
-    if (dense && M_out * (K / 2) <= KEEP_BYTES)
+    if (dense && M_out * (K / 2) >= KEEP_FROM && M_out * (K / 2) <= KEEP_BYTES)
         hipLaunchKernelGGL((quant_from_fp8_kernel<true, false, true, QUANT_THREADS>), dim3(blocks), dim3(QUANT_THREADS), 0,
                            stream, a);
     else if (dense)

@@ -11,7 +11,8 @@ from tests.test_gpu_parity import DEV, assert_same, host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K", [(32, 4096), (32768, 4096), (32800, 4096)])  # 64 MiB of nibbles exactly, and above
+@pytest.mark.parametrize("M,K", [(32, 4096), (6112, 4096), (6144, 4096),     # just below 12 MiB of nibbles, and exactly
+                                 (32768, 4096), (32800, 4096)])              # 64 MiB exactly, and above
 def test_chain_around_the_limit(M, K):
     x8, s = synth.student_t_fp8(M, K, seed=M % 7, device=DEV)
     q, sf = mx.mxfp4_quant_from_fp8(x8, s)

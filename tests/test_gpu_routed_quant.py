@@ -51,12 +51,13 @@ def check(buf, at, ld_q, ld_sf, K, rows, wq, wsf):
 
 
 @pytest.mark.parametrize("layout", ["records", "planes", "planes8"])
-@pytest.mark.parametrize("K,M,fan", [(1920, 37, 3), (2048, 37, 3), (2176, 9, 1), (5120, 21, 8), (6016, 6, 9),
-                                     (6144, 13, 1), (6144, 13, 2), (6272, 5, 9), (7680, 7, 1), (7808, 7, 1),
-                                     (8192, 5, 1), (16896, 3, 1), (98304, 2, 2)])
+@pytest.mark.parametrize("K,M,fan", [(1920, 37, 3), (2048, 37, 3), (2048, 1023, 2), (2048, 1024, 2), (2176, 1025, 3),
+                                     (2176, 9, 1), (5120, 21, 8), (6016, 6, 9), (6016, 1030, 1), (6144, 1024, 1),
+                                     (6144, 13, 1), (6144, 13, 2), (6272, 5, 9), (7680, 1024, 1), (7808, 512, 1),
+                                     (8192, 512, 1), (8192, 511, 1), (16896, 342, 1), (98304, 2, 2), (98304, 79, 1)])
 def test_scatter_kernels(K, M, fan, layout):
-    """One lane per chunk, one wave per row (several segments from 7681 elements on) and one workgroup per row; fan-outs
-    of 1, 2 and past the eight indices read ahead; scale bytes as 16-byte pieces and as dwords."""
+    """One lane per chunk, one wave per row (from 1024 rows on; several segments of a row count, from 7681 elements on) and
+    one workgroup per row; fan-outs of 1, 2 and past the eight indices read ahead; scale bytes as 16-byte pieces and as dwords."""
     rng, x8, s, wq, wsf = source(M, K, K + fan)
     M_out = M * fan + 5
     dst = rng.permutation(M_out)[: M * fan].reshape(M, fan).astype(np.int32)
