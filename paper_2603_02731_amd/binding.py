@@ -7,6 +7,7 @@ is missing or cannot be loaded the calls raise.
 Each wrapper first hands its arguments to its native counterpart (csrc/call_path.cpp), which
 checks, allocates and calls the library for the plain case and returns None, with nothing
 launched, for any other; the wrapper then does the same in Python and raises where it has to.
+A launch that fails is raised by either, and not tried again.
 """
 import ctypes
 import importlib.machinery
@@ -72,7 +73,7 @@ def lib():
         if os.path.exists(CALL_PATH):
             loader = importlib.machinery.ExtensionFileLoader("_call_path", CALL_PATH)
             module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_call_path", loader))
-            module.bind(*(ctypes.cast(getattr(L, n), _vp).value for n in _NATIVE))
+            module.bind(_check, "cuda", *(ctypes.cast(getattr(L, n), _vp).value for n in _NATIVE))
             _call = module
         _lib = L
     return _lib

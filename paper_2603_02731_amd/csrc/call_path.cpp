@@ -4,7 +4,8 @@
 // allocate the outputs and marshal the call (7-9 us).  Each function here takes the arguments of one wrapper in their
 // order and either does all of it natively and returns the wrapper's result, or returns None and has launched
 // nothing.  It only accepts calls that the wrapper accepts: plain tensors, exact types, default stream argument,
-// non-empty sizes.  Everything else -- errors above all -- is left to the wrapper, which checks again and raises.
+// non-empty sizes.  Everything else -- refusals above all -- is left to the wrapper, which checks again and raises.
+// Only a launch that the runtime reports as failed is raised from here: the kernel may have been queued all the same.
 // Calls back to back: quantizing [256,512] 9.2 -> 5.1 us, the three flat conversions of a small matrix 28.1 -> 15.3 us.
 #include <Python.h>
 
@@ -31,10 +32,17 @@ struct Library {
     decltype(&mxfp4_row_to_fp8_col_grouped) fp8_col_grouped[2];
 } lib;
 constexpr Py_ssize_t N_FUNCTIONS = sizeof(Library) / sizeof(void *);
-bool bound = false;
+c10::DeviceType device_type; // whose tensors are taken
+PyObject *check = nullptr;   // the binding's (name, status) -> raises; nullptr: not bound yet
 
 // Thrown (and caught in this file) where a call is left to the Python wrapper.
 struct NotHere {};
+
+// Thrown (and caught in this file) where the library could not tell that its launch succeeded.
+struct LaunchFailed {
+    const char *name;
+    mxfp4_status status;
+};
 
 inline void need(bool ok)
 {
@@ -47,7 +55,8 @@ inline const at::Tensor &tensor(PyObject *o, at::ScalarType type)
 {
     need(THPVariable_CheckExact(o));
     const at::Tensor &t = THPVariable_Unpack(o);
-    need(t.scalar_type() == type && t.layout() == at::kStrided && t.is_contiguous() && t.is_cuda());
+    need(t.scalar_type() == type && t.layout() == at::kStrided && t.is_contiguous() &&
+         t.device().type() == device_type);
     return t;
 }
 
@@ -136,7 +145,10 @@ inline int64_t experts(const at::Tensor &off, const at::Tensor &q)
     return off.size(0) - 1;
 }
 
-inline void *current_stream(const at::Tensor &t) { return c10::hip::getCurrentHIPStream(t.get_device()).stream(); }
+inline void *current_stream(const at::Tensor &t)
+{
+    return t.is_cuda() ? c10::hip::getCurrentHIPStream(t.get_device()).stream() : nullptr;
+}
 
 inline uint8_t *bytes_of(const at::Tensor &t) { return static_cast<uint8_t *>(t.data_ptr()); }
 
@@ -144,18 +156,22 @@ inline uint8_t *bytes_of(const at::Tensor &t) { return static_cast<uint8_t *>(t.
 template <class Body>
 PyObject *call(Py_ssize_t n, Py_ssize_t want, PyObject *stream, Body &&body)
 {
-    if (!bound || n != want || stream != Py_None || at::impl::torch_function_mode_enabled())
+    if (!check || n != want || stream != Py_None || at::impl::torch_function_mode_enabled())
         Py_RETURN_NONE;
     try {
         Output out[2];
-        mxfp4_status st = body(out);
-        if (st != MXFP4_OK)
-            Py_RETURN_NONE; // nothing was launched: the wrapper's own call reports it
+        if (body(out) != MXFP4_OK)
+            Py_RETURN_NONE; // refused by the library before a launch: the wrapper's own call reports it
         PyObject *a = out[0].result(), *b = out[1].result();
         PyObject *pair = a && b ? PyTuple_Pack(2, a, b) : nullptr;
         Py_XDECREF(a);
         Py_XDECREF(b);
         return pair;
+    } catch (const LaunchFailed &f) {
+        Py_XDECREF(PyObject_CallFunction(check, "si", f.name, (int)f.status)); // raises
+        if (!PyErr_Occurred())
+            PyErr_SetString(PyExc_RuntimeError, f.name);
+        return nullptr;
     } catch (const NotHere &) {
     } catch (const std::exception &) { // a tensor without storage, an allocation that failed: raised by the wrapper
     }
@@ -163,14 +179,16 @@ PyObject *call(Py_ssize_t n, Py_ssize_t want, PyObject *stream, Body &&body)
     Py_RETURN_NONE;
 }
 
-// Calls into the library without the interpreter lock: a launch may wait for room in the queue.
+// Calls the entry point `name` without the interpreter lock: a launch may wait for room in the queue.
 template <class F, class... Args>
-mxfp4_status launch(F f, Args... args)
+mxfp4_status launch(const char *name, F f, Args... args)
 {
     mxfp4_status st;
     Py_BEGIN_ALLOW_THREADS
     st = f(args...);
     Py_END_ALLOW_THREADS
+    if (st == MXFP4_ERR_LAUNCH)
+        throw LaunchFailed{name, st};
     return st;
 }
 
@@ -193,8 +211,8 @@ PyObject *quant_from_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
             idx = static_cast<const int32_t *>(g.data_ptr());
         }
         quant_outputs(a[3], a[4], a[5], a[6], x, rows, K, false, out, ld);
-        return launch(lib.quant, bytes_of(x), static_cast<const float *>(s.data_ptr()), M, K, idx, rows,
-                      static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
+        return launch("mxfp4_quant_from_fp8", lib.quant, bytes_of(x), static_cast<const float *>(s.data_ptr()), M, K, idx,
+                      rows, static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
                       current_stream(x));
     });
 }
@@ -214,7 +232,8 @@ PyObject *quant_from_fp8_scatter(PyObject *, PyObject *const *a, Py_ssize_t n)
         rows = stride_or(a[3], 0);
         need(rows > 0);
         quant_outputs(a[4], a[5], a[6], a[7], x, rows, K, true, out, ld);
-        return launch(lib.scatter, bytes_of(x), static_cast<const float *>(s.data_ptr()), M, K,
+        return launch("mxfp4_quant_from_fp8_scatter", lib.scatter, bytes_of(x),
+                      static_cast<const float *>(s.data_ptr()), M, K,
                       static_cast<const int32_t *>(d.data_ptr()), (int32_t)fanout, rows,
                       static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
                       current_stream(x));
@@ -229,7 +248,7 @@ PyObject *quant_from_bf16(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t M, K, ld[2];
         matrix(x, 128, &M, &K);
         quant_outputs(a[1], a[2], a[3], a[4], x, M, K, false, out, ld);
-        return launch(lib.quant_bf16, static_cast<const uint16_t *>(x.data_ptr()), M, K,
+        return launch("mxfp4_quant_from_bf16", lib.quant_bf16, static_cast<const uint16_t *>(x.data_ptr()), M, K,
                       static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
                       current_stream(x));
     });
@@ -246,9 +265,10 @@ PyObject *quant_from_fp8_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t E = experts(off, x);
         same_device(x, s);
         quant_outputs(a[3], a[4], Py_None, Py_None, x, M, K, false, out, ld);
-        return launch(lib.quant_grouped, bytes_of(x), static_cast<const float *>(s.data_ptr()),
-                      static_cast<const int32_t *>(off.data_ptr()), (int32_t)E, M, K,
-                      static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()), current_stream(x));
+        return launch("mxfp4_quant_from_fp8_grouped", lib.quant_grouped, bytes_of(x),
+                      static_cast<const float *>(s.data_ptr()), static_cast<const int32_t *>(off.data_ptr()), (int32_t)E,
+                      M, K, static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()),
+                      current_stream(x));
     });
 }
 
@@ -278,8 +298,8 @@ PyObject *dequant_to_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
         }
         out[0] = output(a[6], q, at::kByte, {M, K}, M * K);
         out[1] = output(a[7], q, at::kFloat, {M, K / 128}, M * (K / 128) * 4);
-        return launch(lib.dequant, bytes_of(q), ld_q, bytes_of(sf), ld_sf, M, K, static_cast<uint8_t *>(out[0].data()),
-                      static_cast<float *>(out[1].data()), current_stream(q));
+        return launch("mxfp4_dequant_to_fp8", lib.dequant, bytes_of(q), ld_q, bytes_of(sf), ld_sf, M, K,
+                      static_cast<uint8_t *>(out[0].data()), static_cast<float *>(out[1].data()), current_stream(q));
     });
 }
 
@@ -302,8 +322,8 @@ PyObject *row_to_col(PyObject *, PyObject *const *a, Py_ssize_t n)
         need(M % 32 == 0);
         out[0] = output(a[2], q, at::kByte, {K, M / 2}, K * (M / 2));
         out[1] = output(a[3], q, at::kByte, {K, M / 32}, K * (M / 32));
-        return launch(lib.row_to_col, bytes_of(q), bytes_of(sf), M, K, static_cast<uint8_t *>(out[0].data()),
-                      static_cast<uint8_t *>(out[1].data()), current_stream(q));
+        return launch("mxfp4_row_to_col", lib.row_to_col, bytes_of(q), bytes_of(sf), M, K,
+                      static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()), current_stream(q));
     });
 }
 
@@ -317,9 +337,9 @@ PyObject *row_to_col_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t E = experts(off, q), n2 = K * (M / 2 + E), n32 = K * (M / 32 + E);
         out[0] = output(a[3], q, at::kByte, {n2}, n2);
         out[1] = output(a[4], q, at::kByte, {n32}, n32);
-        return launch(lib.row_to_col_grouped, bytes_of(q), bytes_of(sf), static_cast<const int32_t *>(off.data_ptr()),
-                      (int32_t)E, M, K, static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()),
-                      current_stream(q));
+        return launch("mxfp4_row_to_col_grouped", lib.row_to_col_grouped, bytes_of(q), bytes_of(sf),
+                      static_cast<const int32_t *>(off.data_ptr()), (int32_t)E, M, K,
+                      static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()), current_stream(q));
     });
 }
 
@@ -340,8 +360,9 @@ PyObject *row_to_fp8_col(PyObject *, PyObject *const *a, Py_ssize_t n)
         need(M % 128 == 0);
         out[0] = output(a[2], q, at::kByte, {K, M}, K * M);
         out[1] = output(a[3], q, at::kFloat, {K, M / 128}, K * (M / 128) * 4);
-        return launch(lib.fp8_col[requant], bytes_of(q), bytes_of(sf), M, K, static_cast<uint8_t *>(out[0].data()),
-                      static_cast<float *>(out[1].data()), current_stream(q));
+        return launch(requant ? "mxfp4_row_to_fp8_col_requant" : "mxfp4_row_to_fp8_col", lib.fp8_col[requant], bytes_of(q),
+                      bytes_of(sf), M, K, static_cast<uint8_t *>(out[0].data()), static_cast<float *>(out[1].data()),
+                      current_stream(q));
     });
 }
 
@@ -356,31 +377,42 @@ PyObject *row_to_fp8_col_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t E = experts(off, q), n128 = K * (M / 128 + E);
         out[0] = output(a[3], q, at::kByte, {M * K}, M * K);
         out[1] = output(a[4], q, at::kFloat, {n128}, n128 * 4);
-        return launch(lib.fp8_col_grouped[requant], bytes_of(q), bytes_of(sf),
+        return launch(requant ? "mxfp4_row_to_fp8_col_requant_grouped" : "mxfp4_row_to_fp8_col_grouped",
+                      lib.fp8_col_grouped[requant], bytes_of(q), bytes_of(sf),
                       static_cast<const int32_t *>(off.data_ptr()), (int32_t)E, M, K,
                       static_cast<uint8_t *>(out[0].data()), static_cast<float *>(out[1].data()), current_stream(q));
     });
 }
 
-// The addresses of the loaded library's entry points, in the order of Library.
+// bind(check, device, address...): what raises for a status, the type of device whose tensors are taken, and the entry
+// points of the loaded library in the order of Library.
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != N_FUNCTIONS) {
-        PyErr_Format(PyExc_TypeError, "bind takes %zd addresses", N_FUNCTIONS);
+    if (n != N_FUNCTIONS + 2 || !PyCallable_Check(a[0]) || !PyUnicode_Check(a[1])) {
+        PyErr_Format(PyExc_TypeError, "bind takes a callable, a device type and %zd addresses", N_FUNCTIONS);
         return nullptr;
     }
     void *at[N_FUNCTIONS];
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        at[i] = PyLong_AsVoidPtr(a[i]);
+    for (Py_ssize_t i = 0; i < N_FUNCTIONS; ++i) {
+        at[i] = PyLong_AsVoidPtr(a[i + 2]);
         if (!at[i]) {
             if (!PyErr_Occurred())
                 PyErr_SetString(PyExc_ValueError, "a null address");
             return nullptr;
         }
     }
+    const bool host = PyUnicode_CompareWithASCIIString(a[1], "cpu") == 0; // stub entry points, in tests
+    if (!host && PyUnicode_CompareWithASCIIString(a[1], "cuda") != 0) {
+        PyErr_SetString(PyExc_ValueError, "the device type is cuda or cpu");
+        return nullptr;
+    }
     static_assert(sizeof(at) == sizeof(lib), "one address per entry point");
     memcpy(&lib, at, sizeof(lib));
-    bound = true;
+    device_type = host ? c10::DeviceType::CPU : c10::DeviceType::CUDA;
+    PyObject *before = check;
+    Py_INCREF(a[0]);
+    check = a[0];
+    Py_XDECREF(before);
     Py_RETURN_NONE;
 }
 
