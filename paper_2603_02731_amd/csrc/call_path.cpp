@@ -50,12 +50,12 @@ inline void need(bool ok)
         throw NotHere();
 }
 
-// A tensor argument: torch.Tensor itself (no subclass), dense, of the given type.
+// A tensor argument: torch.Tensor itself (no subclass), dense (a nested tensor has that layout too), of the given type.
 inline const at::Tensor &tensor(PyObject *o, at::ScalarType type)
 {
     need(THPVariable_CheckExact(o));
     const at::Tensor &t = THPVariable_Unpack(o);
-    need(t.scalar_type() == type && t.layout() == at::kStrided && t.is_contiguous() &&
+    need(t.scalar_type() == type && t.layout() == at::kStrided && !t.is_nested() && t.is_contiguous() &&
          t.device().type() == device_type);
     return t;
 }

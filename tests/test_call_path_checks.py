@@ -99,3 +99,22 @@ def test_refusal_of_the_library_is_left_to_the_wrapper(stub, name, status):
     stub.status = status
     done, calls = stub.launches(name, *args)
     assert done is None and len(calls) == 1
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_nested_tensors_are_refused(stub, name, monkeypatch):
+    """A nested tensor of equal rows has sizes and storage like a matrix; the wrapper has always refused it."""
+    _, args = plain()[name]
+    monkeypatch.setattr(binding, "_call", stub.call)
+    for i in (0, 1):
+        if not isinstance(args[i], torch.Tensor):
+            continue
+        nested = torch._nested_view_from_buffer(args[i].view(-1), torch.tensor([[args[i].shape[1]]] * args[i].shape[0]),
+                                                torch.ones(args[i].shape[0], 1, dtype=torch.int64),
+                                                torch.arange(args[i].shape[0]) * args[i].shape[1])
+        bad = args[:i] + [nested] + args[i + 1:]
+        done, calls = stub.launches(name, *bad)
+        assert done is None and not calls
+        with pytest.raises((RuntimeError, ValueError)):
+            getattr(mx, "mxfp4_" + name.split()[0])(*bad)
+        assert not stub.calls
