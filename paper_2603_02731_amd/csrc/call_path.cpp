@@ -50,6 +50,12 @@ inline void need(bool ok)
         throw NotHere();
 }
 
+// Without the interpreter lock while it lives: an allocation may wait for the device, a launch for room in the queue.
+struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // A tensor argument: torch.Tensor itself (no subclass), dense (a nested tensor has that layout too), of the given type.
 inline const at::Tensor &tensor(PyObject *o, at::ScalarType type)
 {
@@ -115,6 +121,7 @@ inline Output output(PyObject *o, const at::Tensor &like, at::ScalarType type, a
         out.given = o;
     } else {
         const auto options = at::TensorOptions().dtype(type).device(like.device());
+        Unlocked u;
         out.t = zero ? at::zeros(shape, options) : at::empty(shape, options);
     }
     return out;
@@ -179,14 +186,14 @@ PyObject *call(Py_ssize_t n, Py_ssize_t want, PyObject *stream, Body &&body)
     Py_RETURN_NONE;
 }
 
-// Calls the entry point `name` without the interpreter lock: a launch may wait for room in the queue.
+// Calls the entry point `name`.
 template <class F, class... Args>
 mxfp4_status launch(const char *name, F f, Args... args)
 {
-    mxfp4_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f(args...);
-    Py_END_ALLOW_THREADS
+    const mxfp4_status st = [&] {
+        Unlocked u;
+        return f(args...);
+    }();
     if (st == MXFP4_ERR_LAUNCH)
         throw LaunchFailed{name, st};
     return st;

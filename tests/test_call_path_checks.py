@@ -4,6 +4,8 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import shutil
+import threading
+import time
 
 import pytest
 import torch
@@ -118,3 +120,28 @@ def test_nested_tensors_are_refused(stub, name, monkeypatch):
         with pytest.raises((RuntimeError, ValueError)):
             getattr(mx, "mxfp4_" + name.split()[0])(*bad)
         assert not stub.calls
+
+
+def test_other_threads_run_while_outputs_are_allocated(stub):
+    """Zero-filling 2 GiB takes long enough for a thread that only takes notes of the time to run many times."""
+    x, s, dst = u8(1, 8192), torch.zeros(1, 64), torch.zeros(1, 1, dtype=torch.int32)
+    seen, stop = [], threading.Event()
+
+    def ticks():
+        while not stop.is_set():
+            seen.append(time.perf_counter())
+            time.sleep(1e-3)
+
+    t = threading.Thread(target=ticks)
+    t.start()
+    try:
+        begin = time.perf_counter()
+        done, calls = stub.launches("quant_from_fp8_scatter", x, s, dst, 1 << 19, None, None, None, None, None)
+        end = time.perf_counter()
+    finally:
+        stop.set()
+        t.join()
+    assert done is not None and len(calls) == 1
+    # the middle of the call: nothing runs there if the lock is held through the allocations
+    fifth = (end - begin) / 5
+    assert any(begin + fifth < at < end - fifth for at in seen)
