@@ -41,7 +41,8 @@ def native(name):
 
 @pytest.mark.parametrize("name", sorted(arguments("cpu")))
 def test_leaves_other_calls_to_the_wrapper(name):
-    """Host tensors, wrong types, subclasses, strides, missing and surplus arguments: None, and nothing is raised."""
+    """Host tensors, alone or beside arguments of wrong types, strides and numbers: None, and nothing is raised.  (That
+    each single check refuses its argument is tested against stub entry points in test_call_path_checks.)"""
     _, args = arguments("cpu")[name]
     f = native(name)
 
@@ -95,6 +96,7 @@ def test_same_results_as_the_wrapper(name, monkeypatch):
 
 @pytest.mark.gpu
 def test_refusals_still_raise_and_streams_are_kept():
+    """Results on side streams; which stream a call is handed is tested in test_call_path_checks."""
     x8, s = synth.tiny_roundtrip_fp8(seed=1)
     x, s = x8.to(DEV), s.to(DEV)
     mx.mxfp4_quant_from_fp8(x, s)
