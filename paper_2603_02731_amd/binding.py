@@ -13,12 +13,15 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
+from .build import call_path
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmxfp4.so")
-CALL_PATH = os.path.join(_HERE, "_call_path.so")
+CALL_PATH = call_path()
 
 OK, ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_OFFSETS, ERR_LAUNCH = 0, -1, -2, -3, -4, -5
 
@@ -41,6 +44,20 @@ class Mxfp4Error(RuntimeError):
     def __init__(self, name, status, text):
         super().__init__(f"{name}: {text} (status {status})")
         self.status = status
+
+
+def _load_call_path(L):
+    """The native call path bound to the library's entry points, or None with a warning where there is none for this
+    Python and PyTorch."""
+    loader = importlib.machinery.ExtensionFileLoader("_call_path", CALL_PATH)
+    try:
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_call_path", loader))
+    except ImportError as e:
+        warnings.warn(f"no native call path, calls take their way through Python (some 4 us longer): {e}", RuntimeWarning,
+                      stacklevel=3)
+        return None
+    module.bind(_check, "cuda", *(ctypes.cast(getattr(L, n), _vp).value for n in _NATIVE))
+    return module
 
 
 def lib():
@@ -70,11 +87,7 @@ def lib():
             getattr(L, n).restype = ctypes.c_int
         L.mxfp4_status_string.argtypes = [ctypes.c_int]
         L.mxfp4_status_string.restype = ctypes.c_char_p
-        if os.path.exists(CALL_PATH):
-            loader = importlib.machinery.ExtensionFileLoader("_call_path", CALL_PATH)
-            module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_call_path", loader))
-            module.bind(_check, "cuda", *(ctypes.cast(getattr(L, n), _vp).value for n in _NATIVE))
-            _call = module
+        _call = _load_call_path(L)
         _lib = L
     return _lib
 

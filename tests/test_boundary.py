@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import paper_2603_02731_amd as mx
-from paper_2603_02731_amd import binding
+from paper_2603_02731_amd import binding, build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -232,3 +232,58 @@ def test_nothing_in_the_product_path_touches_the_oracle():
                 text = open(os.path.join(dirpath, f)).read()
                 assert "mxfp4_ref" not in text, f"{f} names the oracle's library"
                 assert not re.search(r"^\s*(from|import)\s+oracle\b", text, flags=re.M), f"{f} imports the oracle"
+
+
+@pytest.fixture
+def reloaded(monkeypatch):
+    """binding.lib() as in a new process; what was loaded comes back afterwards."""
+    mx.lib()
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_call", None)
+
+
+@pytest.mark.parametrize("what", ["missing", "not a library", "another interface"])
+def test_library_loads_without_a_call_path_that_fits(reloaded, monkeypatch, tmp_path, what):
+    """Built against another PyTorch, broken or not built: the library itself needs none of it, and says so once."""
+    path = tmp_path / "_call_path.so"
+    if what == "not a library":
+        path.write_bytes(b"\x7fELF nothing")
+    elif what == "another interface":
+        path.write_bytes(open(binding.LIB_PATH, "rb").read())  # loads, but exports no such module
+    monkeypatch.setattr(binding, "CALL_PATH", str(path))
+    with pytest.warns(RuntimeWarning, match="no native call path"):
+        mx.lib()
+    assert binding._call is None
+    with pytest.raises(TypeError, match="HIP device tensor"):
+        mx.mxfp4_quant_from_fp8(_t((4, 128)), _t((4, 1), torch.float32))
+
+
+def test_call_path_is_named_after_what_it_is_built_against(monkeypatch):
+    path = build.call_path()
+    assert torch.__version__ in path and path == binding.CALL_PATH
+    monkeypatch.setattr(torch, "__version__", "1.2.3")
+    assert build.call_path() != path
+
+
+@pytest.mark.parametrize("hipcc", ["hipcc", build.HIPCC])
+def test_call_path_finds_the_headers_of_any_compiler_name(monkeypatch, hipcc):
+    monkeypatch.setattr(build, "HIPCC", hipcc)
+    commands = []
+    monkeypatch.setattr(build, "_run", lambda cmd, target: commands.append(cmd))
+    build.build(force=True)
+    include = commands[1][commands[1].index(build._rocm_include()) - 1:][:2]
+    assert include[0] == "-isystem" and os.path.exists(os.path.join(include[1], "hip", "hip_runtime_api.h"))
+
+
+def test_library_is_built_where_the_call_path_cannot_be(monkeypatch, tmp_path, capsys):
+    done = []
+
+    def run(cmd, target):
+        if target == build.call_path():
+            raise RuntimeError("g++ failed")
+        done.append(target)
+    monkeypatch.setattr(build, "_run", run)
+    monkeypatch.setattr(build, "call_path", lambda: str(tmp_path / "_call_path.so"))
+    (tmp_path / "_call_path.so").write_bytes(b"of older sources")
+    assert build.build(force=True) == build.LIB and done == [build.LIB]
+    assert "g++ failed" in capsys.readouterr().err and not (tmp_path / "_call_path.so").exists()
