@@ -15,6 +15,8 @@
 #include "mxfp4_device.hpp"
 #include "mxfp4_kernels.hpp"
 
+#include <algorithm>
+
 namespace mxfp4 {
 
 // Lanes per workgroup (each lane takes QUANT_UNROLL chunks).  Dense rows: 512 x 2 runs; at [65536,7168] over
@@ -482,26 +484,36 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
 }
 
 // Gather by owners.  Every source row that several output rows ask for is read and quantized once: a workgroup owns
-// a range of source rows, scans the whole index for the output rows that want one of them, sorts these by source row
-// in LDS, and its waves write each of its rows to all of its destinations.  No communication between workgroups and
-// no scratch memory: all of them read the same index (a few bytes per output row against K * 17/32 written).
+// source rows, scans the whole index for the output rows that want one of them, sorts these by source row in LDS, and its
+// waves quantize each row and write it to all of its destinations.  No communication between workgroups and no scratch
+// memory: all of them read the same index (a few bytes per output row against K * 17/32 written).
 //
-// Balance.  Routing maps ask for every token about equally often.  Where they do not (many output rows padded with
-// one and the same index, say) the owner of such rows would work on alone: every workgroup counts a sample of the
-// index per owner while it scans, all see the same counts, and the rows of an owner with several times its share
-// (and the zero rows of indices that name no source row) are dealt out by output row instead.
-// Bound by the writes: 8192 rows of 7168 to eight records each 78 us = 4.0 TB/s of what has to move (lane-wise 115, where
+// Balance.  Routing maps ask for every token about equally often, and the owner of a row is a hash of it, so that sources
+// of which only a part is in use (the first quarter, every eighth row) spread over all workgroups.  Where a few rows are
+// asked for by many (output rows padded with one and the same index, say), every workgroup counts the same sample of the
+// index per owner while it scans; the rows of an owner with a quarter more than its share, and the zero rows of indices
+// that name no source row, are dealt out by output row: every workgroup takes those of its own slice of the outputs.
+// Bound by the writes: 8192 rows of 7168 to eight records each 81.5 us = 3.8 TB/s of what has to move (lane-wise 120, where
 // half is reading every row eight times from the memory-side cache and a quarter quantizing it as often; the scatter form
-// of the same routing 60 us, without the scan and with four workgroups per compute unit).  One workgroup of 16 waves
-// per compute unit (110 registers): two of them at 64 registers spill, 93 us.  Skewed maps of 65536 slots (lane-wise / by
-// owners): half of the slots unused 88 / 79, a quarter naming one row 101 / 90, all naming one row 86 / 64; slots that name
-// 512 of the 8192 rows at random 94 / 117 and a power law 97 / 129 are what the dealing does not pay for.
+// of the same routing 60 us, without the scan and with four workgroups per compute unit), 20 thousand of a workgroup's 160
+// thousand cycles before its first write.  One workgroup of 16 waves per compute unit: two of them at 64 registers spill.
+// Maps of 65536 slots, 7168 long rows (us, lane-wise / by owners): shuffled 118 / 83, a quarter of the slots naming one row 101 / 85,
+// the last of every 16 slots 116 / 86, all naming one row 87 / 71, half unused 89 / 83, the first 512 rows only 91 / 76, every
+// eighth row 96 / 76, 128 rows at random 86 / 87, a power law (exponents 1/4 and 1/8) 97 / 98 and 91 / 93.  With 32768 slots:
+// routes 60 / 41, one row in a quarter 52 / 48, half unused 45 / 43, first 512 rows 45 / 40, but 128 rows at random 43 / 49 and
+// the power laws 48 / 56 and 46 / 52, where some owners just below the line have more to write than one compute unit can.
 constexpr int OWNER_WAVES = 16;
 constexpr uint32_t OWNER_THREADS = 64 * OWNER_WAVES;
 constexpr uint32_t OWNER_GROUPS = 512; // workgroups at most: counters of the sample
 constexpr uint32_t OWNER_ROWS = 256;   // source rows of a workgroup at most
-constexpr uint32_t DEALT_ROWS = 8;
-constexpr uint32_t OWNER_LIST = 8192;  // output rows a workgroup sorts; more of them take the unsorted path
+constexpr uint32_t OWNER_LIST = 8192;  // output rows a workgroup sorts at a time
+// What the list is sorted by: own rows, the owners of dealt rows, rows of zeros.
+constexpr uint32_t KEY_DEALT = OWNER_ROWS, KEY_ZERO = KEY_DEALT + OWNER_GROUPS, OWNER_KEYS = (KEY_ZERO + 64) / 64 * 64;
+constexpr uint32_t OWNER_UNITS = OWNER_KEYS + OWNER_WAVES;
+constexpr uint32_t SLICE_RUN = 32;     // output rows that are dealt out together
+constexpr uint32_t OUT_BITS = 21;
+constexpr int VMCNT_0 = 0x0F70; // operand of s_waitcnt: no vector memory operation outstanding, the other counters at any value
+static_assert(OWNER_LIST / 2 * OWNER_GROUPS <= 1u << OUT_BITS && OWNER_KEYS <= 1u << (32 - OUT_BITS), "key and output row in a dword");
 
 struct QuantOwnerArgs {
     const uint8_t *x;
@@ -514,191 +526,244 @@ struct QuantOwnerArgs {
     uint32_t M_src;
     uint32_t M_out;
     uint32_t K;
-    uint32_t seg;        // elements of a row taken at a time
-    uint32_t rows_per_wg;
-    uint32_t owner_of;   // ceil(2^32 / rows_per_wg): source row -> workgroup by a high multiplication, exact below 2^24
-    uint32_t heavy;      // sampled indices above which an owner's rows are dealt out
-};
-
-// The output rows of `todo` (bit l: row base + l, source row in lane l's src), one after the other by one wave; runs of
-// the same source row, zero rows among them, are quantized once.
-template <bool WIDE_SF>
-__device__ __forceinline__ void quant_rows_of(const QuantOwnerArgs &a, const uint64_t todo, uint32_t src, uint32_t base,
-                                              uint8_t *rec, uint32_t lane)
-{
-    if (todo == 0ull)
-        return;
-    src = min(src, a.M_src); // no source row, negative indices included: a zero row
-    for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
-        const uint32_t n = min(a.seg, a.K - k0);
-        RowPieces r;
-        uint32_t held = 0xFFFFFFFFu;
-        for (uint64_t rest = todo; rest != 0ull; rest &= rest - 1ull) {
-            const int l = __ffsll((unsigned long long)rest) - 1;
-            const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)src, l);
-            if (row != held) {
-                const bool zero = row == a.M_src;
-                const uint32_t from = zero ? 0u : row;
-                quant_segment<WIDE_SF>(a.x + (size_t)from * a.K + k0,
-                                       a.x_scale + (size_t)from * (a.K >> 7) + (k0 >> 7), n, zero, rec, lane, &r);
-                held = row;
-            }
-            const uint32_t d = base + (uint32_t)l;
-            store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u, a.sf + (size_t)d * a.ld_sf + k0 / 32u, lane);
-        }
+    uint32_t seg;     // elements of a row taken at a time
+    uint32_t shift;   // 2^shift workgroups
+    uint32_t samples; // of every four quads of the index
+    uint32_t heavy;   // sampled indices above which an owner's rows are dealt out
+    // The owner of a row: of every 2^shift consecutive ones each has another, in an order that changes from run to run.
+    __device__ __forceinline__ uint32_t turn(uint32_t run) const { return __umul24(run, 77u); }
+    __device__ __forceinline__ uint32_t owner(uint32_t row) const { return (row + turn(row >> shift)) & ((1u << shift) - 1u); }
+    __device__ __forceinline__ uint32_t row(uint32_t owner, uint32_t run) const
+    {
+        return (run << shift) + ((owner - turn(run)) & ((1u << shift) - 1u));
     }
-}
+};
 
 template <bool WIDE_SF>
 __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(const QuantOwnerArgs a)
 {
     __shared__ __align__(16) uint8_t s_rec[OWNER_WAVES][WAVE_LDS]; // first the unsorted list, then the waves' rows
     __shared__ uint32_t s_sorted[OWNER_LIST];
-    __shared__ uint32_t s_sample[OWNER_GROUPS]; // sampled indices per owner
-    __shared__ uint32_t s_fill[OWNER_ROWS];     // output rows per owned row; then where the next one goes
-    __shared__ uint32_t s_start[OWNER_ROWS + 1];
+    __shared__ __align__(16) uint32_t s_sample[OWNER_GROUPS][4]; // sampled indices per owner; by lane, as crowds add to one
+    __shared__ uint32_t s_fill[OWNER_KEYS];     // output rows per key; then where the next one goes
+    __shared__ uint32_t s_units[OWNER_UNITS];   // parts of the sorted list for one wave: start << 16 | entries
     __shared__ uint32_t s_n;
     static_assert(sizeof(s_rec) >= OWNER_LIST * sizeof(uint32_t), "the unsorted list fits into the waves' rows");
     uint32_t *s_list = reinterpret_cast<uint32_t *>(s_rec);
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t row0 = blockIdx.x * a.rows_per_wg;
-    const uint32_t n_rows = min(a.rows_per_wg, a.M_src - row0);
-    if (tid < OWNER_GROUPS)
-        s_sample[tid] = 0u;
-    if (tid < OWNER_ROWS)
-        s_fill[tid] = 0u;
-    if (tid == 0u)
-        s_n = 0u;
-    __syncthreads();
+    // consecutive source rows, whose output rows are often neighbours too, belong to workgroups of one XCD: output rows share
+    // 128-byte lines, which the XCD's L2 puts together
+    const uint32_t me = a.shift < 3u ? blockIdx.x : (blockIdx.x % NUM_XCD << (a.shift - 3u)) + blockIdx.x / NUM_XCD;
 
-    // ---- scan: lane l of a step takes the four indices 4l.. of a run
-    constexpr int STEP = 4;
-    auto take = [&](uint32_t src, uint32_t out) {
-        const uint32_t t = src - row0;
-        if (t < n_rows) {
-            const uint32_t at = atomicAdd(&s_n, 1u);
-            if (at < OWNER_LIST) {
-                s_list[at] = (t << 24) | out;
-                atomicAdd(&s_fill[t], 1u);
-            }
+    auto clear_list = [&] {
+        for (uint32_t i = tid; i < OWNER_KEYS; i += OWNER_THREADS)
+            s_fill[i] = 0u;
+        if (tid == 0u)
+            s_n = 0u;
+    };
+    auto push = [&](uint32_t key, uint32_t out) {
+        const uint32_t at = atomicAdd(&s_n, 1u);
+        if (at < OWNER_LIST) {
+            s_list[at] = (key << OUT_BITS) | out;
+            atomicAdd(&s_fill[key], 1u);
         }
     };
+
+    auto sampled = [&](uint32_t owner) {
+        const u32x4 n = *reinterpret_cast<const u32x4 *>(s_sample[owner]);
+        return n.x + n.y + n.z + n.w;
+    };
+
+    // ---- the output rows in quads [q0, q1) of the index (and, at its end, the last one to three) that want a row of ours
+    constexpr int STEP = 4;
     const uint32_t quads = a.M_out / 4u;
     const u32x4_unaligned *idx4 = reinterpret_cast<const u32x4_unaligned *>(a.gather_idx);
-    for (uint32_t base = 0; base < quads; base += OWNER_THREADS * STEP) {
-        u32x4 v[STEP];
+    auto scan = [&](uint32_t q0, uint32_t q1, bool sample) {
+        for (uint32_t base = q0; base < q1; base += OWNER_THREADS * STEP) {
+            u32x4 v[STEP];
 #pragma unroll
-        for (int u = 0; u < STEP; ++u) {
-            const uint32_t p = base + u * OWNER_THREADS + tid;
-            v[u] = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-            if (p < quads)
-                v[u] = idx4[p];
+            for (int u = 0; u < STEP; ++u) {
+                const uint32_t p = base + u * OWNER_THREADS + tid;
+                v[u] = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+                if (p < q1)
+                    v[u] = idx4[p];
+            }
+            // A wave samples `samples` of its four runs of 256 indices; which ones changes from wave to wave and step to step
+            // without a pattern.
+            const uint32_t turn = ((base / OWNER_THREADS * OWNER_WAVES + wave) * 0x9E3779B1u) >> 30;
+#pragma unroll
+            for (int u = 0; u < STEP; ++u) {
+                const uint32_t p = base + u * OWNER_THREADS + tid;
+                const uint32_t o[4] = {a.owner(v[u].x), a.owner(v[u].y), a.owner(v[u].z), a.owner(v[u].w)};
+                if ((o[0] == me) | (o[1] == me) | (o[2] == me) | (o[3] == me)) // one branch for four: the scan is bound by its
+                                                                               // instructions
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (o[e] == me && v[u][e] < a.M_src) // also not the negative ones
+                            push(v[u][e] >> a.shift, p * 4u + e);
+                if (sample && (((uint32_t)u - turn) & 3u) < a.samples)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (v[u][e] < a.M_src)
+                            atomicAdd(&s_sample[o[e]][lane & 3u], 1u);
+            }
         }
-#pragma unroll
-        for (int u = 0; u < STEP; ++u) {
-            const uint32_t p = base + u * OWNER_THREADS + tid;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                take(v[u][e], p * 4u + e);
-            if ((lane & 3u) == 0u && v[u].x < a.M_src) // every sixteenth index
-                atomicAdd(&s_sample[__umulhi(v[u].x, a.owner_of)], 1u);
+        if (q1 >= quads && tid < (a.M_out & 3u)) {
+            const uint32_t out = q1 * 4u + tid, src = (uint32_t)a.gather_idx[out];
+            if (a.owner(src) == me && src < a.M_src)
+                push(src >> a.shift, out);
         }
-    }
-    if (tid < (a.M_out & 3u))
-        take((uint32_t)a.gather_idx[quads * 4u + tid], quads * 4u + tid);
-    __syncthreads();
+    };
 
-    const bool shared_out = s_sample[blockIdx.x] > a.heavy; // this owner's rows are dealt out
-    const uint32_t listed = s_n;
-    const bool sorted = listed <= OWNER_LIST && !shared_out;
-    if (sorted) {
-        if (wave == 0u) { // where each owned row's destinations start
-            uint32_t before = 0;
-#pragma unroll
-            for (uint32_t b = 0; b < OWNER_ROWS; b += 64u) {
+    // ---- the output rows of our slice, every 2^shift-th run of SLICE_RUN, that are dealt out
+    auto scan_dealt = [&] {
+        for (uint32_t out = ((tid / SLICE_RUN << a.shift) + me) * SLICE_RUN + tid % SLICE_RUN; out < a.M_out;
+             out += OWNER_THREADS << a.shift) {
+            const uint32_t src = (uint32_t)a.gather_idx[out];
+            if (src >= a.M_src)
+                push(KEY_ZERO, out);
+            else if (sampled(a.owner(src)) > a.heavy)
+                push(KEY_DEALT + a.owner(src), out);
+        }
+    };
+
+    // ---- sorts the list, with the first `keys` of its keys in use, and writes its rows
+    auto write_rows = [&](uint32_t listed, uint32_t keys) {
+        // A unit is a source row and its destinations; rows with more of them than a wave's share are cut into several.
+        uint32_t most_log2 = 4;
+        while (OWNER_WAVES << most_log2 < listed)
+            ++most_log2;
+        if (wave == 0u) {
+            uint32_t before = 0, units = 0;
+            for (uint32_t b = 0; b < keys; b += 64u) {
                 const uint32_t c = s_fill[b + lane];
                 const uint32_t incl = wave_inclusive_sum(c);
-                s_start[b + lane] = before + incl - c;
+                const uint32_t parts = (c + (1u << most_log2) - 1u) >> most_log2;
+                const uint32_t units_incl = wave_inclusive_sum(parts);
+                const uint32_t start = before + incl - c;
+                s_fill[b + lane] = start;
+                for (uint32_t i = 0; i < parts; ++i) {
+                    const uint32_t at = i << most_log2;
+                    s_units[units + units_incl - parts + i] = (start + at) << 16 | min(c - at, 1u << most_log2);
+                }
                 before += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                units += (uint32_t)__builtin_amdgcn_readlane((int)units_incl, 63);
             }
             if (lane == 0u)
-                s_start[OWNER_ROWS] = before;
+                s_n = units;
         }
-        __syncthreads();
-        if (tid < OWNER_ROWS)
-            s_fill[tid] = s_start[tid];
         __syncthreads();
         for (uint32_t i = tid; i < listed; i += OWNER_THREADS) {
             const uint32_t e = s_list[i];
-            s_sorted[atomicAdd(&s_fill[e >> 24], 1u)] = e & 0xFFFFFFu;
+            s_sorted[atomicAdd(&s_fill[e >> OUT_BITS], 1u)] = e;
         }
+        const uint32_t units = s_n;
         __syncthreads();
-        for (uint32_t t = wave; t < n_rows; t += OWNER_WAVES) {
-            const uint32_t j0 = __builtin_amdgcn_readfirstlane(s_start[t]);
-            const uint32_t j1 = __builtin_amdgcn_readfirstlane(s_start[t + 1u]);
-            if (j0 == j1)
-                continue;
-            const uint32_t row = row0 + t;
-            for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
-                const uint32_t n = min(a.seg, a.K - k0);
-                RowPieces r;
-                quant_segment<WIDE_SF>(a.x + (size_t)row * a.K + k0,
-                                       a.x_scale + (size_t)row * (a.K >> 7) + (k0 >> 7), n, false, s_rec[wave], lane, &r);
-                for (uint32_t j = j0; j < j1; ++j) {
-                    const uint32_t d = __builtin_amdgcn_readfirstlane(s_sorted[j]);
-                    store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u, a.sf + (size_t)d * a.ld_sf + k0 / 32u,
-                                           lane);
+        __builtin_amdgcn_s_waitcnt(VMCNT_0);
+        for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
+            const uint32_t n = min(a.seg, a.K - k0);
+            RowPieces r;
+            uint32_t held = 0xFFFFFFFFu; // the source row in r; M_src: zeros
+            for (uint32_t u = wave; u < units; u += OWNER_WAVES) {
+                const uint32_t unit = __builtin_amdgcn_readfirstlane(s_units[u]);
+                const uint32_t end = (unit >> 16) + (unit & 0xFFFFu);
+                for (uint32_t j = unit >> 16; j < end; j += 64u) {
+                    const uint32_t e = j + lane < end ? s_sorted[j + lane] : 0u;
+                    const uint32_t key = e >> OUT_BITS, out = e & ((1u << OUT_BITS) - 1u);
+                    uint32_t src = key < KEY_DEALT ? a.row(me, key) : a.M_src;
+                    if (key >= KEY_DEALT && key < KEY_ZERO) // used at once: the wait for it, and for every store before it,
+                        src = min((uint32_t)a.gather_idx[out], a.M_src); // stays on this side of the branch
+                    const int some = (int)min(64u, end - j);
+                    for (int l = 0; l < some; ++l) {
+                        const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)src, l);
+                        const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)out, l);
+                        if (row != held) {
+                            const bool zero = row == a.M_src;
+                            const uint32_t from = zero ? 0u : row;
+                            quant_segment<WIDE_SF>(a.x + (size_t)from * a.K + k0,
+                                                   a.x_scale + (size_t)from * (a.K >> 7) + (k0 >> 7), n, zero, s_rec[wave],
+                                                   lane, &r);
+                            // The loads are in.  Said here, and before the loop, no store has to wait for them, and with them
+                            // for the stores before it, where the paths join.
+                            __builtin_amdgcn_s_waitcnt(VMCNT_0);
+                            held = row;
+                        }
+                        store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u,
+                                               a.sf + (size_t)d * a.ld_sf + k0 / 32u, lane);
+                    }
                 }
             }
         }
-    } else if (!shared_out) {
-        // more output rows than the list holds although the sample saw no crowd: one after the other
-        for (uint32_t base = wave * 64u; base < a.M_out; base += OWNER_THREADS) {
-            const uint32_t out = base + lane;
-            const uint32_t src = out < a.M_out ? (uint32_t)a.gather_idx[out] : 0xFFFFFFFFu;
-            quant_rows_of<WIDE_SF>(a, __ballot(src - row0 < n_rows), src, base, s_rec[wave], lane);
+    };
+
+    // All of it at once, or, where that is more output rows than the list holds, first those that are dealt to us, then ours
+    // from as much of the index at a time as cannot overflow the list.
+    constexpr uint32_t PART = OWNER_LIST / 4u - 1u; // quads; the last part has up to three indices more
+    if (tid < OWNER_GROUPS)
+        *reinterpret_cast<u32x4 *>(s_sample[tid]) = u32x4{0u, 0u, 0u, 0u};
+    bool own = true, whole = true, dealt = true;
+    for (uint32_t q0 = 0, q1 = quads;;) {
+        clear_list();
+        __syncthreads();
+        scan(q0, q1, whole);
+        __syncthreads();
+        if (whole)
+            own = sampled(me) <= a.heavy; // else our rows are dealt out too
+        const uint32_t own_listed = s_n;
+        __syncthreads();
+        if (!own) {
+            clear_list();
+            __syncthreads();
         }
-    }
-
-    // ---- the rows that are dealt out by output row, a few consecutive ones per wave
-    for (uint32_t base = (blockIdx.x * OWNER_WAVES + wave) * DEALT_ROWS; base < a.M_out;
-         base += gridDim.x * OWNER_WAVES * DEALT_ROWS) {
-        const uint32_t out = base + lane;
-        const bool there = lane < DEALT_ROWS && out < a.M_out;
-        const uint32_t src = there ? (uint32_t)a.gather_idx[out] : 0u;
-        bool deal = there && src >= a.M_src; // also negative: a zero row
-        if (there && src < a.M_src)
-            deal = s_sample[__umulhi(src, a.owner_of)] > a.heavy;
-        quant_rows_of<WIDE_SF>(a, __ballot(deal), src, base, s_rec[wave], lane);
+        if (dealt)
+            scan_dealt();
+        __syncthreads();
+        const uint32_t listed = s_n;
+        __syncthreads();
+        if (listed > OWNER_LIST) {
+            whole = false;
+            q1 = 0u;
+            continue;
+        }
+        write_rows(listed, own && listed == own_listed ? (((a.M_src - 1u) >> a.shift) + 64u) & ~63u : OWNER_KEYS);
+        if (whole || !own || q1 >= quads)
+            break;
+        dealt = false;
+        q0 = q1;
+        q1 = min(q0 + PART, quads);
+        __syncthreads();
     }
 }
 
-// One workgroup per compute unit, as many as its sample counters allow.
-static uint32_t owner_groups()
+// One workgroup per compute unit, or the next lower power of two.
+static uint32_t owner_shift()
 {
-    const uint32_t cus = compute_units();
-    return cus < OWNER_GROUPS ? cus : OWNER_GROUPS;
+    const uint32_t most = std::min(compute_units(), OWNER_GROUPS);
+    uint32_t shift = 0;
+    while (2u << shift <= most)
+        ++shift;
+    return shift;
 }
 
-// Gather by owners: where every source row is asked for at least twice on average and there are at least four of them per
-// workgroup, if what it saves exceeds its phases, its waves' time per row and the scan of the index (4 bytes per output row
-// and workgroup, from the L2).  Per million elements the lane-wise kernel takes 0.245 us of output, this one 0.106 us of
-// output and 0.158 us of source, 0.124 us per thousand source rows and some 3 us to begin with, 5 where rows are short.
-// Measured (us, one lane per chunk -> by owners), copies grouped by expert: K = 7168: 8192 rows x 8 115 -> 78, 1929 x 3 12.2
-// -> 10.4, 4179 x 2 17.0 -> 15.8, 65536 x 8 1054 -> 603; K = 3584: 1639 x 8 12.7 -> 11.0, 13111 x 2 26.3 -> 25.2, but 8358 x 2
-// 17.0 -> 18.1; K = 2560: 2295 x 8 12.6 -> 12.5, 45886 x 2 65.2 -> 64.0, but 18355 x 2 25.3 -> 26.9; K = 2048: 2868 x 8 12.2 ->
-// 11.3, 57357 x 2 65.2 -> 61.7, but 22943 x 2 25.0 -> 26.1; K = 1536: 9560 x 8 29.2 -> 28.6, but 6798 x 5 15.0 -> 15.9; K = 512:
-// 65536 x 8 67 -> 104.
+// Gather by owners: where every source row is asked for at least twice on average, there are at least four of them per
+// workgroup, rows are long and what quantizing them once saves is well above the kernel's phases before the first write.  Per
+// million elements the lane-wise kernel takes 0.245 us of output, this one 0.106 us of output and 0.158 us of source and 0.124 us
+// per thousand source rows (on 256 compute units; fewer of them save more).  The line lies where maps with crowds and unused
+// slots still lose nothing, not where routing maps begin to gain.  Measured on both sides of it (us, lane-wise / by owners;
+// the same with a quarter of the slots naming one row; with 40 % unused; naming 512 rows): saving 28 us, 58600 x 4096 from an
+// eighth as many rows 58 / 44, 49 / 49, 46 / 44, 43 / 39; 33500 x 7168 59 / 43, 51 / 50, 47 / 45, 46 / 42; 29800 x 8064 60 / 42,
+// 52 / 56, 47 / 44, 46 / 40; saving 14, 16700 x 7168 30 / 24, but 26 / 32, 25 / 26, 25 / 25; 3584 long rows, saving 28, 61 / 51, but
+// 53 / 55, 48 / 51, 45 / 50; 2048 long ones, saving 27, 59 / 51, but 52 / 58, 46 / 52, 42 / 48.
 static bool gather_by_owners(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q)
 {
-    const int64_t groups = owner_groups();
-    if (K < 2048 || M_src < 4 * groups || M_src > OWNER_ROWS * groups || M_out < 2 * M_src ||
+    const int64_t groups = (int64_t)1 << owner_shift();
+    if (K < 4096 || M_src < 4 * groups || M_src > OWNER_ROWS * groups || M_out < 2 * M_src ||
         M_out > OWNER_LIST / 2 * groups || ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) != 0u)
         return false;
     const int64_t saved_fs = (139 * M_out - 158 * M_src) * K - 124000 * M_src; // in 10^-15 s, from the rates above
-    return saved_fs >= (K < 3584 ? (int64_t)5000000000 : (int64_t)3000000000);
+    return saved_fs >= (int64_t)25000000000;
 }
 
 hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
@@ -719,11 +784,11 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
         o.K = (uint32_t)K;
         uint32_t segs_per_row;
         o.seg = wave_segment(K, &segs_per_row);
-        const uint32_t most = owner_groups();
-        o.rows_per_wg = (uint32_t)((M_src + most - 1) / most);
-        o.owner_of = (uint32_t)((((uint64_t)1 << 32) + o.rows_per_wg - 1) / o.rows_per_wg);
-        const uint32_t groups = (o.M_src + o.rows_per_wg - 1) / o.rows_per_wg;
-        o.heavy = 16u + 4u * (o.M_out / 16u / groups); // every sixteenth index is sampled
+        o.shift = owner_shift();
+        const uint32_t groups = 1u << o.shift;
+        // a quarter of the index, or as much as gives 64 sampled indices per owner
+        o.samples = o.M_out >= 256u * groups ? 1u : o.M_out >= 128u * groups ? 2u : 4u;
+        o.heavy = 5u * (o.M_out / 4u * o.samples / groups) / 4u + 8u;
         const bool wide = K % 512 == 0 && ((reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_sf) & 15u) == 0u;
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_owner_kernel<true>, dim3(groups), dim3(OWNER_THREADS), 0, stream, o);

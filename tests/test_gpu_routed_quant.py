@@ -69,48 +69,160 @@ def test_scatter_kernels(K, M, fan, layout):
     check(buf, at, ld_q, ld_sf, K, dst[~nowhere], wq[src], wsf[src])
 
 
+# ---- gather by owners
+
+GROUPS = 1 << (torch.cuda.get_device_properties(0).multi_processor_count.bit_length() - 1) if torch.cuda.is_available() else 256
+
+
+def saved(M, K, n):
+    """What the launch expects to save, in 10^-15 s."""
+    return (139 * n - 158 * M) * K - 124000 * M
+
+
+def least(M, K):
+    """The smallest number of output rows from which M source rows are gathered by owners."""
+    n = -(-(25 * 10 ** 9 + 124000 * M) // K + 158 * M) // 139
+    while saved(M, K, n) < 25 * 10 ** 9:
+        n += 1
+    assert saved(M, K, n - 1) < 25 * 10 ** 9 and n <= 4096 * GROUPS
+    return max(n, 2 * M)
+
+
+def unsampled(n):
+    """bool [n]: the places of the index at which no sample is taken (runs of 256, chosen by a hash of their number)."""
+    samples = 1 if n >= 256 * GROUPS else 2 if n >= 128 * GROUPS else 4
+    run = np.arange(n) // 256
+    step, u, wave = run // 64, run // 16 % 4, run % 16
+    turn = ((step * 64 + wave) * 0x9E3779B1 % 2 ** 32) >> 30
+    return (u - turn) % 4 >= samples
+
+
 def index_of(kind, M, n, rng):
     """int32 [n] gather indices into M source rows."""
     idx = (np.arange(n) % M).astype(np.int32)
     rng.shuffle(idx)
+    at = np.arange(n)
     if kind == "padded":        # every fifth slot unused, some far outside
         idx[::5] = -1
         idx[7::50] = M
         idx[9::50] = 2 ** 31 - 1
     elif kind == "crowd":       # a quarter of the slots name one row: its owner's rows are dealt out
         idx[rng.random(n) < 0.25] = 5
-    elif kind == "hidden":      # a crowd where no sample is taken (every sixteenth slot): the list overflows
-        idx[np.arange(n) % 16 != 0] = np.where(rng.random(n) < 0.5, 3, idx)[np.arange(n) % 16 != 0]
+    elif kind == "sixteenth":   # a crowd in every slot but each sixteenth
+        idx[at % 16 != 0] = np.where(rng.random(n) < 0.5, 3, idx)[at % 16 != 0]
+    elif kind == "hidden":      # a crowd only where no sample is taken: the list of its owner overflows
+        idx[unsampled(n)] = 3
+    elif kind == "two hidden":  # the same with rows dealt to that owner as well
+        idx[unsampled(n)] = np.where(rng.random(n) < 0.9, 3, -1)[unsampled(n)]
+    elif kind == "last slot":   # the last of every eight slots names row 0
+        idx[at % 8 == 7] = 0
     elif kind == "one":         # all slots name the last row
         idx[:] = M - 1
+    elif kind == "none":
+        idx[:] = -(2 ** 31)
     elif kind == "sorted":
         idx.sort()
+    elif kind == "quarter":     # only the first quarter of the source is in use
+        idx[:] = rng.integers(0, M // 4, n)
+    elif kind == "eighth row":  # rows at a stride of a power of two
+        idx[:] = rng.integers(0, M // 8, n) * 8
+    elif kind == "few":         # fewer rows than workgroups
+        idx[:] = rng.integers(0, 100, n)
+    elif kind == "power":
+        idx[:] = (rng.random(n) ** 6 * M).astype(np.int32)
     return idx
 
 
-@pytest.mark.parametrize("layout", ["records", "planes8"])
-@pytest.mark.parametrize("K,M,n,kind", [
-    (2048, 1024, 19175, "mixed"), (2048, 1024, 19174, "mixed"),                     # work just above and below the rule
-    (2048, 1023, 21846, "mixed"), (1920, 1024, 32768, "mixed"),                     # too few rows; too short rows
-    (7168, 4200, 8401, "sorted"), (7168, 4200, 8399, "sorted"),                     # two copies a row, and just under
-    (2176, 1300, 30001, "padded"), (2048, 1029, 40003, "crowd"), (2048, 1024, 30010, "hidden"),
-    (7808, 1030, 5003, "padded"), (8192, 1024, 5003, "mixed"), (2048, 2047, 24577, "one")])
-def test_gather_by_owners(K, M, n, kind, layout):
-    """Both sides of the rule for gathering by owners, ends of the index that are no whole quad, an index that starts
-    at any multiple of 4 bytes, unused slots, crowds that the sample sees and ones that it does not."""
-    rng, x8, s, wq, wsf = source(M, K, K + n)
-    idx = index_of(kind, M, n, rng)
+def gathered(rng, x8, s, wq, wsf, idx, K, layout):
+    """Gathers into guarded outputs through an index that starts at an odd multiple of 4 bytes; every byte of the
+    buffer is compared."""
+    n, M = len(idx), x8.shape[0]
     buf, q, sf, ld_q, ld_sf, at = outputs(n, K, layout)
     padded = torch.zeros(n + 1, dtype=torch.int32, device=DEV)
     padded[1:] = dev(idx)
     mx.mxfp4_quant_from_fp8(dev(x8), dev(s), padded[1:], q=q, sf=sf, ld_q=ld_q, ld_sf=ld_sf)
-    src = np.where((idx >= 0) & (idx < M), idx, M)
-    check(buf, at, ld_q, ld_sf, K, np.arange(n), wq[src], wsf[src])
+    src = dev(np.where((idx >= 0) & (idx < M), idx, M).astype(np.int64))
+    want = torch.full_like(buf, 0xA5)
+    for start, ld, w in ((at[0], ld_q, dev(wq)), (at[1], ld_sf, dev(wsf))):
+        want.as_strided((n, w.shape[1]), (ld, 1), start).copy_(w[src])
+    if not torch.equal(buf, want):
+        bad = torch.nonzero(buf != want).view(-1)
+        raise AssertionError(f"{bad.numel()} of {buf.numel()} bytes differ, the first at {int(bad[0])} (rows start at {at}, "
+                             f"{ld_q} and {ld_sf} bytes apart)")
+
+
+@pytest.mark.parametrize("layout", ["records", "planes8"])
+@pytest.mark.parametrize("K,M,n,kind", [
+    (2048, 1024, 19175, "mixed"), (2048, 1023, 21846, "mixed"), (1920, 1024, 32768, "mixed"), (7168, 4200, 8401, "sorted"),
+    (7168, 4200, 8399, "sorted"), (2176, 1300, 30001, "padded"), (2048, 1029, 40003, "crowd"), (2048, 1024, 30010, "sixteenth"),
+    (7808, 1030, 5003, "padded"), (8192, 1024, 5003, "mixed"), (2048, 2047, 24577, "one")])
+def test_gather(K, M, n, kind, layout):
+    """Short rows and small maps: one lane per chunk."""
+    rng, x8, s, wq, wsf = source(M, K, K + n)
+    gathered(rng, x8, s, wq, wsf, index_of(kind, M, n, rng), K, layout)
+
+
+@pytest.mark.parametrize("layout", ["records", "planes8"])
+@pytest.mark.parametrize("K,rows,over,kind", [
+    (4096, 4, 0, "mixed"), (4096, 4, -1, "mixed"), (3968, 4, 1000, "mixed"),     # the rule's line, and rows too short for it
+    (4096, 4, 0, "hidden"), (4096, 5, 1, "two hidden"), (4224, 5, 2, "hidden"),  # longer lists than there is room for
+    (7168, 9, 3, "crowd"), (4224, 4, 0, "sixteenth"), (4096, 6, 1, "last slot"), (4096, 4, 5, "one"), (4096, 4, 2, "none"),
+    (6272, 5, 0, "padded"), (7680, 4, 3, "sorted"), (7808, 4, 1, "power"), (8192, 4, 2, "quarter"), (4096, 16, 0, "eighth row"),
+    (16896, 4, 3, "few"), (7168, 4, 40001, "mixed")])
+def test_gather_by_owners(K, rows, over, kind, layout):
+    """Both sides of the rule (`over` output rows above it; a few more source rows than `rows` per workgroup), ends of the
+    index that are no whole quad, unused slots, crowds that the sample sees and ones that it does not, sources of which a part
+    is used, rows of one and several segments, scale bytes as 16-byte pieces and as dwords."""
+    M = rows * GROUPS + (rows > 4) * 7
+    n = least(M, K) + over
+    rng, x8, s, wq, wsf = source(M, K, K + n)
+    gathered(rng, x8, s, wq, wsf, index_of(kind, M, n, rng), K, layout)
+
+
+def test_gather_sides_of_the_row_counts():
+    """Fewer rows than four per workgroup, and fewer than two output rows per source row, on the lane-wise side."""
+    for M, n in ((4 * GROUPS - 1, least(4 * GROUPS, 7168) + 100), (32 * GROUPS, 64 * GROUPS - 1), (32 * GROUPS, 64 * GROUPS)):
+        rng, x8, s, wq, wsf = source(M, 7168, n)
+        gathered(rng, x8, s, wq, wsf, index_of("padded", M, n, rng), 7168, "records")
+
+
+def test_gather_takes_no_map_to_one_workgroup():
+    """Maps that name one row in the slots of a fixed sample, or use a part of the source: one workgroup doing their work
+    alone takes 5 to 20 times as long as the workgroups together."""
+    M, K, n = 32 * GROUPS, 7168, 256 * GROUPS
+    x = torch.randint(0, 120, (M, K), dtype=torch.uint8, device=DEV)
+    s = torch.ones(M, K // 128, device=DEV)
+    q, sf = torch.empty(n, K // 2, dtype=torch.uint8, device=DEV), torch.empty(n, K // 32, dtype=torch.uint8, device=DEV)
+
+    def us(idx):
+        idx = dev(idx)
+        times = []
+        for _ in range(5):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            mx.mxfp4_quant_from_fp8(x, s, idx, q=q, sf=sf)
+            e[0].record()
+            for _ in range(5):
+                mx.mxfp4_quant_from_fp8(x, s, idx, q=q, sf=sf)
+            e[1].record()
+            torch.cuda.synchronize()
+            times.append(e[0].elapsed_time(e[1]) * 200)
+        return min(times)
+
+    rng = np.random.default_rng(1)
+    even = us(index_of("mixed", M, n, rng))
+    every = np.arange(n)
+    maps = {k: index_of(k, M, n, rng) for k in ("crowd", "sixteenth", "last slot", "one", "none", "quarter", "eighth row", "few")}
+    for slots in (16, 32, 64):
+        maps[f"last of {slots}"] = np.where(every % slots == slots - 1, 0, index_of("mixed", M, n, rng)).astype(np.int32)
+        maps[f"first of {slots}"] = np.where(every % slots != 0, 0, index_of("mixed", M, n, rng)).astype(np.int32)
+    slow = {k: round(t) for k, t in ((k, us(v)) for k, v in maps.items()) if t > 2.5 * even}
+    assert not slow, f"{slow} us against {even:.0f} for an even map"
 
 
 def test_gather_by_owners_under_capture():
     """Replays of a captured gather, with the inputs changed and eager work between the replays."""
-    K, M, n = 2048, 1024, 20480
+    K, M = 4096, 4 * GROUPS
+    n = least(M, K)
     rng, x8, s, _, _ = source(M, K, 1)
     x, xs = dev(x8), dev(s)
     idx = dev(index_of("padded", M, n, rng))
