@@ -753,8 +753,9 @@ static uint32_t owner_shift()
 // per thousand source rows (on 256 compute units; fewer of them save more).  The line lies where maps with crowds and unused
 // slots still lose nothing, not where routing maps begin to gain.  Measured on both sides of it (us, lane-wise / by owners;
 // the same with a quarter of the slots naming one row; with 40 % unused; naming 512 rows): saving 28 us, 58600 x 4096 from an
-// eighth as many rows 58 / 44, 49 / 49, 46 / 44, 43 / 39; 33500 x 7168 59 / 43, 51 / 50, 47 / 45, 46 / 42; 29800 x 8064 60 / 42,
-// 52 / 56, 47 / 44, 46 / 40; saving 14, 16700 x 7168 30 / 24, but 26 / 32, 25 / 26, 25 / 25; 3584 long rows, saving 28, 61 / 51, but
+// eighth as many rows 58 / 44, 49 / 49, 46 / 44, 43 / 39; 33500 x 7168 59 / 43, 51 / 50, 47 / 45, 46 / 42; rows of two
+// segments, 29800 x 8064 60 / 42, but 52 / 56, 47 / 44, 46 / 40; saving 54, 57000 x 8064 115 / 75, 101 / 91, 89 / 76, 87 / 68; saving
+// 14, 16700 x 7168 30 / 24, but 26 / 32, 25 / 26, 25 / 25; 3584 long rows, saving 28, 61 / 51, but
 // 53 / 55, 48 / 51, 45 / 50; 2048 long ones, saving 27, 59 / 51, but 52 / 58, 46 / 52, 42 / 48.
 static bool gather_by_owners(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q)
 {
@@ -763,7 +764,7 @@ static bool gather_by_owners(int64_t M_src, int64_t K, int64_t M_out, const uint
         M_out > OWNER_LIST / 2 * groups || ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) != 0u)
         return false;
     const int64_t saved_fs = (139 * M_out - 158 * M_src) * K - 124000 * M_src; // in 10^-15 s, from the rates above
-    return saved_fs >= (int64_t)25000000000;
+    return saved_fs >= (K > (int64_t)WAVE_SEG ? (int64_t)40000000000 : (int64_t)25000000000); // rows of one segment or more
 }
 
 hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,

@@ -81,10 +81,11 @@ def saved(M, K, n):
 
 def least(M, K):
     """The smallest number of output rows from which M source rows are gathered by owners."""
-    n = -(-(25 * 10 ** 9 + 124000 * M) // K + 158 * M) // 139
-    while saved(M, K, n) < 25 * 10 ** 9:
+    enough = (25 if K <= 7680 else 40) * 10 ** 9
+    n = ((enough + 124000 * M) // K + 158 * M) // 139
+    while saved(M, K, n) < enough:
         n += 1
-    assert saved(M, K, n - 1) < 25 * 10 ** 9 and n <= 4096 * GROUPS
+    assert saved(M, K, n - 1) < enough and n <= 4096 * GROUPS
     return max(n, 2 * M)
 
 
