@@ -451,13 +451,18 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     //   K = 7168 43 / 38 / 37, 51 / 51 / 49, 40 / 37 / 41; 65536 tokens of 7168, 8 copies (2 GB) 598 / 520 / 480.
     // A wave per row leaves lanes idle below 1024 elements and has its stores contiguous above; a workgroup per row
     // writes the longest runs, which pays for long rows with several copies, and it is done soonest where there are few
-    // rows (us, wave / workgroup: 61 rows of 4096, 8 copies 5.6 / 3.8, 488 rows 6.1 / 5.7).  Scale planes that are not on
-    // 16-byte boundaries stay with the lanes (1860 rows of 8064, 4 copies 8.7 against 11.0 us by workgroups).
+    // rows (us, wave / workgroup: 61 rows of 4096, 8 copies 5.6 / 3.8, 488 rows 6.1 / 5.7).  Between 4608 and 6144 elements
+    // the workgroup needs four copies, and more of them than the memory-side cache takes in (wave / workgroup, 140, 300 and 600
+    // million elements of records): K = 5632 8 copies 22 / 20, 46 / 42, 91 / 81, 4 copies 24 / 22, 51 / 44, 98 / 86, 2 copies 31 / 31,
+    // 59 / 62, 115 / 127; K = 4608 8 copies 22 / 21, 48 / 43, 93 / 82, 4 copies 24 / 24, 52 / 47, 99 / 91; K = 6016 8 copies 18 / 19,
+    // 38 / 38, 77 / 72, 4 copies 19 / 22, 45 / 42, 88 / 82.  Scale planes that are not on 16-byte boundaries stay with the
+    // lanes (1860 rows of 8064, 4 copies 8.7 against 11.0 us by workgroups).
     uint32_t segs_per_row;
     const uint32_t seg = wave_segment(K, &segs_per_row);
     const uint32_t rec = (uint32_t)((K / 2 + K / 32 + 15) & ~(int64_t)15);
     const int64_t units = M_src * segs_per_row;
-    if (rows16 && K >= 2048 && ((K >= 6144 && fanout >= 2) || units < 1024) && rec <= 48u * 1024u) {
+    const bool many = K >= 4608 && fanout >= 4 && M_src * K >= ((int64_t)1 << 28) / fanout;
+    if (rows16 && K >= 2048 && ((K >= 6144 && fanout >= 2) || many || units < 1024) && rec <= 48u * 1024u) {
         const bool records = sf == q + K / 2 && ld_sf == ld_q;
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_scatter_row_kernel<true>, dim3((uint32_t)M_src), dim3(SCATTER_THREADS), rec,
@@ -467,7 +472,7 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
                                stream, a, records);
         return hipGetLastError();
     }
-    if (rows16 && K >= 2048 && units < ((int64_t)1 << 31)) {
+    if (rows16 && K >= 2048) {
         const uint32_t blocks = (uint32_t)((units + SCATTER_WAVES - 1) / SCATTER_WAVES);
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_scatter_wave_kernel<true>, dim3(blocks), dim3(64 * SCATTER_WAVES), 0, stream,

@@ -69,6 +69,21 @@ def test_scatter_kernels(K, M, fan, layout):
     check(buf, at, ld_q, ld_sf, K, dst[~nowhere], wq[src], wsf[src])
 
 
+@pytest.mark.parametrize("K,M,fan", [(5632, 11916, 4), (5632, 11915, 4), (5632, 15887, 3), (4608, 7282, 8), (4480, 7490, 8)])
+def test_scatter_of_many_copies(K, M, fan):
+    """Both sides of the size, the row length and the fan-out from which a workgroup takes a row of less than 6144 elements."""
+    rng, x8, s, wq, wsf = source(M, K, K + M)
+    M_out = M * fan + 3
+    dst = rng.permutation(M_out)[: M * fan].reshape(M, fan).astype(np.int32)
+    buf, q, sf, ld_q, ld_sf, at = outputs(M_out, K, "records")
+    mx.mxfp4_quant_from_fp8_scatter(dev(x8), dev(s), dev(dst), M_out, q=q, sf=sf, ld_q=ld_q, ld_sf=ld_sf)
+    want = torch.full_like(buf, 0xA5)
+    rows = dev(dst.reshape(-1).astype(np.int64))
+    for start, ld, w in ((at[0], ld_q, wq), (at[1], ld_sf, wsf)):
+        want.as_strided((M_out, w.shape[1]), (ld, 1), start)[rows] = dev(w[:M]).repeat_interleave(fan, dim=0)
+    assert torch.equal(buf, want)
+
+
 # ---- gather by owners
 
 GROUPS = 1 << (torch.cuda.get_device_properties(0).multi_processor_count.bit_length() - 1) if torch.cuda.is_available() else 256
