@@ -446,6 +446,22 @@ __global__ void __launch_bounds__(T_THREADS) row_to_col_kernel(const RowToColArg
     }
 }
 
+// Dynamic LDS with which exactly three workgroups fit on a compute unit, from what the kernel itself has.
+static uint32_t lds_for_three()
+{
+    constexpr uint32_t LDS_OF_CU = 160u * 1024u, SHARE = 52u * 1024u;
+    static_assert(3u * SHARE <= LDS_OF_CU && 4u * SHARE > LDS_OF_CU, "three workgroups, not four");
+    static const uint32_t more = [] {
+        hipFuncAttributes f;
+        if (hipFuncGetAttributes(&f, reinterpret_cast<const void *>(row_to_col_kernel)) != hipSuccess) {
+            (void)hipGetLastError();
+            return 0u;
+        }
+        return f.sharedSizeBytes < SHARE ? SHARE - (uint32_t)f.sharedSizeBytes : 0u;
+    }();
+    return more;
+}
+
 hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const int32_t *expert_offsets,
                              int32_t num_experts, int64_t M, int64_t K, uint8_t *q_col, uint8_t *sf_col,
                              hipStream_t stream)
@@ -469,15 +485,18 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
     // Un-padded splits: k-rows start at any byte, and every tile shares its outer 64-byte segments with its neighbours.  The
     // two halves meet in the L2 if the tiles finish close together; what leaves it half written costs the memory a
     // read, modify and write, once the matrix is too large for the 256 MB memory-side cache.  Three workgroups per compute
-    // unit instead of four keep less in flight between the halves.  Measured (us, four -> three, Zipf-sized experts of any
-    // length): [65536,7168] in 32 154.5 -> 137.1, 16 150 -> 130, 64 148 -> 132; [32768,7168] in 16 73.1 -> 68.9, 32 75.8 ->
-    // 73.9; [65536,4096] in 32 88.5 -> 81.5.  Smaller matrices (40.6 -> 41.4 at [32768,4096]), splits of 512 rows (143 ->
-    // 150) and padded ones (95.3 -> 96.8) do not gain: total rows that are no multiple of 128 tell that some split is
-    // not padded to whole tile halves.
-    const bool unpadded = expert_offsets && M % 128 != 0;
-    const bool three_per_cu = unpadded && M >= 1024 * (int64_t)num_experts && M * K >= (int64_t)32768 * 7168;
-    constexpr uint32_t LDS_FOR_THREE = 52u * 1024u, LDS_STATIC = 37376u; // a compute unit has 160 KiB
-    hipLaunchKernelGGL(row_to_col_kernel, grid, dim3(T_THREADS), three_per_cu ? LDS_FOR_THREE - LDS_STATIC : 0u, stream, a);
+    // unit instead of four keep less in flight between the halves.  The launch cannot see the splits: a total that is no
+    // multiple of 128 rows tells that some split is not padded to whole tile halves, while one that is, and un-padded batches
+    // often have such totals, keeps four, since padded splits of the same sizes lose by three.  Measured (us, four ->
+    // three): [65533,7168] in 32 Zipf-sized experts 154.6 -> 136.5, in 16 154.3 -> 136.2, in one 152.2 -> 131.1; 32 experts of
+    // 2041 rows 155.5 -> 136.6; [66001,7168] in 64 153.6 -> 140.3, [131069,7168] in 64 305.5 -> 264.5, [61437,7168] in 32 141.7 ->
+    // 127.1, [33001,7168] in 16 68.4 -> 67.3, in 32 75.0 -> 71.9; [65533,4096] in 32 87.4 -> 80.1; [131069,2048] in 32 83.1 -> 77.0.
+    // Not taken: totals of [65536,7168], in 32 un-padded 154.6 -> 136.7, but padded 103.1 -> 104.6 and equal 94.1 -> 96.3;
+    // smaller matrices (40.6 -> 41.4 at [32768,4096]); 512 rows per expert (135.4 -> 151.4 for 128 of 513).  Lost: splits
+    // that are all one row short of whole tile halves have their pitch (32 of 2047 95.1 -> 99.5).
+    const bool three_per_cu = expert_offsets && M % 128 != 0 && M >= 1024 * (int64_t)num_experts &&
+                              M * K >= (int64_t)32768 * 7168;
+    hipLaunchKernelGGL(row_to_col_kernel, grid, dim3(T_THREADS), three_per_cu ? lds_for_three() : 0u, stream, a);
     return hipGetLastError();
 }
 
