@@ -283,12 +283,20 @@ __device__ __forceinline__ void store_streaming(void *p, u32x4 v)
 // A packed matrix (its nibble bytes) up to this size is expected to be read again from the 256 MB memory-side cache:
 // what is quantized is then de-quantized and transposed.  The dense quantizer sends such nibbles off with
 // store_through, which passes them on like a streaming store but leaves them in that cache, and the de-quantizer reads
-// them without the non-temporal hint, so that they stay there for the next reader.  Quantize, de-quantize, transpose
-// in this order (us, hints everywhere -> this; the same with warm and with cold inputs): [4096,7168] 29.0 -> 26.0,
-// [8192,7168] 50.8 -> 42.2, [16384,7168] 88.0 -> 76.4, [16384,2048] 30.9 -> 27.4.  Alone, cold: quantizer 9.7 -> 9.9,
-// 16.2 -> 16.3, 29.5 -> 29.7; de-quantizer 9.9 -> 10.0, 17.1 -> 17.3, 30.3 -> 30.9 (warm 8.8 -> 7.9, 17.1 -> 14.0,
-// 30.5 -> 26.4).  Above, the chain still gains but the single kernels lose: [32768,7168] 55.6 -> 57.9 and 57.1 -> 58.8.
-// Below 12 MiB the quantizer's non-temporal stores are the faster ones: [3000,7168] alone 7.0 against 7.3 us.
+// them without the non-temporal hint, so that they stay there for the next reader.  Measured cold, rotated buffers of 900 MB
+// (us, hints everywhere -> this):
+//   nibbles         quantize, de-quantize, transpose   quantizer alone   de-quantizer alone
+//    7.9 MiB [2304,7168]    21.6 -> 21.5 if it applied    7.25 ->  7.23     7.17 ->  7.15
+//   10   MiB [2912,7168]    27.2 -> 24.8 if it applied    7.79 ->  7.98     7.98 ->  8.02
+//   12   MiB [3520,7168]    29.5 -> 26.8                  8.81 ->  9.09     9.02 ->  9.03
+//   14   MiB [4096,7168]    29.1 -> 26.0                  9.75 -> 10.01     9.94 -> 10.11
+//   16   MiB [4672,7168]    35.3 -> 32.5                 10.44 -> 10.80    11.36 -> 11.39
+//   28   MiB [8192,7168]    50.9 -> 42.3                 16.30 -> 16.29    17.09 -> 17.29
+//   56   MiB [16384,7168]   88.0 -> 76.4                 29.5  -> 29.7     30.3  -> 30.9
+// A program that only quantizes loses up to 3 % at 12 to 16 MiB, one that reads the matrix again gains three to eight
+// times that and more.  Below 12 MiB the quantizer keeps its non-temporal stores: nothing is gained at 8 MiB and the gain
+// of the chain between was not taken for the single kernel's sake.  Above 64 MiB the chain still gains but the single
+// kernels lose: [32768,7168] 55.6 -> 57.9 and 57.1 -> 58.8.
 constexpr int64_t KEEP_BYTES = (int64_t)64 << 20;
 constexpr int64_t KEEP_FROM = (int64_t)12 << 20; // of the quantizer's output
 
