@@ -533,7 +533,8 @@ struct QuantOwnerArgs {
     uint32_t K;
     uint32_t seg;     // elements of a row taken at a time
     uint32_t shift;   // 2^shift workgroups
-    uint32_t samples; // of every four quads of the index
+    uint32_t samples; // runs of four that are sampled
+    uint32_t eighths; // of the steps in which they are
     uint32_t heavy;   // sampled indices above which an owner's rows are dealt out
     // The owner of a row: of every 2^shift consecutive ones each has another, in an order that changes from run to run.
     __device__ __forceinline__ uint32_t turn(uint32_t run) const { return __umul24(run, 77u); }
@@ -595,9 +596,10 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
                 if (p < q1)
                     v[u] = idx4[p];
             }
-            // A wave samples `samples` of its four runs of 256 indices; which ones changes from wave to wave and step to step
-            // without a pattern.
-            const uint32_t turn = ((base / OWNER_THREADS * OWNER_WAVES + wave) * 0x9E3779B1u) >> 30;
+            // A wave samples `samples` of its four runs of 256 indices, in `eighths` of its steps; which ones changes from wave
+            // to wave and step to step without a pattern.
+            const uint32_t hash = (base / OWNER_THREADS * OWNER_WAVES + wave) * 0x9E3779B1u;
+            const uint32_t turn = hash >> 30, some = sample && (hash >> 27 & 7u) < a.eighths ? a.samples : 0u;
 #pragma unroll
             for (int u = 0; u < STEP; ++u) {
                 const uint32_t p = base + u * OWNER_THREADS + tid;
@@ -608,7 +610,7 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
                     for (int e = 0; e < 4; ++e)
                         if (o[e] == me && v[u][e] < a.M_src) // also not the negative ones
                             push(v[u][e] >> a.shift, p * 4u + e);
-                if (sample && (((uint32_t)u - turn) & 3u) < a.samples)
+                if ((((uint32_t)u - turn) & 3u) < some)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (v[u][e] < a.M_src)
@@ -792,9 +794,10 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
         o.seg = wave_segment(K, &segs_per_row);
         o.shift = owner_shift();
         const uint32_t groups = 1u << o.shift;
-        // a quarter of the index, or as much as gives 64 sampled indices per owner
+        // as much of the index as gives 64 sampled indices per owner, a thirty-second of it at least
         o.samples = o.M_out >= 256u * groups ? 1u : o.M_out >= 128u * groups ? 2u : 4u;
-        o.heavy = 5u * (o.M_out / 4u * o.samples / groups) / 4u + 8u;
+        o.eighths = std::min(8u, std::max(1u, 2048u * groups / o.M_out));
+        o.heavy = 5u * (o.M_out / 32u * o.samples * o.eighths / groups) / 4u + 8u;
         const bool wide = K % 512 == 0 && ((reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_sf) & 15u) == 0u;
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_owner_kernel<true>, dim3(groups), dim3(OWNER_THREADS), 0, stream, o);

@@ -107,10 +107,11 @@ def least(M, K):
 def unsampled(n):
     """bool [n]: the places of the index at which no sample is taken (runs of 256, chosen by a hash of their number)."""
     samples = 1 if n >= 256 * GROUPS else 2 if n >= 128 * GROUPS else 4
+    eighths = min(8, max(1, 2048 * GROUPS // n))
     run = np.arange(n) // 256
     step, u, wave = run // 64, run // 16 % 4, run % 16
-    turn = ((step * 64 + wave) * 0x9E3779B1 % 2 ** 32) >> 30
-    return (u - turn) % 4 >= samples
+    hashed = (step * 64 + wave) * 0x9E3779B1 % 2 ** 32
+    return ((u - (hashed >> 30)) % 4 >= samples) | ((hashed >> 27 & 7) >= eighths)
 
 
 def index_of(kind, M, n, rng):
