@@ -498,13 +498,13 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
 // asked for by many (output rows padded with one and the same index, say), every workgroup counts the same sample of the
 // index per owner while it scans; the rows of an owner with a quarter more than its share, and the zero rows of indices
 // that name no source row, are dealt out by output row: every workgroup takes those of its own slice of the outputs.
-// Bound by the writes: 8192 rows of 7168 to eight records each 81.5 us = 3.8 TB/s of what has to move (lane-wise 120, where
+// Bound by the writes: 8192 rows of 7168 to eight records each 80 us = 3.9 TB/s of what has to move (lane-wise 119, where
 // half is reading every row eight times from the memory-side cache and a quarter quantizing it as often; the scatter form
 // of the same routing 60 us, without the scan and with four workgroups per compute unit), 20 thousand of a workgroup's 160
 // thousand cycles before its first write.  One workgroup of 16 waves per compute unit: two of them at 64 registers spill.
-// Maps of 65536 slots, 7168 long rows (us, lane-wise / by owners): shuffled 118 / 83, a quarter of the slots naming one row 101 / 85,
-// the last of every 16 slots 116 / 86, all naming one row 87 / 71, half unused 89 / 83, the first 512 rows only 91 / 76, every
-// eighth row 96 / 76, 128 rows at random 86 / 87, a power law (exponents 1/4 and 1/8) 97 / 98 and 91 / 93.  With 32768 slots:
+// Maps of 65536 slots, 7168 long rows (us, lane-wise / by owners): shuffled 118 / 82, a quarter of the slots naming one row 101 / 84,
+// the last of every 16 slots 116 / 85, all naming one row 83 / 70, half unused 88 / 82, the first 512 rows only 86 / 76, every
+// eighth row 96 / 75, 128 rows at random 84 / 88, a power law (exponents 1/4 and 1/8) 96 / 96 and 92 / 93.  With 32768 slots:
 // routes 60 / 41, one row in a quarter 52 / 48, half unused 45 / 43, first 512 rows 45 / 40, but 128 rows at random 43 / 49 and
 // the power laws 48 / 56 and 46 / 52, where some owners just below the line have more to write than one compute unit can.
 constexpr int OWNER_WAVES = 16;
@@ -576,7 +576,6 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
             atomicAdd(&s_fill[key], 1u);
         }
     };
-
     auto sampled = [&](uint32_t owner) {
         const u32x4 n = *reinterpret_cast<const u32x4 *>(s_sample[owner]);
         return n.x + n.y + n.z + n.w;
