@@ -12,7 +12,7 @@ inline mxfp4_status launched(hipError_t e) { return e == hipSuccess ? MXFP4_OK :
 
 constexpr int64_t kMaxWorkItems = ((int64_t)1 << 32) - 4096; // kernels index their work with 32 bits
 constexpr int64_t kMaxRows = (int64_t)1 << 31;
-static_assert(mxfp4::MAX_EXPERT_CHUNKS * 64 >= MXFP4_MAX_EXPERTS, "the expert lookup of the grouped kernels holds every expert's offsets");
+static_assert(mxfp4::MAX_EXPERTS >= MXFP4_MAX_EXPERTS, "the expert lookup of the grouped kernels holds every expert's offsets");
 
 } // namespace
 
@@ -188,6 +188,9 @@ static mxfp4_status row_to_fp8_col_common(const uint8_t *q_row, const uint8_t *s
         (expert_offsets && !aligned(expert_offsets, 4)))
         return MXFP4_ERR_ALIGN;
     const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (expert_offsets && mxfp4::fp8_col_in_segments(M, K, num_experts))
+        return launched(mxfp4::launch_row_to_fp8_col_grouped(q_row, sf_row, expert_offsets, num_experts, M, K, x_col,
+                                                             x_col_scale, requant, stream));
     return launched(requant ? mxfp4::launch_row_to_fp8_col_requant(q_row, sf_row, expert_offsets, num_experts, M, K,
                                                                    x_col, x_col_scale, stream)
                             : mxfp4::launch_row_to_fp8_col(q_row, sf_row, expert_offsets, num_experts, M, K, x_col,

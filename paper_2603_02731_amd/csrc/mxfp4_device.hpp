@@ -99,6 +99,27 @@ __device__ __forceinline__ float row_scale_operand(const uint32_t (&sb)[8])
     return u2f(j == 3 ? sb[I >> 2] >> 1 : sb[I >> 2] << (23 - 8 * j));
 }
 
+// The row scales of a tile go to LDS as [k-block][row].  Lane t holds the 8 bytes of row `row`, rows of a quad of lanes being
+// four consecutive ones on a multiple of 4: the four are byte-transposed inside the quad, so that lane q stores k-blocks q and
+// 4 + q of all of them as a dword each (eight byte stores per lane otherwise).
+template <uint32_t STRIDE>
+__device__ __forceinline__ void store_row_scales(uint8_t *s_row_sf, const u32x2 v, uint32_t row, uint32_t lane)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t t = perm(dpp_read<DPP_QUAD_XOR1>(v[h]), v[h], (lane & 1u) ? 0x03070105u : 0x06020400u);
+        t = perm(dpp_read<DPP_QUAD_XOR2>(t), t, (lane & 2u) ? 0x03020706u : 0x05040100u);
+        *reinterpret_cast<uint32_t *>(&s_row_sf[(4u * h + (lane & 3u)) * STRIDE + (row & ~3u)]) = t;
+    }
+}
+
+// Bit 7 of byte i is set where that byte of x is 256 - ADD or more: its top bit is set and its low seven bits plus ADD reach 128.
+template <uint32_t ADD>
+__device__ __forceinline__ uint32_t bytes_from(uint32_t x)
+{
+    return ((x & 0x7F7F7F7Fu) + ADD * 0x01010101u) & x & 0x80808080u;
+}
+
 // Workgroup -> tile for the transposing kernels.  The hardware deals consecutive workgroup ids
 // round-robin to the 8 XCDs, each with its own L2.  Id i therefore takes entry i/8 of XCD (i%8)'s
 // own contiguous share of a tile order in which mbm x MBK tiles form a macro block walked
@@ -171,6 +192,27 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v)
     return v;
 }
 
+// n / d for a divisor known at launch, exact for every 32-bit n (Granlund and Montgomery, "Division by invariant
+// integers using multiplication", 1994): a high multiplication and four cheap instructions instead of the 20 to 25 of a
+// division, which the kernels over row-strided buffers would pay for every 16 elements.
+struct FastDiv {
+    uint32_t mul, shift; // shift = ceil(log2 d) - 1, d >= 2
+    FastDiv() = default;
+    explicit FastDiv(uint32_t d)
+    {
+        uint32_t l = 1;
+        while (l < 32u && ((uint64_t)1 << l) < d)
+            ++l;
+        mul = (uint32_t)((((((uint64_t)1 << l) - d) << 32) / d) + 1u);
+        shift = l - 1u;
+    }
+    __device__ __forceinline__ uint32_t operator()(uint32_t n) const
+    {
+        const uint32_t t = __umulhi(mul, n);
+        return (t + ((n - t) >> 1)) >> shift;
+    }
+};
+
 // Ragged inputs: workgroup -> (expert, row tile inside it, k tile).  Expert e contributes
 // ceil(T_e / TILE_ROWS) row tiles, T_e = off[e+1] - off[e].  The order is expert after expert, each
 // expert's tiles in the macro-block walk of tile_of_workgroup over its own row tiles: a macro block
@@ -189,59 +231,60 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v)
 // On success `tile_m` is the tile index inside the expert and, for a non-zero UNIT_A / UNIT_B,
 // `a_before` / `b_before` the sum of ceil(T_j / UNIT) over the experts before it (where its
 // outputs start when the splits are not padded).
-constexpr int MAX_EXPERT_CHUNKS = 16; // 64 experts each: MXFP4_MAX_EXPERTS of the C ABI
-template <uint32_t TILE_ROWS, uint32_t UNIT_A, uint32_t UNIT_B, uint32_t MBM_MAX, uint32_t MBK>
-__device__ __forceinline__ bool tile_of_grouped_workgroup(const int32_t *off, int32_t num_experts, uint32_t id,
-                                                          uint32_t tiles_k, uint32_t *tile_m, uint32_t *tile_k,
-                                                          uint32_t *row_base, uint32_t *rows,
-                                                          uint32_t *a_before = nullptr, uint32_t *b_before = nullptr)
+constexpr int MAX_EXPERTS = 1024; // MXFP4_MAX_EXPERTS of the C ABI
+
+struct ExpertTile {
+    uint32_t tile_m, tile_k; // tile_m: inside the expert
+    uint32_t row_base, rows;
+    uint32_t a_before, b_before;
+};
+
+// n / d for uniform n below 2^24 and d below 2^12: the compiler then divides in a few FP32 instructions.
+__device__ __forceinline__ uint32_t small_div(uint32_t n, uint32_t d) { return (n & 0xFFFFFFu) / (d & 0xFFFu); }
+
+template <int CHUNKS, uint32_t TILE_ROWS, uint32_t UNIT_A, uint32_t UNIT_B, uint32_t MBM_MAX>
+__device__ __forceinline__ bool expert_tile(const int32_t *off, uint32_t num_experts, uint32_t id, uint32_t tiles_k,
+                                            FastDiv by_tiles_k, ExpertTile *t)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    uint32_t lo[MAX_EXPERT_CHUNKS], hi[MAX_EXPERT_CHUNKS];
+    uint32_t lo[CHUNKS], len[CHUNKS];
 #pragma unroll
-    for (int c = 0; c < MAX_EXPERT_CHUNKS; ++c) {
-        lo[c] = hi[c] = 0u;
-        if (c * 64 >= num_experts)
-            break;
-        const int32_t e = c * 64 + (int32_t)lane;
-        if (e < num_experts) {
-            lo[c] = (uint32_t)off[e];
-            hi[c] = (uint32_t)off[e + 1];
-        }
+    for (int c = 0; c < CHUNKS; ++c) { // all at once; lanes past the last expert see an empty one
+        const uint32_t e = c * 64 + lane;
+        lo[c] = (uint32_t)off[min(e, num_experts)];
+        len[c] = (uint32_t)off[min(e + 1u, num_experts)];
     }
-    uint32_t total = 0; // row tiles of all experts
-    uint32_t incl[MAX_EXPERT_CHUNKS]; // prefix sums of the tile counts inside each chunk
+    uint32_t nt[CHUNKS], incl[CHUNKS], before[CHUNKS]; // tiles, their prefix sums inside the chunk, those of earlier chunks
+    uint32_t total = 0;
 #pragma unroll
-    for (int c = 0; c < MAX_EXPERT_CHUNKS; ++c) {
-        incl[c] = 0u;
-        if (c * 64 >= num_experts)
-            break;
-        incl[c] = wave_inclusive_sum((hi[c] - lo[c] + TILE_ROWS - 1u) / TILE_ROWS);
+    for (int c = 0; c < CHUNKS; ++c) {
+        len[c] -= lo[c];
+        nt[c] = (len[c] + TILE_ROWS - 1u) / TILE_ROWS;
+        incl[c] = wave_inclusive_sum(nt[c]);
+        before[c] = total;
         total += (uint32_t)__builtin_amdgcn_readlane((int)incl[c], 63);
     }
     uint32_t entry;
     if (!order_entry_of_workgroup(id, total * tiles_k, &entry))
         return false;
-    const uint32_t tile = entry / tiles_k; // the expert whose row tiles include this index holds the entry
-
-    uint32_t before = 0, abefore = 0, bbefore = 0; // tiles / units of the experts in earlier chunks
+    const uint32_t tile = tiles_k == 1u ? entry : by_tiles_k(entry); // the expert whose row tiles include it holds the entry
+    uint32_t a_chunks = 0, b_chunks = 0;
 #pragma unroll
-    for (int c = 0; c < MAX_EXPERT_CHUNKS; ++c) {
-        if (c * 64 >= num_experts)
-            break;
-        const uint32_t len = hi[c] - lo[c];
-        const uint32_t nt = (len + TILE_ROWS - 1u) / TILE_ROWS;
-        const uint32_t na = UNIT_A ? (len + UNIT_A - 1u) / (UNIT_A ? UNIT_A : 1u) : 0u;
-        const uint32_t nb = UNIT_B ? (len + UNIT_B - 1u) / (UNIT_B ? UNIT_B : 1u) : 0u;
-        const uint32_t aincl = UNIT_A ? wave_inclusive_sum(na) : 0u;
-        const uint32_t bincl = UNIT_B ? wave_inclusive_sum(nb) : 0u;
-        const uint64_t hit = __ballot(before + incl[c] > tile);
-        if (hit != 0ull) {
+    for (int c = 0; c < CHUNKS; ++c) {
+        const uint32_t na = UNIT_A ? (len[c] + UNIT_A - 1u) / (UNIT_A ? UNIT_A : 1u) : 0u;
+        const uint32_t nb = UNIT_B ? (len[c] + UNIT_B - 1u) / (UNIT_B ? UNIT_B : 1u) : 0u;
+        const uint32_t a_incl = UNIT_A ? wave_inclusive_sum(na) : 0u, b_incl = UNIT_B ? wave_inclusive_sum(nb) : 0u;
+        const uint64_t hit = __ballot(before[c] + incl[c] > tile);
+        if (CHUNKS == 1 || hit != 0ull) {
             const int l = __ffsll((unsigned long long)hit) - 1;
-            const uint32_t excl = (uint32_t)__builtin_amdgcn_readlane((int)(incl[c] - nt), l);
-            *row_base = (uint32_t)__builtin_amdgcn_readlane((int)lo[c], l);
-            *rows = (uint32_t)__builtin_amdgcn_readlane((int)len, l);
-            const uint32_t nt_e = (uint32_t)__builtin_amdgcn_readlane((int)nt, l);
+            const uint32_t nt_e = (uint32_t)__builtin_amdgcn_readlane((int)nt[c], l);
+            const uint32_t tiles_before = before[c] + (uint32_t)__builtin_amdgcn_readlane((int)incl[c], l) - nt_e;
+            t->row_base = (uint32_t)__builtin_amdgcn_readlane((int)lo[c], l);
+            t->rows = (uint32_t)__builtin_amdgcn_readlane((int)len[c], l);
+            if (UNIT_A)
+                t->a_before = a_chunks + (uint32_t)__builtin_amdgcn_readlane((int)(a_incl - na), l);
+            if (UNIT_B)
+                t->b_before = b_chunks + (uint32_t)__builtin_amdgcn_readlane((int)(b_incl - nb), l);
             // macro block: the expert's width over the number of XCD shares it extends over (one expert is
             // then walked like a single matrix, see macro_block_rows), halved while above MBM_MAX
             // (the divisions only for an expert of at least 1.5 shares)
@@ -252,20 +295,32 @@ __device__ __forceinline__ bool tile_of_grouped_workgroup(const int32_t *off, in
             }
             while (mbm > MBM_MAX)
                 mbm = (mbm + 1u) / 2u;
-            tile_of_order_entry<MBK>(entry - (before + excl) * tiles_k, nt_e, tiles_k, mbm, tile_m, tile_k);
-            if (UNIT_A)
-                *a_before = abefore + (uint32_t)__builtin_amdgcn_readlane((int)(aincl - na), l);
-            if (UNIT_B)
-                *b_before = bbefore + (uint32_t)__builtin_amdgcn_readlane((int)(bincl - nb), l);
+            // the m-fastest walk of the macro row; that it goes by blocks of a few column tiles does not show in it
+            const uint32_t l_in = entry - tiles_before * tiles_k, per_macro_row = mbm * tiles_k;
+            const uint32_t mg = l_in < per_macro_row ? 0u : l_in / per_macro_row;
+            const uint32_t rem = l_in - mg * per_macro_row, mb_rows = min(mbm, nt_e - mg * mbm);
+            t->tile_k = per_macro_row <= 0xFFFFFFu ? small_div(rem, mb_rows) : rem / mb_rows;
+            t->tile_m = mg * mbm + rem - t->tile_k * mb_rows;
             return true;
         }
-        before += (uint32_t)__builtin_amdgcn_readlane((int)incl[c], 63);
         if (UNIT_A)
-            abefore += (uint32_t)__builtin_amdgcn_readlane((int)aincl, 63);
+            a_chunks += (uint32_t)__builtin_amdgcn_readlane((int)a_incl, 63);
         if (UNIT_B)
-            bbefore += (uint32_t)__builtin_amdgcn_readlane((int)bincl, 63);
+            b_chunks += (uint32_t)__builtin_amdgcn_readlane((int)b_incl, 63);
     }
     return false; // not reached: tile < total
+}
+
+template <uint32_t TILE_ROWS, uint32_t UNIT_A, uint32_t UNIT_B, uint32_t MBM_MAX>
+__device__ __forceinline__ bool tile_of_expert_workgroup(const int32_t *off, int32_t num_experts, uint32_t id, uint32_t tiles_k,
+                                                         FastDiv by_tiles_k, ExpertTile *t)
+{
+    if (num_experts <= 64)
+        return expert_tile<1, TILE_ROWS, UNIT_A, UNIT_B, MBM_MAX>(off, (uint32_t)num_experts, id, tiles_k, by_tiles_k, t);
+    if (num_experts <= 256)
+        return expert_tile<4, TILE_ROWS, UNIT_A, UNIT_B, MBM_MAX>(off, (uint32_t)num_experts, id, tiles_k, by_tiles_k, t);
+    return expert_tile<MAX_EXPERTS / 64, TILE_ROWS, UNIT_A, UNIT_B, MBM_MAX>(off, (uint32_t)num_experts, id, tiles_k,
+                                                                             by_tiles_k, t);
 }
 
 // Streaming stores for outputs that this kernel does not read again: the non-temporal hint together
@@ -324,27 +379,6 @@ __device__ __forceinline__ void store_head_bytes(uint8_t *dst, const u32x4 v, ui
     if (n & 1u)
         dst[pos + (n & 2u)] = (uint8_t)(d >> (8u * (n & 2u)));
 }
-
-// n / d for a divisor known at launch, exact for every 32-bit n (Granlund and Montgomery, "Division by invariant
-// integers using multiplication", 1994): a high multiplication and four cheap instructions instead of the 20 to 25 of a
-// division, which the kernels over row-strided buffers would pay for every 16 elements.
-struct FastDiv {
-    uint32_t mul, shift; // shift = ceil(log2 d) - 1, d >= 2
-    FastDiv() = default;
-    explicit FastDiv(uint32_t d)
-    {
-        uint32_t l = 1;
-        while (l < 32u && ((uint64_t)1 << l) < d)
-            ++l;
-        mul = (uint32_t)((((((uint64_t)1 << l) - d) << 32) / d) + 1u);
-        shift = l - 1u;
-    }
-    __device__ __forceinline__ uint32_t operator()(uint32_t n) const
-    {
-        const uint32_t t = __umulhi(mul, n);
-        return (t + ((n - t) >> 1)) >> shift;
-    }
-};
 
 // Compile-time loop: f(std::integral_constant<int, 0>) ... f(std::integral_constant<int, N-1>).
 // The conversion builtins take their byte selector as an immediate.

@@ -46,6 +46,7 @@ struct RowToColArgs {
     uint32_t tiles_k; // 256-column tiles
     uint32_t stage_in; // full tiles fetch their nibbles with 16-byte loads and re-slice them through LDS
     uint32_t mbm;      // row tiles per macro block of the tile order (one matrix; experts: see the lookup)
+    FastDiv by_tiles_k; // experts only
 };
 
 // Macro block of the tile order: 4 column tiles; row tiles by macro_block_rows for one matrix (32 at
@@ -212,10 +213,16 @@ __global__ void __launch_bounds__(T_THREADS) row_to_col_kernel(const RowToColArg
     uint32_t strip, tile_k;
     uint32_t row_base = 0, rows = a.M, bytes_before = 0, blocks_before = 0;
     if (a.expert_offsets) {
-        if (!tile_of_grouped_workgroup<TILE_M, 2, 32, MBM_MAX, MBK>(a.expert_offsets, a.num_experts, blockIdx.x, a.tiles_k,
-                                                                &strip, &tile_k, &row_base, &rows, &bytes_before,
-                                                                &blocks_before))
+        ExpertTile t;
+        if (!tile_of_expert_workgroup<TILE_M, 2, 32, MBM_MAX>(a.expert_offsets, a.num_experts, blockIdx.x, a.tiles_k,
+                                                              a.by_tiles_k, &t))
             return;
+        strip = t.tile_m;
+        tile_k = t.tile_k;
+        row_base = t.row_base;
+        rows = t.rows;
+        bytes_before = t.a_before;
+        blocks_before = t.b_before;
     } else if (!tile_of_workgroup<MBK>(blockIdx.x, a.tiles_m, a.tiles_k, a.mbm, &strip, &tile_k)) {
         return;
     }
@@ -479,6 +486,7 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
     a.tiles_m = (uint32_t)((M + TILE_M - 1) / TILE_M + (expert_offsets ? num_experts : 0));
     a.tiles_k = (uint32_t)((K + TILE_K - 1) / TILE_K);
     a.mbm = macro_block_rows(a.tiles_m);
+    a.by_tiles_k = FastDiv(a.tiles_k);
     const uint32_t total = a.tiles_m * a.tiles_k;
     a.stage_in = total >= 3u * compute_units() ? 1u : 0u; // at least 3 tiles per compute unit
     const dim3 grid((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD);

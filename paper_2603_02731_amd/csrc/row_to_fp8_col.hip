@@ -46,38 +46,21 @@ struct Args {
     uint8_t *x_col;
     float *x_col_scale;
     const int32_t *expert_offsets; // nullptr: one group of M rows
-    int32_t num_experts;
+    int32_t num_experts; // at most 64
     uint32_t M;
     uint32_t K;
     uint32_t tiles_m; // 256-row tiles (an upper bound when grouped)
     uint32_t tiles_k; // 256-column tiles
     uint32_t stage_in; // full tiles fetch their nibbles with 16-byte loads and re-slice them through LDS
     uint32_t mbm;      // row tiles per macro block of the tile order (one matrix; experts: see the lookup)
+    FastDiv by_tiles_k; // experts only
 };
-
-// Decode-scale operand of row I of a slice: exponent field max(127 - (bmax - b_I), 0) in bits
-// 30:23, computed as a signed value so that one max() does the clamp.
-template <int I>
-__device__ __forceinline__ float row_shift_operand(const uint32_t (&sb)[RPL / 4], int bias_minus_bmax)
-{
-    const int b = (int)((sb[I >> 2] >> (8 * (I & 3))) & 0xFFu);
-    return u2f((uint32_t)max((int)((uint32_t)(b + bias_minus_bmax) << 23), 0));
-}
-
-// Maximum of the 8 bytes at p (8-byte aligned, LDS).
-__device__ __forceinline__ uint32_t max_of_8_bytes(const uint8_t *p)
-{
-    const u32x2 v = *reinterpret_cast<const u32x2 *>(p);
-    const uint32_t t = max(max(v.x & 0xFFu, (v.x >> 8) & 0xFFu), max((v.x >> 16) & 0xFFu, v.x >> 24));
-    const uint32_t u = max(max(v.y & 0xFFu, (v.y >> 8) & 0xFFu), max((v.y >> 16) & 0xFFu, v.y >> 24));
-    return max(t, u);
-}
 
 } // namespace fp8col
 
 using namespace fp8col;
 
-__global__ void __launch_bounds__(T_THREADS) row_to_fp8_col_kernel(const Args a)
+__global__ void __launch_bounds__(T_THREADS, 2) row_to_fp8_col_kernel(const Args a)
 {
     __shared__ u32x4 s_out[TILE_K * 16];                 // [c*32 + cg][16 slots]: k-rows of 256 B
     __shared__ alignas(16) uint8_t s_row_sf[8 * TILE_M]; // [k-block of the tile][row]
@@ -89,9 +72,15 @@ __global__ void __launch_bounds__(T_THREADS) row_to_fp8_col_kernel(const Args a)
     uint32_t tile_m, tile_k;
     uint32_t row_base = 0, rows = a.M, groups_before = 0;
     if (a.expert_offsets) {
-        if (!tile_of_grouped_workgroup<TILE_M, 128, 0, MBM_MAX, MBK>(a.expert_offsets, a.num_experts, blockIdx.x, a.tiles_k,
-                                                                 &tile_m, &tile_k, &row_base, &rows, &groups_before))
+        ExpertTile t;
+        if (!expert_tile<1, TILE_M, 128, 0, MBM_MAX>(a.expert_offsets, (uint32_t)a.num_experts, blockIdx.x, a.tiles_k,
+                                                     a.by_tiles_k, &t))
             return;
+        tile_m = t.tile_m;
+        tile_k = t.tile_k;
+        row_base = t.row_base;
+        rows = t.rows;
+        groups_before = t.a_before;
     } else if (!tile_of_workgroup<MBK>(blockIdx.x, a.tiles_m, a.tiles_k, a.mbm, &tile_m, &tile_k)) {
         return;
     }
@@ -322,6 +311,7 @@ hipError_t launch_row_to_fp8_col(const uint8_t *q_row, const uint8_t *sf_row, co
     // upper bound on the number of row tiles: every expert may end in a partial one
     a.tiles_m = (uint32_t)((M + TILE_M - 1) / TILE_M + (expert_offsets ? num_experts : 0));
     a.tiles_k = (uint32_t)((K + TILE_K - 1) / TILE_K);
+    a.by_tiles_k = FastDiv(a.tiles_k);
     const uint32_t total = a.tiles_m * a.tiles_k;
     // at least 4 tiles per compute unit (over rotated buffers: 3-5 % slower at 640 to 896 tiles, 1-4 % faster from 1024 on)
     a.stage_in = total >= 4u * compute_units() ? 1u : 0u;

@@ -38,81 +38,15 @@ struct Args {
     uint8_t *x_col;
     float *x_col_scale;
     const int32_t *expert_offsets; // nullptr: one group of M rows
-    int32_t num_experts;
+    int32_t num_experts; // at most 64
     uint32_t M;
     uint32_t K;
     uint32_t tiles_m; // 256-row tiles (an upper bound when grouped)
     uint32_t tiles_k; // 256-column tiles
     uint32_t stage_in; // full tiles fetch their nibbles with 16-byte loads and re-slice them through LDS
     uint32_t mbm;      // row tiles per macro block of the tile order (one matrix; experts: see the lookup)
+    FastDiv by_tiles_k; // experts only
 };
-
-// Emax = biased exponent of a non-zero column maximum, plus one (FP32 subnormals: 2^-127 and
-// 1.5 * 2^-127 give 1, 2^-128 gives 0).
-__device__ __forceinline__ int emax_of_amax_bits(uint32_t bits)
-{
-    const int ef = (int)(bits >> 23);
-    return ef >= 1 ? ef + 1 : (bits >= 0x00400000u ? 1 : 0);
-}
-
-// FP32 bit pattern of the group scale 2^(Emax - 136) (an FP32 subnormal for Emax <= 9); 1.0 for
-// a group without a non-zero element.
-__device__ __forceinline__ uint32_t scale_bits_of_emax(int emax, bool any_nonzero)
-{
-    if (!any_nonzero)
-        return 0x3F800000u;
-    const int field = emax - 9;
-    return field >= 1 ? (uint32_t)field << 23 : 0x00400000u >> (uint32_t)(-field);
-}
-
-// The integer path.  Column kc of the tile over the rows [r0, r0 + n) of the tile (one scale
-// group): Emax over the non-zero codes of the rows whose scale byte is not NaN, or -1 without
-// any, plus GROUP_HAS_NAN when a NaN byte occurs.  Nibbles come from global memory, scale bytes
-// from the staged copy.
-constexpr int GROUP_HAS_NAN = 1 << 16;
-__device__ __noinline__ int group_emax_int(const uint8_t *tile_src, size_t pitch, const uint8_t *row_sf_kb,
-                                           uint32_t kc, uint32_t r0, uint32_t n)
-{
-    int emax = -1;
-    bool any_nan = false;
-#pragma nounroll
-    for (uint32_t r = r0; r < r0 + n; ++r) {
-        const uint32_t b = row_sf_kb[r];
-        const uint32_t byte = tile_src[(size_t)r * pitch + (kc >> 1)];
-        const uint32_t mag = ((kc & 1u) ? byte >> 4 : byte) & 7u;
-        if (b == 255u)
-            any_nan = true;
-        else if (mag)
-            emax = max(emax, (int)b + (int)(mag >> 1));
-    }
-    return emax + (any_nan ? GROUP_HAS_NAN : 0);
-}
-
-// E4M3 byte of +-e2m1(nib) * 2^(b - 127) / 2^(emax - 136) in integers.  With h = 2 * |e2m1| the
-// quotient is h * 2^(b - emax + 17) quanta of 2^-9 (the E4M3 subnormal step): an exact integer n
-// when the shift is not negative, else rounded to nearest-even; n < 16 is its own code
-// (subnormals and the first binade), above that the binade is the position of the leading bit.
-__device__ __forceinline__ uint32_t e4m3_requant_int(uint32_t nib, uint32_t b, int emax)
-{
-    const uint32_t mag = nib & 7u, sign = (nib & 8u) << 4;
-    const uint32_t h = mag < 4u ? mag : mag == 4u ? 4u : mag == 5u ? 6u : mag == 6u ? 8u : 12u;
-    if (mag == 0u)
-        return sign;
-    const int sh = (int)b - emax + 17;
-    uint32_t n;
-    if (sh >= 0) {
-        n = h << sh;
-    } else if (sh < -5) {
-        n = 0;
-    } else {
-        const uint32_t t = (uint32_t)(-sh), q = h >> t, rem = h & ((1u << t) - 1u), half = 1u << (t - 1u);
-        n = q + ((rem > half || (rem == half && (q & 1u))) ? 1u : 0u);
-    }
-    if (n < 16u)
-        return sign | n;
-    const uint32_t p = 31u - (uint32_t)__builtin_clz(n);
-    return sign | ((p - 2u) << 3) | ((n >> (p - 3u)) & 7u);
-}
 
 } // namespace fp8col_requant
 
@@ -130,9 +64,14 @@ __global__ void __launch_bounds__(T_THREADS) row_to_fp8_col_requant_kernel(const
     uint32_t tile_m, tile_k;
     uint32_t row_base = 0, rows = a.M, groups_before = 0;
     if (a.expert_offsets) {
-        if (!tile_of_grouped_workgroup<TILE_M, 128, 0, 64, 4>(a.expert_offsets, a.num_experts, blockIdx.x, a.tiles_k,
-                                                              &tile_m, &tile_k, &row_base, &rows, &groups_before))
+        ExpertTile t;
+        if (!expert_tile<1, TILE_M, 128, 0, 64>(a.expert_offsets, (uint32_t)a.num_experts, blockIdx.x, a.tiles_k, a.by_tiles_k, &t))
             return;
+        tile_m = t.tile_m;
+        tile_k = t.tile_k;
+        row_base = t.row_base;
+        rows = t.rows;
+        groups_before = t.a_before;
     } else if (!tile_of_workgroup<4>(blockIdx.x, a.tiles_m, a.tiles_k, a.mbm, &tile_m, &tile_k)) {
         return;
     }
@@ -399,6 +338,7 @@ hipError_t launch_row_to_fp8_col_requant(const uint8_t *q_row, const uint8_t *sf
     // upper bound on the number of row tiles: every expert may end in a partial one
     a.tiles_m = (uint32_t)((M + TILE_M - 1) / TILE_M + (expert_offsets ? num_experts : 0));
     a.tiles_k = (uint32_t)((K + TILE_K - 1) / TILE_K);
+    a.by_tiles_k = FastDiv(a.tiles_k);
     const uint32_t total = a.tiles_m * a.tiles_k;
     // at least 4 tiles per compute unit (over rotated buffers: 3-5 % slower at 640 to 896 tiles, 1-4 % faster from 1024 on)
     a.stage_in = total >= 4u * compute_units() ? 1u : 0u;

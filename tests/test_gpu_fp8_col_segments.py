@@ -1,0 +1,82 @@
+"""GPU parity of the ragged FP8-column conversions where tiles write whole 64-byte segments of the output: splits around the
+edges of pieces (16 rows), segments (64), scale groups (128) and tiles (256), outputs and inputs that begin off a segment, half
+tiles along k, special scale bytes in the look-back rows, and both sides of the rule that leaves small padded launches to the
+kernels that write their own rows."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2603_02731_amd as mx
+from oracle import ref
+from paper_2603_02731_amd import synth
+from tests.test_gpu_parity import DEV, assert_same, host
+
+pytestmark = pytest.mark.gpu
+
+SPLITS = {
+    "pieces": [1, 15, 16, 17, 0, 31, 2, 241, 255, 257, 271, 272, 273],
+    "segments": [63, 64, 65, 191, 192, 193, 319, 320, 321, 64, 448],
+    "groups": [127, 128, 129, 383, 384, 385, 256, 511, 512, 513, 0, 769],
+    "one": [1023],
+    "by 16": [16, 272, 48, 528, 304, 1040, 32, 336],      # a total that is a multiple of 16: the small launch keeps its kernels
+    "by 16 at length": [16 * n for n in (1, 3, 17, 33, 65, 20, 50, 31)] * 9,  # the same, above the line at K = 2176
+    "by 64": [64, 320, 576, 192, 128, 832],               # k-rows of whole segments, of half lines
+}
+
+
+def run(rows, K, requant, q, sf, q_off=0, x_off=0):
+    """The grouped call on inputs q_off and an output x_off bytes past a 256-byte boundary, guards behind both outputs."""
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    n, ns = K * int(off[-1]), K * sum(-(-r // 128) for r in rows)
+    src = torch.empty(q.size + 256, dtype=torch.uint8, device=DEV)[q_off:q_off + q.size].view(q.shape)
+    src.copy_(torch.from_numpy(q))
+    x = torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    s = torch.full((ns + 64,), -7.0, device=DEV)
+    mx.mxfp4_row_to_fp8_col_grouped(src, torch.from_numpy(sf).to(DEV), torch.from_numpy(off).to(DEV),
+                                    x_col=x[x_off:x_off + n], x_col_scale=s[:ns], requant=requant, offsets_host=off.tolist())
+    want, want_s = ref.row_to_fp8_col_grouped(q, sf, off, requant=requant)
+    got = host(x)
+    assert (got[:x_off] == 0xA5).all() and (got[x_off + n:] == 0xA5).all(), "bytes around the output written"
+    assert bool((s[ns:] == -7.0).all()), "scales behind the output written"
+    assert_same(host(s)[:ns], want_s, f"group scales K={K} requant={requant}")
+    assert_same(got[x_off:x_off + n], want, f"E4M3 bytes K={K} requant={requant}")
+
+
+@pytest.mark.parametrize("requant", [False, True])
+@pytest.mark.parametrize("name", SPLITS)
+def test_splits_around_the_edges(name, requant):
+    rows = SPLITS[name]
+    K = 2176 if name == "by 16 at length" else 384
+    q, sf = synth.random_mxfp4(sum(rows), K, seed=len(rows), scale_spread=6)
+    run(rows, K, requant, q.numpy(), sf.numpy())
+
+
+@pytest.mark.parametrize("q_off,x_off", [(0, 16), (4, 0), (12, 48), (0, 64)])
+def test_alignment_of_input_and_output(q_off, x_off):
+    rows = [300, 128, 64, 513, 7]
+    q, sf = synth.random_mxfp4(sum(rows), 256, seed=q_off + x_off, scale_spread=6)
+    for requant in (False, True):
+        run(rows, 256, requant, q.numpy(), sf.numpy(), q_off, x_off)
+
+
+@pytest.mark.parametrize("requant", [False, True])
+@pytest.mark.parametrize("center,spread,nan", [(250, 6, 0.0), (3, 4, 0.0), (127, 20, 0.02), (127, 127, 0.002)])
+def test_special_scales_in_the_look_back_rows(center, spread, nan, requant):
+    """Bytes beyond FP32, NaN, and maxima so small that the encoder's operand would be negative, in some groups only."""
+    rows = [777, 130, 515]
+    q, sf = synth.random_mxfp4(sum(rows), 384, seed=center, scale_center=127, scale_spread=3)
+    q2, sf2 = synth.random_mxfp4(sum(rows), 384, seed=spread, scale_center=center, scale_spread=spread, nan_scale_frac=nan)
+    q, sf = q.numpy(), sf.numpy()
+    for lo, hi in ((150, 260), (420, 470), (640, 645), (1000, 1300)):  # far halves, near halves, tiles
+        q[lo:hi], sf[lo:hi] = q2.numpy()[lo:hi], sf2.numpy()[lo:hi]
+    q[300:384] = 0  # a look-back half without a non-zero element
+    run(rows, 384, requant, q, sf)
+
+
+@pytest.mark.parametrize("experts", [64, 65, 256, 257, 1024])
+def test_expert_lookup_at_its_sizes(experts):
+    rng = np.random.default_rng(experts)
+    rows = [int(r) for r in rng.integers(0, 90, experts)]
+    rows[experts // 2], rows[-1] = 600, 1
+    q, sf = synth.random_mxfp4(sum(rows), 128, seed=experts, scale_spread=4)
+    run(rows, 128, False, q.numpy(), sf.numpy())
