@@ -23,6 +23,7 @@
 // the HBM traffic at the algorithmic 0.53125 B read + 0.53125 B written per element.
 #include "mxfp4_device.hpp"
 #include "mxfp4_kernels.hpp"
+#include "row_to_col_slice.hpp"
 
 namespace mxfp4 {
 
@@ -47,6 +48,7 @@ struct RowToColArgs {
     uint32_t stage_in; // full tiles fetch their nibbles with 16-byte loads and re-slice them through LDS
     uint32_t mbm;      // row tiles per macro block of the tile order (one matrix; experts: see the lookup)
     FastDiv by_tiles_k; // experts only
+    uint32_t few;       // experts only: at most one and a half tiles per compute unit
 };
 
 // Macro block of the tile order: 4 column tiles; row tiles by macro_block_rows for one matrix (32 at
@@ -58,37 +60,6 @@ constexpr uint32_t MBM_MAX = 64, MBK = 4;
 __device__ __forceinline__ uint32_t load_nibbles(const uint32_t *p)
 {
     return __builtin_nontemporal_load(p);
-}
-
-// One lane's 32x8 slice through the hardware conversions, in two steps with the column scales between them
-// (the workgroup sends the scale bytes off before it re-quantizes).  Exact while every value
-// e2m1 * 2^(b-127) is an FP32 number, i.e. for row-scale bytes up to 252
-// (6 * 2^125 < 2^128; the smallest, 0.5 * 2^-127, is an FP32 subnormal).
-// Step 1: the UE8M0 bytes of the slice's 8 columns.
-__device__ __forceinline__ void column_scales_hw(const uint32_t (&w)[32], const uint32_t (&sb)[8], uint32_t (&cb)[8])
-{
-    // column maxima of |value| (no NaN can occur: NaN row scales never get here)
-    float amax[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-        amax[c] = 0.0f;
-    static_for<16>([&](auto ip) {
-        constexpr int i = 2 * decltype(ip)::value;
-        const float sa = row_scale_operand<i>(sb), sbb = row_scale_operand<i + 1>(sb);
-        static_for<4>([&](auto jp) {
-            constexpr int j = decltype(jp)::value;
-            const f32x2 fa = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], sa, j);
-            const f32x2 fb = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i + 1], sbb, j);
-            amax[2 * j] = max3_abs_nan(fa.x, fb.x, amax[2 * j]);
-            amax[2 * j + 1] = max3_abs_nan(fa.y, fb.y, amax[2 * j + 1]);
-        });
-    });
-    // the sec. 3.1 rule on the exponent field.  A maximum with at most two significant bits (1.0 or 1.5
-    // times a power of two) never exceeds 1.5 * 2^e, so the byte is its exponent field minus 2, clamped
-    // at 0; zero and FP32 subnormals give 0.
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-        cb[c] = max(f2u(amax[c]) >> 23, 2u) - 2u;
 }
 
 // Step 2: decode again (cheaper than keeping 256 floats live) and re-quantize pairs of rows into output
@@ -201,6 +172,9 @@ __device__ __noinline__ uint64_t requant_slice_int(const uint8_t *src, size_t sr
 //    hardware's own dispatch of one short workgroup per tile is the better scheduler here.
 //  * Macro blocks of 8 / 16 / 64 row tiles: 103 / 108 / 98 us; 1 to 28 column tiles: no difference.  Dword loads
 //    (one per row and lane) instead of the 16-byte loads re-sliced through LDS: 95 us.
+// GENERAL: launches of few tiles and of more than 64 experts.  One matrix and the other launches have an instance without what
+// those need, which cost [65536, 7168] 0.6 % by its presence.
+template <bool GENERAL>
 __global__ void __launch_bounds__(T_THREADS) row_to_col_kernel(const RowToColArgs a)
 {
     __shared__ u32x4 s_out[TILE_K * NRG];                // [c*32 + cg][slot]: 256 k-rows x 128 B
@@ -214,8 +188,10 @@ __global__ void __launch_bounds__(T_THREADS) row_to_col_kernel(const RowToColArg
     uint32_t row_base = 0, rows = a.M, bytes_before = 0, blocks_before = 0;
     if (a.expert_offsets) {
         ExpertTile t;
-        if (!tile_of_expert_workgroup<TILE_M, 2, 32, MBM_MAX>(a.expert_offsets, a.num_experts, blockIdx.x, a.tiles_k,
-                                                              a.by_tiles_k, &t))
+        if (!(GENERAL ? tile_of_expert_workgroup<TILE_M, 2, 32, MBM_MAX>(a.expert_offsets, a.num_experts, blockIdx.x, a.tiles_k,
+                                                                       a.by_tiles_k, &t)
+                    : expert_tile<1, TILE_M, 2, 32, MBM_MAX>(a.expert_offsets, (uint32_t)a.num_experts, blockIdx.x, a.tiles_k,
+                                                             a.by_tiles_k, &t)))
             return;
         strip = t.tile_m;
         tile_k = t.tile_k;
@@ -435,7 +411,40 @@ __global__ void __launch_bounds__(T_THREADS) row_to_col_kernel(const RowToColArg
         // meet in the L2 first: plain stores (32 splits of 1984 rows, pitch 992 bytes: 2.7 ns per row
         // non-temporal, 1.7 plain).
         const bool segments64 = ((reinterpret_cast<uintptr_t>(out_q) | pitch_q) & 63u) == 0u;
-        if (cgx * 8u < cols && have != 0u) {
+        const uint32_t nb = (n_rows + 1u) / 2u; // bytes of the tile in a k-row
+        if (GENERAL && a.few && ((reinterpret_cast<uintptr_t>(out_q) | pitch_q) & 15u) != 0u && nb >= 16u) {
+            // K-rows that begin off a 16-byte boundary: the pieces between the boundaries from there on, put together from two
+            // slots of LDS, then the first and the last 16 bytes of every k-row, which overlap them.
+            auto shifted = [](const u32x4 &x, const u32x4 &y, uint32_t by) { // bytes [by, by + 16) of x, y
+                const bool b8 = (by & 8u) != 0u, b4 = (by & 4u) != 0u;
+                const uint32_t t0 = b8 ? x.z : x.x, t1 = b8 ? x.w : x.y, t2 = b8 ? y.x : x.z, t3 = b8 ? y.y : x.w,
+                               t4 = b8 ? y.z : y.x, t5 = b8 ? y.w : y.y;
+                const uint32_t d0 = b4 ? t1 : t0, d1 = b4 ? t2 : t1, d2 = b4 ? t3 : t2, d3 = b4 ? t4 : t3, d4 = b4 ? t5 : t4;
+                return u32x4{__builtin_amdgcn_alignbyte(d1, d0, by), __builtin_amdgcn_alignbyte(d2, d1, by),
+                             __builtin_amdgcn_alignbyte(d3, d2, by), __builtin_amdgcn_alignbyte(d4, d3, by)};
+            };
+            const uint32_t next = (tid & ~(NRG - 1u)) | ((tid + 1u) & (NRG - 1u)); // the next slot of the k-row
+            if (cgx * 8u < cols) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    uint8_t *at = dst + (size_t)u * pitch_q;
+                    const uint32_t by = (0u - (uint32_t)reinterpret_cast<uintptr_t>(at)) & 15u;
+                    const u32x4 v = shifted(s_out[u * T_THREADS + tid], s_out[u * T_THREADS + next], by);
+                    if (part * 16u + by + 16u <= nb)
+                        *reinterpret_cast<u32x4 *>(at + by) = v;
+                }
+            }
+            const uint32_t kc = (tid & 31u) * 8u + (tid >> 5); // row tid of the LDS tile is column kc
+            if (kc < cols) {
+                uint8_t *row = out_q + (size_t)(k0 + kc) * pitch_q + m0 / 2u;
+                const uint32_t turn = (tid & 31u) >> 1, from = (nb - 16u) >> 4;
+                const u32x4 first = s_out[tid * NRG + (turn & (NRG - 1u))];
+                const u32x4 x = s_out[tid * NRG + ((from + turn) & (NRG - 1u))];
+                const u32x4 y = s_out[tid * NRG + ((from + 1u + turn) & (NRG - 1u))];
+                *reinterpret_cast<u32x4_unaligned *>(row) = first;
+                *reinterpret_cast<u32x4_unaligned *>(row + nb - 16u) = shifted(x, y, (nb - 16u) & 15u);
+            }
+        } else if (cgx * 8u < cols && have != 0u) {
             if (have == 16u && segments64) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
@@ -460,7 +469,7 @@ static uint32_t lds_for_three()
     static_assert(3u * SHARE <= LDS_OF_CU && 4u * SHARE > LDS_OF_CU, "three workgroups, not four");
     static const uint32_t more = [] {
         hipFuncAttributes f;
-        if (hipFuncGetAttributes(&f, reinterpret_cast<const void *>(row_to_col_kernel)) != hipSuccess) {
+        if (hipFuncGetAttributes(&f, reinterpret_cast<const void *>(row_to_col_kernel<true>)) != hipSuccess) {
             (void)hipGetLastError();
             return 0u;
         }
@@ -473,6 +482,14 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
                              int32_t num_experts, int64_t M, int64_t K, uint8_t *q_col, uint8_t *sf_col,
                              hipStream_t stream)
 {
+    // One large matrix whose k-rows are no whole 64-byte segments: tiles that write whole ones, at the price of converting up to
+    // half as many rows once more.  Measured (us, own rows / segments): [65504, 7168] 146 / 119, [49120, 7168] 113 / 94,
+    // [32736, 7168] 75 / 66, [40032, 8192] 118 / 94, [57056, 5120] 93 / 80, [131040, 2048] 78 / 73, [49120, 4096] 65 / 57, but
+    // [32736, 4096] 41 / 42, [65504, 2048] 38 / 41, [16352, 7168] 36 / 40: what smaller ones leave half written meets in the
+    // memory-side cache.  Not for experts, whose last tiles cost as much as whole ones: 16 of 2585 rows, K = 7424, 81 / 92,
+    // [65533, 7168] in 32 Zipf-sized 139 / 134, in 128 142 / 157.
+    if (!expert_offsets && M % 128 != 0 && M * K >= (int64_t)176 << 20)
+        return launch_row_to_col_segments(q_row, sf_row, M, K, q_col, sf_col, stream);
     RowToColArgs a;
     a.q_row = q_row;
     a.sf_row = sf_row;
@@ -490,21 +507,24 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
     const uint32_t total = a.tiles_m * a.tiles_k;
     a.stage_in = total >= 3u * compute_units() ? 1u : 0u; // at least 3 tiles per compute unit
     const dim3 grid((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD);
-    // Un-padded splits: k-rows start at any byte, and every tile shares its outer 64-byte segments with its neighbours.  The
-    // two halves meet in the L2 if the tiles finish close together; what leaves it half written costs the memory a
-    // read, modify and write, once the matrix is too large for the 256 MB memory-side cache.  Three workgroups per compute
-    // unit instead of four keep less in flight between the halves.  The launch cannot see the splits: a total that is no
-    // multiple of 128 rows tells that some split is not padded to whole tile halves, while one that is, and un-padded batches
-    // often have such totals, keeps four, since padded splits of the same sizes lose by three.  Measured (us, four ->
-    // three): [65533,7168] in 32 Zipf-sized experts 154.6 -> 136.5, in 16 154.3 -> 136.2, in one 152.2 -> 131.1; 32 experts of
-    // 2041 rows 155.5 -> 136.6; [66001,7168] in 64 153.6 -> 140.3, [131069,7168] in 64 305.5 -> 264.5, [61437,7168] in 32 141.7 ->
-    // 127.1, [33001,7168] in 16 68.4 -> 67.3, in 32 75.0 -> 71.9; [65533,4096] in 32 87.4 -> 80.1; [131069,2048] in 32 83.1 -> 77.0.
-    // Not taken: totals of [65536,7168], in 32 un-padded 154.6 -> 136.7, but padded 103.1 -> 104.6 and equal 94.1 -> 96.3;
-    // smaller matrices (40.6 -> 41.4 at [32768,4096]); 512 rows per expert (135.4 -> 151.4 for 128 of 513).  Lost: splits
-    // that are all one row short of whole tile halves have their pitch (32 of 2047 95.1 -> 99.5).
-    const bool three_per_cu = expert_offsets && M % 128 != 0 && M >= 1024 * (int64_t)num_experts &&
-                              M * K >= (int64_t)32768 * 7168;
-    hipLaunchKernelGGL(row_to_col_kernel, grid, dim3(T_THREADS), three_per_cu ? lds_for_three() : 0u, stream, a);
+    // A few tiles per compute unit: what an unaligned 16-byte store costs a wave to issue shows (un-padded [2000, 2048] in 8
+    // experts 7.9 -> 7.1 us, [8000, 1024] in 64 10.2 -> 9.4, [3000, 512] in 128 8.4 -> 7.8); with more of them the memory waits
+    // for the additional requests ([16384, 2048] in 16 13.8 -> 14.1, [65536, 7168] in 32 158 -> 170).
+    a.few = 2 * total <= 3 * compute_units() ? 1u : 0u;
+    // Large ragged splits: every tile shares its outer 64-byte segments with its neighbours where the k-rows of an expert are
+    // not whole segments.  The two halves meet in the L2 if the tiles finish close together; what leaves it half written costs
+    // the memory a read, modify and write, once the matrix is too large for the 256 MB memory-side cache.  Three workgroups per
+    // compute unit instead of four keep less in flight between the halves.  Measured (us, four -> three), K = 7168: 65536 rows
+    // un-padded in 32 Zipf-sized experts 157 -> 139, in 64 151 -> 139, in 8 151 -> 137; padded to 16 rows 141 -> 124, to 64
+    // 118 -> 110; padded to 128 rows, which share nothing, 102.4 -> 102.5, 32 equal ones 94.2 -> 93.0, one 95.7 -> 94.6; [65536,
+    // 4096] un-padded in 32 88 -> 80.5, [132992, 2048] padded 61.4 -> 62.5.  Below the line nothing is gained (38.9 -> 39.0 at
+    // [32768, 4096], 37.0 -> 38.1 at [65536, 2048]), nor with 512 rows per expert (135 -> 151 for 128 of 513).
+    const bool three_per_cu = expert_offsets && M * K >= (int64_t)32768 * 7168 && M >= 1024 * (int64_t)num_experts;
+    const uint32_t more = three_per_cu ? lds_for_three() : 0u;
+    if (expert_offsets && (a.few != 0u || num_experts > 64))
+        hipLaunchKernelGGL(row_to_col_kernel<true>, grid, dim3(T_THREADS), more, stream, a);
+    else
+        hipLaunchKernelGGL(row_to_col_kernel<false>, grid, dim3(T_THREADS), more, stream, a);
     return hipGetLastError();
 }
 
