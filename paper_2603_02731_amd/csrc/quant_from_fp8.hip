@@ -249,6 +249,36 @@ __device__ __forceinline__ void store_segment(const RowPieces &r, uint32_t n, ui
         *reinterpret_cast<uint32_t *>(dsf + lane * 4u) = r.sf_dword;
 }
 
+// The same from the wave's LDS, dealt to the lanes so that every wave instruction starts on a 128-byte line of the destination.
+template <bool WIDE_SF>
+__device__ __forceinline__ void store_segment_on_lines(const uint8_t *rec, uint32_t n, uint8_t *dq, uint8_t *dsf, uint32_t lane)
+{
+    const uint32_t nib_pieces = n / 32u, pieces = nib_pieces + (WIDE_SF ? n / 512u : 0u);
+    uint8_t *sf_base = dsf - n / 2u;
+    const uint32_t shift = (uint32_t)(reinterpret_cast<uintptr_t>(dq) >> 4) & 7u;
+    const uint32_t p0 = lane - shift; // wraps below zero for the lanes before the first piece
+    u32x4 v[WAVE_PIECES];
+#pragma unroll
+    for (int i = 0; i < WAVE_PIECES; ++i) {
+        const uint32_t p = p0 + i * 64u;
+        v[i] = *reinterpret_cast<const u32x4 *>(rec + min(p, pieces - 1u) * 16u);
+    }
+#pragma unroll
+    for (int i = 0; i < WAVE_PIECES; ++i) {
+        const uint32_t p = p0 + i * 64u;
+        if (p < pieces)
+            __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4 *>((p < nib_pieces ? dq : sf_base) + p * 16u));
+    }
+    if (pieces + shift > WAVE_PIECES * 64u) {
+        const uint32_t p = p0 + WAVE_PIECES * 64u;
+        if (p < pieces)
+            __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(rec + p * 16u),
+                                        reinterpret_cast<u32x4 *>((p < nib_pieces ? dq : sf_base) + p * 16u));
+    }
+    if (!WIDE_SF && lane < n / 128u)
+        *reinterpret_cast<uint32_t *>(dsf + lane * 4u) = *reinterpret_cast<const uint32_t *>(rec + n / 2u + lane * 4u);
+}
+
 // The routing turned around: every source row is read and quantized once and written to each of
 // its `fanout` destination rows (a token and its top-k experts), instead of being read and
 // quantized again for every destination.  Same lane layout; dense source, strided outputs.
@@ -498,7 +528,7 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
 // asked for by many (output rows padded with one and the same index, say), every workgroup counts the same sample of the
 // index per owner while it scans; the rows of an owner with a quarter more than its share, and the zero rows of indices
 // that name no source row, are dealt out by output row: every workgroup takes those of its own slice of the outputs.
-// Bound by the writes: 8192 rows of 7168 to eight records each 80 us = 3.9 TB/s of what has to move (lane-wise 119, where
+// Bound by the writes: 8192 rows of 7168 to eight records each 78 us = 4.0 TB/s of what has to move (lane-wise 119, where
 // half is reading every row eight times from the memory-side cache and a quarter quantizing it as often; the scatter form
 // of the same routing 60 us, without the scan and with four workgroups per compute unit), 20 thousand of a workgroup's 160
 // thousand cycles before its first write.  One workgroup of 16 waves per compute unit: two of them at 64 registers spill.
@@ -545,7 +575,7 @@ struct QuantOwnerArgs {
     }
 };
 
-template <bool WIDE_SF>
+template <bool WIDE_SF, bool LINES>
 __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(const QuantOwnerArgs a)
 {
     __shared__ __align__(16) uint8_t s_rec[OWNER_WAVES][WAVE_LDS]; // first the unsorted list, then the waves' rows
@@ -696,8 +726,11 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
                             __builtin_amdgcn_s_waitcnt(VMCNT_0);
                             held = row;
                         }
-                        store_segment<WIDE_SF>(r, n, a.q + (size_t)d * a.ld_q + k0 / 2u,
-                                               a.sf + (size_t)d * a.ld_sf + k0 / 32u, lane);
+                        uint8_t *dq = a.q + (size_t)d * a.ld_q + k0 / 2u, *dsf = a.sf + (size_t)d * a.ld_sf + k0 / 32u;
+                        if (LINES)
+                            store_segment_on_lines<WIDE_SF>(s_rec[wave], n, dq, dsf, lane);
+                        else
+                            store_segment<WIDE_SF>(r, n, dq, dsf, lane);
                     }
                 }
             }
@@ -798,10 +831,19 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
         o.eighths = std::min(8u, std::max(1u, 2048u * groups / o.M_out));
         o.heavy = 5u * (o.M_out / 32u * o.samples * o.eighths / groups) / 4u + 8u;
         const bool wide = K % 512 == 0 && ((reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_sf) & 15u) == 0u;
-        if (wide)
-            hipLaunchKernelGGL(quant_from_fp8_owner_kernel<true>, dim3(groups), dim3(OWNER_THREADS), 0, stream, o);
+        // Long rows of one segment that do not begin on 128-byte lines leave by whole lines, read from LDS for every copy: 8192
+        // rows of 7168 to eight records of 3808 bytes 80.3 -> 77.9 us, 65536 x 8 608 -> 585, 4096 to 33500 records 44.0 -> 42.7.
+        // Not on lines already (4096 elements, 2176 bytes: 47.1 -> 47.4, and 3-9 % lost where few rows are asked for often), nor
+        // for shorter or longer rows (6144 65.9 -> 66.2, two segments 83.7 -> 83.1).
+        const bool lines = ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 127u) != 0u && K > 6144 && K <= (int64_t)WAVE_SEG;
+        auto launch = [&](auto w, auto l) {
+            hipLaunchKernelGGL((quant_from_fp8_owner_kernel<decltype(w)::value, decltype(l)::value>), dim3(groups),
+                               dim3(OWNER_THREADS), 0, stream, o);
+        };
+        if (lines)
+            wide ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
         else
-            hipLaunchKernelGGL(quant_from_fp8_owner_kernel<false>, dim3(groups), dim3(OWNER_THREADS), 0, stream, o);
+            wide ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
         return hipGetLastError();
     }
     QuantArgs a;
