@@ -1,6 +1,6 @@
-// Pieces shared by the two row-blocked MXFP4 -> column-wise FP8 kernels (scale alignment and
-// re-quantization): the write-out of a finished 256-column tile part from LDS to the [K, rows]
-// byte matrix of one expert, ragged ends and unaligned rows included.
+// Pieces shared by the row-blocked MXFP4 -> column-wise FP8 kernels (scale alignment and re-quantization): the
+// write-out of a finished 256-column tile from LDS to the [K, rows] byte matrix of one expert, ragged ends and
+// unaligned rows included; the staging of row scales; the arithmetic of either reading.
 #pragma once
 
 #include "mxfp4_device.hpp"

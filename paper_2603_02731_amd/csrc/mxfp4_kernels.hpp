@@ -42,7 +42,7 @@ hipError_t launch_row_to_fp8_col_requant(const uint8_t *q_row, const uint8_t *sf
                                          float *x_col_scale, hipStream_t stream);
 
 // Either reading over ragged experts in whole segments of the output: where fp8_col_in_segments says so.
-bool fp8_col_in_segments(int64_t M, int64_t K, int32_t num_experts);
+bool fp8_col_in_segments(int64_t M, int64_t K, int32_t num_experts, bool requant);
 hipError_t launch_row_to_fp8_col_grouped(const uint8_t *q_row, const uint8_t *sf_row, const int32_t *expert_offsets,
                                          int32_t num_experts, int64_t M, int64_t K, uint8_t *x_col, float *x_col_scale,
                                          bool requant, hipStream_t stream);

@@ -46,7 +46,7 @@ struct Args {
     uint8_t *x_col;
     float *x_col_scale;
     const int32_t *expert_offsets; // nullptr: one group of M rows
-    int32_t num_experts; // at most 64
+    int32_t num_experts; // at most 128
     uint32_t M;
     uint32_t K;
     uint32_t tiles_m; // 256-row tiles (an upper bound when grouped)
@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(T_THREADS, 2) row_to_fp8_col_kernel(const Args
     uint32_t row_base = 0, rows = a.M, groups_before = 0;
     if (a.expert_offsets) {
         ExpertTile t;
-        if (!expert_tile<1, TILE_M, 128, 0, MBM_MAX>(a.expert_offsets, (uint32_t)a.num_experts, blockIdx.x, a.tiles_k,
+        if (!expert_tile<2, TILE_M, 128, 0, MBM_MAX>(a.expert_offsets, (uint32_t)a.num_experts, blockIdx.x, a.tiles_k,
                                                      a.by_tiles_k, &t))
             return;
         tile_m = t.tile_m;
@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(T_THREADS, 2) row_to_fp8_col_kernel(const Args
     uint32_t w[RPL];
     // On grids with many tiles per CU (flat or per-expert) a full tile arrives through 16-byte loads (8 rows x 128 bytes per
     // wave instruction instead of 2) and is cut into the lanes' slices through the tile buffer, behind one
-    // more barrier: 133.6 -> 127.0 us at [65536,7168] launched back to back, 200 -> 190 us over 32 un-padded experts.
+    // more barrier: 133.6 -> 127.0 us at [65536,7168] launched back to back.
     const bool staged = a.stage_in != 0u && n_rows == (uint32_t)TILE_M &&
                         cols == (uint32_t)TILE_K && (reinterpret_cast<uintptr_t>(a.q_row) & 15u) == 0u;
     u32x4 stage_v[8];

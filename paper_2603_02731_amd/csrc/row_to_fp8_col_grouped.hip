@@ -565,15 +565,19 @@ static int64_t tiles_at_most(int64_t M, int64_t K, int32_t num_experts)
     return ((M + TILE_M - 1) / TILE_M + num_experts) * ((K + TILE_K - 1) / TILE_K);
 }
 
-// Launches of about two rounds of the other kernels' workgroups (two per compute unit, one pass) whose total row count tells
-// that the splits may be padded to 16 rows, but not to 128, are left to them: their pieces are aligned, and what a workgroup
-// takes longer here is not made up for.  Measured (us, own rows / segments, re-quantization): padded to 16, [8439, 512] in 64
-// experts 7.8 / 8.9, [2000, 2048] in 8 8.4 / 9.6, [4000, 4096] in 16 10.8 / 11.8; above the line, [16000, 2048] in 16
-// 18.9 / 17.6, [5086, 6272] in 64 28.5 / 22.1.  Not padded, [2000, 2048] 11.7 / 9.9, [6180, 1280] in 16 12.5 / 10.4; padded to
-// 128 the same within 4 %.  Those kernels look for one of at most 64 experts: the longer lookup costs their flat form 1 %.
-bool fp8_col_in_segments(int64_t M, int64_t K, int32_t num_experts)
+// Launches of about one round of the other kernels' workgroups (two per compute unit, one pass), as far as the number of tiles
+// can be told, whose total row count says that the splits may be padded, are left to them: nothing is shared or the pieces are
+// aligned, and what a workgroup takes longer here is not made up for.  For scale alignment only splits padded to 16 rows and not
+// to 128.  Measured (us, own rows / segments, re-quantization): padded to 16, [8439, 512] in 64 experts 7.8 / 8.9, [2000, 2048]
+// in 8 8.4 / 9.6, [4000, 4096] in 16 10.8 / 11.8; to 128, [34135, 768] in 64 10.4 / 11.7, [6483, 1792] in 64 9.9 / 10.5, [10711,
+// 2432] in one 10.8 / 11.3; above the line, [16000, 2048] in 16 18.9 / 17.6, [11113, 3968] in one 19.0 / 14.0; not padded, [2000,
+// 2048] 11.7 / 9.9, [6180, 1280] in 16 12.5 / 10.4.  Those kernels look for one of at most 128 experts: the longer lookup costs their
+// flat form 1 %.
+bool fp8_col_in_segments(int64_t M, int64_t K, int32_t num_experts, bool requant)
 {
-    return num_experts > 64 || M % 16 != 0 || M % 128 == 0 || 4 * tiles_at_most(M, K, num_experts) > 9 * (int64_t)compute_units();
+    const int64_t half_tiles = (M / (TILE_M / 2) + num_experts) * ((K + TILE_K - 1) / TILE_K); // experts end in half a tile each
+    const bool padded = M % 16 == 0 && (requant || M % 128 != 0);
+    return num_experts > 128 || !padded || 10 * half_tiles > 43 * (int64_t)compute_units();
 }
 
 hipError_t launch_row_to_fp8_col_grouped(const uint8_t *q_row, const uint8_t *sf_row, const int32_t *expert_offsets,

@@ -38,7 +38,7 @@ struct Args {
     uint8_t *x_col;
     float *x_col_scale;
     const int32_t *expert_offsets; // nullptr: one group of M rows
-    int32_t num_experts; // at most 64
+    int32_t num_experts; // at most 128
     uint32_t M;
     uint32_t K;
     uint32_t tiles_m; // 256-row tiles (an upper bound when grouped)
@@ -65,7 +65,7 @@ __global__ void __launch_bounds__(T_THREADS) row_to_fp8_col_requant_kernel(const
     uint32_t row_base = 0, rows = a.M, groups_before = 0;
     if (a.expert_offsets) {
         ExpertTile t;
-        if (!expert_tile<1, TILE_M, 128, 0, 64>(a.expert_offsets, (uint32_t)a.num_experts, blockIdx.x, a.tiles_k, a.by_tiles_k, &t))
+        if (!expert_tile<2, TILE_M, 128, 0, 64>(a.expert_offsets, (uint32_t)a.num_experts, blockIdx.x, a.tiles_k, a.by_tiles_k, &t))
             return;
         tile_m = t.tile_m;
         tile_k = t.tile_k;
