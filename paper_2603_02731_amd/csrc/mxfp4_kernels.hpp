@@ -27,7 +27,7 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
                              int32_t num_experts, int64_t M, int64_t K, uint8_t *q_col, uint8_t *sf_col,
                              hipStream_t stream);
 
-// The flat conversion with tiles that write whole segments of the output.
+// The flat conversion with tiles that write whole segments of the output: where row_to_col_in_segments says so.
 hipError_t launch_row_to_col_segments(const uint8_t *q_row, const uint8_t *sf_row, int64_t M, int64_t K, uint8_t *q_col,
                                       uint8_t *sf_col, hipStream_t stream);
 

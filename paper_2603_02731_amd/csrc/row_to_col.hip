@@ -23,6 +23,7 @@
 // the HBM traffic at the algorithmic 0.53125 B read + 0.53125 B written per element.
 #include "mxfp4_device.hpp"
 #include "mxfp4_kernels.hpp"
+#include "row_to_col_rule.hpp"
 #include "row_to_col_slice.hpp"
 
 namespace mxfp4 {
@@ -482,13 +483,7 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
                              int32_t num_experts, int64_t M, int64_t K, uint8_t *q_col, uint8_t *sf_col,
                              hipStream_t stream)
 {
-    // One large matrix whose k-rows are no whole 64-byte segments: tiles that write whole ones, at the price of converting up to
-    // half as many rows once more.  Measured (us, own rows / segments): [65504, 7168] 146 / 119, [49120, 7168] 113 / 94,
-    // [32736, 7168] 75 / 66, [40032, 8192] 118 / 94, [57056, 5120] 93 / 80, [131040, 2048] 78 / 73, [49120, 4096] 65 / 57, but
-    // [32736, 4096] 41 / 42, [65504, 2048] 38 / 41, [16352, 7168] 36 / 40: what smaller ones leave half written meets in the
-    // memory-side cache.  Not for experts, whose last tiles cost as much as whole ones: 16 of 2585 rows, K = 7424, 81 / 92,
-    // [65533, 7168] in 32 Zipf-sized 139 / 134, in 128 142 / 157.
-    if (!expert_offsets && M % 128 != 0 && M * K >= (int64_t)176 << 20)
+    if (!expert_offsets && row_to_col_in_segments(M, K))
         return launch_row_to_col_segments(q_row, sf_row, M, K, q_col, sf_col, stream);
     RowToColArgs a;
     a.q_row = q_row;

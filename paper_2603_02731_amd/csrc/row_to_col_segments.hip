@@ -17,17 +17,14 @@
 // pattern and by half as much arithmetic again.
 #include "mxfp4_device.hpp"
 #include "mxfp4_kernels.hpp"
+#include "row_to_col_rule.hpp"
 #include "row_to_col_slice.hpp"
 
 namespace mxfp4 {
 
 namespace row_to_col_seg {
 
-constexpr uint32_t TILE_M = 256, TILE_K = 256, THREADS = 256, WAVES = 4;
-constexpr uint32_t SEG = 64;                 // the segments of the output that a tile writes whole, in bytes
-constexpr uint32_t LOOK = 2 * SEG;           // the rows they may hold before the tile's own: one 32-row block per wave
-constexpr uint32_t TILE_BYTES = TILE_M / 2;  // of a k-row
-constexpr int PASSES = 2, CPP = 8 / PASSES;  // the tile leaves in passes; columns of a lane per pass
+constexpr uint32_t LOOK = 2 * SEG;           // the rows a tile's segments may hold before its own: one 32-row block per wave
 constexpr uint32_t ROW = SEG + TILE_BYTES + 16; // bytes of an LDS k-row: an odd number of 16-byte slots
 constexpr uint32_t SF = LOOK + TILE_M + 16;  // row-scale bytes of one k-block in LDS: the look-back rows, then the tile's
 
@@ -307,7 +304,8 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
         const uint32_t part = lane & 7u;
         // k-row of the lane in step 0 and the tile's first byte, SEG bytes late: what is subtracted from an offset stays below SEG
         uint8_t *const base = a.q_col + (size_t)(k0 + wv * 64u + p * CPP) * pitch_q + m0 / 2u - SEG;
-        const uint32_t lane_row = (lane >> 3) * 8u * pitch_q;
+        // offsets of 32 bits: store_end, a condition of the launch
+        const uint32_t lane_row = store_row<uint32_t>(lane, 0) * pitch_q;
         auto krow = [&](int i) { return lane_row + (uint32_t)i * pitch_q; }; // of step i, from base
         const uint32_t lane_lds = (wv * 8u + (lane >> 3)) * ROW;
         constexpr uint32_t STEP_LDS = 32 * ROW;

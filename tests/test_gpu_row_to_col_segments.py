@@ -91,3 +91,30 @@ def test_small_splits_leave_in_aligned_pieces(rows, off):
     assert (got[:off] == 0xA5).all() and (got[off + wq.size:] == 0xA5).all() and bool((sb[ws.size:] == 0x5A).all())
     assert_same(host(sb)[:ws.size], ws, "scale bytes")
     assert_same(got[off:off + wq.size], wq, "nibbles")
+
+
+@pytest.mark.parametrize("M", [145592096, 145592128, 150000032])
+def test_rows_on_both_sides_of_32_bit_offsets(M):
+    """The longest matrix whose store offsets have 32 bits in whole segments, and longer ones: rows of a 32032-row pattern over and
+    over, every byte of every k-row against the oracle's columns of the pattern."""
+    K, P = 128, 32 * 1001
+    pq, ps = synth.random_mxfp4(P, K, seed=31, scale_spread=5)
+    wq, ws = par.row_to_col(pq.numpy(), ps.numpy())
+    n, tail = M // P, M % P
+
+    def over_and_over(t):
+        t = t.to(DEV)
+        return torch.cat([t.expand(n, *t.shape).reshape(n * P, -1), t[:tail]])
+
+    q, sf = over_and_over(pq), over_and_over(ps)
+    qb = torch.full((K * (M // 2) + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    sb = torch.full((K * (M // 32) + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+    qc, sc = qb[:-4096].view(K, M // 2), sb[:-64].view(K, M // 32)
+    mx.mxfp4_row_to_col(q, sf, q_col=qc, sf_col=sc)
+    assert bool((qb[-4096:] == 0xA5).all()) and bool((sb[-64:] == 0x5A).all())
+    for got, want, unit, what in ((qc, wq, 2, "nibbles"), (sc, ws, 32, "scale bytes")):
+        want = torch.from_numpy(want).to(DEV)
+        for k in range(K):
+            whole = got[k, :n * (P // unit)].view(n, P // unit)
+            assert bool((whole == want[k]).all()), f"{what} of k-row {k}, {M} rows"
+            assert torch.equal(got[k, n * (P // unit):], want[k, :tail // unit]), f"last {what} of k-row {k}, {M} rows"
