@@ -179,6 +179,14 @@ struct RowPieces {
     uint32_t sf_dword;         // rows whose scale bytes are not whole 16-byte pieces: this lane's dword of them
 };
 
+// Bytes that lanes of a wave exchange through its LDS: what is in front of this is done before what follows.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Elements [k0, k0 + n) of the source row at src / src_scale; n is a multiple of 128, of 512 with WIDE_SF.
 // zero: the row of an index that names no source row.
 template <bool WIDE_SF>
@@ -212,9 +220,7 @@ __device__ __forceinline__ void quant_segment(const uint8_t *src, const float *s
         }
     }
     // the bytes of other lanes of this wave: ordered by the fence, no barrier of the workgroup needed
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_fence();
     const uint32_t nib_pieces = nib_bytes / 16u, pieces = nib_pieces + (WIDE_SF ? n / 512u : 0u);
 #pragma unroll
     for (int i = 0; i < WAVE_PIECES; ++i) {
@@ -226,10 +232,8 @@ __device__ __forceinline__ void quant_segment(const uint8_t *src, const float *s
     out->sf_dword = 0u;
     if (!WIDE_SF && lane < n / 128u)
         out->sf_dword = *reinterpret_cast<const uint32_t *>(rec + nib_bytes + lane * 4u);
-    // the LDS bytes are in registers before the wave's next segment overwrites them
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // these reads of the LDS bytes come before the writes of the wave's next segment
+    wave_fence();
 }
 
 // The finished segment to one destination: dq / dsf are where its nibbles and scale bytes start.
@@ -250,6 +254,7 @@ __device__ __forceinline__ void store_segment(const RowPieces &r, uint32_t n, ui
 }
 
 // The same from the wave's LDS, dealt to the lanes so that every wave instruction starts on a 128-byte line of the destination.
+// A wave_fence has to follow before the LDS is written again.
 template <bool WIDE_SF>
 __device__ __forceinline__ void store_segment_on_lines(const uint8_t *rec, uint32_t n, uint8_t *dq, uint8_t *dsf, uint32_t lane)
 {
@@ -718,6 +723,8 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
                         if (row != held) {
                             const bool zero = row == a.M_src;
                             const uint32_t from = zero ? 0u : row;
+                            if (LINES)
+                                wave_fence(); // the copies of the row before were read from LDS
                             quant_segment<WIDE_SF>(a.x + (size_t)from * a.K + k0,
                                                    a.x_scale + (size_t)from * (a.K >> 7) + (k0 >> 7), n, zero, s_rec[wave],
                                                    lane, &r);
