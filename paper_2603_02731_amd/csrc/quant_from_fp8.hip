@@ -660,7 +660,9 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
 
     // ---- the output rows of our slice, every 2^shift-th run of SLICE_RUN, that are dealt out
     auto scan_dealt = [&] {
-        for (uint32_t out = ((tid / SLICE_RUN << a.shift) + me) * SLICE_RUN + tid % SLICE_RUN; out < a.M_out;
+        uint32_t t = tid;
+        asm volatile("" : "+v"(t)); // where the lane begins is worked out here: held over the loop around it, it would spill
+        for (uint32_t out = ((t / SLICE_RUN << a.shift) + me) * SLICE_RUN + t % SLICE_RUN; out < a.M_out;
              out += OWNER_THREADS << a.shift) {
             const uint32_t src = (uint32_t)a.gather_idx[out];
             if (src >= a.M_src)
