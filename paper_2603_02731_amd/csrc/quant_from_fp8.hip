@@ -705,45 +705,55 @@ __global__ void __launch_bounds__(OWNER_THREADS) quant_from_fp8_owner_kernel(con
         const uint32_t units = s_n;
         __syncthreads();
         __builtin_amdgcn_s_waitcnt(VMCNT_0);
-        for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
-            const uint32_t n = min(a.seg, a.K - k0);
-            RowPieces r;
-            uint32_t held = 0xFFFFFFFFu; // the source row in r; M_src: zeros
-            for (uint32_t u = wave; u < units; u += OWNER_WAVES) {
-                const uint32_t unit = __builtin_amdgcn_readfirstlane(s_units[u]);
-                const uint32_t end = (unit >> 16) + (unit & 0xFFFFu);
-                for (uint32_t j = unit >> 16; j < end; j += 64u) {
-                    const uint32_t e = j + lane < end ? s_sorted[j + lane] : 0u;
-                    const uint32_t key = e >> OUT_BITS, out = e & ((1u << OUT_BITS) - 1u);
-                    uint32_t src = key < KEY_DEALT ? a.row(me, key) : a.M_src;
-                    if (key >= KEY_DEALT && key < KEY_ZERO) // used at once: the wait for it, and for every store before it,
-                        src = min((uint32_t)a.gather_idx[out], a.M_src); // stays on this side of the branch
-                    const int some = (int)min(64u, end - j);
-                    for (int l = 0; l < some; ++l) {
-                        const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)src, l);
-                        const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)out, l);
-                        if (row != held) {
-                            const bool zero = row == a.M_src;
-                            const uint32_t from = zero ? 0u : row;
-                            if (LINES)
-                                wave_fence(); // the copies of the row before were read from LDS
-                            quant_segment<WIDE_SF>(a.x + (size_t)from * a.K + k0,
-                                                   a.x_scale + (size_t)from * (a.K >> 7) + (k0 >> 7), n, zero, s_rec[wave],
-                                                   lane, &r);
-                            // The loads are in.  Said here, and before the loop, no store has to wait for them, and with them
-                            // for the stores before it, where the paths join.
-                            __builtin_amdgcn_s_waitcnt(VMCNT_0);
-                            held = row;
+        auto write = [&](auto on_lines) {
+            constexpr bool ON_LINES = decltype(on_lines)::value;
+            for (uint32_t k0 = 0; k0 < a.K; k0 += a.seg) {
+                const uint32_t n = min(a.seg, a.K - k0);
+                RowPieces r;
+                uint32_t held = 0xFFFFFFFFu; // the source row in r; M_src: zeros
+                for (uint32_t u = wave; u < units; u += OWNER_WAVES) {
+                    const uint32_t unit = __builtin_amdgcn_readfirstlane(s_units[u]);
+                    const uint32_t end = (unit >> 16) + (unit & 0xFFFFu);
+                    for (uint32_t j = unit >> 16; j < end; j += 64u) {
+                        const uint32_t e = j + lane < end ? s_sorted[j + lane] : 0u;
+                        const uint32_t key = e >> OUT_BITS, out = e & ((1u << OUT_BITS) - 1u);
+                        uint32_t src = key < KEY_DEALT ? a.row(me, key) : a.M_src;
+                        if (key >= KEY_DEALT && key < KEY_ZERO) // used at once: the wait for it, and for every store before it,
+                            src = min((uint32_t)a.gather_idx[out], a.M_src); // stays on this side of the branch
+                        const int some = (int)min(64u, end - j);
+                        for (int l = 0; l < some; ++l) {
+                            const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)src, l);
+                            const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)out, l);
+                            if (row != held) {
+                                const bool zero = row == a.M_src;
+                                const uint32_t from = zero ? 0u : row;
+                                if (ON_LINES)
+                                    wave_fence(); // the copies of the row before were read from LDS
+                                quant_segment<WIDE_SF>(a.x + (size_t)from * a.K + k0,
+                                                       a.x_scale + (size_t)from * (a.K >> 7) + (k0 >> 7), n, zero, s_rec[wave],
+                                                       lane, &r);
+                                // The loads are in.  Said here, and before the loop, no store has to wait for them, and with them
+                                // for the stores before it, where the paths join.
+                                __builtin_amdgcn_s_waitcnt(VMCNT_0);
+                                held = row;
+                            }
+                            uint8_t *dq = a.q + (size_t)d * a.ld_q + k0 / 2u, *dsf = a.sf + (size_t)d * a.ld_sf + k0 / 32u;
+                            if (ON_LINES)
+                                store_segment_on_lines<WIDE_SF>(s_rec[wave], n, dq, dsf, lane);
+                            else
+                                store_segment<WIDE_SF>(r, n, dq, dsf, lane);
                         }
-                        uint8_t *dq = a.q + (size_t)d * a.ld_q + k0 / 2u, *dsf = a.sf + (size_t)d * a.ld_sf + k0 / 32u;
-                        if (LINES)
-                            store_segment_on_lines<WIDE_SF>(s_rec[wave], n, dq, dsf, lane);
-                        else
-                            store_segment<WIDE_SF>(r, n, dq, dsf, lane);
                     }
                 }
             }
-        }
+        };
+        // A workgroup with a quarter more than its share of the output rows is waited for by all others and bound by its own compute
+        // unit, where reading every copy from LDS costs 5 %: it keeps the row in registers (power law of exponent 1/8 111 -> 105 us;
+        // the line at an eighth: routes 0.4 us slower).
+        if (LINES && listed <= (a.M_out >> a.shift) + (a.M_out >> (a.shift + 2u)))
+            write(std::true_type{});
+        else
+            write(std::false_type{});
     };
 
     // All of it at once, or, where that is more output rows than the list holds, first those that are dealt to us, then ours
@@ -840,11 +850,16 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
         o.eighths = std::min(8u, std::max(1u, 2048u * groups / o.M_out));
         o.heavy = 5u * (o.M_out / 32u * o.samples * o.eighths / groups) / 4u + 8u;
         const bool wide = K % 512 == 0 && ((reinterpret_cast<uintptr_t>(sf) | (uintptr_t)ld_sf) & 15u) == 0u;
-        // Long rows of one segment that do not begin on 128-byte lines leave by whole lines, read from LDS for every copy: 8192
-        // rows of 7168 to eight records of 3808 bytes 80.3 -> 77.9 us, 65536 x 8 608 -> 585, 4096 to 33500 records 44.0 -> 42.7.
-        // Not on lines already (4096 elements, 2176 bytes: 47.1 -> 47.4, and 3-9 % lost where few rows are asked for often), nor
-        // for shorter or longer rows (6144 65.9 -> 66.2, two segments 83.7 -> 83.1).
-        const bool lines = ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 127u) != 0u && K > 6144 && K <= (int64_t)WAVE_SEG;
+        // Long rows of one segment that do not begin on 64-byte segments leave by whole lines, read from LDS for every copy, so that
+        // no wave instruction ends inside a segment.  Maps of 65536 slots, records or planes 16 bytes off (us, from registers / by
+        // lines: routes; 40 % unused; a quarter of the slots naming one row; a power law of exponent 1/4): K = 6272 71.5 / 69.3,
+        // 73.2 / 68.9, 77.2 / 77.6, 93.5 / 94.5; 6400 73.3 / 70.4, 74.5 / 70.1, 78.4 / 78.7, 94.9 / 96.0; 6656 78.7 / 75.2,
+        // 80.8 / 75.9, 82.3 / 81.1, 98.0 / 97.3; 7168 80.0 / 77.6, 82.3 / 78.6, 83.9 / 83.8, 100.6 / 100.0; 7552 83.6 / 80.1,
+        // 85.0 / 80.1, 88.7 / 88.6, 108.9 / 108.9; 7680 89.7 / 85.3, 91.8 / 86.7, 93.1 / 91.1, 115.4 / 115.2; 65536 x 8 copies of
+        // 7168 608 / 585.  Shorter rows gain less and lose more where rows are asked for unevenly: 6144 73.9 / 72.1, 76.2 / 73.0,
+        // 77.2 / 77.5, 89.5 / 90.6; 4224 53.1 / 51.7, 52.8 / 52.0, 58.5 / 60.6, 71.0 / 73.9.  On whole segments nothing is gained
+        // (planes of 6272 66.8 / 67.3, 7552 77.7 / 78.2; 8064, two segments, 83.2 / 82.8).
+        const bool lines = ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 63u) != 0u && K > 6144 && K <= (int64_t)WAVE_SEG;
         auto launch = [&](auto w, auto l) {
             hipLaunchKernelGGL((quant_from_fp8_owner_kernel<decltype(w)::value, decltype(l)::value>), dim3(groups),
                                dim3(OWNER_THREADS), 0, stream, o);

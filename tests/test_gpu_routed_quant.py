@@ -33,7 +33,7 @@ def outputs(rows, K, layout):
         ld_q = ld_sf = (nq + ns + 15) // 16 * 16 + 16
         at_q, at_sf, size = GUARD, GUARD + nq, GUARD + rows * ld_q
     else:
-        step = {"planes": 16, "planes8": 8}[layout]
+        step = {"planes": 16, "planes8": 8, "planes64": 64}[layout]
         ld_q, ld_sf = nq + step, ns + step // 2
         at_q, at_sf = GUARD, (GUARD + rows * ld_q + 15) // 16 * 16
         size = at_sf + rows * ld_sf
@@ -194,6 +194,17 @@ def test_gather_by_owners(K, rows, over, kind, layout):
     n = least(M, K) + over
     rng, x8, s, wq, wsf = source(M, K, K + n)
     gathered(rng, x8, s, wq, wsf, index_of(kind, M, n, rng), K, layout)
+
+
+@pytest.mark.parametrize("layout", ["records", "planes", "planes64"])
+@pytest.mark.parametrize("K,kind", [(6144, "power"), (6272, "power"), (6656, "mixed"), (7168, "power"), (7552, "crowd"), (7680, "power"),
+                                    (7808, "mixed")])
+def test_gather_by_owners_in_whole_lines(K, kind, layout):
+    """Widths on both sides of the ones whose rows leave by whole lines, rows on and off 64-byte segments, workgroups that have
+    more than their share of the output rows (a power law) and ones that have not."""
+    M = 9 * GROUPS + 7
+    rng, x8, s, wq, wsf = source(M, K, K)
+    gathered(rng, x8, s, wq, wsf, index_of(kind, M, least(M, K) + 3, rng), K, layout)
 
 
 def test_gather_sides_of_the_row_counts():
