@@ -80,3 +80,32 @@ def test_expert_lookup_at_its_sizes(experts):
     rows[experts // 2], rows[-1] = 600, 1
     q, sf = synth.random_mxfp4(sum(rows), 128, seed=experts, scale_spread=4)
     run(rows, 128, False, q.numpy(), sf.numpy())
+
+
+@pytest.mark.parametrize("requant", [False, True])
+@pytest.mark.parametrize("experts,empty,last", [(65, (), 16), (65, (64,), 0), (100, (62, 63, 64), 528), (100, (0, 99), 0),
+                                                (128, (63,), 272), (128, tuple(range(1, 64)), 784), (128, tuple(range(64, 127)), 16)])
+def test_small_padded_launches_of_65_to_128_experts(experts, empty, last, requant):
+    """The kernels that write their own rows look for one of up to 128 experts in two steps of 64: a total that is a multiple of
+    16 and not of 128 and few tiles, experts without rows around the middle, experts of several tiles on both sides of it."""
+    rng = np.random.default_rng(experts + last)
+    rows = [16 * int(n) for n in rng.integers(1, 6, experts)]
+    rows[5], rows[63], rows[64], rows[-1] = 544, 288, 272, last
+    if experts > 70:
+        rows[70] = 1040
+    for e in empty:
+        rows[e] = 0
+    if sum(rows) % 128 == 0:
+        rows[10] += 16
+    assert sum(rows) % 16 == 0 and sum(rows) % 128 != 0 and sum(rows) // 128 + experts < 3 * 256
+    q, sf = synth.random_mxfp4(sum(rows), 128, seed=experts, scale_spread=6)
+    run(rows, 128, requant, q.numpy(), sf.numpy())
+
+
+@pytest.mark.parametrize("experts", [64, 65, 256, 257, 1024])
+def test_expert_lookup_at_its_sizes_requantized(experts):
+    rng = np.random.default_rng(experts + 1)
+    rows = [int(r) for r in rng.integers(0, 70, experts)]
+    rows[experts // 2], rows[-1] = 600, 1
+    q, sf = synth.random_mxfp4(sum(rows), 128, seed=experts, scale_spread=4)
+    run(rows, 128, True, q.numpy(), sf.numpy())
