@@ -102,8 +102,7 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
     const uint32_t Kb = a.K / 32u, pitch = a.K / 2u;
     const uint32_t pitch_q = rows / 2u, pitch_sf = rows / 32u;
 
-    const bool whole = ((reinterpret_cast<uintptr_t>(a.q_col) | pitch_q) & (SEG - 1u)) == 0u; // every k-row is whole segments
-    const bool look = tile_m != 0u && !whole;
+    const bool look = tile_m != 0u; // no k-row is whole segments: M is no multiple of 128
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -134,7 +133,7 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
     u32x4 stage_v[8], stage_l[4];
     if (wv * 64u < n_rows && piece_in) {
         auto row_of = [&](int j) { return (int32_t)min(wv * 64u + j * 8u + (lane >> 3), n_rows - 1u); };
-        if (whole || wv < 2u) { // read once; the last 128 rows are the next tile's look-back
+        if (wv < 2u) { // read once; the last 128 rows are the next tile's look-back
             asm volatile("" : : "v"(tid)); // keeps the two forms of the loads apart
 #pragma unroll
             for (int j = 0; j < 8; ++j)
@@ -313,7 +312,7 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
         auto piece16 = [&](uint32_t at) { return *reinterpret_cast<const u32x4 *>(s_tile + at); };
         // bytes by which a k-row is past the start of a segment
         const uint32_t base_low = (uint32_t)reinterpret_cast<uintptr_t>(base);
-        auto past = [&](uint32_t row) { return whole ? 0u : (base_low + row) & (SEG - 1u); };
+        auto past = [&](uint32_t row) { return (base_low + row) & (SEG - 1u); };
         // Every tile begins and ends on a segment of the k-row: it writes the bytes from the segment that holds its first row on,
         // and leaves what follows its last whole segment to the next tile.
         auto full = [&] { // all pieces are whole
@@ -362,7 +361,7 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
                     }
                 }
         };
-        if (cols == TILE_K && ((whole && n_rows == TILE_M) || (look && !last))) {
+        if (cols == TILE_K && look && !last) {
             full();
         } else {
             ends();
