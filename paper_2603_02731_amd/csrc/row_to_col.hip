@@ -63,81 +63,16 @@ __device__ __forceinline__ uint32_t load_nibbles(const uint32_t *p)
     return __builtin_nontemporal_load(p);
 }
 
-// Step 2: decode again (cheaper than keeping 256 floats live) and re-quantize pairs of rows into output
-// bytes: v_cvt_scalef32_pk_fp4_f32 takes rows (m, m+1) of one column.
-__device__ __forceinline__ void requant_rows_hw(uint32_t (&w)[32], uint32_t (&sb)[8], const uint32_t (&cb)[8],
-                                                uint32_t (&o)[8][4])
-{
-    float cs[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-        cs[c] = u2f(cb[c] << 23);
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            asm volatile("" : "=v"(o[c][g])); // no initial value needed: all four bytes are written
-    static_for<16>([&](auto ip) {
-        constexpr int i = 2 * decltype(ip)::value;
-        constexpr int g = i >> 3, sel = (i >> 1) & 3; // output dword and byte of rows (i, i+1)
-        const float sa = row_scale_operand<i>(sb), sbb = row_scale_operand<i + 1>(sb);
-        static_for<4>([&](auto jp) {
-            constexpr int j = decltype(jp)::value;
-            const f32x2 fa = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], sa, j);
-            const f32x2 fb = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i + 1], sbb, j);
-            o[2 * j][g] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(o[2 * j][g], fa.x, fb.x, cs[2 * j], sel);
-            o[2 * j + 1][g] =
-                __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(o[2 * j + 1][g], fa.y, fb.y, cs[2 * j + 1], sel);
-        });
-    });
-}
-
-// The same slice in integers, for row-scale bytes 253 and 254, whose largest values
-// (4 and 6 times 2^126 or 2^127) exceed FP32.  Never taken by real activations, so it is
-// written for size, not speed: rolled loops that re-read the nibbles (they are still in
-// cache) and the staged row scales, and write straight into the LDS output tile.
-// Every non-zero E2M1 value is (1 + M/2) * 2^(E-1) with the pair (E, M) = (field, mantissa),
-// except the subnormal 0.5 = 1.0 * 2^-1, i.e. (0, 0).  With at most two significant bits,
-// ceil(log2(x/6)) = floor(log2 x) - 2, so the column byte is max(0, max(b_row + E) - 3).
-// Relative to it, t = 2*(b_row + E - b_col) + M orders the values; t >= 2 are E2M1 normals
-// and stay exact (code t), and below that RTNE gives t = 1 -> 1.0 (tie .75, even code 2),
-// t = 0 and -1 -> 0.5 (code 1), t = -2 -> 0 (tie .25), lower -> 0.
-// Only the first n_valid rows of the slice exist (fewer than 32 at the ragged end of a split).
+// A slice in integers, straight into the LDS output tile: its 8 column bytes.
 __device__ __noinline__ uint64_t requant_slice_int(const uint8_t *src, size_t src_pitch, const uint8_t *row_sf,
                                                    uint32_t *out_row0, uint32_t out_row_stride, int n_valid)
 {
     uint64_t col_bytes = 0;
 #pragma nounroll
     for (int c = 0; c < 8; ++c) {
-        int emax = -1024;
-#pragma nounroll
-        for (int i = 0; i < n_valid; ++i) {
-            const uint32_t wi = *reinterpret_cast<const uint32_t *>(src + (size_t)i * src_pitch);
-            const int mag = (int)(wi >> (4 * c)) & 7;
-            if (mag)
-                emax = max(emax, (int)row_sf[i] + (mag >> 1));
-        }
-        const int bc = max(0, emax - 3);
+        const uint32_t bc = column_byte_int(src, src_pitch, row_sf, c, n_valid);
         col_bytes |= (uint64_t)bc << (8 * c);
-#pragma nounroll
-        for (int g = 0; g < 4; ++g) {
-            uint32_t acc = 0;
-#pragma nounroll
-            for (int i8 = 0; i8 < 8; ++i8) {
-                const int i = g * 8 + i8;
-                if (i >= n_valid)
-                    break; // the nibbles of rows that do not exist stay 0
-                const uint32_t wi = *reinterpret_cast<const uint32_t *>(src + (size_t)i * src_pitch);
-                const uint32_t nib = (wi >> (4 * c)) & 0xFu;
-                const int mag = (int)(nib & 7u);
-                const int em = mag == 1 ? 0 : mag; // 2*E + M of the normalised value
-                const int t2 = max(em + 2 * ((int)row_sf[i] - bc) + 2, 0);
-                int code = min(7, max(t2 - 2, (t2 + 1) >> 1));
-                code = mag ? code : 0;
-                acc |= ((nib & 8u) | (uint32_t)code) << (4 * i8);
-            }
-            out_row0[c * out_row_stride + g] = acc;
-        }
+        column_codes_int(src, src_pitch, row_sf, c, n_valid, bc, out_row0 + c * out_row_stride);
     }
     return col_bytes;
 }
@@ -390,7 +325,7 @@ __global__ void __launch_bounds__(T_THREADS) row_to_col_kernel(const RowToColArg
     // ---- step 2: re-quantize into the tile buffer
     if (hw) {
         uint32_t o[8][4];
-        requant_rows_hw(w, sb, cb, o);
+        requant_columns_hw<0, 4>(w, sb, cb, o);
 #pragma unroll
         for (int c = 0; c < 8; ++c)
             s_out[(c * 32 + cg) * NRG + slot] = u32x4{o[c][0], o[c][1], o[c][2], o[c][3]};

@@ -79,6 +79,17 @@ __device__ __forceinline__ void look_codes(const uint32_t (&w)[16], const uint32
     });
 }
 
+// The integer path, by columns.
+__device__ __noinline__ uint32_t slow_byte(const uint8_t *src, size_t src_pitch, const uint8_t *row_sf, int c)
+{
+    return column_byte_int(src, src_pitch, row_sf, c, 32);
+}
+
+__device__ __noinline__ void slow_codes(const uint8_t *src, size_t src_pitch, const uint8_t *row_sf, int c, uint32_t bc, uint32_t *out)
+{
+    column_codes_int(src, src_pitch, row_sf, c, 32, bc, out);
+}
+
 } // namespace row_to_col_seg
 
 using namespace row_to_col_seg;
@@ -221,7 +232,7 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
         } else {
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                cb[c] = column_byte_int(src, pitch, my_row_sf, c, 32);
+                cb[c] = slow_byte(src, pitch, my_row_sf, c);
         }
 #pragma unroll
         for (int c = 0; c < 8; ++c)
@@ -238,7 +249,7 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                cbl[c] = column_byte_int(src_l, pitch, my_row_sf_l, 2 * (int)h + (c & 1) + (c >> 1) * 4, 32);
+                cbl[c] = slow_byte(src_l, pitch, my_row_sf_l, 2 * (int)h + (c & 1) + (c >> 1) * 4);
         }
     }
     __syncthreads();
@@ -269,15 +280,15 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
             uint8_t *my = s_tile + cg * ROW + SEG + rg * 16u;
             if (!special) {
                 uint32_t o[CPP][4];
-                requant_columns_hw<p * CPP / 2>(w, sb, cb, o);
+                requant_columns_hw<p * CPP / 2, CPP / 2>(w, sb, cb, o);
 #pragma unroll
                 for (int c = 0; c < CPP; ++c)
                     *reinterpret_cast<u32x4 *>(my + c * 32u * ROW) = u32x4{o[c][0], o[c][1], o[c][2], o[c][3]};
             } else {
 #pragma unroll
                 for (int c = 0; c < CPP; ++c)
-                    column_codes_int(src, pitch, my_row_sf, p * CPP + c, 32, cb[p * CPP + c],
-                                     reinterpret_cast<uint32_t *>(my + c * 32u * ROW));
+                    slow_codes(src, pitch, my_row_sf, p * CPP + c, cb[p * CPP + c],
+                               reinterpret_cast<uint32_t *>(my + c * 32u * ROW));
             }
         }
         if (active_l) {
@@ -291,8 +302,8 @@ __global__ void __launch_bounds__(THREADS, 4) row_to_col_segments_kernel(const r
             } else {
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
-                    column_codes_int(src_l, pitch, my_row_sf_l, p * CPP + 2 * (int)h + c, 32, cbl[2 * p + c],
-                                     reinterpret_cast<uint32_t *>(my + c * 32u * ROW));
+                    slow_codes(src_l, pitch, my_row_sf_l, p * CPP + 2 * (int)h + c, cbl[2 * p + c],
+                               reinterpret_cast<uint32_t *>(my + c * 32u * ROW));
             }
         }
         __syncthreads();

@@ -1,4 +1,4 @@
-// Pieces shared by the two MXFP4 row -> column kernels: a 32-row slice of 8 columns, through the hardware conversions or in integers.
+// Shared by the two MXFP4 row -> column kernels: a 32-row slice of 8 columns, through the hardware conversions or in integers.
 #pragma once
 
 #include "mxfp4_device.hpp"
@@ -36,13 +36,18 @@ __device__ __forceinline__ void column_scales_hw(const uint32_t (&w)[32], const 
         cb[c] = max(f2u(amax[c]) >> 23, 2u) - 2u;
 }
 
-// Step 2 for the four columns of the nibble bytes J0 and J0 + 1.
-template <int J0>
+// Step 2 for the columns of the NJ nibble bytes from J0 on: decode again (cheaper than keeping 256 floats live) and re-quantize
+// pairs of rows into output bytes: v_cvt_scalef32_pk_fp4_f32 takes rows (m, m+1) of one column.
+template <int J0, int NJ>
 __device__ __forceinline__ void requant_columns_hw(const uint32_t (&w)[32], const uint32_t (&sb)[8], const uint32_t (&cb)[8],
-                                                   uint32_t (&o)[4][4])
+                                                   uint32_t (&o)[2 * NJ][4])
 {
+    float cs[2 * NJ];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 2 * NJ; ++c)
+        cs[c] = u2f(cb[2 * J0 + c] << 23);
+#pragma unroll
+    for (int c = 0; c < 2 * NJ; ++c)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
             asm volatile("" : "=v"(o[c][g])); // no initial value needed: all four bytes are written
@@ -50,21 +55,25 @@ __device__ __forceinline__ void requant_columns_hw(const uint32_t (&w)[32], cons
         constexpr int i = 2 * decltype(ip)::value;
         constexpr int g = i >> 3, sel = (i >> 1) & 3; // output dword and byte of rows (i, i+1)
         const float sa = row_scale_operand<i>(sb), sbb = row_scale_operand<i + 1>(sb);
-        static_for<2>([&](auto jp) {
+        static_for<NJ>([&](auto jp) {
             constexpr int jl = decltype(jp)::value, j = J0 + jl;
             const f32x2 fa = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], sa, j);
             const f32x2 fb = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i + 1], sbb, j);
-            o[2 * jl][g] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(o[2 * jl][g], fa.x, fb.x, u2f(cb[2 * j] << 23), sel);
+            o[2 * jl][g] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(o[2 * jl][g], fa.x, fb.x, cs[2 * jl], sel);
             o[2 * jl + 1][g] =
-                __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(o[2 * jl + 1][g], fa.y, fb.y, u2f(cb[2 * j + 1] << 23), sel);
+                __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(o[2 * jl + 1][g], fa.y, fb.y, cs[2 * jl + 1], sel);
         });
     });
 }
 
-// One column (c of the dword at src, n_valid rows) in integers: its UE8M0 byte, 255 where a row scale is NaN.  See
-// requant_slice_int for the arithmetic.
-[[maybe_unused]] static __device__ __noinline__ uint32_t column_byte_int(const uint8_t *src, size_t src_pitch,
-                                                                         const uint8_t *row_sf, int c, int n_valid)
+// One column (c of the dwords at src) of the same slice in integers, for row-scale bytes 253 and 254, whose largest values
+// (4 and 6 times 2^126 or 2^127) exceed FP32, and for NaN.  Never taken by real activations, so it is
+// written for size, not speed: rolled loops that re-read the nibbles (they are still in
+// cache) and the staged row scales.  Only the first n_valid rows of the slice exist (fewer than 32 at the ragged end of a split).
+// Every non-zero E2M1 value is (1 + M/2) * 2^(E-1) with the pair (E, M) = (field, mantissa),
+// except the subnormal 0.5 = 1.0 * 2^-1, i.e. (0, 0).  With at most two significant bits,
+// ceil(log2(x/6)) = floor(log2 x) - 2, so the column byte is max(0, max(b_row + E) - 3); 255 where a row scale is NaN.
+__device__ __forceinline__ uint32_t column_byte_int(const uint8_t *src, size_t src_pitch, const uint8_t *row_sf, int c, int n_valid)
 {
     int emax = -1024;
     bool nan = false;
@@ -79,10 +88,11 @@ __device__ __forceinline__ void requant_columns_hw(const uint32_t (&w)[32], cons
     return nan ? 255u : (uint32_t)max(0, emax - 3);
 }
 
-// Its 32 codes relative to that byte.
-[[maybe_unused]] static __device__ __noinline__ void column_codes_int(const uint8_t *src, size_t src_pitch,
-                                                                      const uint8_t *row_sf, int c, int n_valid, uint32_t bc,
-                                                                      uint32_t *out)
+// Its 32 codes relative to that byte: t = 2*(b_row + E - b_col) + M orders the values; t >= 2 are E2M1 normals
+// and stay exact (code t), and below that RTNE gives t = 1 -> 1.0 (tie .75, even code 2),
+// t = 0 and -1 -> 0.5 (code 1), t = -2 -> 0 (tie .25), lower -> 0.
+__device__ __forceinline__ void column_codes_int(const uint8_t *src, size_t src_pitch, const uint8_t *row_sf, int c, int n_valid,
+                                                 uint32_t bc, uint32_t *out)
 {
 #pragma nounroll
     for (int g = 0; g < 4; ++g) {
