@@ -17,11 +17,12 @@
 // of LDS with byte alignments (unaligned 16-byte LDS reads: 55 us more).
 //
 // Measured at 65536 rows of K = 7168 in 32 experts (us, kernels that write their own rows only / this one; scale alignment and
-// re-quantization): Zipf-sized 192 / 161 and 190 / 169, padded to 128 rows 150 / 143 and 153 / 141, equal 2041 rows 179 / 159
-// and 187 / 164; K = 2048 58 / 44 and 60 / 46; 128 experts 214 / 181 and 221 / 189; 128 of 500 rows 200 / 171 and 188 / 180;
-// 80 of 780 rows, where every fourth tile has 12 rows, 174 / 178 and 184 / 187.  A mover of the same bytes in the same tiles
-// takes 155 (Zipf-sized) and 133 (padded).  Bound by that pattern, and in a workgroup's 33 thousand cycles by the wait for its
-// loads (8), the two conversions (4) and the two write-outs (6).
+// re-quantization): Zipf-sized 192 / 159 and 190 / 166, padded to 128 rows 149 / 142 and 152 / 141, equal 2041 rows 179 / 153
+// and 187 / 160; K = 2048 58 / 46 and 60 / 50; 128 experts 214 / 179 and 221 / 187; 128 of 500 rows 200 / 170 and 188 / 176;
+// 80 of 780 rows, where every fourth tile has 12 rows, 174 / 167 and 184 / 176; 100 of 268 104 / 102 and 111 / 102; 50 of 190, one
+// tile along the rows each, 39 / 28 and 41 / 30.  A mover of the same bytes in the same tiles takes 155 (Zipf-sized) and 133
+// (padded).  Bound by that pattern, and in a workgroup's 33 thousand cycles by the wait for its loads (8), the two conversions (4)
+// and the two write-outs (6).
 // Not kept: whole 128-byte lines (every lane converts twice the look-back rows; the mover gains 4 %); one pass (87 KB) 259;
 // four passes and four workgroups per compute unit 172 against 168.
 #include "fp8_col_tile.hpp"
@@ -454,6 +455,7 @@ __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(cons
         // ---- out.  A wave instruction writes 4 k-rows of 16 lanes x 16 bytes, eight columns apart; step i of a wave has the
         // LDS k-rows 4 * (wv + WAVES * i).., i.e. the columns c = p * CPP + i / 2 of the column groups 4 * wv + 16 * (i % 2)..
         constexpr int STEPS = 32 * CPP / 4 / WAVES;
+        constexpr uint32_t PPS = SEG / 16; // pieces of a segment
         const uint32_t part = lane & 15u;
         // k-row of the lane in step 0 and the tile's first row, SEG bytes late: what is subtracted from an offset stays below SEG
         uint8_t *const base = out_x + (size_t)(k0 + wv * 32u + p * CPP) * rows + m0 - SEG;
@@ -475,7 +477,7 @@ __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(cons
         auto past = [&](uint32_t row) { return (base_low + row) & (SEG - 1u); };
         // Every tile begins and ends on a segment of the k-row: it writes the bytes from the segment that holds its first row on,
         // and leaves what follows its last whole segment to the next tile.
-        auto full = [&](auto read) { // all pieces are whole
+        auto full = [&](auto read, auto first) { // all pieces are whole; first: without the first segment of the k-rows
             u32x4 v[STEPS];
             uint32_t off[STEPS];
 #pragma unroll
@@ -486,10 +488,13 @@ __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(cons
             }
 #pragma unroll
             for (int i = 0; i < STEPS; ++i)
-                __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4 *>(base + off[i]));
+                if (!decltype(first)::value || part >= PPS)
+                    __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4 *>(base + off[i]));
         };
-        // The first or last tile of the expert, or one that ends early: the ends of its k-rows take the 16 bytes at the end, some
-        // of them once more.
+        // The only tile of an expert, or one of 128 columns: the ends of its k-rows take the 16 bytes at the end, some of them once
+        // more.  The first and the last of several tiles do without its tests and double stores at every step (through it 80 of 780 rows
+        // took 182 us, 128 of 270 142, now 167 and 129); the only tile of an expert has both ends, which are better written together
+        // with the rest (50 of 190 rows 28 us, in the others' way 35).
         const int n = (int)n_rows;
         auto lo_of = [&](int sh) { return tile_m == 0u ? 0 : -sh; }; // the bytes that are this tile's, from its first row
         auto hi_of = [&](int sh) { return last ? n : (int)TILE_M - sh; };
@@ -525,11 +530,69 @@ __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(cons
                     }
                 }
         };
+        // The segments of a last tile that it writes whole.
+        auto before_the_end = [&](auto read) {
+            u32x4 v[STEPS];
+            uint32_t off[STEPS];
+            bool take[STEPS];
+#pragma unroll
+            for (int i = 0; i < STEPS; ++i) {
+                const int sh = (int)past(krow(i));
+                const uint32_t from = (uint32_t)((int)(part * 16u + SEG) - sh);
+                take[i] = (int)((part / PPS + 1u) * SEG) - sh <= n && !((i & 1) && cols != TILE_K); // 128 columns: the even steps
+                off[i] = krow(i) + from;
+                v[i] = read(lane_lds + i * STEP_LDS + from);
+            }
+#pragma unroll
+            for (int i = 0; i < STEPS; ++i)
+                if (take[i])
+                    __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4 *>(base + off[i]));
+        };
+        // One segment of every k-row that another k-row or tile completes, 16 k-rows to a wave instruction: the one that begins
+        // seg_at(bytes by which the k-row is past the start of a segment) from the tile's first row.
+        auto shared_segment = [&](auto seg_at) {
+            constexpr int N = 32 * CPP / 16 / WAVES;
+            u32x4 v[N];
+            uint8_t *dst[N];
+            bool take[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const uint32_t kr = 16u * (wv + WAVES * i) + lane / PPS, kt = (kr & 31u) * 8u + p * CPP + (kr >> 5);
+                dst[i] = out_x + (size_t)(k0 + kt) * rows + m0 - SEG;
+                const int sh = (int)((uint32_t)reinterpret_cast<uintptr_t>(dst[i]) & (SEG - 1u));
+                const uint32_t from = clamped(seg_at(sh) + (int)(lane % PPS * 16u), sh, &take[i]);
+                take[i] = take[i] && kt < cols;
+                dst[i] += from;
+                v[i] = read16(kr * ROW + from);
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (take[i])
+                    *reinterpret_cast<u32x4_unaligned *>(dst[i]) = v[i];
+        };
+        auto last_segment = [&](int sh) { return ((n + sh) & ~(int)(SEG - 1u)) - sh; };
         if (cols == TILE_K && ((whole && n_rows == TILE_M) || (look && !last))) {
             if (by16)
-                full(aligned16);
+                full(aligned16, std::false_type{});
             else
-                full(read16);
+                full(read16, std::false_type{});
+        } else if (cols == TILE_K && !last) { // the first of several
+            full(read16, std::true_type{});
+            shared_segment([](int sh) { return -sh; });
+        } else if (tile_m != 0u && last) {
+            // The two halves of the segment at the end of a k-row meet in the L2; the other one, of the next k-row, is written at the
+            // end of a pass (above).  A long last tile is there later than the first tile and writes its half first (128 of 500 rows
+            // 178 -> 171 us), a short one sooner and writes it last (128 of 300, K = 2048, 42 -> 33).  In launches that the memory-side
+            // cache holds, where the halves meet all the same, it is written last (Zipf-sized [65536, 2048] 47.5 -> 44.7).
+            const bool early = a.stream != 0u && n_rows > SEG;
+            if (early)
+                shared_segment(last_segment);
+            if (by16)
+                before_the_end(aligned16);
+            else
+                before_the_end(read16);
+            if (!early)
+                shared_segment(last_segment);
         } else if (rows >= 16u) {
             if (by16 && (n_rows & 15u) == 0u)
                 ends(aligned16);

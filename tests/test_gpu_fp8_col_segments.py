@@ -18,6 +18,8 @@ SPLITS = {
     "segments": [63, 64, 65, 191, 192, 193, 319, 320, 321, 64, 448],
     "groups": [127, 128, 129, 383, 384, 385, 256, 511, 512, 513, 0, 769],
     "one": [1023],
+    "long last tiles": [449, 455, 500, 511, 330, 505, 480, 496],  # nearly a whole tile behind a whole one
+    "short last tiles": [268, 258, 780, 300, 524, 319, 1026],
     "by 16": [16, 272, 48, 528, 304, 1040, 32, 336],      # a total that is a multiple of 16: the small launch keeps its kernels
     "by 16 at length": [16 * n for n in (1, 3, 17, 33, 65, 20, 50, 31)] * 9,  # the same, above the line at K = 2176
     "by 64": [64, 320, 576, 192, 128, 832],               # k-rows of whole segments, of half lines
