@@ -226,7 +226,7 @@ struct FastDiv {
 // really exist (the launch can only bound it: with the bound in its place the ids that round the
 // grid up would all fall into the last XCD's share and the others would carry its tiles).
 // Uniform per workgroup; every wave evaluates it on its own, 64 experts per lane-parallel step:
-// the offsets of all experts (CHUNKS = 1, 4 or 16 times 64) are requested at once and without branches
+// the offsets of all experts (CHUNKS = 1, 2, 4 or 16 times 64) are requested at once and without branches
 // between the requests, so the lookup waits for memory once, then wave prefix sums of the tile counts and
 // a ballot find the expert.  It is in front of every load of the tile: with branches between the requests (a
 // wait at each), the column tiles divided by and two more divisions in the macro block it took 2400 cycles
