@@ -20,7 +20,7 @@
 // re-quantization): Zipf-sized 192 / 159 and 190 / 166, padded to 128 rows 149 / 142 and 152 / 141, equal 2041 rows 179 / 153
 // and 187 / 160; K = 2048 58 / 46 and 60 / 50; 128 experts 214 / 179 and 221 / 187; 128 of 500 rows 200 / 170 and 188 / 176;
 // 80 of 780 rows, where every fourth tile has 12 rows, 174 / 167 and 184 / 176; 100 of 268 104 / 102 and 111 / 102; 50 of 190, one
-// tile along the rows each, 39 / 28 and 41 / 30.  A mover of the same bytes in the same tiles takes 155 (Zipf-sized) and 133
+// tile along the rows each, 39 / 26 and 41 / 28.  A mover of the same bytes in the same tiles takes 155 (Zipf-sized) and 133
 // (padded).  Bound by that pattern, and in a workgroup's 33 thousand cycles by the wait for its loads (8), the two conversions (4)
 // and the two write-outs (6).
 // Not kept: whole 128-byte lines (every lane converts twice the look-back rows; the mover gains 4 %); one pass (87 KB) 259;
@@ -571,7 +571,26 @@ __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(cons
                     *reinterpret_cast<u32x4_unaligned *>(dst[i]) = v[i];
         };
         auto last_segment = [&](int sh) { return ((n + sh) & ~(int)(SEG - 1u)) - sh; };
-        if (cols == TILE_K && ((whole && n_rows == TILE_M) || (look && !last))) {
+        auto clamped_pieces = [&] {
+            if (by16 && (n_rows & 15u) == 0u)
+                ends(aligned16);
+            else
+                ends(read16);
+            if (last && n > (int)(TILE_M - SEG)) { // past the 256 bytes that begin before the first row of the tile
+                for (uint32_t kr = tid / PPS; kr < 32u * CPP; kr += THREADS / PPS) {
+                    const uint32_t kt = (kr & 31u) * 8u + p * CPP + (kr >> 5);
+                    uint8_t *dst = out_x + (size_t)(k0 + kt) * rows + m0;
+                    const int sh = (int)((uint32_t)reinterpret_cast<uintptr_t>(dst) & (SEG - 1u));
+                    bool take;
+                    const uint32_t from = clamped((int)(TILE_M + tid % PPS * 16u) - sh, sh, &take);
+                    if (take && kt < cols)
+                        *reinterpret_cast<u32x4_unaligned *>(dst - SEG + from) = read16(kr * ROW + from);
+                }
+            }
+        };
+        if (tile_m == 0u && last && rows >= 16u && !(whole && n_rows == TILE_M && cols == TILE_K)) {
+            clamped_pieces(); // a copy of its own, where both ends are the k-rows': 50 of 190 rows 27.5 -> 26.2 us
+        } else if (cols == TILE_K && ((whole && n_rows == TILE_M) || (look && !last))) {
             if (by16)
                 full(aligned16, std::false_type{});
             else
@@ -594,21 +613,7 @@ __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(cons
             if (!early)
                 shared_segment(last_segment);
         } else if (rows >= 16u) {
-            if (by16 && (n_rows & 15u) == 0u)
-                ends(aligned16);
-            else
-                ends(read16);
-            if (last && n > (int)(TILE_M - SEG)) { // past the 256 bytes that begin before the first row of the tile
-                for (uint32_t kr = tid / (SEG / 16u); kr < 32u * CPP; kr += THREADS / (SEG / 16u)) {
-                    const uint32_t kt = (kr & 31u) * 8u + p * CPP + (kr >> 5);
-                    uint8_t *dst = out_x + (size_t)(k0 + kt) * rows + m0;
-                    const int sh = (int)((uint32_t)reinterpret_cast<uintptr_t>(dst) & (SEG - 1u));
-                    bool take;
-                    const uint32_t from = clamped((int)(TILE_M + tid % (SEG / 16u) * 16u) - sh, sh, &take);
-                    if (take && kt < cols)
-                        *reinterpret_cast<u32x4_unaligned *>(dst - SEG + from) = read16(kr * ROW + from);
-                }
-            }
+            clamped_pieces();
         } else {
             for (uint32_t kr = tid; kr < 32u * CPP; kr += THREADS) {
                 const uint32_t kt = (kr & 31u) * 8u + p * CPP + (kr >> 5);
