@@ -635,12 +635,14 @@ static int64_t tiles_at_most(int64_t M, int64_t K, int32_t num_experts)
 
 // Launches of about one round of the other kernels' workgroups (two per compute unit, one pass), as far as the number of tiles
 // can be told, whose total row count says that the splits may be padded, are left to them: nothing is shared or the pieces are
-// aligned, and what a workgroup takes longer here is not made up for.  For scale alignment only splits padded to 16 rows and not
-// to 128.  Measured (us, own rows / segments, re-quantization): padded to 16, [8439, 512] in 64 experts 7.8 / 8.9, [2000, 2048]
-// in 8 8.4 / 9.6, [4000, 4096] in 16 10.8 / 11.8; to 128, [34135, 768] in 64 10.4 / 11.7, [6483, 1792] in 64 9.9 / 10.5, [10711,
-// 2432] in one 10.8 / 11.3; above the line, [16000, 2048] in 16 18.9 / 17.6, [11113, 3968] in one 19.0 / 14.0; not padded, [2000,
-// 2048] 11.7 / 9.9, [6180, 1280] in 16 12.5 / 10.4.  Those kernels look for one of at most 128 experts: the longer lookup costs their
-// flat form 1 %.
+// aligned, and what a workgroup takes longer here is not made up for.  Measured (us, own rows / segments, re-quantization): padded
+// to 16, [8864, 512] in 64 experts 7.6 / 9.0, [2064, 2048] in 8 7.7 / 9.3, [4112, 4096] in 16 11.2 / 12.4; to 128, [9984, 1792] in 64
+// 9.2 / 10.4, [10752, 2432] in one 10.9 / 11.3, [38144, 768] in 64 10.9 / 10.6; above the line, [16128, 2048] in 16 18.6 / 16.1,
+// [11136, 3968] in one 18.8 / 15.6; not padded, [6180, 1280] in 16 12.1 / 10.6.  For scale alignment only totals that are multiples of
+// 16 and not of 128: one of 128 may as well be that of un-padded splits, which lose more by their own rows than padded ones by
+// segments (padded / the same un-padded, own rows / segments: [4224, 3072] in 4 7.3 / 7.5, 11.9 / 10.1; [9984, 2048] in 32 8.9 / 9.2,
+// 13.7 / 11.9; [14208, 2048] in 4 10.2 / 9.8, 14.5 / 12.8).  Those kernels look for one of at most 128 experts: the longer lookup
+// costs their flat form 1 %.
 bool fp8_col_in_segments(int64_t M, int64_t K, int32_t num_experts, bool requant)
 {
     const int64_t half_tiles = (M / (TILE_M / 2) + num_experts) * ((K + TILE_K - 1) / TILE_K); // experts end in half a tile each
