@@ -387,14 +387,34 @@ __global__ void __launch_bounds__(64 * SCATTER_WAVES) quant_from_fp8_scatter_wav
 // Bound by the writes to many places: 65536 tokens of 7168, eight copies grouped by expert 508 -> 479 us = 5.2 TB/s with the
 // pieces dealt that way (shuffled copies 553 -> 511; a kernel that only copies finished records: 477 and 500); 256 lanes and
 // four workgroups per compute unit 484, 1024 lanes 584, one wave per row 520.
+//
+// Rows by runs of 32 to one XCD.  The copies of neighbouring source rows are often neighbours in the output, and records
+// share lines and segments, which one L2 puts together but two do not.  Workgroup ids go round the eight XCDs, so in every
+// 256 of them the rows are dealt in runs.  Us, row = id / runs of 4 / 16 / 32 / 64 / 256 / one eighth of the rows each:
+// 65536 x 7168 to eight records grouped by expert 480 / 475 / 470 / 467 / 466 / 471 / 486, shuffled 508 / 508 / 503 / 501 / 501 /
+// 503 / 504; two copies 171 -> 161, three of 30000 x 7680 103.5 -> 100.9.  Plain stores instead of non-temporal ones on top of
+// that gain 2 % for copies grouped by expert and cost 15 % for shuffled ones; the waves of a workgroup dealt over the copies change
+// nothing.  Few rows are all in flight at once: 512 rows of 7168, eight copies 7.5 -> 7.7, hence SCATTER_RUNS_FROM.
+// The kernel of one wave per row gains nothing from runs (65536 x 2048, eight copies 139.7 -> 142.6).
 constexpr int SCATTER_THREADS = 512;
+constexpr uint32_t SCATTER_RUN = 32, SCATTER_RUNS_FROM = 2048;
+static_assert((SCATTER_RUN & (SCATTER_RUN - 1u)) == 0u, "runs are taken apart by masks");
+
+// The source row of workgroup `id`; the last rows, which do not fill a run for every XCD, in the order of the ids.
+__device__ __forceinline__ uint32_t scatter_row_of(uint32_t id, uint32_t rows)
+{
+    constexpr uint32_t ALL = NUM_XCD * SCATTER_RUN;
+    if (rows < SCATTER_RUNS_FROM || id >= rows / ALL * ALL)
+        return id;
+    return id / ALL * ALL + id % NUM_XCD * SCATTER_RUN + id / NUM_XCD % SCATTER_RUN;
+}
 
 template <bool WIDE_SF> // the K/32 scale bytes of a row are a whole number of 16-byte pieces (K % 512 == 0)
 __global__ void __launch_bounds__(SCATTER_THREADS) quant_from_fp8_scatter_row_kernel(const QuantScatterArgs a,
                                                                                      const bool records)
 {
     extern __shared__ __align__(16) uint8_t s_row[];
-    const uint32_t tid = threadIdx.x, row = blockIdx.x;
+    const uint32_t tid = threadIdx.x, row = scatter_row_of(blockIdx.x, gridDim.x);
     const uint32_t C = a.chunks_per_row; // 16-element chunks per row
     const uint32_t nib_bytes = C * 8u;
     const uint8_t *src = a.x + (size_t)row * C * 16u;

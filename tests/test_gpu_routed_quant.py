@@ -84,6 +84,19 @@ def test_scatter_of_many_copies(K, M, fan):
     assert torch.equal(buf, want)
 
 
+@pytest.mark.parametrize("K,M", [(6144, 2047), (6144, 2048), (6272, 2049), (6144, 2303), (6144, 2304), (6144, 2561)])
+def test_scatter_rows_in_runs(K, M):
+    """Rows dealt to the XCDs in runs: below and from the number of rows on, with and without rows left over after the last
+    round of runs; every row is written once, to all of its destinations."""
+    rng, x8, s, wq, wsf = source(M, K, K + M)
+    M_out = M * 2 + 3
+    dst = rng.permutation(M_out)[: M * 2].reshape(M, 2).astype(np.int32)
+    buf, q, sf, ld_q, ld_sf, at = outputs(M_out, K, "records")
+    mx.mxfp4_quant_from_fp8_scatter(dev(x8), dev(s), dev(dst), M_out, q=q, sf=sf, ld_q=ld_q, ld_sf=ld_sf)
+    src = np.repeat(np.arange(M), 2)
+    check(buf, at, ld_q, ld_sf, K, dst.reshape(-1), wq[src], wsf[src])
+
+
 # ---- gather by owners
 
 GROUPS = 1 << (torch.cuda.get_device_properties(0).multi_processor_count.bit_length() - 1) if torch.cuda.is_available() else 256
