@@ -76,6 +76,20 @@ mxfp4_status mxfp4_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_
                                   const int32_t *gather_idx, int64_t M_out, uint8_t *q,
                                   int64_t ld_q, uint8_t *sf, int64_t ld_sf, void *hip_stream);
 
+/* mxfp4_quant_from_fp8 with device memory to work in, which makes large gathers of rows that are wanted several times faster (the
+ * index is turned around first, so that every source row is read and quantized once).  The same results, refusals and alignments.
+ *   workspace        device memory, 16-byte aligned, that no other work uses until this call's has run; its contents do not
+ *                    matter.  In stream order: it may go back to a stream-ordered allocator, or to the next call on the same
+ *                    stream, as soon as this call returns.  NULL, or fewer workspace_bytes than
+ *                    mxfp4_quant_from_fp8_gather_workspace says: the call is mxfp4_quant_from_fp8.
+ * mxfp4_quant_from_fp8_gather_workspace: the bytes a call with these arguments makes use of; 0 where it is mxfp4_quant_from_fp8
+ * anyway.  Launches nothing. */
+int64_t mxfp4_quant_from_fp8_gather_workspace(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q);
+mxfp4_status mxfp4_quant_from_fp8_gather(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
+                                         const int32_t *gather_idx, int64_t M_out, uint8_t *q, int64_t ld_q,
+                                         uint8_t *sf, int64_t ld_sf, void *workspace, int64_t workspace_bytes,
+                                         void *hip_stream);
+
 /* The same quantizer with the routing turned around (paper sec. 3.2: quantization sits right before
  * the dispatch): a token is read and quantized ONCE and its packed row written to each of its
  * destinations, instead of once per destination as with gather_idx.

@@ -25,7 +25,7 @@ CALL_PATH = call_path()
 
 OK, ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_OFFSETS, ERR_LAUNCH = 0, -1, -2, -3, -4, -5
 
-EXPORTS = ("mxfp4_quant_from_fp8", "mxfp4_quant_from_fp8_scatter", "mxfp4_quant_from_bf16", "mxfp4_dequant_to_fp8", "mxfp4_row_to_col",
+EXPORTS = ("mxfp4_quant_from_fp8", "mxfp4_quant_from_fp8_gather", "mxfp4_quant_from_fp8_gather_workspace", "mxfp4_quant_from_fp8_scatter", "mxfp4_quant_from_bf16", "mxfp4_dequant_to_fp8", "mxfp4_row_to_col",
            "mxfp4_quant_from_fp8_grouped", "mxfp4_row_to_col_grouped", "mxfp4_row_to_fp8_col",
            "mxfp4_row_to_fp8_col_grouped", "mxfp4_row_to_fp8_col_requant", "mxfp4_row_to_fp8_col_requant_grouped",
            "mxfp4_stream_copy", "mxfp4_stream_mix", "mxfp4_tile_copy", "mxfp4_record_fanout", "mxfp4_status_string")
@@ -33,7 +33,8 @@ EXPORTS = ("mxfp4_quant_from_fp8", "mxfp4_quant_from_fp8_scatter", "mxfp4_quant_
 # the order in which csrc/call_path.cpp holds the entry points
 _NATIVE = ("mxfp4_quant_from_fp8", "mxfp4_quant_from_fp8_scatter", "mxfp4_quant_from_bf16", "mxfp4_dequant_to_fp8",
            "mxfp4_row_to_col", "mxfp4_quant_from_fp8_grouped", "mxfp4_row_to_col_grouped", "mxfp4_row_to_fp8_col",
-           "mxfp4_row_to_fp8_col_requant", "mxfp4_row_to_fp8_col_grouped", "mxfp4_row_to_fp8_col_requant_grouped")
+           "mxfp4_row_to_fp8_col_requant", "mxfp4_row_to_fp8_col_grouped", "mxfp4_row_to_fp8_col_requant_grouped",
+           "mxfp4_quant_from_fp8_gather_workspace", "mxfp4_quant_from_fp8_gather")
 
 _lib = None
 _call = None  # the native call path, loaded with the library
@@ -69,6 +70,8 @@ def lib():
             _build.build(force=True)
         L = ctypes.CDLL(LIB_PATH)  # raises OSError if it cannot be loaded: no fallback
         L.mxfp4_quant_from_fp8.argtypes = [_vp, _vp, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _i64, _vp]
+        L.mxfp4_quant_from_fp8_gather.argtypes = [_vp, _vp, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _i64, _vp, _i64, _vp]
+        L.mxfp4_quant_from_fp8_gather_workspace.argtypes = [_i64, _i64, _i64, _vp, _i64]
         L.mxfp4_quant_from_fp8_scatter.argtypes = [_vp, _vp, _i64, _i64, _vp, _i32, _i64, _vp, _i64, _vp, _i64, _vp]
         L.mxfp4_quant_from_bf16.argtypes = [_vp, _i64, _i64, _vp, _i64, _vp, _i64, _vp]
         L.mxfp4_dequant_to_fp8.argtypes = [_vp, _i64, _vp, _i64, _i64, _i64, _vp, _vp, _vp]
@@ -85,6 +88,7 @@ def lib():
         L.mxfp4_record_fanout.argtypes = [_vp, _i64, _vp, _i64, _i32, _i64, _i64, _vp, _vp]
         for n in EXPORTS[:-1]:
             getattr(L, n).restype = ctypes.c_int
+        L.mxfp4_quant_from_fp8_gather_workspace.restype = _i64
         L.mxfp4_status_string.argtypes = [ctypes.c_int]
         L.mxfp4_status_string.restype = ctypes.c_char_p
         _call = _load_call_path(L)
@@ -206,9 +210,22 @@ def mxfp4_quant_from_fp8(x, x_scale, gather_idx=None, q=None, sf=None, ld_q=None
         M_out = M_src
     q, sf, ld_q, ld_sf = _quant_outputs(x, M_out, K, q, sf, ld_q, ld_sf, torch.empty)
     dev = _on_device(x=x, x_scale=x_scale, gather_idx=gather_idx, q=q, sf=sf)
-    st = lib().mxfp4_quant_from_fp8(x.data_ptr(), x_scale.data_ptr(), M_src, K,
-                                    None if gather_idx is None else gather_idx.data_ptr(), M_out,
-                                    q.data_ptr(), ld_q, sf.data_ptr(), ld_sf, _stream(stream, dev))
+    idx = None if gather_idx is None else gather_idx.data_ptr()
+    # memory to work in is given back when the call returns: to the current stream, so only a call on that one gets any
+    size = lib().mxfp4_quant_from_fp8_gather_workspace(M_src, K, M_out, q.data_ptr(), ld_q) if idx and stream is None else 0
+    work = None
+    if size > 0:
+        try:
+            work = torch.empty(size, dtype=torch.uint8, device=x.device)
+        except torch.OutOfMemoryError:
+            pass  # it is done without
+    if work is not None:
+        st = lib().mxfp4_quant_from_fp8_gather(x.data_ptr(), x_scale.data_ptr(), M_src, K, idx, M_out, q.data_ptr(), ld_q,
+                                               sf.data_ptr(), ld_sf, work.data_ptr(), size, _stream(None, dev))
+        _check("mxfp4_quant_from_fp8_gather", st)
+        return q, sf
+    st = lib().mxfp4_quant_from_fp8(x.data_ptr(), x_scale.data_ptr(), M_src, K, idx, M_out, q.data_ptr(), ld_q, sf.data_ptr(),
+                                    ld_sf, _stream(stream, dev))
     _check("mxfp4_quant_from_fp8", st)
     return q, sf
 

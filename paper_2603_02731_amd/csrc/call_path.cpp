@@ -30,6 +30,8 @@ struct Library {
     decltype(&mxfp4_row_to_col_grouped) row_to_col_grouped;
     decltype(&mxfp4_row_to_fp8_col) fp8_col[2];                 // alignment, re-quantization
     decltype(&mxfp4_row_to_fp8_col_grouped) fp8_col_grouped[2];
+    decltype(&mxfp4_quant_from_fp8_gather_workspace) gather_workspace;
+    decltype(&mxfp4_quant_from_fp8_gather) quant_gather;
 } lib;
 constexpr Py_ssize_t N_FUNCTIONS = sizeof(Library) / sizeof(void *);
 c10::DeviceType device_type; // whose tensors are taken
@@ -218,6 +220,18 @@ PyObject *quant_from_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
             idx = static_cast<const int32_t *>(g.data_ptr());
         }
         quant_outputs(a[3], a[4], a[5], a[6], x, rows, K, false, out, ld);
+        // A gather that may gain by memory to work in (smaller ones do not, whatever the library's rule) gets it from the allocator
+        // of the current stream, and gives it back there.
+        constexpr int64_t WORTH_ASKING = (int64_t)1 << 27; // elements of output
+        if (idx && rows < ((int64_t)1 << 31) && K < ((int64_t)1 << 31) && rows * K >= WORTH_ASKING) {
+            const int64_t size = lib.gather_workspace(M, K, rows, static_cast<uint8_t *>(out[0].data()), ld[0]);
+            if (size > 0) {
+                const at::Tensor work = output(Py_None, x, at::kByte, {size}, size).t;
+                return launch("mxfp4_quant_from_fp8_gather", lib.quant_gather, bytes_of(x), static_cast<const float *>(s.data_ptr()),
+                              M, K, idx, rows, static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()),
+                              ld[1], work.data_ptr(), size, current_stream(x));
+            }
+        }
         return launch("mxfp4_quant_from_fp8", lib.quant, bytes_of(x), static_cast<const float *>(s.data_ptr()), M, K, idx,
                       rows, static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
                       current_stream(x));

@@ -38,9 +38,15 @@ uint32_t compute_units()
 
 extern "C" {
 
-mxfp4_status mxfp4_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
-                                  const int32_t *gather_idx, int64_t M_out, uint8_t *q, int64_t ld_q,
-                                  uint8_t *sf, int64_t ld_sf, void *hip_stream)
+int64_t mxfp4_quant_from_fp8_gather_workspace(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q)
+{
+    return mxfp4::gather_lists_workspace(M_src, K, M_out, q, ld_q);
+}
+
+mxfp4_status mxfp4_quant_from_fp8_gather(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
+                                         const int32_t *gather_idx, int64_t M_out, uint8_t *q, int64_t ld_q,
+                                         uint8_t *sf, int64_t ld_sf, void *workspace, int64_t workspace_bytes,
+                                         void *hip_stream)
 {
     if (M_src < 0 || M_out < 0 || K < 0 || K % 128 != 0)
         return MXFP4_ERR_SHAPE;
@@ -56,10 +62,23 @@ mxfp4_status mxfp4_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_
         M_out * (K / 16) >= kMaxWorkItems)
         return MXFP4_ERR_SHAPE;
     if (!aligned(x, 16) || !aligned(x_scale, 4) || !aligned(q, 8) || ld_q % 8 != 0 || !aligned(sf, 4) ||
-        ld_sf % 4 != 0 || (gather_idx && !aligned(gather_idx, 4)))
+        ld_sf % 4 != 0 || (gather_idx && !aligned(gather_idx, 4)) || !aligned(workspace, 16))
         return MXFP4_ERR_ALIGN;
+    if (gather_idx && workspace) {
+        const int64_t need = mxfp4::gather_lists_workspace(M_src, K, M_out, q, ld_q);
+        if (need > 0 && need <= workspace_bytes)
+            return launched(mxfp4::launch_quant_gather_lists(x, x_scale, M_src, K, gather_idx, M_out, q, ld_q, sf, ld_sf,
+                                                             workspace, static_cast<hipStream_t>(hip_stream)));
+    }
     return launched(mxfp4::launch_quant_from_fp8(x, x_scale, M_src, K, gather_idx, M_out, q, ld_q, sf, ld_sf,
                                                  static_cast<hipStream_t>(hip_stream)));
+}
+
+mxfp4_status mxfp4_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
+                                  const int32_t *gather_idx, int64_t M_out, uint8_t *q, int64_t ld_q,
+                                  uint8_t *sf, int64_t ld_sf, void *hip_stream)
+{
+    return mxfp4_quant_from_fp8_gather(x, x_scale, M_src, K, gather_idx, M_out, q, ld_q, sf, ld_sf, nullptr, 0, hip_stream);
 }
 
 mxfp4_status mxfp4_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,

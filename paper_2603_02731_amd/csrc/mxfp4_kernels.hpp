@@ -11,6 +11,13 @@ hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t
                                  const int32_t *gather_idx, int64_t M_out, uint8_t *q, int64_t ld_q,
                                  uint8_t *sf, int64_t ld_sf, hipStream_t stream);
 
+// The gather with every source row quantized once, through lists in a workspace: bytes of it, 0 where the form above is the one
+// to take; and the launches.
+int64_t gather_lists_workspace(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q);
+hipError_t launch_quant_gather_lists(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K, const int32_t *gather_idx,
+                                     int64_t M_out, uint8_t *q, int64_t ld_q, uint8_t *sf, int64_t ld_sf, void *workspace,
+                                     hipStream_t stream);
+
 // Source row i goes to the output rows dst_idx[i*fanout .. i*fanout + fanout - 1].
 hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
                                          const int32_t *dst_idx, int32_t fanout, int64_t M_out, uint8_t *q,

@@ -27,6 +27,20 @@ def test_library_exports_every_declared_symbol():
         assert getattr(L, n) is not None
 
 
+def test_gather_workspace():
+    """The gather's memory to work in: none for small maps, rows wanted less than twice or by very many, unaligned rows, and sizes
+    that no call takes; elsewhere the lists, the counts and the rest of a map, all of them 4-byte words."""
+    size = mx.lib().mxfp4_quant_from_fp8_gather_workspace
+    for M, K, n, at, ld in ((0, 7168, 65536, 64, 3808), (8192, 7168, 0, 64, 3808), (-1, 7168, 65536, 64, 3808), (8192, 0, 65536, 64, 3808),
+                            (1024, 7168, 8192, 64, 3808), (32769, 7168, 65537, 64, 3808), (2048, 7168, 65536, 64, 3808),
+                            (8192, 7168, 65536, 72, 3808), (8192, 7168, 65536, 64, 3592), (131072, 1024, 1 << 20, 64, 512),
+                            (131072, 7168, (1 << 20) + 1, 64, 3808), (1 << 62, 1 << 24, 1 << 62, 64, 3808)):
+        assert size(M, K, n, at, ld) == 0, (M, K, n, at, ld)
+    for M, K, n in ((8192, 7168, 65536), (65536, 7168, 131072), (8192, 7168, 32767 + 16384), (131072, 1536, 1 << 20)):
+        window = -(-n // 32)
+        assert size(M, K, n, 64, K // 2) == 4 * ((M + 1) * 64 + 128 + 128 * window)
+
+
 def test_status_strings():
     for st in range(-5, 1):
         assert mx.status_string(st) and mx.status_string(st) != "unknown status"

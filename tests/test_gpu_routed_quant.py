@@ -220,6 +220,98 @@ def test_gather_by_owners_in_whole_lines(K, kind, layout):
     gathered(rng, x8, s, wq, wsf, index_of(kind, M, least(M, K) + 3, rng), K, layout)
 
 
+@pytest.mark.parametrize("layout", ["records", "planes"])
+@pytest.mark.parametrize("K,M,n,kind", [
+    (1536, 9000, 150187, "mixed"), (1536, 9000, 150186, "mixed"),                              # the rule's line, 4 copies and more
+    (2048, 40000, 131072, "mixed"), (2048, 40000, 131071, "mixed"),                            # the same, fewer copies
+    (2048, 40001, 160003, "mixed"), (2048, 5001, 120047, "mixed"), (2048, 5001, 120048, "mixed"), (2048, 65536, 131071, "sorted"),
+    (2048, 16391, 131085, "padded"), (2048, 16391, 131085, "crowd"), (2048, 16391, 131085, "none"), (2048, 16391, 131085, "one"),
+    (2176, 9001, 120001, "few"), (2176, 9001, 120001, "power"), (2176, 9001, 120001, "eighth row"), (2176, 9001, 120001, "sorted"),
+    (6144, 8001, 65537, "padded"), (6272, 8001, 40004, "crowd"), (6272, 8001, 40005, "padded"), (7168, 4099, 65536, "padded"),
+    (7168, 4099, 40000, "one"), (7680, 4099, 33003, "power"), (7808, 8192, 33000, "crowd"), (12288, 6001, 22000, "padded"),
+    (16896, 2047, 16000, "few"), (98304, 601, 2500, "padded"), (98304, 601, 3100, "crowd")])
+def test_gather_by_lists(K, M, n, kind, layout):
+    """Both sides of the rule, up to and from 65536 and 262144 entries on, windows that end early, rows by waves (of one and
+    several segments) and by workgroups, unused entries, rows with more entries in a window than a list takes, scale bytes as
+    16-byte pieces and as dwords."""
+    rng, x8, s, wq, wsf = source(M, K, K + n)
+    gathered(rng, x8, s, wq, wsf, index_of(kind, M, n, rng), K, layout)
+
+
+@pytest.mark.parametrize("K,M,n,kind", [(1536, 33000, 524288, "padded"), (1536, 33000, 524289, "crowd"), (1536, 150000, 1048576, "mixed"),
+                                        (1536, 150000, 1048577, "mixed"), (2048, 524000, 1048003, "padded")])
+def test_gather_by_lists_of_a_long_index(K, M, n, kind):
+    """More entries than lanes hold, more source rows than there are counters, and an index too long for it.  All rows are zero but
+    the scale bytes' worth of them: the scale of source row i says which it is."""
+    rng = np.random.default_rng(n)
+    idx = index_of(kind, M, n, rng)
+    x = torch.full((M, K), 0x38, dtype=torch.uint8, device=DEV)  # 1.0
+    # blocks of the values 2^(i's digits): the scale byte of tile t is digit t of i in base 128, plus 60
+    row = torch.arange(M, device=DEV)
+    s = torch.ones(M, K // 128, device=DEV)
+    for t in range(3):
+        s[:, t] = torch.exp2(((row >> (7 * t)) % 128 - 60).float())
+    q, sf = mx.mxfp4_quant_from_fp8(x, s, dev(idx))
+    used = torch.from_numpy((idx >= 0) & (idx < M)).to(DEV)
+    digits = torch.stack([sf[:, 4 * t].long() - 65 for t in range(3)], 1)  # 1.0 = 4.0 * 2^-2: byte 127 - 2 for a scale of 2^0
+    got = digits[:, 0] + (digits[:, 1] << 7) + (digits[:, 2] << 14)
+    assert torch.equal(got[used], dev(idx).long()[used])
+    assert bool((q[used] == 0x66).all()) and not bool(q[~used].any()) and not bool(sf[~used].any())
+
+
+def test_gather_in_stale_memory():
+    """The memory to work in holds what an earlier call with another index left in it, or any bytes at all; too little of it, or
+    none, is the plain call."""
+    K, M, n = 2048, 16391, 131085
+    rng, x8, s, wq, wsf = source(M, K, 7)
+    x, xs = dev(x8), dev(s)
+    L = mx.lib()
+    q, sf = torch.empty(n, K // 2, dtype=torch.uint8, device=DEV), torch.empty(n, K // 32, dtype=torch.uint8, device=DEV)
+    size = L.mxfp4_quant_from_fp8_gather_workspace(M, K, n, q.data_ptr(), K // 2)
+    assert size > 0
+    work = torch.zeros(size + 64, dtype=torch.uint8, device=DEV)
+    wq, wsf = dev(wq), dev(wsf)
+    maps = [index_of(k, M, n, rng) for k in ("mixed", "padded", "crowd", "mixed", "one", "mixed")]
+    for i, idx in enumerate(maps * 2):
+        if i == len(maps):
+            work.random_(0, 4)  # small numbers are output rows of the first window
+        given = [size, size, size - 1, size, 0, size][i % 6]
+        d = dev(idx)
+        q.fill_(1)
+        sf.fill_(1)
+        work[size:] = 0xA5
+        assert L.mxfp4_quant_from_fp8_gather(x.data_ptr(), xs.data_ptr(), M, K, d.data_ptr(), n, q.data_ptr(), K // 2, sf.data_ptr(),
+                                             K // 32, work.data_ptr() if given else None, given,
+                                             torch.cuda.current_stream().cuda_stream) == 0
+        src = dev(np.where((idx >= 0) & (idx < M), idx, M).astype(np.int64))
+        assert torch.equal(q, wq[src]) and torch.equal(sf, wsf[src]), f"call {i}"
+        assert bool((work[size:] == 0xA5).all())
+
+
+def test_gather_by_lists_under_capture():
+    """Replays of a captured gather, with the inputs changed and eager calls between the replays."""
+    K, M, n = 2048, 16391, 131085
+    rng, x8, s, _, _ = source(M, K, 1)
+    x, xs = dev(x8), dev(s)
+    idx = dev(index_of("padded", M, n, rng))
+    q, sf = mx.mxfp4_quant_from_fp8(x, xs, idx)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        mx.mxfp4_quant_from_fp8(x, xs, idx, q=q, sf=sf)
+    for i in range(4):
+        y8, ys = synth.student_t_fp8(M, K, seed=20 + i)
+        x.copy_(y8)
+        xs.copy_(ys)
+        idx.copy_(idx.roll(i * 977))
+        want = mx.mxfp4_quant_from_fp8(x, xs, idx, stream=torch.cuda.current_stream())  # no memory to work in: by owners
+        q.zero_()
+        sf.fill_(7)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(q, want[0]) and torch.equal(sf, want[1]), f"replay {i}"
+
+
 def test_gather_sides_of_the_row_counts():
     """Fewer rows than four per workgroup, and fewer than two output rows per source row, on the lane-wise side."""
     for M, n in ((4 * GROUPS - 1, least(4 * GROUPS, 7168) + 100), (32 * GROUPS, 64 * GROUPS - 1), (32 * GROUPS, 64 * GROUPS)):
