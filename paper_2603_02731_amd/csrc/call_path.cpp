@@ -6,15 +6,20 @@
 // nothing.  It only accepts calls that the wrapper accepts: plain tensors, exact types, default stream argument,
 // non-empty sizes.  Everything else -- refusals above all -- is left to the wrapper, which checks again and raises.
 // Only a launch that the runtime reports as failed is raised from here: the kernel may have been queued all the same.
-// Calls back to back: quantizing [256,512] 9.2 -> 5.1 us, the three flat conversions of a small matrix 28.1 -> 15.3 us.
+// Calls back to back (through Python / here): quantizing [256,512] 9.2 / 4.1 us, the three flat conversions of a small matrix 28 /
+// 13.5.  Of the 4.1 the launch is 2.7 and the two outputs 1.1 (5.0 and 1.8 with allocations through the dispatcher).
 #include <Python.h>
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/hip/EmptyTensor.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <string.h>
+
+#include <algorithm>
 
 #include "../../include/mxfp4.h"
 
@@ -97,10 +102,14 @@ inline int64_t stride_or(PyObject *o, int64_t dense)
     return v;
 }
 
-// An output: the caller's buffer (contiguous, at least `bytes` long, on the input's device) or a new tensor.
+// An output: the caller's buffer (contiguous, at least `bytes` long, on the input's device) or a tensor that `launch` allocates.
 struct Output {
     at::Tensor t;
     PyObject *given = nullptr;
+    at::ScalarType type = at::kByte;
+    int64_t shape[2];
+    size_t dims;
+    bool zero;
     void *data() const { return t.data_ptr(); }
     PyObject *result() const
     {
@@ -122,11 +131,26 @@ inline Output output(PyObject *o, const at::Tensor &like, at::ScalarType type, a
         same_device(out.t, like);
         out.given = o;
     } else {
-        const auto options = at::TensorOptions().dtype(type).device(like.device());
-        Unlocked u;
-        out.t = zero ? at::zeros(shape, options) : at::empty(shape, options);
+        out.type = type;
+        out.dims = shape.size();
+        std::copy(shape.begin(), shape.end(), out.shape);
+        out.zero = zero;
     }
     return out;
+}
+
+// A new tensor on the device of `like`.  Without the dispatcher (0.9 us of a call's two outputs) where that has nothing else to do: no
+// mode, trace, transform or inference mode of this thread takes part in factory calls, and no fill of uninitialized memory is asked for.
+inline at::Tensor new_tensor(at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like, bool zero)
+{
+    const auto options = at::TensorOptions().dtype(type).device(like.device());
+    if (zero)
+        return at::zeros(shape, options);
+    const auto &context = at::globalContext();
+    if (like.is_cuda() && c10::impl::tls_local_dispatch_key_set().included_ == c10::default_included_set &&
+        !(context.deterministicAlgorithms() && context.deterministicFillUninitializedMemory()))
+        return at::Tensor(at::detail::empty_cuda(shape, type, like.device(), std::nullopt));
+    return at::empty(shape, options);
 }
 
 inline int64_t strided_bytes(int64_t rows, int64_t row_bytes, int64_t ld)
@@ -137,7 +161,7 @@ inline int64_t strided_bytes(int64_t rows, int64_t row_bytes, int64_t ld)
 
 // The quantizers' two outputs; a stride other than the dense one needs the caller's buffer.
 inline void quant_outputs(PyObject *q, PyObject *sf, PyObject *ld_q_arg, PyObject *ld_sf_arg, const at::Tensor &x,
-                          int64_t rows, int64_t K, bool zero, Output out[2], int64_t ld[2])
+                          int64_t rows, int64_t K, bool zero, Output (&out)[2], int64_t ld[2])
 {
     ld[0] = stride_or(ld_q_arg, K / 2);
     ld[1] = stride_or(ld_sf_arg, K / 32);
@@ -188,13 +212,16 @@ PyObject *call(Py_ssize_t n, Py_ssize_t want, PyObject *stream, Body &&body)
     Py_RETURN_NONE;
 }
 
-// Calls the entry point `name`.
-template <class F, class... Args>
-mxfp4_status launch(const char *name, F f, Args... args)
+// Allocates what the caller did not give and calls the entry point `name` through f, without the interpreter lock.
+template <class F>
+mxfp4_status launch(const char *name, Output (&out)[2], const at::Tensor &like, F &&f)
 {
     const mxfp4_status st = [&] {
         Unlocked u;
-        return f(args...);
+        for (Output &o : out)
+            if (!o.given)
+                o.t = new_tensor(at::IntArrayRef(o.shape, o.dims), o.type, like, o.zero);
+        return f();
     }();
     if (st == MXFP4_ERR_LAUNCH)
         throw LaunchFailed{name, st};
@@ -204,7 +231,7 @@ mxfp4_status launch(const char *name, F f, Args... args)
 // x, x_scale, gather_idx, q, sf, ld_q, ld_sf, stream
 PyObject *quant_from_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 8, n == 8 ? a[7] : Py_None, [&](Output *out) {
+    return call(n, 8, n == 8 ? a[7] : Py_None, [&](Output (&out)[2]) {
         const at::Tensor &x = tensor(a[0], at::kByte), &s = tensor(a[1], at::kFloat);
         int64_t M, K, ld[2];
         matrix(x, 128, &M, &K);
@@ -220,28 +247,29 @@ PyObject *quant_from_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
             idx = static_cast<const int32_t *>(g.data_ptr());
         }
         quant_outputs(a[3], a[4], a[5], a[6], x, rows, K, false, out, ld);
-        // A gather that may gain by memory to work in (smaller ones do not, whatever the library's rule) gets it from the allocator
-        // of the current stream, and gives it back there.
-        constexpr int64_t WORTH_ASKING = (int64_t)1 << 27; // elements of output
-        if (idx && rows < ((int64_t)1 << 31) && K < ((int64_t)1 << 31) && rows * K >= WORTH_ASKING) {
-            const int64_t size = lib.gather_workspace(M, K, rows, static_cast<uint8_t *>(out[0].data()), ld[0]);
-            if (size > 0) {
-                const at::Tensor work = output(Py_None, x, at::kByte, {size}, size).t;
-                return launch("mxfp4_quant_from_fp8_gather", lib.quant_gather, bytes_of(x), static_cast<const float *>(s.data_ptr()),
-                              M, K, idx, rows, static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()),
-                              ld[1], work.data_ptr(), size, current_stream(x));
+        return launch("mxfp4_quant_from_fp8", out, x, [&] {
+            const float *scale = static_cast<const float *>(s.data_ptr());
+            uint8_t *q = static_cast<uint8_t *>(out[0].data()), *sf = static_cast<uint8_t *>(out[1].data());
+            // A gather that may gain by memory to work in (smaller ones do not, whatever the library's rule) gets it from the
+            // allocator of the current stream, and gives it back there.
+            constexpr int64_t WORTH_ASKING = (int64_t)1 << 27; // elements of output
+            if (idx && rows < ((int64_t)1 << 31) && K < ((int64_t)1 << 31) && rows * K >= WORTH_ASKING) {
+                const int64_t size = lib.gather_workspace(M, K, rows, q, ld[0]);
+                if (size > 0) {
+                    const at::Tensor work = new_tensor({size}, at::kByte, x, false);
+                    return lib.quant_gather(bytes_of(x), scale, M, K, idx, rows, q, ld[0], sf, ld[1], work.data_ptr(), size,
+                                            current_stream(x));
+                }
             }
-        }
-        return launch("mxfp4_quant_from_fp8", lib.quant, bytes_of(x), static_cast<const float *>(s.data_ptr()), M, K, idx,
-                      rows, static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
-                      current_stream(x));
+            return lib.quant(bytes_of(x), scale, M, K, idx, rows, q, ld[0], sf, ld[1], current_stream(x));
+        });
     });
 }
 
 // x, x_scale, dst_idx, M_out, q, sf, ld_q, ld_sf, stream
 PyObject *quant_from_fp8_scatter(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 9, n == 9 ? a[8] : Py_None, [&](Output *out) {
+    return call(n, 9, n == 9 ? a[8] : Py_None, [&](Output (&out)[2]) {
         const at::Tensor &x = tensor(a[0], at::kByte), &s = tensor(a[1], at::kFloat), &d = tensor(a[2], at::kInt);
         int64_t M, K, fanout, rows, ld[2];
         matrix(x, 128, &M, &K);
@@ -253,32 +281,34 @@ PyObject *quant_from_fp8_scatter(PyObject *, PyObject *const *a, Py_ssize_t n)
         rows = stride_or(a[3], 0);
         need(rows > 0);
         quant_outputs(a[4], a[5], a[6], a[7], x, rows, K, true, out, ld);
-        return launch("mxfp4_quant_from_fp8_scatter", lib.scatter, bytes_of(x),
-                      static_cast<const float *>(s.data_ptr()), M, K,
-                      static_cast<const int32_t *>(d.data_ptr()), (int32_t)fanout, rows,
-                      static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
-                      current_stream(x));
+        return launch("mxfp4_quant_from_fp8_scatter", out, x, [&] {
+            return lib.scatter(bytes_of(x), static_cast<const float *>(s.data_ptr()), M, K,
+                               static_cast<const int32_t *>(d.data_ptr()), (int32_t)fanout, rows,
+                               static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
+                               current_stream(x));
+        });
     });
 }
 
 // x, q, sf, ld_q, ld_sf, stream
 PyObject *quant_from_bf16(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 6, n == 6 ? a[5] : Py_None, [&](Output *out) {
+    return call(n, 6, n == 6 ? a[5] : Py_None, [&](Output (&out)[2]) {
         const at::Tensor &x = tensor(a[0], at::kBFloat16);
         int64_t M, K, ld[2];
         matrix(x, 128, &M, &K);
         quant_outputs(a[1], a[2], a[3], a[4], x, M, K, false, out, ld);
-        return launch("mxfp4_quant_from_bf16", lib.quant_bf16, static_cast<const uint16_t *>(x.data_ptr()), M, K,
-                      static_cast<uint8_t *>(out[0].data()), ld[0], static_cast<uint8_t *>(out[1].data()), ld[1],
-                      current_stream(x));
+        return launch("mxfp4_quant_from_bf16", out, x, [&] {
+            return lib.quant_bf16(static_cast<const uint16_t *>(x.data_ptr()), M, K, static_cast<uint8_t *>(out[0].data()),
+                                  ld[0], static_cast<uint8_t *>(out[1].data()), ld[1], current_stream(x));
+        });
     });
 }
 
 // x, x_scale, expert_offsets, q, sf, stream
 PyObject *quant_from_fp8_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 6, n == 6 ? a[5] : Py_None, [&](Output *out) {
+    return call(n, 6, n == 6 ? a[5] : Py_None, [&](Output (&out)[2]) {
         const at::Tensor &x = tensor(a[0], at::kByte), &s = tensor(a[1], at::kFloat), &off = tensor(a[2], at::kInt);
         int64_t M, K, ld[2];
         matrix(x, 128, &M, &K);
@@ -286,17 +316,19 @@ PyObject *quant_from_fp8_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t E = experts(off, x);
         same_device(x, s);
         quant_outputs(a[3], a[4], Py_None, Py_None, x, M, K, false, out, ld);
-        return launch("mxfp4_quant_from_fp8_grouped", lib.quant_grouped, bytes_of(x),
-                      static_cast<const float *>(s.data_ptr()), static_cast<const int32_t *>(off.data_ptr()), (int32_t)E,
-                      M, K, static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()),
-                      current_stream(x));
+        return launch("mxfp4_quant_from_fp8_grouped", out, x, [&] {
+            return lib.quant_grouped(bytes_of(x), static_cast<const float *>(s.data_ptr()),
+                                     static_cast<const int32_t *>(off.data_ptr()), (int32_t)E, M, K,
+                                     static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()),
+                                     current_stream(x));
+        });
     });
 }
 
 // q, sf, M, K, ld_q, ld_sf, x, x_scale, stream
 PyObject *dequant_to_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 9, n == 9 ? a[8] : Py_None, [&](Output *out) {
+    return call(n, 9, n == 9 ? a[8] : Py_None, [&](Output (&out)[2]) {
         const at::Tensor &q = tensor(a[0], at::kByte), &sf = tensor(a[1], at::kByte);
         int64_t M, K, ld_q, ld_sf;
         same_device(q, sf);
@@ -319,8 +351,10 @@ PyObject *dequant_to_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
         }
         out[0] = output(a[6], q, at::kByte, {M, K}, M * K);
         out[1] = output(a[7], q, at::kFloat, {M, K / 128}, M * (K / 128) * 4);
-        return launch("mxfp4_dequant_to_fp8", lib.dequant, bytes_of(q), ld_q, bytes_of(sf), ld_sf, M, K,
-                      static_cast<uint8_t *>(out[0].data()), static_cast<float *>(out[1].data()), current_stream(q));
+        return launch("mxfp4_dequant_to_fp8", out, q, [&] {
+            return lib.dequant(bytes_of(q), ld_q, bytes_of(sf), ld_sf, M, K, static_cast<uint8_t *>(out[0].data()),
+                               static_cast<float *>(out[1].data()), current_stream(q));
+        });
     });
 }
 
@@ -336,31 +370,35 @@ inline void row_blocked(const at::Tensor &q, const at::Tensor &sf, int64_t *M, i
 // q_row, sf_row, q_col, sf_col, stream
 PyObject *row_to_col(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 5, n == 5 ? a[4] : Py_None, [&](Output *out) {
+    return call(n, 5, n == 5 ? a[4] : Py_None, [&](Output (&out)[2]) {
         const at::Tensor &q = tensor(a[0], at::kByte), &sf = tensor(a[1], at::kByte);
         int64_t M, K;
         row_blocked(q, sf, &M, &K);
         need(M % 32 == 0);
         out[0] = output(a[2], q, at::kByte, {K, M / 2}, K * (M / 2));
         out[1] = output(a[3], q, at::kByte, {K, M / 32}, K * (M / 32));
-        return launch("mxfp4_row_to_col", lib.row_to_col, bytes_of(q), bytes_of(sf), M, K,
-                      static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()), current_stream(q));
+        return launch("mxfp4_row_to_col", out, q, [&] {
+            return lib.row_to_col(bytes_of(q), bytes_of(sf), M, K, static_cast<uint8_t *>(out[0].data()),
+                                  static_cast<uint8_t *>(out[1].data()), current_stream(q));
+        });
     });
 }
 
 // q_row, sf_row, expert_offsets, q_col, sf_col, stream
 PyObject *row_to_col_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 6, n == 6 ? a[5] : Py_None, [&](Output *out) {
+    return call(n, 6, n == 6 ? a[5] : Py_None, [&](Output (&out)[2]) {
         const at::Tensor &q = tensor(a[0], at::kByte), &sf = tensor(a[1], at::kByte), &off = tensor(a[2], at::kInt);
         int64_t M, K;
         row_blocked(q, sf, &M, &K);
         const int64_t E = experts(off, q), n2 = K * (M / 2 + E), n32 = K * (M / 32 + E);
         out[0] = output(a[3], q, at::kByte, {n2}, n2);
         out[1] = output(a[4], q, at::kByte, {n32}, n32);
-        return launch("mxfp4_row_to_col_grouped", lib.row_to_col_grouped, bytes_of(q), bytes_of(sf),
-                      static_cast<const int32_t *>(off.data_ptr()), (int32_t)E, M, K,
-                      static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()), current_stream(q));
+        return launch("mxfp4_row_to_col_grouped", out, q, [&] {
+            return lib.row_to_col_grouped(bytes_of(q), bytes_of(sf), static_cast<const int32_t *>(off.data_ptr()), (int32_t)E,
+                                          M, K, static_cast<uint8_t *>(out[0].data()), static_cast<uint8_t *>(out[1].data()),
+                                          current_stream(q));
+        });
     });
 }
 
@@ -373,7 +411,7 @@ inline int flag(PyObject *o)
 // q_row, sf_row, x_col, x_col_scale, stream, requant
 PyObject *row_to_fp8_col(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 6, n == 6 ? a[4] : Py_None, [&](Output *out) {
+    return call(n, 6, n == 6 ? a[4] : Py_None, [&](Output (&out)[2]) {
         const int requant = flag(a[5]);
         const at::Tensor &q = tensor(a[0], at::kByte), &sf = tensor(a[1], at::kByte);
         int64_t M, K;
@@ -381,16 +419,17 @@ PyObject *row_to_fp8_col(PyObject *, PyObject *const *a, Py_ssize_t n)
         need(M % 128 == 0);
         out[0] = output(a[2], q, at::kByte, {K, M}, K * M);
         out[1] = output(a[3], q, at::kFloat, {K, M / 128}, K * (M / 128) * 4);
-        return launch(requant ? "mxfp4_row_to_fp8_col_requant" : "mxfp4_row_to_fp8_col", lib.fp8_col[requant], bytes_of(q),
-                      bytes_of(sf), M, K, static_cast<uint8_t *>(out[0].data()), static_cast<float *>(out[1].data()),
-                      current_stream(q));
+        return launch(requant ? "mxfp4_row_to_fp8_col_requant" : "mxfp4_row_to_fp8_col", out, q, [&] {
+            return lib.fp8_col[requant](bytes_of(q), bytes_of(sf), M, K, static_cast<uint8_t *>(out[0].data()),
+                                        static_cast<float *>(out[1].data()), current_stream(q));
+        });
     });
 }
 
 // q_row, sf_row, expert_offsets, x_col, x_col_scale, stream, requant
 PyObject *row_to_fp8_col_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return call(n, 7, n == 7 ? a[5] : Py_None, [&](Output *out) {
+    return call(n, 7, n == 7 ? a[5] : Py_None, [&](Output (&out)[2]) {
         const int requant = flag(a[6]);
         const at::Tensor &q = tensor(a[0], at::kByte), &sf = tensor(a[1], at::kByte), &off = tensor(a[2], at::kInt);
         int64_t M, K;
@@ -398,10 +437,11 @@ PyObject *row_to_fp8_col_grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t E = experts(off, q), n128 = K * (M / 128 + E);
         out[0] = output(a[3], q, at::kByte, {M * K}, M * K);
         out[1] = output(a[4], q, at::kFloat, {n128}, n128 * 4);
-        return launch(requant ? "mxfp4_row_to_fp8_col_requant_grouped" : "mxfp4_row_to_fp8_col_grouped",
-                      lib.fp8_col_grouped[requant], bytes_of(q), bytes_of(sf),
-                      static_cast<const int32_t *>(off.data_ptr()), (int32_t)E, M, K,
-                      static_cast<uint8_t *>(out[0].data()), static_cast<float *>(out[1].data()), current_stream(q));
+        return launch(requant ? "mxfp4_row_to_fp8_col_requant_grouped" : "mxfp4_row_to_fp8_col_grouped", out, q, [&] {
+            return lib.fp8_col_grouped[requant](bytes_of(q), bytes_of(sf), static_cast<const int32_t *>(off.data_ptr()),
+                                                (int32_t)E, M, K, static_cast<uint8_t *>(out[0].data()),
+                                                static_cast<float *>(out[1].data()), current_stream(q));
+        });
     });
 }
 

@@ -117,3 +117,41 @@ def test_refusals_still_raise_and_streams_are_kept():
     torch.cuda.synchronize()
     for r in (got, given):
         assert torch.equal(r[0], want[0]) and torch.equal(r[1], want[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["quant_from_fp8", "row_to_col_grouped"])
+def test_what_takes_part_in_factory_calls_still_does(name):
+    """New outputs are allocated past the dispatcher only where nothing else would happen there: dispatch modes see the
+    allocations, inference mode makes inference tensors, deterministic mode fills what the call does not write."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+    wrapper, args = arguments(DEV)[name]
+
+    class Seen(TorchDispatchMode):
+        def __init__(self):
+            super().__init__()
+            self.ops = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.ops.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    plain = wrapper(*args)
+    with Seen() as seen:
+        got = wrapper(*args)
+    assert sum("aten.empty" in op for op in seen.ops) == 2
+    with torch.inference_mode():
+        inference = wrapper(*args)
+    assert all(t.is_inference() for t in inference) and not any(t.is_inference() for t in plain)
+    before = torch.are_deterministic_algorithms_enabled()
+    torch.use_deterministic_algorithms(True)
+    try:
+        filled = wrapper(*args)
+    finally:
+        torch.use_deterministic_algorithms(before)
+    n = [t.numel() for t in plain]
+    if name == "row_to_col_grouped":  # the outputs are upper bounds: 256 rows in three experts, the middle one empty
+        n = [K * M // 2, K * M // 32]
+        assert all(bool((t.view(-1)[k:] == 255).all()) for t, k in zip(filled, n))
+    for other in (got, inference, filled):
+        assert all(torch.equal(a.view(-1)[:k], b.view(-1)[:k]) for a, b, k in zip(other, plain, n))
