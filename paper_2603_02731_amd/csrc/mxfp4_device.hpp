@@ -64,6 +64,14 @@ __device__ __forceinline__ uint32_t row_shift_left8(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x108 /* row_shl:8 */, 0xF, 0xF, true);
 }
 
+// Bytes that lanes of a wave exchange through its LDS: what is in front of this is done before what follows.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // NaN-propagating maximum of |a|, |b| and c.
 __device__ __forceinline__ float max3_abs_nan(float a, float b, float c)
 {

@@ -64,14 +64,6 @@ struct RowPieces {
     uint32_t sf_dword;         // rows whose scale bytes are not whole 16-byte pieces: this lane's dword of them
 };
 
-// Bytes that lanes of a wave exchange through its LDS: what is in front of this is done before what follows.
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Elements [k0, k0 + n) of the source row at src / src_scale; n is a multiple of 128, of 512 with WIDE_SF.
 // zero: the row of an index that names no source row.  Into the wave's LDS, and from there back as pieces.
 // PARTS: what is loaded at once is the whole segment, or a half of it where registers are short.
