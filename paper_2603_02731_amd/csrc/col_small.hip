@@ -1,14 +1,23 @@
-// Row-blocked MXFP4 -> column-blocked MXFP4 or column-wise FP8 of one small matrix, gfx950.
+// Row-blocked MXFP4 -> column-blocked MXFP4 or column-wise FP8 of a small matrix or of ragged experts, gfx950.
 //
 // The conversions of row_to_col.hip, row_to_fp8_col.hip and row_to_fp8_col_requant.hip for launches that do not fill the chip, which
 // last as long as one workgroup does: load, convert, turn round in LDS, store.  Here a lane takes 8 rows x 8 columns, a quarter of the
 // 32 x 8 slice of those kernels (the quarters of a slice in a quad of lanes, which exchange column maxima by DPP), a workgroup 128 x 128
 // elements, and there are four times as many of them.  MXFP4 needs one barrier, scale alignment two, re-quantization three.
-// Calls in a HIP graph, us (tiles of 256 x 256 / here): row->col [128,7168] 5.3 / 3.0, [2048,2048] 5.8 / 3.6; alignment 5.3 / 3.1 and
-// 6.3 / 3.7, re-quantization 6.1 / 4.2 and 6.9 / 4.8; of either about 2 are the launch.  A byte load per row scale instead of a dword
-// per row turned round in LDS 3.2 and 3.8, nibbles through LDS by 16-byte loads 3.2 and 3.8.
+// Calls in a HIP graph, us (tiles of 256 x 256 / here): row->col [128,7168] 5.0 / 2.6, [2048,2048] 5.3 / 3.2, [5120,2048] 6.1 / 4.6;
+// alignment 5.0 / 2.8, 6.1 / 3.5 and 6.5 / 5.1, re-quantization 5.8 / 3.2, 6.8 / 4.0 and 7.2 / 5.9; of either about 2 are the launch.
+// With every byte from and to HBM [2048,2048] 6.0 / 3.7, 6.3 / 4.0 and 7.0 / 4.6.  A byte load per row scale instead of a dword per row
+// turned round in LDS 0.2 more, nibbles through LDS by 16-byte loads 0.2 more.  The XCDs take contiguous runs of tiles, row tile by row
+// tile, so that neighbours along k, which share 128-byte lines of the nibbles, are in one L2 ([5120,2048] 5.6 -> 4.7; ids as they come
+// deal them to eight).
+// Ragged experts: the same tiles of every expert, rows that the last one does not have as zeros under scale byte 0.  They save half of
+// what the larger tiles spend on last ones and the look-back rows of row_to_fp8_col_grouped.hip, and leave by 16-byte stores at any byte:
+// [4436,1152] in 16 experts, not padded, 6.8 / 4.4, 8.7 / 5.0 and 10.0 / 5.8, [17315,1024] in 128 13.1 / 9.2, 14.1 / 10.6 and 16.4 / 11.3.
 // What a tile costs beside its elements (addresses, half lines, scales four or one at a time) is four times as much too, so where
-// workgroups queue up this is up to twice as slow ([4096,7168] 9.6 / 12.7): col_in_small_tiles.
+// workgroups queue up this is slower ([4096,7168], every byte from and to HBM, 10.2 / 14.6): col_in_small_tiles.
+// Not kept: plain loads, which leave the matrix in the memory-side cache for another pass over it ([8192,7168] of three in turn 25.4 ->
+// 13.5, but 25.1 where every byte comes from HBM, where the larger tiles take 18.0; [2048,2048] 3.7 -> 4.5); 256 x 128, 128 x 256 and
+// 256 x 256 elements with as many lanes as here per element ([2048,2048] 3.3 -> 3.7, 3.8 and 4.6, [4096,7168] no better).
 #include "fp8_col_tile.hpp"
 #include "mxfp4_device.hpp"
 #include "mxfp4_kernels.hpp"
@@ -18,15 +27,19 @@ namespace col_small {
 
 using namespace fp8col;
 
-constexpr uint32_t THREADS = 256, TILE = 128;
+constexpr uint32_t THREADS = 256, TILE = 128, MBM_MAX = 64;
+constexpr int EXPERTS_MAX = 256; // the lookup of more takes registers that cost a third of the waves
 
 struct Args {
     const uint8_t *q_row;
     const uint8_t *sf_row;
     uint8_t *out;
     void *out_sf; // bytes (MXFP4) or floats
+    const int32_t *expert_offsets; // nullptr: one matrix of M rows
+    int32_t num_experts;
     uint32_t M, K;
-    uint32_t tiles_m, tiles_k;
+    uint32_t tiles_m, tiles_k; // tiles_m: of one matrix
+    FastDiv by_tiles_k;
 };
 
 template <class T, class F>
@@ -43,7 +56,7 @@ __device__ __forceinline__ float scale_operand(uint32_t b) { return u2f(b << 23)
 
 using namespace col_small;
 
-template <ColKind KIND>
+template <ColKind KIND, bool EXPERTS>
 __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Args a)
 {
     // The tile's output: column 8 cg + c is LDS row c * 16 + cg, so that what the lanes of a wave write at once lies on different banks.
@@ -54,9 +67,37 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
     __shared__ uint16_t s_max[4][4]; // [32 rows][k-block]: largest scale byte that is not NaN; bit 8: one of FROM or more, 9: a NaN
     __shared__ alignas(16) uint32_t s_amax[KIND == COL_REQUANT ? 4 : 1][TILE]; // [32 rows][column]: bits of the largest |value|, or Emax + 1
 
-    const uint32_t tile_k = blockIdx.x % a.tiles_k, tile_m = blockIdx.x / a.tiles_k;
+    // ---- the tile; of which rows, and where their outputs begin
+    uint32_t tile_k, tile_m, rows = a.M, groups = a.tiles_m, row_base = 0;
+    uint8_t *out = a.out;
+    uint8_t *out_sf8 = static_cast<uint8_t *>(a.out_sf);
+    uint32_t *out_sf32 = static_cast<uint32_t *>(a.out_sf);
+    if (EXPERTS) {
+        ExpertTile t;
+        constexpr uint32_t UNIT_A = KIND == COL_MXFP4 ? 2 : 0, UNIT_B = KIND == COL_MXFP4 ? 32 : TILE;
+        const uint32_t n = (uint32_t)a.num_experts;
+        if (!(n <= 64u ? expert_tile<1, TILE, UNIT_A, UNIT_B, MBM_MAX>(a.expert_offsets, n, blockIdx.x, a.tiles_k, a.by_tiles_k, &t)
+                       : expert_tile<EXPERTS_MAX / 64, TILE, UNIT_A, UNIT_B, MBM_MAX>(a.expert_offsets, n, blockIdx.x, a.tiles_k,
+                                                                                      a.by_tiles_k, &t)))
+            return;
+        tile_m = t.tile_m;
+        tile_k = t.tile_k;
+        row_base = t.row_base;
+        rows = t.rows;
+        groups = (rows + TILE - 1u) / TILE;
+        out += (size_t)a.K * (KIND == COL_MXFP4 ? t.a_before : row_base);
+        out_sf8 += (size_t)a.K * t.b_before;
+        out_sf32 += (size_t)a.K * t.b_before;
+    } else {
+        uint32_t entry;
+        if (!order_entry_of_workgroup(blockIdx.x, a.tiles_m * a.tiles_k, &entry))
+            return;
+        tile_m = a.tiles_k == 1u ? entry : a.by_tiles_k(entry);
+        tile_k = entry - tile_m * a.tiles_k;
+    }
     const uint32_t m0 = tile_m * TILE, k0 = tile_k * TILE;
-    const uint32_t n_rg = min(4u, (a.M - m0) / 32u); // whole blocks of 32 rows; all four for FP8
+    const uint32_t n_rows = min(TILE, rows - m0); // 1..128; of one matrix whole blocks of 32, 128 for FP8
+    const uint32_t n_rg = EXPERTS ? (n_rows + 31u) / 32u : n_rows / 32u;
     const uint32_t tid = threadIdx.x;
     const uint32_t sub = tid & 3u, cg = tid >> 2 & 15u, rg = tid >> 6; // rows 32 rg + 8 sub, columns 8 cg of the tile
     const uint32_t pitch = a.K / 2u, Kb = a.K / 32u, kb = cg >> 2;
@@ -64,17 +105,31 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
     // ---- the lane's 8 x 8 elements and its 8 row-scale bytes
     uint32_t w[8], b[8];
     {
-        const uint32_t row0 = rg < n_rg ? rg * 32u : 0u; // past the end: any rows, not stored
-        const uint8_t *src = a.q_row + (size_t)m0 * pitch + k0 / 2u;
+        const uint8_t *src = a.q_row + (size_t)(row_base + m0) * pitch + k0 / 2u;
+        const uint8_t *src_sf = a.sf_row + (size_t)(row_base + m0) * Kb + k0 / 32u;
         const uint32_t lane = tid & 63u;
         uint32_t sf = 0;
-        if (lane < 32u)
-            sf = *reinterpret_cast<const uint32_t *>(a.sf_row + (size_t)m0 * Kb + k0 / 32u + (row0 + lane) * Kb);
         // uniform row pointers plus a 32-bit lane offset (K is at most 2^24)
-        const uint32_t at = (row0 + sub * 8u) * pitch + cg * 4u;
+        if (!EXPERTS || n_rows == TILE) {
+            const uint32_t row0 = rg < n_rg ? rg * 32u : 0u; // past the end: any rows, not stored
+            if (lane < 32u)
+                sf = *reinterpret_cast<const uint32_t *>(src_sf + (row0 + lane) * Kb);
+            const uint32_t at = (row0 + sub * 8u) * pitch + cg * 4u;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            w[i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(src + (size_t)i * pitch + at));
+            for (int i = 0; i < 8; ++i)
+                w[i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(src + (size_t)i * pitch + at));
+        } else { // rows that an expert does not have are zeros under scale byte 0 (read from its last row, then cleared)
+            const uint32_t row0 = rg * 32u, first = row0 + sub * 8u;
+            if (row0 + lane < min(row0 + 32u, n_rows))
+                sf = *reinterpret_cast<const uint32_t *>(src_sf + (row0 + lane) * Kb);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                w[i] = __builtin_nontemporal_load(
+                    reinterpret_cast<const uint32_t *>(src + min(first + i, n_rows - 1u) * pitch + cg * 4u));
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                w[i] = first + i < n_rows ? w[i] : 0u;
+        }
         // four rows' bytes of four k-blocks, turned round in the quad
         uint32_t t = perm(dpp_read<DPP_QUAD_XOR1>(sf), sf, (lane & 1u) ? 0x03070105u : 0x06020400u);
         t = perm(dpp_read<DPP_QUAD_XOR2>(t), t, (lane & 2u) ? 0x03020706u : 0x05040100u);
@@ -93,8 +148,8 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
 
     if (KIND == COL_MXFP4) {
         largest = quad_reduce(largest, [](uint32_t x, uint32_t y) { return max(x, y); });
-        uint32_t cb[8], o[8];
         if (largest < 253u) {
+            uint32_t cb[8], o[8];
             float amax[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c)
@@ -115,6 +170,11 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                 cb[c] = max(f2u(m) >> 23, 2u) - 2u;
                 asm volatile("" : "=v"(o[c])); // no initial value needed: all four bytes are written
             }
+            if (EXPERTS) { // decode again rather than keep 64 values: 47 registers for 82, the waves of a compute unit are not bound by them
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    asm volatile("" : "+v"(w[i]));
+            }
             static_for<4>([&](auto ip) {
                 constexpr int sel = decltype(ip)::value, i = 2 * sel;
                 static_for<4>([&](auto jp) {
@@ -126,10 +186,18 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                         __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(o[2 * j + 1], fa.y, fb.y, scale_operand(cb[2 * j + 1]), sel);
                 });
             });
-        } else {
-            // values beyond FP32, or NaN: in integers, as column_byte_int and column_codes_int
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
+            for (int c = 0; c < 8; ++c)
+                *reinterpret_cast<uint32_t *>(s_out + (c * 16u + cg) * ROW + rg * 16u + sub * 4u) = o[c];
+            if (sub == 0u) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    s_sf[c * 16u + cg][rg] = (uint8_t)cb[c];
+            }
+        } else {
+            // values beyond FP32, or NaN: in integers, as column_byte_int and column_codes_int (rolled: written for size)
+#pragma nounroll
+            for (uint32_t c = 0; c < 8u; ++c) {
                 int emax = -1024;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
@@ -137,30 +205,25 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                     emax = mag ? max(emax, (int)b[i] + (mag >> 1)) : emax;
                 }
                 emax = quad_reduce(emax, [](int x, int y) { return max(x, y); });
-                cb[c] = largest == 255u ? 255u : (uint32_t)max(0, emax - 3);
-                o[c] = 0u;
+                const uint32_t cb = largest == 255u ? 255u : (uint32_t)max(0, emax - 3);
+                uint32_t o = 0u;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const uint32_t nib = (w[i] >> (4 * c)) & 0xFu;
                     const int mag = (int)(nib & 7u), em = mag == 1 ? 0 : mag;
-                    const int t2 = max(em + 2 * ((int)b[i] - (int)cb[c]) + 2, 0);
+                    const int t2 = max(em + 2 * ((int)b[i] - (int)cb) + 2, 0);
                     const int code = mag ? min(7, max(t2 - 2, (t2 + 1) >> 1)) : 0;
                     if (largest != 255u)
-                        o[c] |= ((nib & 8u) | (uint32_t)code) << (4 * i);
+                        o |= ((nib & 8u) | (uint32_t)code) << (4 * i);
                 }
+                *reinterpret_cast<uint32_t *>(s_out + (c * 16u + cg) * ROW + rg * 16u + sub * 4u) = o;
+                if (sub == 0u)
+                    s_sf[c * 16u + cg][rg] = (uint8_t)cb;
             }
-        }
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-            *reinterpret_cast<uint32_t *>(s_out + (c * 16u + cg) * ROW + rg * 16u + sub * 4u) = o[c];
-        if (sub == 0u) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                s_sf[c * 16u + cg][rg] = (uint8_t)cb[c];
         }
     } else {
         auto out_scale = [&](uint32_t column, uint32_t bits) {
-            static_cast<uint32_t *>(a.out_sf)[(size_t)(k0 + column) * a.tiles_m + tile_m] = bits;
+            out_sf32[(size_t)(k0 + column) * groups + tile_m] = bits;
         };
         // ---- the scale group's largest scale byte, NaN apart, and whether a byte of FROM or more occurs
         constexpr uint32_t FROM = KIND == COL_ALIGN ? 255u : 253u;
@@ -182,8 +245,8 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
             flags |= m >> 8;
         }
         const uint32_t scales = rg * 4u + sub; // lanes 0 to 7 that share 8 columns store a column's scale each
-        uint32_t o[8][2];
         if (KIND == COL_ALIGN) {
+            uint32_t o[8][2];
             if (scales < 8u) {
                 const int e = (int)bmax - 6; // biased exponent of 2^(max - 6 - 127); below 1: an FP32 subnormal
                 const uint32_t bits = flags ? 0x7FC00000u : e >= 1 ? (uint32_t)e << 23 : 0x00400000u >> (uint32_t)(-e);
@@ -216,12 +279,11 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                     o[2 * j + 1][r] = (__builtin_bit_cast(uint32_t, e1) & ~nan[r]) | (0x7F7F7F7Fu & nan[r]);
                 });
             });
-        } else {
-            // ---- the group's largest value of every column: its FP32 bits, or Emax where those do not do
-            uint32_t m[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                m[c] = 0u;
+                *reinterpret_cast<u32x2 *>(s_out + (c * 16u + cg) * ROW + rg * 32u + sub * 8u) = u32x2{o[c][0], o[c][1]};
+        } else {
+            // ---- the group's largest value of every column: its FP32 bits, or Emax where those do not do
             if (flags == 0u) {
                 float amax[8];
 #pragma unroll
@@ -237,28 +299,35 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                         amax[2 * j + 1] = max3_abs_nan(fa.y, fb.y, amax[2 * j + 1]);
                     });
                 });
+                uint32_t m[8];
 #pragma unroll
                 for (int c = 0; c < 8; ++c)
                     m[c] = f2u(quad_reduce(amax[c], [](float x, float y) { return __builtin_elementwise_maximum(x, y); }));
+                if (sub == 0u) {
+                    u32x4 *dst = reinterpret_cast<u32x4 *>(s_amax[rg] + cg * 8u);
+                    dst[0] = u32x4{m[0], m[1], m[2], m[3]};
+                    dst[1] = u32x4{m[4], m[5], m[6], m[7]};
+                }
             } else {
-                // Emax + 1 over the non-zero codes of rows whose scale byte is not NaN, 0 without any
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
+                // Emax + 1 over the non-zero codes of rows whose scale byte is not NaN, 0 without any (rolled: written for size)
+#pragma nounroll
+                for (uint32_t c = 0; c < 8u; ++c) {
                     uint32_t e = 0;
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         const uint32_t mag = (w[i] >> (4 * c)) & 7u;
                         e = mag && b[i] != 255u ? max(e, b[i] + (mag >> 1) + 1u) : e;
                     }
-                    m[c] = quad_reduce(e, [](uint32_t x, uint32_t y) { return max(x, y); });
+                    e = quad_reduce(e, [](uint32_t x, uint32_t y) { return max(x, y); });
+                    if (sub == 0u)
+                        s_amax[rg][cg * 8u + c] = e;
                 }
             }
-            if (sub == 0u) {
-                u32x4 *dst = reinterpret_cast<u32x4 *>(s_amax[rg] + cg * 8u);
-                dst[0] = u32x4{m[0], m[1], m[2], m[3]};
-                dst[1] = u32x4{m[4], m[5], m[6], m[7]};
-            }
             __syncthreads();
+            uint32_t m[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                m[c] = 0u;
 #pragma unroll
             for (uint32_t g = 0; g < 4u; ++g) {
                 const u32x4 *p = reinterpret_cast<const u32x4 *>(s_amax[g] + cg * 8u);
@@ -270,22 +339,21 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                 }
             }
             bool slow = flags != 0u;
-            int emax[8];
             float enc[8];
-            uint32_t mine = 0; // the scale that this lane stores
+            uint32_t mine = 0; // the maximum of the column whose scale this lane stores
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const bool zero = m[c] == 0u;
-                emax[c] = flags != 0u ? (int)m[c] - 1 : zero ? -1 : emax_of_amax_bits(m[c]);
                 const uint32_t ef = m[c] >> 23;
                 slow |= flags == 0u && !zero && ef < 8u; // a maximum below 2^-118: operand exponent negative
                 enc[c] = u2f((zero ? 127u : ef - 8u) << 23);
-                const uint32_t bits = (flags & 2u) ? 0x7FC00000u : scale_bits_of_emax(emax[c], !zero);
-                mine = scales == (uint32_t)c ? bits : mine;
+                mine = scales == (uint32_t)c ? m[c] : mine;
             }
+            auto emax_of = [&](uint32_t v) { return flags != 0u ? (int)v - 1 : v == 0u ? -1 : emax_of_amax_bits(v); };
             if (scales < 8u)
-                out_scale(cg * 8u + scales, mine);
+                out_scale(cg * 8u + scales, (flags & 2u) ? 0x7FC00000u : scale_bits_of_emax(emax_of(mine), mine != 0u));
             if (!slow) {
+                uint32_t o[8][2];
                 static_for<4>([&](auto jp) {
                     constexpr int j = decltype(jp)::value;
                     static_for<2>([&](auto rp) {
@@ -304,38 +372,54 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                         o[2 * j + 1][r] = __builtin_bit_cast(uint32_t, e1);
                     });
                 });
-            } else {
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    o[c][0] = o[c][1] = 0u;
+                for (int c = 0; c < 8; ++c)
+                    *reinterpret_cast<u32x2 *>(s_out + (c * 16u + cg) * ROW + rg * 32u + sub * 8u) = u32x2{o[c][0], o[c][1]};
+            } else {
+#pragma nounroll
+                for (uint32_t c = 0; c < 8u; ++c) {
+                    uint32_t v = 0u;
+#pragma unroll
+                    for (uint32_t g = 0; g < 4u; ++g)
+                        v = max(v, s_amax[g][cg * 8u + c]);
+                    const int emax = emax_of(v);
+                    u32x2 r = {0u, 0u};
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         const uint32_t nib = (w[i] >> (4 * c)) & 0xFu;
-                        const uint32_t v = b[i] == 255u ? 0x7Fu : e4m3_requant_int(nib, b[i], emax[c]);
-                        o[c][i >> 2] |= v << (8 * (i & 3));
+                        r[i >> 2] |= (b[i] == 255u ? 0x7Fu : e4m3_requant_int(nib, b[i], emax)) << (8 * (i & 3));
                     }
+                    *reinterpret_cast<u32x2 *>(s_out + (c * 16u + cg) * ROW + rg * 32u + sub * 8u) = r;
                 }
             }
         }
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-            *reinterpret_cast<u32x2 *>(s_out + (c * 16u + cg) * ROW + rg * 32u + sub * 8u) = u32x2{o[c][0], o[c][1]};
     }
     __syncthreads();
 
-    // ---- out: 16-byte pieces
+    // ---- out: 16-byte pieces.  The k-rows of an expert begin at any byte and end in any piece
     constexpr uint32_t PIECES = BYTES / 16u;
-    const uint32_t pitch_out = KIND == COL_MXFP4 ? a.M / 2u : a.M;
+    const uint32_t pitch_out = KIND == COL_MXFP4 ? (rows + 1u) / 2u : rows, nb = KIND == COL_MXFP4 ? (n_rows + 1u) / 2u : n_rows;
+    // Stores are non-temporal where a tile's pieces are whole 64-byte segments ([2048,2048] with every byte from and to HBM, alignment
+    // 5.1 -> 4.0 us), but for MXFP4 of experts, where that gains below 1024 tiles what it loses above (1152 tiles 7.3 -> 8.4).
+    const bool segments = ((reinterpret_cast<uintptr_t>(out) | pitch_out) & 63u) == 0u;
 #pragma unroll
     for (uint32_t u = 0; u < TILE * PIECES / THREADS; ++u) {
         const uint32_t i = u * THREADS + tid, column = i / PIECES, p = i % PIECES;
-        if (KIND != COL_MXFP4 || p < n_rg)
-            *reinterpret_cast<u32x4 *>(a.out + (size_t)(k0 + column) * pitch_out + (KIND == COL_MXFP4 ? m0 / 2u : m0) + p * 16u) =
-                *reinterpret_cast<const u32x4 *>(s_out + ((column & 7u) * 16u + (column >> 3)) * ROW + p * 16u);
+        uint8_t *dst = out + (size_t)(k0 + column) * pitch_out + (KIND == COL_MXFP4 ? m0 / 2u : m0) + p * 16u;
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(s_out + ((column & 7u) * 16u + (column >> 3)) * ROW + p * 16u);
+        if (!EXPERTS) {
+            if (KIND != COL_MXFP4 || p < n_rg)
+                __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
+        } else if (KIND != COL_MXFP4 && segments && p * 16u + 16u <= nb) {
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
+        } else if (p * 16u + 16u <= nb) {
+            *reinterpret_cast<u32x4_unaligned *>(dst) = v;
+        } else if (p * 16u < nb) {
+            store_head_bytes(dst, v, nb - p * 16u);
+        }
     }
     if (KIND == COL_MXFP4 && tid < TILE) {
-        const uint32_t pitch_sf = a.M / 32u;
-        uint8_t *dst = static_cast<uint8_t *>(a.out_sf) + (size_t)(k0 + tid) * pitch_sf + m0 / 32u;
+        uint8_t *dst = out_sf8 + (size_t)(k0 + tid) * ((rows + 31u) / 32u) + m0 / 32u;
         const uint32_t v = *reinterpret_cast<const uint32_t *>(s_sf[(tid & 7u) * 16u + (tid >> 3)]);
         if (n_rg == 4u)
             *reinterpret_cast<u32_unaligned *>(dst) = v;
@@ -344,35 +428,69 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
     }
 }
 
-// Which matrices: two tiles per compute unit, a little more where a tile is shorter work.  On both sides of the lines, 256 compute units
-// (us, tiles of 256 x 256 / small ones): row->col 640 tiles 6.40 / 5.59 [5120,2048] and 6.15 / 5.79 [20480,512], 704 tiles 6.42 / 5.77,
-// 768 tiles 6.28 / 6.27 and 6.69 / 6.45, 896 tiles 7.19 / 7.50; alignment 576 tiles 6.89 / 6.44 and 6.75 / 6.52, 640 tiles 6.86 / 6.92
-// and 7.21 / 6.76, 768 tiles 6.86 / 7.54; re-quantization 512 tiles 7.48 / 6.67 and 7.01 / 6.78, 576 tiles 7.67 / 7.72 and 7.48 / 8.04.
-bool col_in_small_tiles(int64_t M, int64_t K, ColKind kind)
+// Which matrices: about three tiles per compute unit.  On both sides of the lines, 256 compute units (us, tiles of 256 x 256 / small ones,
+// with every byte from and to HBM, and of three matrices in turn): row->col 704 tiles 6.89 / 6.89 and 6.19 / 5.08 [2816,4096], 6.55 / 5.66
+// and 6.11 / 4.55 [22528,512], 768 tiles 6.99 / 7.22 and 6.35 / 5.23 [3072,4096], 896 tiles 7.07 / 8.68 and 6.35 / 6.46; alignment 704
+// tiles 7.29 / 7.30 and 6.63 / 5.28, 7.00 / 6.19 and 6.50 / 5.07, 896 tiles 7.63 / 9.20 and 6.80 / 8.06; re-quantization 768 tiles
+// 8.07 / 7.30 and 7.39 / 6.29, 896 tiles 8.35 / 8.79 and 7.60 / 7.07.
+//
+// Which experts, by the number of tiles that their splits are expected to have (each ends in half a tile): the larger tiles waste more on
+// last ones, and in what splits at any row make of the k-rows, so that the lines lie higher.  Row->col [8192,2048] in 8 12.2 / 9.5 and
+// 10.1 / 8.0 (1088 tiles), [8192,4096] in 32 16.5 / 15.5 and 15.6 / 15.0 (2560), but [16384,2048] in 4 15.9 / 16.5 and 14.5 / 15.1 (2080);
+// alignment [8192,2048] in 8 12.7 / 10.5 and 11.5 / 9.6, [8192,2048] in 64 15.1 / 10.8 and 13.3 / 10.2 (1536), [16384,2048] in 4 16.8 /
+// 19.7 and 14.6 / 18.5 (2080); re-quantization 15.7 / 11.6 and 14.4 / 10.1, 21.4 / 11.6 and 20.5 / 11.0, [16384,2048] in 16 19.4 / 18.7
+// and 17.4 / 17.5 (2176).  A total of whole groups of 128 rows may be that of padded splits, which waste less: row->col [18432,1024] in 32
+// 9.1 / 8.1 and 8.0 / 7.0 (1280), [17408,2048] in 16 12.0 / 13.4 and 10.7 / 12.7 (2304); alignment [18432,1024] in 32 10.0 / 8.9 and 8.9 /
+// 8.6, [16512,2048] in 4 14.4 / 16.8 and 11.8 / 16.1 (2096); re-quantization [11392,1024] in 64 9.4 / 6.4 and 8.5 / 6.3 (968),
+// [8704,2048] in 8 10.6 / 9.4 and 9.3 / 8.0 (1152), [16512,2048] in 4 17.3 / 16.9 and 16.0 / 16.2.  Splits of less than 256 rows on the
+// average have no whole tile of the larger kind: [17392,2048] in 128 row->col 19.9 / 15.3 and 18.7 / 14.4, alignment 23.4 / 19.6 and
+// 18.8 / 18.4, re-quantization 25.8 / 20.2 and 21.1 / 18.9 (3184); padded, [11392,2048] in 64 11.1 / 9.0 and 9.9 / 8.3, 12.3 / 10.7 and
+// 11.0 / 10.6, 13.7 / 10.2 and 12.5 / 10.1 (1936), [16640,2048] in 128 12.5 / 12.2 and 10.8 / 11.9, 16.7 / 17.2 and 14.5 / 16.0 (3104).
+bool col_in_small_tiles(int64_t M, int64_t K, int32_t num_experts, ColKind kind)
 {
-    const int64_t tiles = (M + TILE - 1) / TILE * (K / TILE), quarters = kind == COL_MXFP4 ? 11 : kind == COL_ALIGN ? 9 : 8;
-    return 4 * tiles <= quarters * (int64_t)compute_units();
+    const int64_t units = compute_units(), tiles_k = K / TILE;
+    if (num_experts == 0)
+        return 4 * ((M + TILE - 1) / TILE * tiles_k) <= (kind == COL_REQUANT ? 12 : 11) * units;
+    if (num_experts > EXPERTS_MAX)
+        return false;
+    const bool padded = M % 128 == 0;
+    const int64_t half_tiles = (2 * (M / TILE) + num_experts) * tiles_k;
+    if (M < 256 * (int64_t)num_experts)
+        return half_tiles <= (padded ? 15 : 24) * units;
+    return half_tiles <= (!padded ? (kind == COL_MXFP4 ? 14 : 12) : kind == COL_REQUANT ? 8 : 10) * units;
 }
 
-hipError_t launch_col_small(const uint8_t *q_row, const uint8_t *sf_row, int64_t M, int64_t K, uint8_t *out, void *out_sf, ColKind kind,
-                            hipStream_t stream)
+template <bool EXPERTS>
+static void launch_kind(const col_small::Args &a, uint32_t tiles, ColKind kind, hipStream_t stream)
+{
+    const dim3 grid((tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD);
+    if (kind == COL_MXFP4)
+        hipLaunchKernelGGL((col_small_kernel<COL_MXFP4, EXPERTS>), grid, dim3(THREADS), 0, stream, a);
+    else if (kind == COL_ALIGN)
+        hipLaunchKernelGGL((col_small_kernel<COL_ALIGN, EXPERTS>), grid, dim3(THREADS), 0, stream, a);
+    else
+        hipLaunchKernelGGL((col_small_kernel<COL_REQUANT, EXPERTS>), grid, dim3(THREADS), 0, stream, a);
+}
+
+hipError_t launch_col_small(const uint8_t *q_row, const uint8_t *sf_row, const int32_t *expert_offsets, int32_t num_experts, int64_t M,
+                            int64_t K, uint8_t *out, void *out_sf, ColKind kind, hipStream_t stream)
 {
     col_small::Args a;
     a.q_row = q_row;
     a.sf_row = sf_row;
     a.out = out;
     a.out_sf = out_sf;
+    a.expert_offsets = expert_offsets;
+    a.num_experts = num_experts;
     a.M = (uint32_t)M;
     a.K = (uint32_t)K;
     a.tiles_m = (uint32_t)((M + TILE - 1) / TILE);
     a.tiles_k = (uint32_t)(K / TILE);
-    const dim3 grid(a.tiles_m * a.tiles_k);
-    if (kind == COL_MXFP4)
-        hipLaunchKernelGGL(col_small_kernel<COL_MXFP4>, grid, dim3(THREADS), 0, stream, a);
-    else if (kind == COL_ALIGN)
-        hipLaunchKernelGGL(col_small_kernel<COL_ALIGN>, grid, dim3(THREADS), 0, stream, a);
+    a.by_tiles_k = FastDiv(a.tiles_k);
+    if (expert_offsets) // every expert may end in part of a tile
+        launch_kind<true>(a, (a.tiles_m + (uint32_t)num_experts) * a.tiles_k, kind, stream);
     else
-        hipLaunchKernelGGL(col_small_kernel<COL_REQUANT>, grid, dim3(THREADS), 0, stream, a);
+        launch_kind<false>(a, a.tiles_m * a.tiles_k, kind, stream);
     return hipGetLastError();
 }
 

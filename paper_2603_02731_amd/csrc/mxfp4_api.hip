@@ -207,7 +207,8 @@ static mxfp4_status row_to_fp8_col_common(const uint8_t *q_row, const uint8_t *s
         (expert_offsets && !aligned(expert_offsets, 4)))
         return MXFP4_ERR_ALIGN;
     const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (expert_offsets && mxfp4::fp8_col_in_segments(M, K, num_experts, requant))
+    if (expert_offsets && !mxfp4::col_in_small_tiles(M, K, num_experts, requant ? mxfp4::COL_REQUANT : mxfp4::COL_ALIGN) &&
+        mxfp4::fp8_col_in_segments(M, K, num_experts, requant))
         return launched(mxfp4::launch_row_to_fp8_col_grouped(q_row, sf_row, expert_offsets, num_experts, M, K, x_col,
                                                              x_col_scale, requant, stream));
     return launched(requant ? mxfp4::launch_row_to_fp8_col_requant(q_row, sf_row, expert_offsets, num_experts, M, K,

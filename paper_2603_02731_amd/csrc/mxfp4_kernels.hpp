@@ -54,12 +54,12 @@ hipError_t launch_row_to_fp8_col_grouped(const uint8_t *q_row, const uint8_t *sf
                                          int32_t num_experts, int64_t M, int64_t K, uint8_t *x_col, float *x_col_scale,
                                          bool requant, hipStream_t stream);
 
-// The flat conversions of a small matrix, by smaller tiles: where col_in_small_tiles says so (M % 32 == 0, M % 128 == 0 for FP8).
+// The same conversions by smaller tiles: where col_in_small_tiles says so (one matrix: M % 32 == 0, M % 128 == 0 for FP8).
 // out_sf: bytes (MXFP4) or floats.
 enum ColKind { COL_MXFP4, COL_ALIGN, COL_REQUANT };
-bool col_in_small_tiles(int64_t M, int64_t K, ColKind kind);
-hipError_t launch_col_small(const uint8_t *q_row, const uint8_t *sf_row, int64_t M, int64_t K, uint8_t *out, void *out_sf, ColKind kind,
-                            hipStream_t stream);
+bool col_in_small_tiles(int64_t M, int64_t K, int32_t num_experts, ColKind kind); // num_experts 0: one matrix
+hipError_t launch_col_small(const uint8_t *q_row, const uint8_t *sf_row, const int32_t *expert_offsets, int32_t num_experts, int64_t M,
+                            int64_t K, uint8_t *out, void *out_sf, ColKind kind, hipStream_t stream);
 
 // Compute units of the current device (hipDeviceAttributeMultiprocessorCount, looked up once per device;
 // 256 if the runtime cannot say): launch heuristics are stated in tiles per compute unit.

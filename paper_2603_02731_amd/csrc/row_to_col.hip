@@ -418,8 +418,8 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
                              int32_t num_experts, int64_t M, int64_t K, uint8_t *q_col, uint8_t *sf_col,
                              hipStream_t stream)
 {
-    if (!expert_offsets && col_in_small_tiles(M, K, COL_MXFP4))
-        return launch_col_small(q_row, sf_row, M, K, q_col, sf_col, COL_MXFP4, stream);
+    if (col_in_small_tiles(M, K, expert_offsets ? num_experts : 0, COL_MXFP4))
+        return launch_col_small(q_row, sf_row, expert_offsets, num_experts, M, K, q_col, sf_col, COL_MXFP4, stream);
     if (!expert_offsets && row_to_col_in_segments(M, K))
         return launch_row_to_col_segments(q_row, sf_row, M, K, q_col, sf_col, stream);
     RowToColArgs a;

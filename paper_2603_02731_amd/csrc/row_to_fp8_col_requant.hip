@@ -326,8 +326,8 @@ hipError_t launch_row_to_fp8_col_requant(const uint8_t *q_row, const uint8_t *sf
                                          int32_t num_experts, int64_t M, int64_t K, uint8_t *x_col,
                                          float *x_col_scale, hipStream_t stream)
 {
-    if (!expert_offsets && col_in_small_tiles(M, K, COL_REQUANT))
-        return launch_col_small(q_row, sf_row, M, K, x_col, x_col_scale, COL_REQUANT, stream);
+    if (col_in_small_tiles(M, K, expert_offsets ? num_experts : 0, COL_REQUANT))
+        return launch_col_small(q_row, sf_row, expert_offsets, num_experts, M, K, x_col, x_col_scale, COL_REQUANT, stream);
     fp8col_requant::Args a;
     a.q_row = q_row;
     a.sf_row = sf_row;

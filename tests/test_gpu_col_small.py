@@ -1,17 +1,19 @@
-"""GPU parity of the flat transposing conversions of small matrices, on both sides of the rule that takes smaller tiles."""
+"""GPU parity of the transposing conversions of small matrices and of ragged experts, on both sides of the rule that takes
+smaller tiles."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2603_02731_amd as mx
-from oracle import parallel as par
+from oracle import parallel as par, ref
 from paper_2603_02731_amd import synth
+from tests.test_gpu_fp8_col_segments import SPLITS
 from tests.test_gpu_parity import DEV, assert_same, host
 
 pytestmark = pytest.mark.gpu
 
 UNITS = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
-KINDS = {"mxfp4": 11, "align": 9, "requant": 8}  # quarters of a compute unit's tiles up to which tiles are small
+KINDS = {"mxfp4": 11, "align": 11, "requant": 12}  # quarters of a compute unit's tiles up to which tiles are small
 
 
 def convert(kind, q, sf):
@@ -72,3 +74,77 @@ def test_sides_of_the_rule(kind, over):
     check(kind, q, sf, f"{kind} {tiles} tiles")
     q, sf = synth.random_mxfp4(128, 128 * tiles, seed=tiles, scale_spread=9, nan_scale_frac=0.001, device=DEV)
     check(kind, q, sf, f"{kind} {tiles} tiles beside each other")
+
+
+def half_tiles(rows, K):
+    """Twice the number of 128 x 128 tiles that splits of these total rows are expected to have, as the rule counts them."""
+    return (2 * (sum(rows) // 128) + len(rows)) * (K // 128)
+
+
+def limit(kind, rows):
+    """Half tiles up to which experts go by small ones."""
+    padded = sum(rows) % 128 == 0
+    if sum(rows) < 256 * len(rows):
+        return (15 if padded else 24) * UNITS
+    return ({"mxfp4": 10, "align": 10, "requant": 8}[kind] if padded else {"mxfp4": 14, "align": 12, "requant": 12}[kind]) * UNITS
+
+
+def check_experts(kind, rows, K, seed, q_off=0, out_off=0, **recipe):
+    """The grouped call on nibbles q_off and an output out_off bytes past a 256-byte boundary, with guards around both outputs."""
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    q, sf = (t.numpy() for t in synth.random_mxfp4(int(off[-1]), K, seed=seed, **{"scale_spread": 6, **recipe}))
+    src = torch.empty(q.size + 256, dtype=torch.uint8, device=DEV)[q_off:q_off + q.size].view(q.shape)
+    src.copy_(torch.from_numpy(q))
+    args = src, torch.from_numpy(sf).to(DEV), torch.from_numpy(off).to(DEV)
+    mxfp4 = kind == "mxfp4"
+    n, ns = (K * sum(-(-r // u) for r in rows) for u in ((2, 32) if mxfp4 else (1, 128)))
+    data = torch.full((n + 512,), 0xA5, dtype=torch.uint8, device=DEV)
+    scale = torch.full((ns + 64,), 0x5A if mxfp4 else -7.0, dtype=torch.uint8 if mxfp4 else torch.float32, device=DEV)
+    out = data[out_off:out_off + n]
+    if mxfp4:
+        mx.mxfp4_row_to_col_grouped(*args, q_col=out, sf_col=scale[:ns], offsets_host=off.tolist())
+        want, ws = ref.row_to_col_grouped(q, sf, off)
+    else:
+        mx.mxfp4_row_to_fp8_col_grouped(*args, x_col=out, x_col_scale=scale[:ns], requant=kind == "requant", offsets_host=off.tolist())
+        want, ws = ref.row_to_fp8_col_grouped(q, sf, off, requant=kind == "requant")
+    got, gs = host(data), host(scale)
+    assert (got[:out_off] == 0xA5).all() and (got[out_off + n:] == 0xA5).all() and (gs[ns:] == (0x5A if mxfp4 else -7.0)).all()
+    assert_same(gs[:ns].view(np.uint8), np.ascontiguousarray(ws).view(np.uint8).ravel(), f"{kind} scales")
+    assert_same(got[out_off:out_off + n], np.ascontiguousarray(want).ravel(), kind)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("name", SPLITS)
+def test_experts(kind, name):
+    """Splits around the edges of pieces, blocks, scale groups and tiles, by small tiles."""
+    rows, K = SPLITS[name], 384
+    assert half_tiles(rows, K) <= limit(kind, rows)
+    check_experts(kind, rows, K, seed=len(rows))
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("name", SPLITS)
+def test_experts_above_the_line(kind, name):
+    """The same splits, as often as it takes to leave the small tiles: the kernels for larger launches keep these edges."""
+    rows, K = list(SPLITS[name]), 2176
+    while half_tiles(rows, K) <= limit(kind, rows):
+        rows += SPLITS[name]
+    assert len(rows) <= 256
+    check_experts(kind, rows, K, seed=len(rows))
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("E", [1, 64, 65, 256, 257])
+def test_numbers_of_experts(kind, E):
+    """Both lookups of the small tiles, and one expert more than they take; empty experts at either end and in between."""
+    rows = [0 if e % 7 == 0 or e == E - 1 else 1 + (37 * e) % 150 for e in range(E)] if E > 1 else [77]
+    check_experts(kind, rows, 256, seed=E)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("scales", SCALES)
+def test_scales_of_experts(kind, scales):
+    """Row scales beyond FP32 and NaN bytes in last tiles that experts do not fill."""
+    center, spread, nan = SCALES[scales]
+    check_experts(kind, [33, 161, 0, 128, 7, 300], 384, seed=5, q_off=4, out_off=16, scale_center=center, scale_spread=spread,
+                  nan_scale_frac=nan)
