@@ -102,6 +102,10 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
     const uint32_t sub = tid & 3u, cg = tid >> 2 & 15u, rg = tid >> 6; // rows 32 rg + 8 sub, columns 8 cg of the tile
     const uint32_t pitch = a.K / 2u, Kb = a.K / 32u, kb = cg >> 2;
 
+    // Of this wave's 32 rows there are some: splits of 58 rows on the average take 17.1 us where waves without rows do nothing, else 18.4
+    // ([7424,3712] in 128, MXFP4), of 32 rows 20.2 and 26.3 ([4096,7168] in 128).
+    const bool present = !EXPERTS || (uint32_t)__builtin_amdgcn_readfirstlane((int)rg) < n_rg;
+
     // ---- the lane's 8 x 8 elements and its 8 row-scale bytes
     uint32_t w[8], b[8];
     {
@@ -118,7 +122,7 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 w[i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(src + (size_t)i * pitch + at));
-        } else { // rows that an expert does not have are zeros under scale byte 0 (read from its last row, then cleared)
+        } else if (present) { // rows that an expert does not have are zeros under scale byte 0 (read from its last row, then cleared)
             const uint32_t row0 = rg * 32u, first = row0 + sub * 8u;
             if (row0 + lane < min(row0 + 32u, n_rows))
                 sf = *reinterpret_cast<const uint32_t *>(src_sf + (row0 + lane) * Kb);
@@ -129,6 +133,10 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 w[i] = first + i < n_rows ? w[i] : 0u;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                w[i] = 0u;
         }
         // four rows' bytes of four k-blocks, turned round in the quad
         uint32_t t = perm(dpp_read<DPP_QUAD_XOR1>(sf), sf, (lane & 1u) ? 0x03070105u : 0x06020400u);
@@ -148,7 +156,9 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
 
     if (KIND == COL_MXFP4) {
         largest = quad_reduce(largest, [](uint32_t x, uint32_t y) { return max(x, y); });
-        if (largest < 253u) {
+        if (!present) {
+            // nothing to write
+        } else if (largest < 253u) {
             uint32_t cb[8], o[8];
             float amax[8];
 #pragma unroll
@@ -252,39 +262,46 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
                 const uint32_t bits = flags ? 0x7FC00000u : e >= 1 ? (uint32_t)e << 23 : 0x00400000u >> (uint32_t)(-e);
                 out_scale(cg * 8u + scales, bits);
             }
-            float dsc[8];
-            const float enc = u2f(121u << 23); // the encoder divides by 2^-6: Algorithm 1's delta
-            uint32_t nan[2] = {0u, 0u};
+            if (present) {
+                float dsc[8];
+                const float enc = u2f(121u << 23); // the encoder divides by 2^-6: Algorithm 1's delta
+                uint32_t nan[2] = {0u, 0u};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                dsc[i] = u2f((uint32_t)max((int)((b[i] + 127u - bmax) << 23), 0));
-                nan[i >> 2] |= b[i] == 255u ? 0xFFu << (8 * (i & 3)) : 0u;
-            }
-            static_for<4>([&](auto jp) {
-                constexpr int j = decltype(jp)::value;
-                static_for<2>([&](auto rp) {
-                    constexpr int r = decltype(rp)::value;
-                    const f32x2 f0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r], dsc[4 * r], j);
-                    const f32x2 f1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r + 1], dsc[4 * r + 1], j);
-                    const f32x2 f2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r + 2], dsc[4 * r + 2], j);
-                    const f32x2 f3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r + 3], dsc[4 * r + 3], j);
-                    s16x2 e0, e1; // no initial value needed: both words are written
-                    asm volatile("" : "=v"(e0), "=v"(e1));
-                    e0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e0, f0.x, f1.x, enc, false);
-                    e0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e0, f2.x, f3.x, enc, true);
-                    e1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e1, f0.y, f1.y, enc, false);
-                    e1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e1, f2.y, f3.y, enc, true);
-                    // rows under a NaN scale byte are NaN
-                    o[2 * j][r] = (__builtin_bit_cast(uint32_t, e0) & ~nan[r]) | (0x7F7F7F7Fu & nan[r]);
-                    o[2 * j + 1][r] = (__builtin_bit_cast(uint32_t, e1) & ~nan[r]) | (0x7F7F7F7Fu & nan[r]);
+                for (int i = 0; i < 8; ++i) {
+                    dsc[i] = u2f((uint32_t)max((int)((b[i] + 127u - bmax) << 23), 0));
+                    nan[i >> 2] |= b[i] == 255u ? 0xFFu << (8 * (i & 3)) : 0u;
+                }
+                static_for<4>([&](auto jp) {
+                    constexpr int j = decltype(jp)::value;
+                    static_for<2>([&](auto rp) {
+                        constexpr int r = decltype(rp)::value;
+                        const f32x2 f0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r], dsc[4 * r], j);
+                        const f32x2 f1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r + 1], dsc[4 * r + 1], j);
+                        const f32x2 f2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r + 2], dsc[4 * r + 2], j);
+                        const f32x2 f3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[4 * r + 3], dsc[4 * r + 3], j);
+                        s16x2 e0, e1; // no initial value needed: both words are written
+                        asm volatile("" : "=v"(e0), "=v"(e1));
+                        e0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e0, f0.x, f1.x, enc, false);
+                        e0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e0, f2.x, f3.x, enc, true);
+                        e1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e1, f0.y, f1.y, enc, false);
+                        e1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(e1, f2.y, f3.y, enc, true);
+                        // rows under a NaN scale byte are NaN
+                        o[2 * j][r] = (__builtin_bit_cast(uint32_t, e0) & ~nan[r]) | (0x7F7F7F7Fu & nan[r]);
+                        o[2 * j + 1][r] = (__builtin_bit_cast(uint32_t, e1) & ~nan[r]) | (0x7F7F7F7Fu & nan[r]);
+                    });
                 });
-            });
 #pragma unroll
-            for (int c = 0; c < 8; ++c)
-                *reinterpret_cast<u32x2 *>(s_out + (c * 16u + cg) * ROW + rg * 32u + sub * 8u) = u32x2{o[c][0], o[c][1]};
+                for (int c = 0; c < 8; ++c)
+                    *reinterpret_cast<u32x2 *>(s_out + (c * 16u + cg) * ROW + rg * 32u + sub * 8u) = u32x2{o[c][0], o[c][1]};
+            }
         } else {
             // ---- the group's largest value of every column: its FP32 bits, or Emax where those do not do
-            if (flags == 0u) {
+            if (!present) {
+                if (sub == 0u) {
+                    u32x4 *dst = reinterpret_cast<u32x4 *>(s_amax[rg] + cg * 8u);
+                    dst[0] = dst[1] = u32x4{0u, 0u, 0u, 0u};
+                }
+            } else if (flags == 0u) {
                 float amax[8];
 #pragma unroll
                 for (int c = 0; c < 8; ++c)
@@ -352,7 +369,9 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
             auto emax_of = [&](uint32_t v) { return flags != 0u ? (int)v - 1 : v == 0u ? -1 : emax_of_amax_bits(v); };
             if (scales < 8u)
                 out_scale(cg * 8u + scales, (flags & 2u) ? 0x7FC00000u : scale_bits_of_emax(emax_of(mine), mine != 0u));
-            if (!slow) {
+            if (!present) {
+                // nothing to write
+            } else if (!slow) {
                 uint32_t o[8][2];
                 static_for<4>([&](auto jp) {
                     constexpr int j = decltype(jp)::value;
@@ -446,6 +465,13 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
 // average have no whole tile of the larger kind: [17392,2048] in 128 row->col 19.9 / 15.3 and 18.7 / 14.4, alignment 23.4 / 19.6 and
 // 18.8 / 18.4, re-quantization 25.8 / 20.2 and 21.1 / 18.9 (3184); padded, [11392,2048] in 64 11.1 / 9.0 and 9.9 / 8.3, 12.3 / 10.7 and
 // 11.0 / 10.6, 13.7 / 10.2 and 12.5 / 10.1 (1936), [16640,2048] in 128 12.5 / 12.2 and 10.8 / 11.9, 16.7 / 17.2 and 14.5 / 16.0 (3104).
+// Splits of at most 64 rows on the average waste three quarters of a larger tile and half of a small one, of 32 rows still more
+// ([2048,7168] in 256 row->col 50 / 35 and 48 / 34, alignment 53 / 39 and 51 / 38, re-quantization 63 / 46 and 62 / 45).  Those lines lie
+// where Zipf-sized splits, most of whose rows are in a few experts, lose nothing either: row->col [8190,7168] in 128 49 / 45 and 45 / 43
+// (7112), [16384,7168] in 256 83 / 92 and 78 / 89 (14336); alignment [2048,8064] in 32 20.0 / 17.6 and 17.5 / 16.5 (2016), [4096,7168] in 64
+// 30.7 / 29.4 and 24.9 / 27.8 (3584); re-quantization [4096,7168] in 64 32.7 / 30.0 and 29.0 / 28.5, [8190,7168] in 128 61 / 60 and 54 / 56;
+// of more than 64 rows alignment [7700,2048] in 64 15.2 / 14.4 and 13.5 / 13.8 (1472), [12000,2048] in 64 16.6 / 20.0 and 14.4 / 18.8 (2000),
+// re-quantization there 19.0 / 18.1 and 16.8 / 17.0.
 bool col_in_small_tiles(int64_t M, int64_t K, int32_t num_experts, ColKind kind)
 {
     const int64_t units = compute_units(), tiles_k = K / TILE;
@@ -455,9 +481,16 @@ bool col_in_small_tiles(int64_t M, int64_t K, int32_t num_experts, ColKind kind)
         return false;
     const bool padded = M % 128 == 0;
     const int64_t half_tiles = (2 * (M / TILE) + num_experts) * tiles_k;
+    auto up_to = [&](int mxfp4, int align, int requant) { // half tiles per compute unit
+        return half_tiles <= (kind == COL_MXFP4 ? mxfp4 : kind == COL_ALIGN ? align : requant) * units;
+    };
+    if (M <= 32 * (int64_t)num_experts)
+        return true;
+    if (M <= 64 * (int64_t)num_experts)
+        return up_to(56, 24, 32);
     if (M < 256 * (int64_t)num_experts)
-        return half_tiles <= (padded ? 15 : 24) * units;
-    return half_tiles <= (!padded ? (kind == COL_MXFP4 ? 14 : 12) : kind == COL_REQUANT ? 8 : 10) * units;
+        return padded ? up_to(15, 12, 15) : up_to(24, 12, 15);
+    return padded ? up_to(10, 10, 8) : up_to(14, 12, 12);
 }
 
 template <bool EXPERTS>

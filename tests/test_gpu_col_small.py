@@ -83,10 +83,12 @@ def half_tiles(rows, K):
 
 def limit(kind, rows):
     """Half tiles up to which experts go by small ones."""
-    padded = sum(rows) % 128 == 0
-    if sum(rows) < 256 * len(rows):
-        return (15 if padded else 24) * UNITS
-    return ({"mxfp4": 10, "align": 10, "requant": 8}[kind] if padded else {"mxfp4": 14, "align": 12, "requant": 12}[kind]) * UNITS
+    M, E, padded = sum(rows), len(rows), sum(rows) % 128 == 0
+    if M <= 32 * E:
+        return float("inf")
+    up_to = ((56, 24, 32) if M <= 64 * E else ((15, 12, 15) if padded else (24, 12, 15)) if M < 256 * E else
+             (10, 10, 8) if padded else (14, 12, 12))
+    return up_to[list(KINDS).index(kind)] * UNITS
 
 
 def check_experts(kind, rows, K, seed, q_off=0, out_off=0, **recipe):
