@@ -140,12 +140,29 @@ struct QuantScatterArgs {
     uint32_t M_out;
 };
 
+// The first HELD destinations are requested with the elements: behind a store a load would wait for it (stores and loads are
+// counted together).  HELD 1, 4 or 8, the least that holds the fan-out, 8 for more: no branches between the loads, few that are
+// not wanted.  Us, calls in a HIP graph with every byte from and to HBM, loads behind the conversion / this way:
+// 1035 x 1024 to one row 3.1 / 2.6, 40000 x 640 11.8 / 10.6, 2285 x 1152 to three 4.6 / 4.0 and four 5.0 / 4.4, 2174 x 896 to seven
+// 4.8 / 4.1, 65536 x 512 to eight 61 / 58, 65536 x 1024 to three 37.0 / 37.3, to eight 85.8 / 85.2.
+template <int HELD>
 __global__ void __launch_bounds__(QUANT_THREADS_ROUTED) quant_from_fp8_scatter_kernel(const QuantScatterArgs a)
 {
     const uint32_t c0 = blockIdx.x * (QUANT_THREADS_ROUTED * QUANT_UNROLL) + threadIdx.x;
 
+    // Destinations from j0 on of a row; past the fan-out one that no output has.
+    auto destinations = [&](uint32_t row, uint32_t j0, uint32_t(&d)[HELD]) {
+        const int32_t *dst = a.dst_idx + (size_t)row * a.fanout;
+#pragma unroll
+        for (int j = 0; j < HELD; ++j)
+            d[j] = (uint32_t)dst[HELD == 1 ? j0 : min(j0 + j, a.fanout - 1u)];
+#pragma unroll
+        for (int j = 1; j < HELD; ++j)
+            d[j] = j0 + j < a.fanout ? d[j] : 0xFFFFFFFFu;
+    };
     u32x4 w[QUANT_UNROLL];
     float s[QUANT_UNROLL];
+    uint32_t row[QUANT_UNROLL], d[QUANT_UNROLL][HELD];
 #pragma unroll
     for (int u = 0; u < QUANT_UNROLL; ++u) {
         const uint32_t c = c0 + u * QUANT_THREADS_ROUTED;
@@ -153,6 +170,8 @@ __global__ void __launch_bounds__(QUANT_THREADS_ROUTED) quant_from_fp8_scatter_k
             break; // n_chunks is a multiple of 8: the 8 lanes of a tile leave together
         w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.x + (size_t)c * 16));
         s[u] = a.x_scale[c >> 3];
+        row[u] = a.row_of(c);
+        destinations(row[u], 0u, d[u]);
     }
 
 #pragma unroll
@@ -166,25 +185,21 @@ __global__ void __launch_bounds__(QUANT_THREADS_ROUTED) quant_from_fp8_scatter_k
         uint32_t t = b | (dpp_read<DPP_QUAD_XOR2>(b) << 8); // lanes 0,1: B0 | B1 << 8
         t |= row_shift_left4(t) << 16;                       // lane 0: ... | B2 << 16 | B3 << 24
 
-        const uint32_t row = a.row_of(c);
-        const uint32_t cc = c - row * a.chunks_per_row;
-        const int32_t *dst = a.dst_idx + (size_t)row * a.fanout;
-        // the destinations are read eight at a time before any store: a store (bytes, may alias
-        // anything) between two index loads would put every load's latency on the lane's path
-        for (uint32_t j0 = 0; j0 < a.fanout; j0 += 8u) {
-            uint32_t d[8];
+        const uint32_t cc = c - row[u] * a.chunks_per_row;
+        for (uint32_t j0 = 0;;) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                d[j] = j0 + j < a.fanout ? (uint32_t)dst[j0 + j] : 0xFFFFFFFFu;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (d[j] >= a.M_out) // also skips negative entries and the tail of the batch
+            for (int j = 0; j < HELD; ++j) {
+                if (d[u][j] >= a.M_out) // also skips negative entries and the slots past the fan-out
                     continue;
                 __builtin_nontemporal_store(u32x2{out[0], out[1]},
-                                            reinterpret_cast<u32x2 *>(a.q + (size_t)d[j] * a.ld_q + (size_t)cc * 8));
+                                            reinterpret_cast<u32x2 *>(a.q + (size_t)d[u][j] * a.ld_q + (size_t)cc * 8));
                 if ((threadIdx.x & 7u) == 0u)
-                    *reinterpret_cast<uint32_t *>(a.sf + (size_t)d[j] * a.ld_sf + (size_t)(cc >> 3) * 4) = t;
+                    *reinterpret_cast<uint32_t *>(a.sf + (size_t)d[u][j] * a.ld_sf + (size_t)(cc >> 3) * 4) = t;
             }
+            j0 += HELD;
+            if (j0 >= a.fanout)
+                break;
+            destinations(row[u], j0, d[u]);
         }
     }
 }
@@ -277,19 +292,25 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     //   K = 4096 34 / 33 / 35, 50 / 49 / 67, 40 / 36 / 57; K = 5120 45 / 40 / 36, 50 / 51 / 58, 40 / 37 / 50;
     //   K = 7168 43 / 38 / 37, 51 / 51 / 49, 40 / 37 / 41; 65536 tokens of 7168, 8 copies (2 GB) 598 / 520 / 480.
     // A wave per row leaves lanes idle below 1024 elements and has its stores contiguous above; a workgroup per row
-    // writes the longest runs, which pays for long rows with several copies, and it is done soonest where there are few
-    // rows (us, wave / workgroup: 61 rows of 4096, 8 copies 5.6 / 3.8, 488 rows 6.1 / 5.7).  Between 4608 and 6144 elements
+    // writes the longest runs, which pays for long rows with several copies.  Between 4608 and 6144 elements
     // the workgroup needs four copies, and more of them than the memory-side cache takes in (wave / workgroup, 140, 300 and 600
     // million elements of records): K = 5632 8 copies 22 / 20, 46 / 42, 91 / 81, 4 copies 24 / 22, 51 / 44, 98 / 86, 2 copies 31 / 31,
     // 59 / 62, 115 / 127; K = 4608 8 copies 22 / 21, 48 / 43, 93 / 82, 4 copies 24 / 24, 52 / 47, 99 / 91; K = 6016 8 copies 18 / 19,
     // 38 / 38, 77 / 72, 4 copies 19 / 22, 45 / 42, 88 / 82.  Scale planes that are not on 16-byte boundaries stay with the
     // lanes (1860 rows of 8064, 4 copies 8.7 against 11.0 us by workgroups).
+    // A lane per chunk has its elements and destinations on the way at once and waits for nothing else: it takes what has one copy (us,
+    // wave or workgroup per row / lanes, every byte from and to HBM, calls in a HIP graph: 500 x 2048 2.9 / 2.6, 65536 x 2048 39.2 / 37.4,
+    // 16000 x 7168 34.0 / 33.0, 65536 x 7168 125 / 122, but 100 x 2048 2.36 / 2.44) and small launches: 2000 x 2048 two, four and eight
+    // copies 4.1 / 3.7, 4.8 / 4.1 and 6.1 / 5.3, 1000 x 4096 3.7 / 3.6, 4.6 / 4.0 and 5.7 / 5.1, 2000 x 3072 5.3 / 4.8, 6.2 / 5.6 and 8.8 /
+    // 8.1, 150 x 7168 3.2 / 3.2, 3.6 / 3.4 and 4.4 / 4.2; above the lines 3000 x 4096 6.6 / 7.0, 8.2 / 8.1 and 13.1 / 13.1, 12000 x 2048
+    // 11.8 / 11.5, 15.7 / 17.1 and 25.9 / 26.2, 600 x 7168 4.2 / 4.2, 4.8 / 4.8 and 6.1 / 6.3, 3000 x 7168 11.2 / 10.9, 14.9 / 16.7, 23.6 / 28.6.
+    const bool lanes = fanout == 1 || M_src * K <= (K < 6144 ? (int64_t)6 << 20 : (int64_t)3 << 19);
     uint32_t segs_per_row;
     const uint32_t seg = wave_segment(K, &segs_per_row);
     const uint32_t rec = (uint32_t)((K / 2 + K / 32 + 15) & ~(int64_t)15);
     const int64_t units = M_src * segs_per_row;
     const bool many = K >= 4608 && fanout >= 4 && M_src * K >= ((int64_t)1 << 28) / fanout;
-    if (rows16 && K >= 2048 && ((K >= 6144 && fanout >= 2) || many || units < 1024) && rec <= 48u * 1024u) {
+    if (rows16 && !lanes && (K >= 6144 || many) && rec <= 48u * 1024u) {
         const bool records = sf == q + K / 2 && ld_sf == ld_q;
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_scatter_row_kernel<true>, dim3((uint32_t)M_src), dim3(ROW_THREADS), rec,
@@ -299,7 +320,7 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
                                stream, a, records);
         return hipGetLastError();
     }
-    if (rows16 && K >= 2048) {
+    if (rows16 && !lanes && K >= 2048) {
         const uint32_t blocks = (uint32_t)((units + SCATTER_WAVES - 1) / SCATTER_WAVES);
         if (wide)
             hipLaunchKernelGGL(quant_from_fp8_scatter_wave_kernel<true>, dim3(blocks), dim3(64 * SCATTER_WAVES), 0, stream,
@@ -311,7 +332,12 @@ hipError_t launch_quant_from_fp8_scatter(const uint8_t *x, const float *x_scale,
     }
     constexpr uint32_t per_block = QUANT_THREADS_ROUTED * QUANT_UNROLL;
     const uint32_t blocks = (a.n_chunks + per_block - 1) / per_block;
-    hipLaunchKernelGGL(quant_from_fp8_scatter_kernel, dim3(blocks), dim3(QUANT_THREADS_ROUTED), 0, stream, a);
+    if (fanout == 1)
+        hipLaunchKernelGGL(quant_from_fp8_scatter_kernel<1>, dim3(blocks), dim3(QUANT_THREADS_ROUTED), 0, stream, a);
+    else if (fanout <= 4)
+        hipLaunchKernelGGL(quant_from_fp8_scatter_kernel<4>, dim3(blocks), dim3(QUANT_THREADS_ROUTED), 0, stream, a);
+    else
+        hipLaunchKernelGGL(quant_from_fp8_scatter_kernel<8>, dim3(blocks), dim3(QUANT_THREADS_ROUTED), 0, stream, a);
     return hipGetLastError();
 }
 

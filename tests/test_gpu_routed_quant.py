@@ -56,8 +56,8 @@ def check(buf, at, ld_q, ld_sf, K, rows, wq, wsf):
                                      (6144, 13, 1), (6144, 13, 2), (6272, 5, 9), (7680, 1024, 1), (7808, 512, 1),
                                      (8192, 512, 1), (8192, 511, 1), (16896, 342, 1), (98304, 2, 2), (98304, 79, 1)])
 def test_scatter_kernels(K, M, fan, layout):
-    """One lane per chunk, one wave per row (from 1024 rows on; several segments of a row count, from 7681 elements on) and
-    one workgroup per row; fan-outs of 1, 2 and past the eight indices read ahead; scale bytes as 16-byte pieces and as dwords."""
+    """Small launches and fan-outs of one, by a lane per chunk whatever the row length (98304 elements: of many tiles), and a wave or a
+    workgroup per row; fan-outs of 1, 2 and past the eight indices read ahead; scale bytes as 16-byte pieces and as dwords."""
     rng, x8, s, wq, wsf = source(M, K, K + fan)
     M_out = M * fan + 5
     dst = rng.permutation(M_out)[: M * fan].reshape(M, fan).astype(np.int32)
@@ -67,6 +67,16 @@ def test_scatter_kernels(K, M, fan, layout):
     mx.mxfp4_quant_from_fp8_scatter(dev(x8), dev(s), dev(dst), M_out, q=q, sf=sf, ld_q=ld_q, ld_sf=ld_sf)
     src, _ = np.nonzero(~nowhere)
     check(buf, at, ld_q, ld_sf, K, dst[~nowhere], wq[src], wsf[src])
+
+
+@pytest.mark.parametrize("layout", ["records", "planes"])
+@pytest.mark.parametrize("K,M,fan", [(1024, 301, 4), (1024, 301, 5), (640, 77, 17),  # destinations held by fours and eights, and past them
+                                     (2048, 3072, 2), (2048, 3073, 2), (2176, 2891, 9), (2176, 2892, 9),  # lanes, a wave per row
+                                     (6016, 1045, 3), (6016, 1046, 3), (6144, 256, 2), (6144, 257, 2), (6272, 251, 9),  # a workgroup
+                                     (7808, 201, 4), (7808, 202, 4), (98304, 16, 2), (98304, 17, 2)])  # and rows of several segments
+def test_scatter_sides_of_the_small_launches(K, M, fan, layout):
+    """Both sides of the sizes up to which a lane takes a chunk of long rows, and the kernels above them."""
+    test_scatter_kernels(K, M, fan, layout)
 
 
 @pytest.mark.parametrize("K,M,fan", [(5632, 11916, 4), (5632, 11915, 4), (5632, 15887, 3), (4608, 7282, 8), (4480, 7490, 8)])
