@@ -439,9 +439,10 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
     const uint32_t total = a.tiles_m * a.tiles_k;
     a.stage_in = total >= 3u * compute_units() ? 1u : 0u; // at least 3 tiles per compute unit
     const dim3 grid((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD);
-    // A few tiles per compute unit: what an unaligned 16-byte store costs a wave to issue shows (un-padded [2000, 2048] in 8
-    // experts 7.9 -> 7.1 us, [8000, 1024] in 64 10.2 -> 9.4, [3000, 512] in 128 8.4 -> 7.8); with more of them the memory waits
-    // for the additional requests ([16384, 2048] in 16 13.8 -> 14.1, [65536, 7168] in 32 158 -> 170).
+    // A few tiles per compute unit (more than 256 experts, totals that look padded and are not: col_in_small_tiles takes the others):
+    // what an unaligned 16-byte store costs a wave to issue shows (by these tiles un-padded [2000, 2048] in 8 experts 7.9 -> 7.1 us,
+    // [8000, 1024] in 64 10.2 -> 9.4, [3000, 512] in 128 8.4 -> 7.8); with more of them the memory waits for the additional requests
+    // ([16384, 2048] in 16 13.8 -> 14.1, [65536, 7168] in 32 158 -> 170).
     a.few = 2 * total <= 3 * compute_units() ? 1u : 0u;
     // Large ragged splits: every tile shares its outer 64-byte segments with its neighbours where the k-rows of an expert are
     // not whole segments.  The two halves meet in the L2 if the tiles finish close together; what leaves it half written costs

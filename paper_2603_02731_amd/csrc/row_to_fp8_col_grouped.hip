@@ -633,7 +633,7 @@ static int64_t tiles_at_most(int64_t M, int64_t K, int32_t num_experts)
     return ((M + TILE_M - 1) / TILE_M + num_experts) * ((K + TILE_K - 1) / TILE_K);
 }
 
-// Launches of about one round of the other kernels' workgroups (two per compute unit, one pass), as far as the number of tiles
+// Of the launches that col_in_small_tiles leaves, those of about one round of the other kernels' workgroups (two per compute unit, one pass), as far as the number of tiles
 // can be told, whose total row count says that the splits may be padded, are left to them: nothing is shared or the pieces are
 // aligned, and what a workgroup takes longer here is not made up for.  Measured (us, own rows / segments, re-quantization): padded
 // to 16, [8864, 512] in 64 experts 7.6 / 9.0, [2064, 2048] in 8 7.7 / 9.3, [4112, 4096] in 16 11.2 / 12.4; to 128, [9984, 1792] in 64

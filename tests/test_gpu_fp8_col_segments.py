@@ -1,7 +1,8 @@
 """GPU parity of the ragged FP8-column conversions where tiles write whole 64-byte segments of the output: splits around the
 edges of pieces (16 rows), segments (64), scale groups (128) and tiles (256), outputs and inputs that begin off a segment, half
 tiles along k, special scale bytes in the look-back rows, and both sides of the rule that leaves small padded launches to the
-kernels that write their own rows."""
+kernels that write their own rows.  Small launches among these go by the tiles of 128 x 128; test_gpu_col_small.py takes the same
+splits above that line."""
 import numpy as np
 import pytest
 import torch
