@@ -14,10 +14,11 @@
 // what the larger tiles spend on last ones and the look-back rows of row_to_fp8_col_grouped.hip, and leave by 16-byte stores at any byte:
 // [4436,1152] in 16 experts, not padded, 6.8 / 4.4, 8.7 / 5.0 and 10.0 / 5.8, [17315,1024] in 128 13.1 / 9.2, 14.1 / 10.6 and 16.4 / 11.3.
 // What a tile costs beside its elements (addresses, half lines, scales four or one at a time) is four times as much too, so where
-// workgroups queue up this is slower ([4096,7168], every byte from and to HBM, 10.2 / 14.6): col_in_small_tiles.
+// workgroups queue up this is slower ([4096,7168], every byte from and to HBM, 10.2 / 14.6): col_small_rule.hpp.
 // Not kept: plain loads, which leave the matrix in the memory-side cache for another pass over it ([8192,7168] of three in turn 25.4 ->
 // 13.5, but 25.1 where every byte comes from HBM, where the larger tiles take 18.0; [2048,2048] 3.7 -> 4.5); 256 x 128, 128 x 256 and
 // 256 x 256 elements with as many lanes as here per element ([2048,2048] 3.3 -> 3.7, 3.8 and 4.6, [4096,7168] no better).
+#include "col_small_rule.hpp"
 #include "fp8_col_tile.hpp"
 #include "mxfp4_device.hpp"
 #include "mxfp4_kernels.hpp"
@@ -27,8 +28,7 @@ namespace col_small {
 
 using namespace fp8col;
 
-constexpr uint32_t THREADS = 256, TILE = 128, MBM_MAX = 64;
-constexpr int EXPERTS_MAX = 256; // the lookup of more takes registers that cost a third of the waves
+constexpr uint32_t MBM_MAX = 64;
 
 struct Args {
     const uint8_t *q_row;
@@ -447,56 +447,15 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
     }
 }
 
-// Which matrices: about three tiles per compute unit.  On both sides of the lines, 256 compute units (us, tiles of 256 x 256 / small ones,
-// with every byte from and to HBM, and of three matrices in turn): row->col 704 tiles 6.89 / 6.89 and 6.19 / 5.08 [2816,4096], 6.55 / 5.66
-// and 6.11 / 4.55 [22528,512], 768 tiles 6.99 / 7.22 and 6.35 / 5.23 [3072,4096], 896 tiles 7.07 / 8.68 and 6.35 / 6.46; alignment 704
-// tiles 7.29 / 7.30 and 6.63 / 5.28, 7.00 / 6.19 and 6.50 / 5.07, 896 tiles 7.63 / 9.20 and 6.80 / 8.06; re-quantization 768 tiles
-// 8.07 / 7.30 and 7.39 / 6.29, 896 tiles 8.35 / 8.79 and 7.60 / 7.07.
-//
-// Which experts, by the number of tiles that their splits are expected to have (each ends in half a tile): the larger tiles waste more on
-// last ones, and in what splits at any row make of the k-rows, so that the lines lie higher.  Row->col [8192,2048] in 8 12.2 / 9.5 and
-// 10.1 / 8.0 (1088 tiles), [8192,4096] in 32 16.5 / 15.5 and 15.6 / 15.0 (2560), but [16384,2048] in 4 15.9 / 16.5 and 14.5 / 15.1 (2080);
-// alignment [8192,2048] in 8 12.7 / 10.5 and 11.5 / 9.6, [8192,2048] in 64 15.1 / 10.8 and 13.3 / 10.2 (1536), [16384,2048] in 4 16.8 /
-// 19.7 and 14.6 / 18.5 (2080); re-quantization 15.7 / 11.6 and 14.4 / 10.1, 21.4 / 11.6 and 20.5 / 11.0, [16384,2048] in 16 19.4 / 18.7
-// and 17.4 / 17.5 (2176).  A total of whole groups of 128 rows may be that of padded splits, which waste less: row->col [18432,1024] in 32
-// 9.1 / 8.1 and 8.0 / 7.0 (1280), [17408,2048] in 16 12.0 / 13.4 and 10.7 / 12.7 (2304); alignment [18432,1024] in 32 10.0 / 8.9 and 8.9 /
-// 8.6, [16512,2048] in 4 14.4 / 16.8 and 11.8 / 16.1 (2096); re-quantization [11392,1024] in 64 9.4 / 6.4 and 8.5 / 6.3 (968),
-// [8704,2048] in 8 10.6 / 9.4 and 9.3 / 8.0 (1152), [16512,2048] in 4 17.3 / 16.9 and 16.0 / 16.2.  Splits of less than 256 rows on the
-// average have no whole tile of the larger kind: [17392,2048] in 128 row->col 19.9 / 15.3 and 18.7 / 14.4, alignment 23.4 / 19.6 and
-// 18.8 / 18.4, re-quantization 25.8 / 20.2 and 21.1 / 18.9 (3184); padded, [11392,2048] in 64 11.1 / 9.0 and 9.9 / 8.3, 12.3 / 10.7 and
-// 11.0 / 10.6, 13.7 / 10.2 and 12.5 / 10.1 (1936), [16640,2048] in 128 12.5 / 12.2 and 10.8 / 11.9, 16.7 / 17.2 and 14.5 / 16.0 (3104).
-// Splits of at most 64 rows on the average waste three quarters of a larger tile and half of a small one, of 32 rows still more
-// ([2048,7168] in 256 row->col 50 / 35 and 48 / 34, alignment 53 / 39 and 51 / 38, re-quantization 63 / 46 and 62 / 45).  Those lines lie
-// where Zipf-sized splits, most of whose rows are in a few experts, lose nothing either: row->col [8190,7168] in 128 49 / 45 and 45 / 43
-// (7112), [16384,7168] in 256 83 / 92 and 78 / 89 (14336); alignment [2048,8064] in 32 20.0 / 17.6 and 17.5 / 16.5 (2016), [4096,7168] in 64
-// 30.7 / 29.4 and 24.9 / 27.8 (3584); re-quantization [4096,7168] in 64 32.7 / 30.0 and 29.0 / 28.5, [8190,7168] in 128 61 / 60 and 54 / 56;
-// of more than 64 rows alignment [7700,2048] in 64 15.2 / 14.4 and 13.5 / 13.8 (1472), [12000,2048] in 64 16.6 / 20.0 and 14.4 / 18.8 (2000),
-// re-quantization there 19.0 / 18.1 and 16.8 / 17.0.
 bool col_in_small_tiles(int64_t M, int64_t K, int32_t num_experts, ColKind kind)
 {
-    const int64_t units = compute_units(), tiles_k = K / TILE;
-    if (num_experts == 0)
-        return 4 * ((M + TILE - 1) / TILE * tiles_k) <= (kind == COL_REQUANT ? 12 : 11) * units;
-    if (num_experts > EXPERTS_MAX)
-        return false;
-    const bool padded = M % 128 == 0;
-    const int64_t half_tiles = (2 * (M / TILE) + num_experts) * tiles_k;
-    auto up_to = [&](int mxfp4, int align, int requant) { // half tiles per compute unit
-        return half_tiles <= (kind == COL_MXFP4 ? mxfp4 : kind == COL_ALIGN ? align : requant) * units;
-    };
-    if (M <= 32 * (int64_t)num_experts)
-        return true;
-    if (M <= 64 * (int64_t)num_experts)
-        return up_to(56, 24, 32);
-    if (M < 256 * (int64_t)num_experts)
-        return padded ? up_to(15, 12, 15) : up_to(24, 12, 15);
-    return padded ? up_to(10, 10, 8) : up_to(14, 12, 12);
+    return col_in_small_tiles(M, K, num_experts, kind, compute_units());
 }
 
 template <bool EXPERTS>
-static void launch_kind(const col_small::Args &a, uint32_t tiles, ColKind kind, hipStream_t stream)
+static void launch_kind(const col_small::Args &a, int64_t tiles, ColKind kind, hipStream_t stream)
 {
-    const dim3 grid((tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD);
+    const dim3 grid((uint32_t)((tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD));
     if (kind == COL_MXFP4)
         hipLaunchKernelGGL((col_small_kernel<COL_MXFP4, EXPERTS>), grid, dim3(THREADS), 0, stream, a);
     else if (kind == COL_ALIGN)
@@ -520,10 +479,11 @@ hipError_t launch_col_small(const uint8_t *q_row, const uint8_t *sf_row, const i
     a.tiles_m = (uint32_t)((M + TILE - 1) / TILE);
     a.tiles_k = (uint32_t)(K / TILE);
     a.by_tiles_k = FastDiv(a.tiles_k);
-    if (expert_offsets) // every expert may end in part of a tile
-        launch_kind<true>(a, (a.tiles_m + (uint32_t)num_experts) * a.tiles_k, kind, stream);
+    const int64_t tiles = col_small_workgroups(M, K, expert_offsets ? num_experts : 0);
+    if (expert_offsets)
+        launch_kind<true>(a, tiles, kind, stream);
     else
-        launch_kind<false>(a, a.tiles_m * a.tiles_k, kind, stream);
+        launch_kind<false>(a, tiles, kind, stream);
     return hipGetLastError();
 }
 

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "col_small_rule.hpp"
+
 namespace mxfp4 {
 
 hipError_t launch_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_t M_src, int64_t K,
@@ -56,7 +58,6 @@ hipError_t launch_row_to_fp8_col_grouped(const uint8_t *q_row, const uint8_t *sf
 
 // The same conversions by smaller tiles: where col_in_small_tiles says so (one matrix: M % 32 == 0, M % 128 == 0 for FP8).
 // out_sf: bytes (MXFP4) or floats.
-enum ColKind { COL_MXFP4, COL_ALIGN, COL_REQUANT };
 bool col_in_small_tiles(int64_t M, int64_t K, int32_t num_experts, ColKind kind); // num_experts 0: one matrix
 hipError_t launch_col_small(const uint8_t *q_row, const uint8_t *sf_row, const int32_t *expert_offsets, int32_t num_experts, int64_t M,
                             int64_t K, uint8_t *out, void *out_sf, ColKind kind, hipStream_t stream);

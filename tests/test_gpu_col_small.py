@@ -8,6 +8,7 @@ import paper_2603_02731_amd as mx
 from oracle import parallel as par, ref
 from paper_2603_02731_amd import synth
 from tests.test_gpu_fp8_col_segments import SPLITS
+from tests.rules import small_tiles
 from tests.test_gpu_parity import DEV, assert_same, host
 
 pytestmark = pytest.mark.gpu
@@ -76,19 +77,9 @@ def test_sides_of_the_rule(kind, over):
     check(kind, q, sf, f"{kind} {tiles} tiles beside each other")
 
 
-def half_tiles(rows, K):
-    """Twice the number of 128 x 128 tiles that splits of these total rows are expected to have, as the rule counts them."""
-    return (2 * (sum(rows) // 128) + len(rows)) * (K // 128)
-
-
-def limit(kind, rows):
-    """Half tiles up to which experts go by small ones."""
-    M, E, padded = sum(rows), len(rows), sum(rows) % 128 == 0
-    if M <= 32 * E:
-        return float("inf")
-    up_to = ((56, 24, 32) if M <= 64 * E else ((15, 12, 15) if padded else (24, 12, 15)) if M < 256 * E else
-             (10, 10, 8) if padded else (14, 12, 12))
-    return up_to[list(KINDS).index(kind)] * UNITS
+def small(kind, rows, K):
+    """These splits go by small tiles."""
+    return small_tiles(kind, sum(rows), K, len(rows), UNITS)
 
 
 def check_experts(kind, rows, K, seed, q_off=0, out_off=0, **recipe):
@@ -120,7 +111,7 @@ def check_experts(kind, rows, K, seed, q_off=0, out_off=0, **recipe):
 def test_experts(kind, name):
     """Splits around the edges of pieces, blocks, scale groups and tiles, by small tiles."""
     rows, K = SPLITS[name], 384
-    assert half_tiles(rows, K) <= limit(kind, rows)
+    assert small(kind, rows, K)
     check_experts(kind, rows, K, seed=len(rows))
 
 
@@ -129,10 +120,20 @@ def test_experts(kind, name):
 def test_experts_above_the_line(kind, name):
     """The same splits, as often as it takes to leave the small tiles: the kernels for larger launches keep these edges."""
     rows, K = list(SPLITS[name]), 2176
-    while half_tiles(rows, K) <= limit(kind, rows):
+    while small(kind, rows, K):
         rows += SPLITS[name]
     assert len(rows) <= 256
     check_experts(kind, rows, K, seed=len(rows))
+
+
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("kind,each,line", [("mxfp4", 1, 336), ("align", 1, 336), ("requant", 1, 336), ("align", 32, 96)])
+def test_sides_of_the_lines_for_few_rows(kind, each, line, over):
+    """256 experts of one row, of 32 rows: the widest matrix that goes by small tiles, and 128 columns more."""
+    rows = [each] * 256
+    K = 128 * (line * UNITS // (2 * (sum(rows) // 128) + 256) + over)
+    assert small(kind, rows, K) == (over == 0)
+    check_experts(kind, rows, K, seed=each + over)
 
 
 @pytest.mark.parametrize("kind", KINDS)
