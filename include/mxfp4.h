@@ -80,7 +80,8 @@ mxfp4_status mxfp4_quant_from_fp8(const uint8_t *x, const float *x_scale, int64_
  * index is turned around first, so that every source row is read and quantized once).  The same results, refusals and alignments.
  *   workspace        device memory, 16-byte aligned, that no other work uses until this call's has run; its contents do not
  *                    matter.  In stream order: it may go back to a stream-ordered allocator, or to the next call on the same
- *                    stream, as soon as this call returns.  NULL, or fewer workspace_bytes than
+ *                    stream, as soon as this call returns; where the stream is being captured, it is the graph's for as long
+ *                    as that may be launched.  NULL, or fewer workspace_bytes than
  *                    mxfp4_quant_from_fp8_gather_workspace says: the call is mxfp4_quant_from_fp8.
  * mxfp4_quant_from_fp8_gather_workspace: the bytes a call with these arguments makes use of; 0 where it is mxfp4_quant_from_fp8
  * anyway.  Launches nothing. */

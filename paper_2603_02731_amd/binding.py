@@ -191,6 +191,35 @@ def _quant_outputs(x, M_out, K, q, sf, ld_q, ld_sf, fill):
     return q, sf, ld_q, ld_sf
 
 
+def _in_graph_pool(device):
+    """Whether new tensors of the current stream come from a pool of their own, as they do under a capture of PyTorch's."""
+    t = torch.empty(1, dtype=torch.uint8, device=device)
+    at = t.data_ptr()
+    for s in torch.cuda.memory_snapshot():
+        if s["address"] <= at < s["address"] + s["total_size"]:
+            return tuple(s.get("segment_pool_id", (0, 0))) != (0, 0)
+    return False
+
+
+def _gather_workspace(size, device):
+    """Memory for a gather to work in, or None where it has to do without.  It goes back to the allocator when the call returns, in
+    stream order.  A graph that the program captures by HIP's own calls would keep the address of memory that the allocator then
+    gives to others: no memory there.  A graph of torch.cuda.graph has a pool that nothing else is given memory from."""
+    captured = True
+    try:
+        with torch.cuda.device(device):
+            captured = torch.cuda.is_current_stream_capturing()
+        if captured and not _in_graph_pool(device):
+            return None
+        return torch.empty(size, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+    except RuntimeError:  # under a capture: an allocator that does not say where its memory is
+        if captured:
+            return None
+        raise
+
+
 def mxfp4_quant_from_fp8(x, x_scale, gather_idx=None, q=None, sf=None, ld_q=None, ld_sf=None, stream=None):
     """x uint8 [M_src,K] (E4M3), x_scale float32 [M_src,K/128] -> (q uint8 [M_out,K/2], sf uint8 [M_out,K/32]).
     gather_idx: optional int32 [M_out].  q/sf may be preallocated; with ld_q/ld_sf they may be views
@@ -213,12 +242,7 @@ def mxfp4_quant_from_fp8(x, x_scale, gather_idx=None, q=None, sf=None, ld_q=None
     idx = None if gather_idx is None else gather_idx.data_ptr()
     # memory to work in is given back when the call returns: to the current stream, so only a call on that one gets any
     size = lib().mxfp4_quant_from_fp8_gather_workspace(M_src, K, M_out, q.data_ptr(), ld_q) if idx and stream is None else 0
-    work = None
-    if size > 0:
-        try:
-            work = torch.empty(size, dtype=torch.uint8, device=x.device)
-        except torch.OutOfMemoryError:
-            pass  # it is done without
+    work = _gather_workspace(size, x.device) if size > 0 else None
     if work is not None:
         st = lib().mxfp4_quant_from_fp8_gather(x.data_ptr(), x_scale.data_ptr(), M_src, K, idx, M_out, q.data_ptr(), ld_q,
                                                sf.data_ptr(), ld_sf, work.data_ptr(), size, _stream(None, dev))

@@ -183,6 +183,14 @@ inline void *current_stream(const at::Tensor &t)
     return t.is_cuda() ? c10::hip::getCurrentHIPStream(t.get_device()).stream() : nullptr;
 }
 
+// What goes to that stream is recorded into a graph (or its state cannot be told).
+inline bool capturing(const at::Tensor &t)
+{
+    hipStreamCaptureStatus status;
+    return t.is_cuda() && (hipStreamIsCapturing(static_cast<hipStream_t>(current_stream(t)), &status) != hipSuccess ||
+                           status != hipStreamCaptureStatusNone);
+}
+
 inline uint8_t *bytes_of(const at::Tensor &t) { return static_cast<uint8_t *>(t.data_ptr()); }
 
 // Runs `body` (which returns the library's status) as a wrapper's call: the pair of outputs, or None.
@@ -256,6 +264,7 @@ PyObject *quant_from_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
             if (idx && rows < ((int64_t)1 << 31) && K < ((int64_t)1 << 31) && rows * K >= WORTH_ASKING) {
                 const int64_t size = lib.gather_workspace(M, K, rows, q, ld[0]);
                 if (size > 0) {
+                    need(!capturing(x)); // whose memory a graph may keep is looked up by the wrapper
                     const at::Tensor work = new_tensor({size}, at::kByte, x, false);
                     return lib.quant_gather(bytes_of(x), scale, M, K, idx, rows, q, ld[0], sf, ld[1], work.data_ptr(), size,
                                             current_stream(x));

@@ -1,5 +1,6 @@
 """Host-side checks that need no GPU: the C-ABI library loads, exports every symbol the
 header declares, and rejects bad arguments before anything is launched."""
+import contextlib
 import ctypes
 import os
 import re
@@ -39,6 +40,22 @@ def test_gather_workspace():
     for M, K, n in ((8192, 7168, 65536), (65536, 7168, 131072), (8192, 7168, 32767 + 16384), (131072, 1536, 1 << 20)):
         window = -(-n // 32)
         assert size(M, K, n, 64, K // 2) == 4 * ((M + 1) * 64 + 128 + 128 * window)
+
+
+@pytest.mark.parametrize("captured,pool,given", [(False, (0, 0), True), (True, (7, 0), True), (True, (0, 0), False), (True, None, False)])
+def test_gather_gets_memory_only_where_no_graph_outlives_it(monkeypatch, captured, pool, given):
+    """Under a capture that the allocator does not know of (its memory comes from no pool of a graph, or it cannot say) a gather gets
+    no memory to work in: the graph would keep the address of what is given back when the call returns."""
+    def snapshot():
+        if pool is None:
+            raise RuntimeError("no snapshot")
+        return [{"address": 0, "total_size": 1, "segment_pool_id": (9, 9)}, {"address": 1, "total_size": 1 << 62, "segment_pool_id": pool}]
+
+    monkeypatch.setattr(torch.cuda, "device", lambda device: contextlib.nullcontext())
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: captured)
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", snapshot)
+    work = binding._gather_workspace(64, torch.device("cpu"))
+    assert (work is not None) == given and (work is None or work.numel() == 64)
 
 
 def test_status_strings():

@@ -1,12 +1,14 @@
 """GPU parity of the routed quantizers on both sides of every rule that picks a kernel: a gathered or scattered row is
 the oracle's flat row, and bytes that no row owns keep their contents."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2603_02731_amd as mx
 from oracle import parallel as par
-from paper_2603_02731_amd import synth
+from paper_2603_02731_amd import binding, synth
 from tests.test_gpu_parity import DEV, assert_same, dev, host
 
 pytestmark = pytest.mark.gpu
@@ -320,6 +322,69 @@ def test_gather_by_lists_under_capture():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(q, want[0]) and torch.equal(sf, want[1]), f"replay {i}"
+
+
+def hip_runtime():
+    """The HIP runtime that PyTorch has loaded."""
+    with open("/proc/self/maps") as f:
+        return ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+
+
+@pytest.mark.parametrize("by", ["torch", "hip"])
+def test_memory_of_a_captured_gather(by, monkeypatch):
+    """A graph of PyTorch's has a pool that its memory to work in stays in.  A graph that the program captures by HIP's own calls has
+    none: it takes the kernels without, and what the allocator gives to other tensors afterwards is theirs."""
+    K, M, n = 2048, 16391, 131085
+    rng, x8, s, _, _ = source(M, K, 2)
+    x, xs = dev(x8), dev(s)
+    idx = dev(index_of("padded", M, n, rng))
+    stream, routes = torch.cuda.Stream(), []
+
+    class Recording:
+        def __getattr__(self, name):
+            routes.append(name)
+            return getattr(library, name)
+
+    library, recording = mx.lib(), Recording()
+    q, sf = (torch.empty(n, w, dtype=torch.uint8, device=DEV) for w in (K // 2, K // 32))
+    size = library.mxfp4_quant_from_fp8_gather_workspace(M, K, n, q.data_ptr(), K // 2)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        mx.mxfp4_quant_from_fp8(x, xs, idx, q=q, sf=sf)  # its memory is with the allocator now
+        stream.synchronize()
+        monkeypatch.setattr(binding, "lib", lambda: recording)
+        if by == "torch":
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                mx.mxfp4_quant_from_fp8(x, xs, idx, q=q, sf=sf)
+            replay = graph.replay
+        else:
+            hip, raw, handle = hip_runtime(), ctypes.c_void_p(), ctypes.c_void_p(stream.cuda_stream)
+            assert hip.hipStreamBeginCapture(handle, 1) == 0  # 1: other threads may do as they like
+            try:
+                mx.mxfp4_quant_from_fp8(x, xs, idx, q=q, sf=sf)
+            finally:
+                ended = hip.hipStreamEndCapture(handle, ctypes.byref(raw))
+            assert ended == 0
+            executable = ctypes.c_void_p()
+            assert hip.hipGraphInstantiate(ctypes.byref(executable), raw, None, None, ctypes.c_size_t(0)) == 0
+
+            def replay():
+                assert hip.hipGraphLaunch(executable, handle) == 0
+        monkeypatch.undo()
+        assert ("mxfp4_quant_from_fp8_gather" in routes) == (by == "torch") and ("mxfp4_quant_from_fp8" in routes) == (by == "hip")
+        others = [torch.full((size,), 0x5A, dtype=torch.uint8, device=DEV) for _ in range(4)]
+        for i in range(3):
+            idx.copy_(idx.roll(i * 977))
+            want = mx.mxfp4_quant_from_fp8(x, xs, idx)
+            q.fill_(1)
+            sf.fill_(7)
+            replay()
+            stream.synchronize()
+            assert torch.equal(q, want[0]) and torch.equal(sf, want[1]), f"replay {i}"
+            assert all(bool((t == 0x5A).all()) for t in others), f"replay {i}: another tensor was written to"
+        if by == "hip":
+            assert hip.hipGraphExecDestroy(executable) == 0 and hip.hipGraphDestroy(raw) == 0
 
 
 def test_gather_sides_of_the_row_counts():
