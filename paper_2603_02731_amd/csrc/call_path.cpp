@@ -265,9 +265,14 @@ PyObject *quant_from_fp8(PyObject *, PyObject *const *a, Py_ssize_t n)
                 const int64_t size = lib.gather_workspace(M, K, rows, q, ld[0]);
                 if (size > 0) {
                     need(!capturing(x)); // whose memory a graph may keep is looked up by the wrapper
-                    const at::Tensor work = new_tensor({size}, at::kByte, x, false);
-                    return lib.quant_gather(bytes_of(x), scale, M, K, idx, rows, q, ld[0], sf, ld[1], work.data_ptr(), size,
-                                            current_stream(x));
+                    at::Tensor work;
+                    try {
+                        work = new_tensor({size}, at::kByte, x, false);
+                    } catch (const c10::OutOfMemoryError &) { // it is done without; the allocator has tried hard, once is enough
+                    }
+                    if (work.defined())
+                        return lib.quant_gather(bytes_of(x), scale, M, K, idx, rows, q, ld[0], sf, ld[1], work.data_ptr(), size,
+                                                current_stream(x));
                 }
             }
             return lib.quant(bytes_of(x), scale, M, K, idx, rows, q, ld[0], sf, ld[1], current_stream(x));

@@ -387,6 +387,27 @@ def test_memory_of_a_captured_gather(by, monkeypatch):
             assert hip.hipGraphExecDestroy(executable) == 0 and hip.hipGraphDestroy(raw) == 0
 
 
+def test_gather_where_there_is_no_memory_to_work_in():
+    """An allocator at its limit, which frees what it holds before it gives up, is asked once, and the call is done without."""
+    K, M, n = 2048, 16391, 131085
+    rng, x8, s, _, _ = source(M, K, 3)
+    x, xs, idx = dev(x8), dev(s), dev(index_of("padded", M, n, rng))
+    want = mx.mxfp4_quant_from_fp8(x, xs, idx)
+    q, sf = (torch.zeros(n, w, dtype=torch.uint8, device=DEV) for w in (K // 2, K // 32))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    full = [torch.empty(1 << 20, dtype=torch.uint8, device=DEV) for _ in range(20)]  # so that what is reserved is in use
+    torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        before = torch.cuda.memory_stats()["num_ooms"]
+        got = mx.mxfp4_quant_from_fp8(x, xs, idx, q=q, sf=sf)
+        asked = torch.cuda.memory_stats()["num_ooms"] - before
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert got[0] is q and torch.equal(q, want[0]) and torch.equal(sf, want[1]) and len(full) == 20
+    assert asked == 1
+
+
 def test_gather_sides_of_the_row_counts():
     """Fewer rows than four per workgroup, and fewer than two output rows per source row, on the lane-wise side."""
     for M, n in ((4 * GROUPS - 1, least(4 * GROUPS, 7168) + 100), (32 * GROUPS, 64 * GROUPS - 1), (32 * GROUPS, 64 * GROUPS)):
