@@ -35,7 +35,8 @@ def test_gather_workspace():
     for M, K, n, at, ld in ((0, 7168, 65536, 64, 3808), (8192, 7168, 0, 64, 3808), (-1, 7168, 65536, 64, 3808), (8192, 0, 65536, 64, 3808),
                             (1024, 7168, 8192, 64, 3808), (32769, 7168, 65537, 64, 3808), (2048, 7168, 65536, 64, 3808),
                             (8192, 7168, 65536, 72, 3808), (8192, 7168, 65536, 64, 3592), (131072, 1024, 1 << 20, 64, 512),
-                            (131072, 7168, (1 << 20) + 1, 64, 3808), (1 << 62, 1 << 24, 1 << 62, 64, 3808)):
+                            (131072, 7168, (1 << 20) + 1, 64, 3808), (1 << 62, 1 << 24, 1 << 62, 64, 3808), (1 << 19, 5 << 42, 1 << 20, 64, 3808),
+                            (1 << 19, 1 << 31, 1 << 20, 64, 3808)):  # the last two: products past 64 bits, and rows no call takes
         assert size(M, K, n, at, ld) == 0, (M, K, n, at, ld)
     for M, K, n in ((8192, 7168, 65536), (65536, 7168, 131072), (8192, 7168, 32767 + 16384), (131072, 1536, 1 << 20)):
         window = -(-n // 32)
