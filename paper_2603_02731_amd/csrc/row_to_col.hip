@@ -49,7 +49,7 @@ struct RowToColArgs {
     uint32_t stage_in; // full tiles fetch their nibbles with 16-byte loads and re-slice them through LDS
     uint32_t mbm;      // row tiles per macro block of the tile order (one matrix; experts: see the lookup)
     FastDiv by_tiles_k; // experts only
-    uint32_t few;       // experts only: at most one and a half tiles per compute unit
+    uint32_t few;       // row_to_col_in_aligned_pieces
 };
 
 // Macro block of the tile order: 4 column tiles; row tiles by macro_block_rows for one matrix (32 at
@@ -108,8 +108,8 @@ __device__ __noinline__ uint64_t requant_slice_int(const uint8_t *src, size_t sr
 //    hardware's own dispatch of one short workgroup per tile is the better scheduler here.
 //  * Macro blocks of 8 / 16 / 64 row tiles: 103 / 108 / 98 us; 1 to 28 column tiles: no difference.  Dword loads
 //    (one per row and lane) instead of the 16-byte loads re-sliced through LDS: 95 us.
-// GENERAL: launches of few tiles and of more than 64 experts.  One matrix and the other launches have an instance without what
-// those need, which cost [65536, 7168] 0.6 % by its presence.
+// GENERAL: launches of more than 64 experts.  One matrix and the other launches have an instance without what those need, which
+// cost [65536, 7168] 0.6 % by its presence.
 template <bool GENERAL>
 __global__ void __launch_bounds__(T_THREADS) row_to_col_kernel(const RowToColArgs a)
 {
@@ -439,11 +439,7 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
     const uint32_t total = a.tiles_m * a.tiles_k;
     a.stage_in = total >= 3u * compute_units() ? 1u : 0u; // at least 3 tiles per compute unit
     const dim3 grid((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD);
-    // A few tiles per compute unit (more than 256 experts, totals that look padded and are not: col_in_small_tiles takes the others):
-    // what an unaligned 16-byte store costs a wave to issue shows (by these tiles un-padded [2000, 2048] in 8 experts 7.9 -> 7.1 us,
-    // [8000, 1024] in 64 10.2 -> 9.4, [3000, 512] in 128 8.4 -> 7.8); with more of them the memory waits for the additional requests
-    // ([16384, 2048] in 16 13.8 -> 14.1, [65536, 7168] in 32 158 -> 170).
-    a.few = 2 * total <= 3 * compute_units() ? 1u : 0u;
+    a.few = expert_offsets && row_to_col_in_aligned_pieces(M, K, num_experts, compute_units()) ? 1u : 0u;
     // Large ragged splits: every tile shares its outer 64-byte segments with its neighbours where the k-rows of an expert are
     // not whole segments.  The two halves meet in the L2 if the tiles finish close together; what leaves it half written costs
     // the memory a read, modify and write, once the matrix is too large for the 256 MB memory-side cache.  Three workgroups per
@@ -454,7 +450,7 @@ hipError_t launch_row_to_col(const uint8_t *q_row, const uint8_t *sf_row, const 
     // [32768, 4096], 37.0 -> 38.1 at [65536, 2048]), nor with 512 rows per expert (135 -> 151 for 128 of 513).
     const bool three_per_cu = expert_offsets && M * K >= (int64_t)32768 * 7168 && M >= 1024 * (int64_t)num_experts;
     const uint32_t more = three_per_cu ? lds_for_three() : 0u;
-    if (expert_offsets && (a.few != 0u || num_experts > 64))
+    if (expert_offsets && num_experts > 64)
         hipLaunchKernelGGL(row_to_col_kernel<true>, grid, dim3(T_THREADS), more, stream, a);
     else
         hipLaunchKernelGGL(row_to_col_kernel<false>, grid, dim3(T_THREADS), more, stream, a);

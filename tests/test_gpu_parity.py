@@ -16,6 +16,7 @@ from tests.test_oracle_quant import scale_sweep
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+UNITS = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
 
 
 def dev(a):

@@ -1,6 +1,6 @@
 """GPU parity of row->col where tiles write whole 64-byte segments of the output (one large matrix whose k-rows are no whole
-segments, on both sides of the rule), of large splits of any length, and of small un-padded splits, whose k-rows leave
-in aligned pieces."""
+segments, on both sides of the rule), of large splits of any length, and of small launches of many un-padded splits, whose k-rows
+leave in aligned pieces."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +9,8 @@ import paper_2603_02731_amd as mx
 from oracle import parallel as par
 from oracle import ref
 from paper_2603_02731_amd import synth
-from tests.test_gpu_parity import DEV, assert_same, host
+from tests.rules import aligned_pieces
+from tests.test_gpu_parity import DEV, UNITS, assert_same, host
 
 pytestmark = pytest.mark.gpu
 
@@ -76,9 +77,12 @@ def test_large_splits(rows, K):
 
 
 @pytest.mark.parametrize("rows", [[1, 31, 32, 33, 29, 30], [255, 256, 257, 511, 0, 513, 37], [1023, 2, 225, 226, 227, 240, 241]])
+@pytest.mark.parametrize("K,more", [(384, 0), (256, 250), (128, 310)])
 @pytest.mark.parametrize("off", [0, 16])
-def test_small_splits_leave_in_aligned_pieces(rows, off):
-    K = 384
+def test_small_splits_leave_in_aligned_pieces(rows, K, more, off):
+    """With so many experts more that small tiles do not take them: these leave in pieces on 16-byte boundaries."""
+    rows = rows + [(7 * i) % 67 for i in range(more)] + ([300, 15] if more else [])
+    assert aligned_pieces(sum(rows), K, len(rows), UNITS) == (more > 0)
     o = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
     q, sf = synth.random_mxfp4(int(o[-1]), K, seed=len(rows), scale_spread=5)
     q, sf = q.numpy(), sf.numpy()

@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 from paper_2603_02731_amd import build
+from tests.rules import aligned_pieces
 
 PROGRAM = r"""
 #include <cstdio>
@@ -29,6 +30,9 @@ int main(int argc, char **argv)
                 }
         printf("%d %d\n", (int)row_to_col_in_segments(M, K), wraps);
     }
+    long long M, K, E, units;
+    while (argc == 1 && scanf("%lld %lld %lld %lld", &M, &K, &E, &units) == 4)
+        printf("%d\n", (int)row_to_col_in_aligned_pieces(M, K, (int)E, units));
 }
 """
 
@@ -44,7 +48,11 @@ def rule(tmp_path_factory):
     subprocess.run([cxx, "-std=c++17", "-Wall", "-Werror", "-I", build.CSRC, str(folder / "rule.cpp"), "-o",
                     str(folder / "rule")], check=True)
 
-    def ask(cases):
+    def ask(cases=None, experts=None):
+        if experts is not None:
+            text = "".join(" ".join(map(str, c)) + "\n" for c in experts)
+            out = subprocess.run([str(folder / "rule")], input=text, check=True, capture_output=True, text=True).stdout.split()
+            return [bool(int(v)) for v in out]
         out = subprocess.run([str(folder / "rule")] + [str(v) for c in cases for v in c], check=True, capture_output=True,
                              text=True).stdout.split()
         return [(bool(int(a)), int(b)) for a, b in zip(out[0::2], out[1::2])]
@@ -66,3 +74,10 @@ def test_no_offset_wraps_where_the_kernel_is_taken(rule):
 def test_size_from_which_it_is_taken(rule):
     assert [t for t, _ in rule([(45088, 4096), (45024, 4096), (45056, 4096), (180320, 1024), (32, 128), (2 ** 24 - 32, 2 ** 24)])] == \
         [True, False, False, True, False, True]
+
+
+def test_the_tests_state_the_same_rule_for_aligned_pieces(rule):
+    cases = [(M, K, E, units) for M in (1, 255, 257, 16384, 32000) for K in (128, 256, 384, 4096)
+             for E in (1, 2, 64, 256, 257, 320, 383, 384, 1024) for units in (64, 256, 304)]
+    assert rule(experts=cases) == [aligned_pieces(*c) for c in cases]
+    assert any(aligned_pieces(*c) for c in cases)
