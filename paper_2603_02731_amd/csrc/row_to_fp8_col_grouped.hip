@@ -28,6 +28,7 @@
 #include "fp8_col_tile.hpp"
 #include "mxfp4_device.hpp"
 #include "mxfp4_kernels.hpp"
+#include "row_to_fp8_col_rule.hpp"
 
 namespace mxfp4 {
 
@@ -214,12 +215,6 @@ __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(cons
     if (look && wv < GROUP / 64u)
         stage_scales(sfl, tid);
 
-    // the bytes of other lanes of a wave: ordered by the fence
-    auto wave_fence = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     // the lane's slices, a dword (8 columns) per row: 32 rows of the tile, 8 of the near and 8 of the far half
     uint32_t w[32], wl[REQUANT ? 16 : 8];
     {
@@ -633,21 +628,9 @@ static int64_t tiles_at_most(int64_t M, int64_t K, int32_t num_experts)
     return ((M + TILE_M - 1) / TILE_M + num_experts) * ((K + TILE_K - 1) / TILE_K);
 }
 
-// Of the launches that col_in_small_tiles leaves, those of about one round of the other kernels' workgroups (two per compute unit, one pass), as far as the number of tiles
-// can be told, whose total row count says that the splits may be padded, are left to them: nothing is shared or the pieces are
-// aligned, and what a workgroup takes longer here is not made up for.  Measured (us, own rows / segments, re-quantization): padded
-// to 16, [8864, 512] in 64 experts 7.6 / 9.0, [2064, 2048] in 8 7.7 / 9.3, [4112, 4096] in 16 11.2 / 12.4; to 128, [9984, 1792] in 64
-// 9.2 / 10.4, [10752, 2432] in one 10.9 / 11.3, [38144, 768] in 64 10.9 / 10.6; above the line, [16128, 2048] in 16 18.6 / 16.1,
-// [11136, 3968] in one 18.8 / 15.6; not padded, [6180, 1280] in 16 12.1 / 10.6.  For scale alignment only totals that are multiples of
-// 16 and not of 128: one of 128 may as well be that of un-padded splits, which lose more by their own rows than padded ones by
-// segments (padded / the same un-padded, own rows / segments: [4224, 3072] in 4 7.3 / 7.5, 11.9 / 10.1; [9984, 2048] in 32 8.9 / 9.2,
-// 13.7 / 11.9; [14208, 2048] in 4 10.2 / 9.8, 14.5 / 12.8).  Those kernels look for one of at most 128 experts: the longer lookup
-// costs their flat form 1 %.
 bool fp8_col_in_segments(int64_t M, int64_t K, int32_t num_experts, bool requant)
 {
-    const int64_t half_tiles = (M / (TILE_M / 2) + num_experts) * ((K + TILE_K - 1) / TILE_K); // experts end in half a tile each
-    const bool padded = M % 16 == 0 && (requant || M % 128 != 0);
-    return num_experts > 128 || !padded || 10 * half_tiles > 43 * (int64_t)compute_units();
+    return fp8_col_in_segments(M, K, num_experts, requant, compute_units());
 }
 
 hipError_t launch_row_to_fp8_col_grouped(const uint8_t *q_row, const uint8_t *sf_row, const int32_t *expert_offsets,

@@ -17,6 +17,20 @@ def small_tiles(kind, M, K, E=0, units=256):
     return (2 * (M // 128) + E) * (K // 128) <= line * units
 
 
+def own_rows(kind, M, K, E, units=256):
+    """Not by small tiles, and the FP8-column kernels that write their own rows take these rows of E experts."""
+    padded = M % 16 == 0 and (kind == "requant" or M % 128 != 0)
+    return (not small_tiles(kind, M, K, E, units) and E <= 128 and padded and
+            10 * (M // 128 + E) * -(-K // 256) <= 43 * units)
+
+
+def times_as_wide(kind, M, K, E=0, units=256, own=False):
+    """How often rows of K columns are repeated beside each other until small tiles leave them (to the FP8-column kernels that write
+    their own rows, where `own`, else to those that do not)."""
+    return next(n for n in range(1, 4000) if not small_tiles(kind, M, n * K, E, units) and
+                (kind == "mxfp4" or E == 0 or own_rows(kind, M, n * K, E, units) == own))
+
+
 def aligned_pieces(M, K, E, units=256):
     """Row -> column by tiles of 256 x 256 whose pieces are put together on 16-byte boundaries."""
     return E > 256 and 2 * (-(-M // 256) + E) * -(-K // 256) <= 3 * units
