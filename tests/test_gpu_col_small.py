@@ -8,12 +8,11 @@ import paper_2603_02731_amd as mx
 from oracle import parallel as par, ref
 from paper_2603_02731_amd import synth
 from tests.test_gpu_fp8_col_segments import SPLITS
-from tests.rules import small_tiles
-from tests.test_gpu_parity import DEV, assert_same, host
+from tests.rules import small_tiles, times_as_wide
+from tests.test_gpu_parity import DEV, UNITS, assert_same, host
 
 pytestmark = pytest.mark.gpu
 
-UNITS = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
 KINDS = {"mxfp4": 11, "align": 11, "requant": 12}  # quarters of a compute unit's tiles up to which tiles are small
 
 
@@ -54,6 +53,8 @@ def test_scales(kind, scales):
     q[128:256, :64] = 0x80  # zeros of either sign, a whole group of 128 columns
     q[300:340, 64:80] = 0
     check(kind, q, sf, f"{kind} {scales}")
+    n = times_as_wide(kind, 640, 896, units=UNITS)  # the same by the larger tiles
+    check(kind, q.repeat(1, n), sf.repeat(1, n), f"{kind} {scales}, {n} times as wide")
 
 
 @pytest.mark.parametrize("kind", KINDS)
@@ -146,8 +147,12 @@ def test_numbers_of_experts(kind, E):
 
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("scales", SCALES)
-def test_scales_of_experts(kind, scales):
-    """Row scales beyond FP32 and NaN bytes in last tiles that experts do not fill."""
+@pytest.mark.parametrize("above", [False, True])
+def test_scales_of_experts(kind, scales, above):
+    """Row scales beyond FP32 and NaN bytes in last tiles that experts do not fill, and in every row that larger tiles convert."""
     center, spread, nan = SCALES[scales]
-    check_experts(kind, [33, 161, 0, 128, 7, 300], 384, seed=5, q_off=4, out_off=16, scale_center=center, scale_spread=spread,
-                  nan_scale_frac=nan)
+    rows, K = [33, 161, 0, 128, 7, 300], 2176 if above else 384
+    while above and small(kind, rows, K):
+        rows = rows + [33, 561, 0, 128, 7, 300]
+    assert small(kind, rows, K) == (not above)
+    check_experts(kind, rows, K, seed=5, q_off=4, out_off=16, scale_center=center, scale_spread=spread, nan_scale_frac=nan)

@@ -2,8 +2,11 @@
 
 Every comparison is exact equality of packed nibbles, scale bytes, E4M3 bytes and FP32
 scale bit patterns.  Sizes span several tiles and ragged tails; the edge cases of each
-conversion (zero blocks, NaN, subnormals, saturation, huge scale spreads) are included.
+conversion (zero blocks, NaN, subnormals, saturation, huge scale spreads) are included, by
+the tiles of small matrices and by those of large ones.
 """
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -12,6 +15,7 @@ import paper_2603_02731_amd as mx
 from oracle import ref
 from paper_2603_02731_amd import synth
 from oracle import parallel as par
+from tests.rules import small_tiles, times_as_wide
 from tests.test_oracle_quant import scale_sweep
 
 pytestmark = pytest.mark.gpu
@@ -53,11 +57,27 @@ def check_dequant(q, sf):
     assert_same(host(x), wx, "dequant E4M3 bytes")
 
 
+def check_wide(kind, convert, q, sf, want, want_scales):
+    """The same columns again and again beside each other: as often as it takes for tiles of 256 x 256, and for their nibbles to arrive
+    by 16-byte loads (where the rows fill a tile).  want, want_scales: the oracle's result for the columns once."""
+    M, K = q.shape[0], 2 * q.shape[1]
+    staged = (3 if kind == "mxfp4" else 4) * UNITS  # tiles
+    want, want_scales = dev(want), dev(want_scales)
+    for n in (times_as_wide(kind, M, K, units=UNITS), -(-(-(-staged // -(-M // 256)) * 256) // K)):
+        assert not small_tiles(kind, M, n * K, units=UNITS)
+        data, scales = convert(dev(q).repeat(1, n), dev(sf).repeat(1, n))
+        for got, w, what in ((scales, want_scales, "scales"), (data, want, "elements")):
+            got, w = (t.view(torch.int32) if t.dtype == torch.float32 else t for t in (got, w))
+            bad = (got.view(n, *w.shape) != w).sum().item()
+            assert bad == 0, f"{kind} {what}, {n} times as wide: {bad} differ"
+
+
 def check_row_to_col(q, sf):
     qc, sc = mx.mxfp4_row_to_col(dev(q), dev(sf))
     wq, ws = par.row_to_col(q, sf)
     assert_same(host(sc), ws, "row->col scale bytes")
     assert_same(host(qc), wq, "row->col nibbles")
+    check_wide("mxfp4", mx.mxfp4_row_to_col, q, sf, wq, ws)
 
 
 # ------------------------------------------------------------------ config 1: tiny round trip
@@ -329,6 +349,7 @@ def check_row_to_fp8_col(q, sf):
     wx, wxs = ref.row_to_fp8_col(q, sf)
     assert_same(host(xs), wxs, "row->FP8 col: group scales")
     assert_same(host(x), wx, "row->FP8 col: E4M3 bytes")
+    check_wide("align", mx.mxfp4_row_to_fp8_col, q, sf, wx, wxs)
 
 
 @pytest.mark.parametrize("M,K,center,spread,nan", [
@@ -503,6 +524,7 @@ def check_row_to_fp8_col_requant(q, sf):
     wx, wxs = ref.row_to_fp8_col(q, sf, requant=True)
     assert_same(host(xs), wxs, "row->FP8 col (requant): group scales")
     assert_same(host(x), wx, "row->FP8 col (requant): E4M3 bytes")
+    check_wide("requant", functools.partial(mx.mxfp4_row_to_fp8_col, requant=True), q, sf, wx, wxs)
 
 
 @pytest.mark.parametrize("M,K,center,spread,nan", [
@@ -591,13 +613,18 @@ def test_quant_scatter_equals_gather_and_leaves_other_rows_alone():
     assert_same(got[one[:, 0], K // 2:], fsf, "scatter into records: scale bytes")
 
 
-@pytest.mark.parametrize("K,M,fan,pad", [(512, 37, 8, 0), (7168, 133, 8, 0), (7168, 64, 11, 32), (640, 203, 3, 12),
-                                          (1536, 50, 1, 0), (16384, 9, 2, 0), (32768, 5, 9, 0), (2048, 130, 8, 16)])
-def test_quant_scatter_whole_rows_through_lds(K, M, fan, pad):
-    """Outputs whose rows start on 16-byte boundaries take the kernel that writes whole rows out of LDS: records
-    of K/2 + K/32 bytes (plus padding), 1, 2 or 4 rows per workgroup, scale bytes as 16-byte pieces (K % 512 == 0)
-    or dwords, fan-outs beyond the eight prefetched indices, row counts that end inside a workgroup, entries that
-    point nowhere; the bytes between and around the records stay as they were."""
+@pytest.mark.parametrize("K,M,fan,pad,whole", [
+    (512, 37, 8, 0, False), (7168, 133, 8, 0, False), (7168, 64, 11, 32, False), (640, 203, 3, 12, False), (1536, 50, 1, 0, False),
+    (16384, 9, 2, 0, False), (32768, 5, 9, 0, False), (2048, 130, 8, 16, False),
+    (7168, 233, 8, 0, True), (7168, 221, 11, 32, True), (16384, 97, 2, 0, True), (32768, 49, 9, 0, True), (6272, 255, 3, 16, True),
+    (2048, 3085, 8, 16, True), (2176, 2894, 3, 0, True)])
+def test_quant_scatter_whole_rows_through_lds(K, M, fan, pad, whole):
+    """Outputs whose rows start on 16-byte boundaries.  From 1.5 Mi elements of rows of 6144 and longer, and from 6 Mi of shorter ones
+    of 2048 on, a workgroup or a wave writes whole rows out of LDS; smaller launches, and the rest, are a lane's per chunk.  Records
+    of K/2 + K/32 bytes (plus padding), scale bytes as 16-byte pieces (K % 512 == 0) or dwords, fan-outs beyond the eight
+    prefetched indices, row counts that end inside a workgroup, entries that point nowhere; the bytes between and around
+    the records stay as they were."""
+    assert (M * K > (6 << 20 if K < 6144 else 3 << 19)) == whole
     rng = np.random.default_rng(K + M)
     x8, s = synth.student_t_fp8(M, K, seed=K % 97)
     x8, s = x8.numpy(), s.numpy()
