@@ -29,13 +29,13 @@ def source(M, K, seed):
 
 def outputs(rows, K, layout):
     """(buffer, q, sf, ld_q, ld_sf, views): records on 16-byte boundaries with a gap, or two planes with rows on
-    8- and 4-byte boundaries; guard bytes around all of it."""
+    8- and 4-byte boundaries or without gaps (dense: both on 16 bytes where K % 512 == 0); guard bytes around all of it."""
     nq, ns = K // 2, K // 32
     if layout == "records":
         ld_q = ld_sf = (nq + ns + 15) // 16 * 16 + 16
         at_q, at_sf, size = GUARD, GUARD + nq, GUARD + rows * ld_q
     else:
-        step = {"planes": 16, "planes8": 8, "planes64": 64}[layout]
+        step = {"planes": 16, "planes8": 8, "planes64": 64, "dense": 0}[layout]
         ld_q, ld_sf = nq + step, ns + step // 2
         at_q, at_sf = GUARD, (GUARD + rows * ld_q + 15) // 16 * 16
         size = at_sf + rows * ld_sf
@@ -71,13 +71,14 @@ def test_scatter_kernels(K, M, fan, layout):
     check(buf, at, ld_q, ld_sf, K, dst[~nowhere], wq[src], wsf[src])
 
 
-@pytest.mark.parametrize("layout", ["records", "planes"])
+@pytest.mark.parametrize("layout", ["records", "planes", "dense"])
 @pytest.mark.parametrize("K,M,fan", [(1024, 301, 4), (1024, 301, 5), (640, 77, 17),  # destinations held by fours and eights, and past them
                                      (2048, 3072, 2), (2048, 3073, 2), (2176, 2891, 9), (2176, 2892, 9),  # lanes, a wave per row
-                                     (6016, 1045, 3), (6016, 1046, 3), (6144, 256, 2), (6144, 257, 2), (6272, 251, 9),  # a workgroup
+                                     (6016, 1045, 3), (6016, 1046, 3), (6144, 256, 2), (6144, 257, 2), (6272, 251, 9), (7168, 221, 9),  # a workgroup
                                      (7808, 201, 4), (7808, 202, 4), (98304, 16, 2), (98304, 17, 2)])  # and rows of several segments
 def test_scatter_sides_of_the_small_launches(K, M, fan, layout):
-    """Both sides of the sizes up to which a lane takes a chunk of long rows, and the kernels above them."""
+    """Both sides of the sizes up to which a lane takes a chunk of long rows, and the kernels above them, which take records and dense
+    planes (scale rows on 16 bytes); other planes are the lanes'."""
     test_scatter_kernels(K, M, fan, layout)
 
 
@@ -250,6 +251,17 @@ def test_gather_by_lists(K, M, n, kind, layout):
     gathered(rng, x8, s, wq, wsf, index_of(kind, M, n, rng), K, layout)
 
 
+@pytest.mark.parametrize("K,M,n,kind", [(7168, 4099, 65537, "padded"), (7168, 6401, 33003, "crowd"), (8192, 6001, 33001, "mixed"),
+                                        (6656, 7001, 36003, "few"), (8192, 9001, 33001, "power"), (7168, 16385, 37450, "one"),
+                                        (6272, 7001, 37003, "padded")])
+def test_gather_by_lists_into_dense_planes(K, M, n, kind):
+    """What a call without outputs gets: rows of five copies and more by workgroups, of fewer by waves, nibbles and scale bytes of a row
+    in two places, as 16-byte pieces where K % 512 == 0."""
+    rng, x8, s, wq, wsf = source(M, K, K + n)
+    assert mx.lib().mxfp4_quant_from_fp8_gather_workspace(M, K, n, 64, K // 2) > 0
+    gathered(rng, x8, s, wq, wsf, index_of(kind, M, n, rng), K, "dense")
+
+
 @pytest.mark.parametrize("K,M,n,kind", [(1536, 33000, 524288, "padded"), (1536, 33000, 524289, "crowd"), (1536, 150000, 1048576, "mixed"),
                                         (1536, 150000, 1048577, "mixed"), (2048, 524000, 1048003, "padded")])
 def test_gather_by_lists_of_a_long_index(K, M, n, kind):
@@ -396,15 +408,19 @@ def test_gather_where_there_is_no_memory_to_work_in():
     q, sf = (torch.zeros(n, w, dtype=torch.uint8, device=DEV) for w in (K // 2, K // 32))
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
-    full = [torch.empty(1 << 20, dtype=torch.uint8, device=DEV) for _ in range(20)]  # so that what is reserved is in use
+    size = mx.lib().mxfp4_quant_from_fp8_gather_workspace(M, K, n, q.data_ptr(), K // 2)
+    full = []
     torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory)
     try:
+        with pytest.raises(torch.OutOfMemoryError):
+            while len(full) < 10000:
+                full.append(torch.empty(size, dtype=torch.uint8, device=DEV))
         before = torch.cuda.memory_stats()["num_ooms"]
         got = mx.mxfp4_quant_from_fp8(x, xs, idx, q=q, sf=sf)
         asked = torch.cuda.memory_stats()["num_ooms"] - before
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
-    assert got[0] is q and torch.equal(q, want[0]) and torch.equal(sf, want[1]) and len(full) == 20
+    assert got[0] is q and torch.equal(q, want[0]) and torch.equal(sf, want[1])
     assert asked == 1
 
 
