@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(THREADS) col_small_kernel(const col_small::Arg
         if (sub == 0u && (cg & 3u) == 0u)
             s_max[rg][kb] = (uint16_t)(finite | any << 8);
         __syncthreads();
-                    uint32_t bmax = 0, flags = 0;
+        uint32_t bmax = 0, flags = 0;
 #pragma unroll
         for (uint32_t g = 0; g < 4u; ++g) {
             const uint32_t m = s_max[g][kb];

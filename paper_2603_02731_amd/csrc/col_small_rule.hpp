@@ -69,7 +69,9 @@ constexpr int EXPERTS_MAX = 256; // the lookup of more takes registers that cost
 constexpr bool col_in_small_tiles(int64_t M, int64_t K, int32_t num_experts, ColKind kind, int64_t units)
 {
     const int64_t tiles_k = K / col_small::TILE, E = num_experts;
-    auto pick = [kind](int64_t mxfp4, int64_t align, int64_t requant) { return kind == COL_MXFP4 ? mxfp4 : kind == COL_ALIGN ? align : requant; };
+    auto pick = [kind](int64_t mxfp4, int64_t align, int64_t requant) {
+        return kind == COL_MXFP4 ? mxfp4 : kind == COL_ALIGN ? align : requant;
+    };
     if (E == 0) // quarters of a tile per compute unit
         return 4 * ((M + col_small::TILE - 1) / col_small::TILE * tiles_k) <= pick(11, 11, 12) * units;
     if (E > col_small::EXPERTS_MAX)

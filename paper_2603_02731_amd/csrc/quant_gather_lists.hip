@@ -277,7 +277,8 @@ int64_t gather_lists_workspace(int64_t M_src, int64_t K, int64_t M_out, const ui
 {
     const bool many = M_out / 4 >= M_src;
     if (M_src <= 0 || K <= 0 || K >= (int64_t)1 << 31 || M_out / 2 < M_src || M_out / 24 > M_src || M_out > ENTRIES_MOST ||
-        K < (many ? 1536 : 2048) || M_out * K < (many ? (int64_t)220 << 20 : (int64_t)256 << 20) || ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) != 0u)
+        K < (many ? 1536 : 2048) || M_out * K < (many ? (int64_t)220 << 20 : (int64_t)256 << 20) ||
+        ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) != 0u)
         return 0;
     const int64_t window = (M_out + WINDOWS - 1) / WINDOWS;
     return 4 * ((M_src + 1) * PLACES + GROUPS + window * GROUPS);

@@ -133,7 +133,8 @@ __device__ __forceinline__ u32x4 combined_halves(const float (&amax)[8])
 template <bool REQUANT>
 __global__ void __launch_bounds__(THREADS, 3) row_to_fp8_col_grouped_kernel(const fp8col_grouped::Args a)
 {
-    __shared__ alignas(16) uint8_t s_tile[32 * CPP * ROW > WAVES * 8192 ? 32 * CPP * ROW : WAVES * 8192]; // [cl*32 + cg][window row - FAR]: the k-rows of a pass
+    // [cl*32 + cg][window row - FAR]: the k-rows of a pass
+    __shared__ alignas(16) uint8_t s_tile[32 * CPP * ROW > WAVES * 8192 ? 32 * CPP * ROW : WAVES * 8192];
     __shared__ alignas(16) uint8_t s_row_sf[8 * SF];       // [k-block of the tile][window row]
     __shared__ alignas(8) uint8_t s_max16[REQUANT ? 8 : 8 * (WIN / 16)]; // [k-block][16-row group]: max of the non-NaN bytes
     __shared__ uint8_t s_flag[WIN / 64 * 8]; // [64-row group][k-block]: a NaN scale byte (REQUANT: a byte >= 253) occurs
