@@ -23,7 +23,8 @@
 // tile along the rows each, 39 / 26 and 41 / 28.  A mover of the same bytes in the same tiles takes 155 (Zipf-sized) and 133
 // (padded).  Bound by that pattern, and in a workgroup's 33 thousand cycles by the wait for its loads (8), the two conversions (4)
 // and the two write-outs (6).
-// Not kept: whole 128-byte lines (every lane converts twice the look-back rows; the mover gains 4 %); one pass (87 KB) 259;
+// Not kept: whole 128-byte lines (every lane converts twice the look-back rows, which re-quantization has loaded already and scale
+// alignment has not; the mover gains 4 %); one pass (87 KB) 259;
 // four passes and four workgroups per compute unit 172 against 168.
 #include "fp8_col_tile.hpp"
 #include "mxfp4_device.hpp"
