@@ -21,6 +21,8 @@ namespace mxfp4 {
 // source row.  A place that was not written may pass by chance, or because an earlier call left it: then that output row gets the
 // right bytes twice.
 constexpr uint32_t WINDOWS = 32, EACH = 2, PLACES = WINDOWS * EACH, SHARES = 4, GROUPS = WINDOWS * SHARES;
+constexpr uint32_t COPIES_MOST = 24; // of a row on the average, rounded down: a share of the rest is no more
+static_assert(COPIES_MOST <= 64u, "a share is what a wave reads at once");
 static_assert(PLACES == 64u && EACH == 2u, "a list is what a wave reads at once; its two entries of a window are neighbours");
 static_assert(GROUPS == 128u && (SHARES & (SHARES - 1u)) == 0u, "two groups to a lane; shares by masks");
 
@@ -133,7 +135,9 @@ __device__ __forceinline__ uint64_t listed(uint32_t out, uint32_t source, uint32
     return __ballot(out != 0xFFFFFFFFu && source == row && !twice);
 }
 
-// An equal share of the rest, entry by entry.
+// An equal share of the rest: a lane finds one entry, its output row and its source row, all lanes together, so that a share waits for them once and not for two loads in a chain per entry (us, a chain per entry / this way: copies of
+// a row next to each other 8192 x 8 of 7168 82 / 78, 65536 x 8 624 / 606, 16384 x 8 of 2048 56 / 51, 65536 x 4 of 2048 125 / 115; a quarter
+// of the entries naming one row there 102 / 99, every one 129 / 119; maps that leave little to the rest unchanged).
 struct Rest {
     uint32_t n, all;      // lane i: entries of groups 2 i and 2 i + 1, 16 bits each
     uint32_t incl;        // lane i: entries up to and with these groups
@@ -150,25 +154,35 @@ struct Rest {
         i = min(worker * each, all);
         end = min(i + each, all);
     }
-    __device__ __forceinline__ uint32_t next(const GatherListsArgs &a) // the output row of entry i
+    __device__ __forceinline__ static uint32_t of_lane(uint32_t v, uint32_t lane)
     {
-        const int l = __ffsll((unsigned long long)__ballot(incl > i)) - 1;
-        const uint32_t two = (uint32_t)__builtin_amdgcn_readlane((int)n, l), even = two & 0xFFFFu;
-        const uint32_t at = i++ - ((uint32_t)__builtin_amdgcn_readlane((int)incl, l) - even - (two >> 16));
-        const uint32_t group = 2u * (uint32_t)l + (at < even ? 0u : 1u);
-        return __builtin_amdgcn_readfirstlane(a.rest[(size_t)group * a.window + (at < even ? at : at - even)]);
+        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane * 4u), (int)v);
+    }
+    // Entry i + lane (the last one for the lanes past the end): its output row.
+    __device__ __forceinline__ uint32_t output(const GatherListsArgs &a, uint32_t lane) const
+    {
+        const uint32_t t = min(i + lane, end - 1u);
+        uint32_t l = 0; // the first lane whose groups end behind the entry
+#pragma unroll
+        for (uint32_t step = 32; step != 0u; step /= 2u)
+            l += of_lane(incl, l + step - 1u) <= t ? step : 0u;
+        const uint32_t two = of_lane(n, l), even = two & 0xFFFFu;
+        const uint32_t at = t - (of_lane(incl, l) - even - (two >> 16));
+        return a.rest[(size_t)(2u * l + (at < even ? 0u : 1u)) * a.window + (at < even ? at : at - even)];
     }
 };
 
 // A wave's share of the rest, elements [k0, k0 + n) of the rows.
 template <bool WIDE_SF>
-__device__ __forceinline__ void write_rest(const GatherListsArgs &a, Rest &rest, uint32_t k0, uint32_t n, uint8_t *rec, uint32_t lane)
+__device__ __forceinline__ void write_rest(const GatherListsArgs &a, const Rest &rest, uint32_t k0, uint32_t n, uint8_t *rec, uint32_t lane)
 {
     uint32_t held = 0xFFFFFFFFu; // the source row in LDS
-    while (rest.i < rest.end) {
+    if (rest.i == rest.end)
+        return;
+    const uint32_t dsts = rest.output(a, lane), srcs = a.source(dsts);
+    for (uint32_t l = 0; l < rest.end - rest.i; ++l) {
         asm volatile("" : "+v"(lane)); // addresses are worked out where they are used: held over the loop they would spill
-        const uint32_t dst = rest.next(a);
-        const uint32_t src = __builtin_amdgcn_readfirstlane(a.source(dst));
+        const uint32_t dst = (uint32_t)__builtin_amdgcn_readlane((int)dsts, l), src = (uint32_t)__builtin_amdgcn_readlane((int)srcs, l);
         if (src != held) {
             held = src;
             const uint32_t from = src < a.M_src ? src : 0u;
@@ -271,12 +285,14 @@ constexpr int64_t ENTRIES_MOST = (int64_t)WINDOWS * BUILD_THREADS * 32; // of an
 //   below it: 8192 x 8 of 3072 (201) 38.3 / 34.6, 35.5 / 37.0, 35.2 / 37.5; 8192 x 8 of 2048 (134) 24.6 / 24.5, 24.3 / 30.3;
 //   fewer copies: 32768 x 2 of 4096 (268) 68 / 55, 65 / 59, 60 / 57; 65536 x 2 of 2048 (268) 71 / 59, 66 / 67, 60 / 64;
 //   below it: 32768 x 2 of 3072 (201) 50 / 45, 43 / 49, 37 / 48.
-// Maps in which many rows have more than two entries in every window lose on 1/32 of the index each (512 of 8192 rows named 128
-// times each at random 73 / 92; a power law of exponent 1/4 100 / 85).
+// Maps in which many rows have more than two entries in a window lose: 512 of 8192 rows named 128 times each at random 73 / 92, 1024 64
+// times 72 / 114, 2048 32 times 74 / 86 (but a power law of exponent 1/4 97 / 85), and those with a row's copies next to each other:
+// 8192 x 8 of 7168 74 / 78, 65536 x 8 556 / 606, 16384 x 8 of 2048 48 / 51 (but 65536 x 4 129 / 115).  Not kept for the latter: runs of
+// up to eight entries as one, with their length (73, but routing maps 65.0 -> 65.6, of 2048 43.4 -> 44.7).
 int64_t gather_lists_workspace(int64_t M_src, int64_t K, int64_t M_out, const uint8_t *q, int64_t ld_q)
 {
     const bool many = M_out / 4 >= M_src;
-    if (M_src <= 0 || K <= 0 || K >= (int64_t)1 << 31 || M_out / 2 < M_src || M_out / 24 > M_src || M_out > ENTRIES_MOST ||
+    if (M_src <= 0 || K <= 0 || K >= (int64_t)1 << 31 || M_out / 2 < M_src || M_out / COPIES_MOST > M_src || M_out > ENTRIES_MOST ||
         K < (many ? 1536 : 2048) || M_out * K < (many ? (int64_t)220 << 20 : (int64_t)256 << 20) ||
         ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld_q) & 15u) != 0u)
         return 0;
