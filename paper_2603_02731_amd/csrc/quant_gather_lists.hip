@@ -135,9 +135,10 @@ __device__ __forceinline__ uint64_t listed(uint32_t out, uint32_t source, uint32
     return __ballot(out != 0xFFFFFFFFu && source == row && !twice);
 }
 
-// An equal share of the rest: a lane finds one entry, its output row and its source row, all lanes together, so that a share waits for them once and not for two loads in a chain per entry (us, a chain per entry / this way: copies of
-// a row next to each other 8192 x 8 of 7168 82 / 78, 65536 x 8 624 / 606, 16384 x 8 of 2048 56 / 51, 65536 x 4 of 2048 125 / 115; a quarter
-// of the entries naming one row there 102 / 99, every one 129 / 119; maps that leave little to the rest unchanged).
+// An equal share of the rest: a lane finds one entry, its output row and its source row, all lanes together, so that a share waits for
+// them once and not for two loads in a chain per entry (us, a chain per entry / this way: copies of a row next to each other 8192 x 8 of
+// 7168 82 / 78, 65536 x 8 624 / 606, 16384 x 8 of 2048 56 / 51, 65536 x 4 of 2048 125 / 115; a quarter of the entries naming one row there
+// 102 / 99, every one 129 / 119; maps that leave little to the rest unchanged).
 struct Rest {
     uint32_t n, all;      // lane i: entries of groups 2 i and 2 i + 1, 16 bits each
     uint32_t incl;        // lane i: entries up to and with these groups
