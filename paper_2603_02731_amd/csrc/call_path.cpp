@@ -187,8 +187,12 @@ inline void *current_stream(const at::Tensor &t)
 inline bool capturing(const at::Tensor &t)
 {
     hipStreamCaptureStatus status;
-    return t.is_cuda() && (hipStreamIsCapturing(static_cast<hipStream_t>(current_stream(t)), &status) != hipSuccess ||
-                           status != hipStreamCaptureStatusNone);
+    if (!t.is_cuda())
+        return false;
+    if (hipStreamIsCapturing(static_cast<hipStream_t>(current_stream(t)), &status) == hipSuccess)
+        return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError(); // not to be taken for an error of the launch
+    return true;
 }
 
 inline uint8_t *bytes_of(const at::Tensor &t) { return static_cast<uint8_t *>(t.data_ptr()); }

@@ -1,7 +1,9 @@
 """GPU parity on seeded random shapes: every entry point against the CPU oracle, bit for bit, on
 shapes and expert splits that no other test fixes by hand (tiles of 128 and 256 columns, partial
 row tiles, odd split lengths, empty experts, unaligned k-rows), with guard bytes around every
-output of the ragged forms.  MXFP4_EXTRA_SEEDS=n in the environment adds n further seeds to each test."""
+output of the ragged forms; transposing conversions by the tiles of small matrices and, with the columns repeated,
+by those of large ones.  MXFP4_EXTRA_SEEDS=n in the environment adds n further seeds to each test."""
+import functools
 import os
 
 import numpy as np
@@ -11,6 +13,8 @@ import torch
 import paper_2603_02731_amd as mx
 from oracle import ref
 from paper_2603_02731_amd import synth
+from tests.rules import times_as_wide
+from tests.test_gpu_parity import UNITS, check_wide
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -59,6 +63,26 @@ def random_splits(rng, total_cap):
     return T
 
 
+def wide_experts(kind, q, sf, T, wants):
+    """The grouped conversion of the same columns again and again beside each other, as often as it takes to leave the small tiles:
+    every expert's k-rows are the oracle's (wants: data, scales), as often, and nothing around the outputs is written."""
+    M, K = q.shape[0], 2 * q.shape[1]
+    n = times_as_wide(kind, M, K, len(T), UNITS)
+    off = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
+    units, fill = ((2, 32), (0xA5, 0x5A)) if kind == "mxfp4" else ((1, 128), (0xA5, -7.0))
+    types = (torch.uint8, torch.uint8 if kind == "mxfp4" else torch.float32)
+    bufs = [guarded(n * w.size, t, f) for w, t, f in zip(wants, types, fill)]
+    args = dev(q).repeat(1, n), dev(sf).repeat(1, n), torch.from_numpy(off).to(DEV)
+    if kind == "mxfp4":
+        mx.mxfp4_row_to_col_grouped(*args, q_col=bufs[0][1], sf_col=bufs[1][1], offsets_host=off)
+    else:
+        mx.mxfp4_row_to_fp8_col_grouped(*args, x_col=bufs[0][1], x_col_scale=bufs[1][1], requant=kind == "requant", offsets_host=off)
+    for (buf, _), w, u, f in zip(bufs, wants, units, fill):
+        ends = np.cumsum([0] + [K * -(-t // u) for t in T])
+        want = np.concatenate([np.tile(w.reshape(-1)[a:b], n) for a, b in zip(ends, ends[1:])])
+        same(check_guards(buf, want.size, f, kind), want, f"{kind} T={T} K={n} x {K}")
+
+
 @pytest.mark.parametrize("seed", range(12 + EXTRA))
 def test_flat_entry_points_on_random_shapes(seed):
     rng = np.random.default_rng(1000 + seed)
@@ -79,12 +103,14 @@ def test_flat_entry_points_on_random_shapes(seed):
     wqc, wsc = ref.row_to_col(wq, wsf)
     same(host(sc), wsc, f"row->col scales [{M},{K}]")
     same(host(qc), wqc, f"row->col nibbles [{M},{K}]")
+    check_wide("mxfp4", mx.mxfp4_row_to_col, wq, wsf, wqc, wsc)
     if M % 128 == 0:
         for requant in (False, True):
             xc, xcs = mx.mxfp4_row_to_fp8_col(q, sf, requant=requant)
             wxc, wxcs = ref.row_to_fp8_col(wq, wsf, requant=requant)
             same(host(xcs), wxcs, f"row->FP8 col scales [{M},{K}] requant={requant}")
             same(host(xc), wxc, f"row->FP8 col bytes [{M},{K}] requant={requant}")
+            check_wide("requant" if requant else "align", functools.partial(mx.mxfp4_row_to_fp8_col, requant=requant), wq, wsf, wxc, wxcs)
 
 
 @pytest.mark.parametrize("seed", range(12 + EXTRA))
@@ -105,6 +131,7 @@ def test_grouped_entry_points_on_random_splits(seed):
     mx.mxfp4_row_to_col_grouped(dev(q), dev(sf), offd, q_col=qv, sf_col=sv, offsets_host=off)
     same(check_guards(sbuf, wsc.size, 0x5A, "sf_col"), wsc, f"grouped row->col scales T={T} K={K}")
     same(check_guards(qbuf, wqc.size, 0xA5, "q_col"), wqc, f"grouped row->col nibbles T={T} K={K}")
+    wide_experts("mxfp4", q, sf, T, (wqc, wsc))
 
     for requant in (False, True):
         wx, wxs = ref.row_to_fp8_col_grouped(q, sf, off, requant=requant)
@@ -113,6 +140,7 @@ def test_grouped_entry_points_on_random_splits(seed):
         mx.mxfp4_row_to_fp8_col_grouped(dev(q), dev(sf), offd, x_col=xv, x_col_scale=fv, requant=requant, offsets_host=off)
         same(check_guards(fbuf, wxs.size, -7.0, "x_col_scale"), wxs, f"grouped FP8 col scales T={T} K={K} requant={requant}")
         same(check_guards(xbuf, wx.size, 0xA5, "x_col"), wx, f"grouped FP8 col bytes T={T} K={K} requant={requant}")
+        wide_experts("requant" if requant else "align", q, sf, T, (wx, wxs))
 
 
 @pytest.mark.parametrize("seed", range(10 + EXTRA))
